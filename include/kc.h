@@ -48,9 +48,9 @@ extern "C" {
 typedef struct kc_config {
   uint32_t log2_buckets;   /* buckets B = 2^log2_buckets (1..20); 0 = from the input size */
   uint32_t force_hbm;      /* 1 = route every bucket through the chunk-list merge (testing) */
-  uint32_t small_variant;  /* on-chip sort block shape: 0 auto, 1 = 256x16, 2 = 512x16,
-                              3 = 256x8 with 16-bit digit counts (keys per thread halved for
-                              128-bit keys); auto = 3 for k <= 31, 1 for k >= 32 */
+  uint32_t small_variant;  /* on-chip block shape of the bucket count, by the slots of its hash
+                              table (half as many for 128-bit keys): 0 auto, 1 = 4,096 (512
+                              threads), 2 = 8,192 (1,024), 3 = 2,048 (256); auto = 1 */
   uint32_t lanes;          /* batch / server: concurrent stream lanes (0 = 8) */
   uint64_t hbm_budget;     /* max bytes of a count's device workspace (see kc_workspace_size:
                               above it a count runs in rounds); 0 = no limit other than free HBM */
@@ -74,9 +74,9 @@ typedef struct kc_totals {
   uint64_t n_records;      /* supermer records the partition wrote */
   uint64_t flags;          /* internal status; 0 on success */
   uint64_t large_keys;     /* k-mers of large buckets (cut into chunks, merged through HBM) */
-  uint64_t tiny_buckets;   /* buckets sorted by one wave each */
+  uint64_t tiny_buckets;   /* non-empty buckets of at most a quarter of the table's slots */
   uint64_t tiny_kmers;
-  uint64_t small_buckets;  /* buckets sorted by one block each */
+  uint64_t small_buckets;  /* larger ones counted on chip */
   uint64_t small_kmers;
   uint64_t large_buckets;
   uint64_t chunks;         /* on-chip chunks of the large buckets */
@@ -365,9 +365,9 @@ int kc_server_destroy(kc_server *s);
  *   1 extract     (minimizers, supermers into span slots)           -- one kernel
  *   2 partition   (two-pass record partition into buckets, bucket plan)
  *   3 expand      (k-mers of large buckets into HBM)                -- one kernel
- *   4 block_sort  (small buckets and chunks: one block each)       -- one kernel
- *   5 wave_sort   (tiny buckets: one wave each)                     -- one kernel
- *   6 merge       (chunk lists: compact, HBM radix sort, summed runs)
+ *   4 block_sort  (chunks of large buckets counted on chip)         -- one kernel
+ *   5 wave_sort   (all other buckets counted on chip)               -- one kernel
+ *   6 merge       (chunk lists: compact, sort, summed runs)
  *   7 output      (survivor compaction, sort by key, copy, totals)
  * A plain count in rounds (memory-bounded) uses 1 for the count pass and the round
  * plan, 2 for all rounds (3-6 empty) and 7 for the final sort of the survivors.

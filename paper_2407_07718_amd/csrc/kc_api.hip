@@ -68,10 +68,6 @@ int fail(int code, const char* fmt, ...) {
 #define KC_RADIX_NB_MAX 1024
 #endif
 constexpr int RADIX_T = KC_RADIX_T;   // HBM radix passes: threads per block ...
-// k-mers of a bucket sorted by one wave: 896 64-bit keys keep a block of four waves within
-// 40 KB of LDS (16-bit digit counts), so that four blocks share a CU
-constexpr u32 WAVE_CAP_64 = 896, WAVE_CAP_128 = 512;
-constexpr int WAVES_PER_BLOCK = 4;
 constexpr int SEG_WAVES_PER_BLOCK = 2;   // k_seg_wave: more, smaller blocks measured slightly faster
 constexpr u32 RUN_BLOCKS = 1024;   // blocks of the merged-run kernel
 #ifndef KC_RADIX_ITEMS_64
@@ -97,9 +93,9 @@ struct Plan {
   u32 span = 0;
   u32 nb_large = 1, nb_surv = 1;        // radix blocks
   // offsets into the workspace
-  u64 o_packed, o_nmask, o_starts, o_X, o_Y, o_Z, o_bcnt, o_recoff, o_cursor, o_small, o_large,
-      o_lkoff, o_ctrl, o_cnt_large, o_cnt_surv, o_tot_large, o_tot_surv, o_bc, o_hp, o_blkcnt, o_chstart, o_chlen,
-      o_tiny, o_kall, o_klcnt, o_kloff, o_scnt, o_soff, o_bsum, o_scanbuf, o_phist, o_lch0, o_seg, o_mhist;
+  u64 o_packed, o_nmask, o_starts, o_X, o_Y, o_Z, o_bcnt, o_recoff, o_large,
+      o_ctrl, o_cnt_large, o_cnt_surv, o_tot_large, o_tot_surv, o_bc, o_hp, o_blkcnt, o_chstart, o_chlen,
+      o_kall, o_klcnt, o_kloff, o_scnt, o_soff, o_bsum, o_scanbuf, o_phist, o_lch0, o_seg, o_mhist;
   int log_c = 0, log_f = 0;
   u32 part_nblk = 1, part_spb = 1, nblk_cap = 1;   // extract blocks: this count's, and the bound over m
   u64 n_packed, n_mask, bytes = 0;
@@ -130,19 +126,23 @@ enum Ctrl : int {
 };
 static_assert(C_META + 8 <= C_FLAGS, "meta overlaps the flags");
 
-// On-chip block shapes of the bucket sort: 1 = 256 threads x 16 keys (x 8 for 128-bit keys),
-// 2 = 512 x 16 (x 8), 3 = 256 x 8 (x 4) with 16-bit digit counts, whose 30 KB of LDS and
-// 91 VGPRs let five blocks share a CU instead of three.  Measured fastest: 3 for 64-bit
-// keys, 1 for 128-bit keys (where 3 sends too many buckets to the chunk lists).
-u32 default_variant(int key_words) { return key_words == 1 ? 3u : 1u; }
-u32 small_cap(int key_words, u32 variant) {
-  if (key_words == 1) return variant == 2 ? 512u * 16u : variant == 3 ? 256u * 8u : 256u * 16u;
-  return variant == 2 ? 512u * 8u : variant == 3 ? 256u * 4u : 256u * 8u;
+// On-chip shapes of the bucket count, as slots of the block's hash table (half as many for
+// 128-bit keys): 1 = 4,096 (the default: the most that leaves three blocks of 512 threads per
+// CU), 2 = 8,192, 3 = 2,048.
+constexpr u32 DEFAULT_VARIANT = 1;
+u32 hash_slots(int key_words, u32 variant) {
+  return (variant == 2 ? 8192u : variant == 3 ? 2048u : 4096u) >> (key_words - 1);
 }
-// Mean bucket size the bucket count aims at: about a third of the on-chip capacity (of the
-// 256 x 16 shape for the 256 x 8 one, whose gain is occupancy, not smaller buckets).
-u64 bucket_target(int key_words, u32 variant) {
-  return std::max<u64>(1, small_cap(key_words, variant == 3 ? 1u : variant) / 3);
+// Buckets of a count of n_max k-mers: a mean of at most the table's slots, but for small
+// inputs up to 1,024 buckets of 512 k-mers, so that every CU has some.  Larger buckets would
+// suit repeated k-mers (1 Gbp at 20x: 15.1 ms with 3,800 k-mers per bucket, 14.7 ms with 7,600),
+// but where nearly all are distinct they overflow the table and are counted in classes
+// (400 Mbp at 0.8x: 12.2 ms with 3,050, 13.2 ms with 6,100).
+int auto_log_b(u64 n_max, u64 slots) {
+  int lb = 1, few = 1;
+  while (lb < 20 && (n_max >> lb) > slots) ++lb;
+  while (few < 10 && (n_max >> few) > 512) ++few;
+  return std::max(lb, few);
 }
 
 void plan_layout(Plan* p);
@@ -158,19 +158,19 @@ bool make_plan(u64 R, u64 n_reads, u64 n_max, int k, int m, uint32_t min_freq, c
   p->rec_words = k <= 31 ? 4 : 8;
   const int cap_bases = k <= 31 ? 51 : 115;   // record bits left after bucket and g
   p->gmax = std::min(64, cap_bases - k + 1);
-  p->variant = (cfg && cfg->small_variant) ? cfg->small_variant : default_variant(p->key_words);
+  p->variant = (cfg && cfg->small_variant) ? cfg->small_variant : DEFAULT_VARIANT;
   if (p->variant > 3) return false;
-  p->cap_chunk = small_cap(p->key_words, p->variant);
-  p->cap = (cfg && cfg->force_hbm) ? 0u : p->cap_chunk;
-  p->cap_tiny = (cfg && cfg->force_hbm) ? 0u : (p->key_words == 1 ? WAVE_CAP_64 : WAVE_CAP_128);
+  const u32 slots = hash_slots(p->key_words, p->variant);
+  // chunks of large buckets and buckets counted on chip may hold more k-mers than the table has
+  // slots: only distinct ones take one, and an item that overflows is counted in classes
+  p->cap_chunk = 2 * slots;
+  p->cap = (cfg && cfg->force_hbm) ? 0u : std::min(8 * slots, 32768u);
+  p->cap_tiny = (cfg && cfg->force_hbm) ? 0u : slots / 4;
   if (cfg && cfg->log2_buckets) {
     if (cfg->log2_buckets > 20) return false;
     p->log_b = (int)cfg->log2_buckets;
   } else {
-    const u64 target = bucket_target(p->key_words, p->variant);
-    int lb = 1;
-    while (lb < 20 && (n_max >> lb) > target) ++lb;
-    p->log_b = lb;
+    p->log_b = auto_log_b(n_max, slots);
   }
   p->B = 1u << p->log_b;
   p->log_c = std::min(9, p->log_b);
@@ -244,11 +244,7 @@ void plan_layout(Plan* p) {
   p->o_blkcnt = take(4ull * p->nblk_cap);
   p->o_bcnt = take(8ull * p->B);
   p->o_recoff = take(4ull * (p->B + 1));
-  p->o_cursor = take(4ull * p->B);
-  p->o_small = take(4ull * p->B);
-  p->o_tiny = take(4ull * p->B);
   p->o_large = take(4ull * p->B);
-  p->o_lkoff = take(8ull * p->B);
   p->o_kall = take(8ull * p->B);
   p->o_ctrl = take(8ull * C_WORDS);
   p->o_cnt_large = take(4ull * 256 * p->nb_large);
@@ -298,7 +294,7 @@ bool plan_rounds(Plan* p, u64 budget) {
   q.pool_cap = 1;
   q.max_rounds = 1;
   plan_layout(&q);
-  const u64 min_cap = 16ull * p->cap_chunk;
+  const u64 min_cap = 16ull * 2048;
   if (budget <= q.bytes + 1024 * 1024) return false;
   const u64 free_b = budget - q.bytes - 1024 * 1024;   // (slack for alignment and the round table)
   const u64 pool = std::max<u64>(1, std::min<u64>(p->n_max + 1, free_b / 2 / per_pool));
@@ -494,12 +490,12 @@ int seg_sort(K* keys, u32* vals, K* tmp_k, u32* tmp_v, K* out_k, u32* out_v, u64
 // Pointers of one count's workspace regions.
 template <typename K>
 struct Ws {
-  u32 *packed, *nmask, *starts, *recA, *ptmp_rec, *recB, *klsc, *s0c, *kl0c, *kl1c;
+  u32 *packed, *nmask, *starts, *recA, *ptmp_rec, *recB, *s0c, *kl0c, *kl1c;
   K *lk0, *s0k, *kl0k, *kl1k;
   u64* bcnt;
-  u32 *recoff, *cursor, *small, *tiny, *klcnt, *kloff, *scnt, *soff, *large, *blkcnt, *chlen, *bc, *hp, *lch0, *phist,
+  u32 *recoff, *klcnt, *kloff, *scnt, *soff, *large, *blkcnt, *chlen, *bc, *hp, *lch0, *phist,
       *mhist;
-  u64 *kall, *bsum, *scanbuf, *lkoff, *ctrl, *chstart, *seg;
+  u64 *kall, *bsum, *scanbuf, *ctrl, *chstart, *seg;
   u64 *counters, *meta, *surv_n, *nruns, *surv_nc, *kl_n, *kl_nc;
   u32* flags;
 };
@@ -518,7 +514,6 @@ Ws<K> ws_ptrs(const Plan& P, void* ws) {
   W.ptmp_rec = reinterpret_cast<u32*>(Y);                   // coarse partition
   W.recB = reinterpret_cast<u32*>(X);                       // bucket order
   W.lk0 = reinterpret_cast<K*>(Y);                          // large keys -> chunk lists
-  W.klsc = reinterpret_cast<u32*>(Y + WK * N);
   W.s0k = reinterpret_cast<K*>(Z);                          // survivors at bucket slots
   W.s0c = reinterpret_cast<u32*>(Z + WK * N);
   W.kl0k = reinterpret_cast<K*>(X);                         // chunk-list sort buffers
@@ -527,9 +522,6 @@ Ws<K> ws_ptrs(const Plan& P, void* ws) {
   W.kl1c = reinterpret_cast<u32*>(Y + WK * N);
   W.bcnt = at<u64>(ws, P.o_bcnt);
   W.recoff = at<u32>(ws, P.o_recoff);
-  W.cursor = at<u32>(ws, P.o_cursor);
-  W.small = at<u32>(ws, P.o_small);
-  W.tiny = at<u32>(ws, P.o_tiny);
   W.kall = at<u64>(ws, P.o_kall);
   W.klcnt = at<u32>(ws, P.o_klcnt);
   W.kloff = at<u32>(ws, P.o_kloff);
@@ -538,7 +530,6 @@ Ws<K> ws_ptrs(const Plan& P, void* ws) {
   W.bsum = at<u64>(ws, P.o_bsum);
   W.scanbuf = at<u64>(ws, P.o_scanbuf);
   W.large = at<u32>(ws, P.o_large);
-  W.lkoff = at<u64>(ws, P.o_lkoff);
   W.ctrl = at<u64>(ws, P.o_ctrl);
   W.blkcnt = at<u32>(ws, P.o_blkcnt);
   W.chstart = at<u64>(ws, P.o_chstart);
@@ -569,7 +560,7 @@ Ws<K> ws_ptrs(const Plan& P, void* ws) {
 // merged lists' segment-start bits, the sets of the merged runs' survivors, and the
 // wide-key survivor buffers (capacity wide_cap).
 struct MultiDev {
-  u32 n_sets = 0;
+  u32 n_sets = 0, n_buckets = 0;   // (the sets' buckets; the plan's number is a power of two)
   const u32* bset = nullptr;
   u32* seg_bits = nullptr;
   u32* rset = nullptr;
@@ -688,17 +679,31 @@ void launch_partition(const Plan& P, const Ws<K>& W, const u32* blk_base, hipStr
     hipLaunchKernelGGL(k_part_fine<8>, dim3(1u << P.log_c), dim3(1024), 0, st, pp);
 }
 
+// The block shape of the bucket count's kernels for a variant (see hash_slots).
+template <int T_, u32 SLOTS_>
+struct HashShape {
+  static constexpr int T = T_;
+  static constexpr u32 SLOTS = SLOTS_;
+};
+template <typename K, typename F>
+int with_hash_shape(u32 variant, F f) {
+  constexpr u32 D = sizeof(K) / 8;
+  if (variant == 2) return f(HashShape<1024, 8192 / D>());
+  if (variant == 3) return f(HashShape<256, 2048 / D>());
+  return f(HashShape<512, 4096 / D>());
+}
+
 template <typename K>
 int count_buckets(const Plan& P, const Ws<K>& W, const u32* blk_base, uint32_t lo, uint32_t hi, uint64_t hist_len,
                   uint64_t* d_hist, DevTotals* d_tot, K* out_k, u32* out_c, const u64* out_base, u64 out_cap,
-                  bool marks, int n_cu, hipStream_t st, const MultiDev* md = nullptr) {
+                  bool marks, int n_cu, hipStream_t st, const MultiDev* md = nullptr, const u32* rng = nullptr) {
   const bool ms = md != nullptr;
   int rc = KC_OK;
   if (marks) stage_mark(2, st);
   launch_partition<K>(P, W, blk_base, st);
   {
-    PlanArgs pa{W.bcnt, P.B, P.cap_tiny, P.cap, P.cap_chunk, W.bsum, W.tiny, W.recoff, W.cursor, W.small, W.large,
-                W.lkoff, W.chstart, W.chlen, P.chunk_cap, W.kall, W.meta, W.lch0};
+    PlanArgs pa{W.bcnt, P.B, P.cap_tiny, P.cap, P.cap_chunk, W.bsum, W.recoff, W.large,
+                W.chstart, W.chlen, P.chunk_cap, W.kall, W.meta, W.lch0};
     const u32 nbp = (P.B + PLAN_BLOCK - 1) / PLAN_BLOCK;
     if (nbp == 1) {
       hipLaunchKernelGGL(k_plan_write<true>, dim3(1), dim3(PLAN_T), 0, st, pa);
@@ -715,9 +720,7 @@ int count_buckets(const Plan& P, const Ws<K>& W, const u32* blk_base, uint32_t l
   ca.rec = W.recB;
   ca.rec_off = W.recoff;
   ca.bcnt = W.bcnt;
-  ca.small_list = W.small;
   ca.large_list = W.large;
-  ca.large_koff = W.lkoff;
   ca.chunk_start = W.chstart;
   ca.chunk_len = W.chlen;
   ca.meta = W.meta;
@@ -733,52 +736,40 @@ int count_buckets(const Plan& P, const Ws<K>& W, const u32* blk_base, uint32_t l
   ca.surv_c = W.s0c;
   ca.surv_cnt = W.scnt;
   ca.lkeys = W.lk0;
-  ca.kl_k = W.lk0;             // a chunk's list overwrites its own keys (read into LDS first)
-  ca.kl_c = W.klsc;
+  ca.kl_k = W.s0k;             // a large bucket has no survivors there
+  ca.kl_c = W.s0c;
   ca.kl_cnt = W.klcnt;
   ca.bset = ms ? md->bset : nullptr;
   ca.n_sets = ms ? md->n_sets : 1u;
+  ca.rng = rng;
+  ca.log_f = P.log_f;
   // large buckets: expand their k-mers into HBM, cut later into chunks
   hipLaunchKernelGGL((k_expand_large<K, 256>), dim3(1024), dim3(256), 0, st, ca, W.lk0);
   if (marks) stage_mark(4, st);
-  constexpr bool WIDE = sizeof(K) == 16;
-  auto block_sort = [&](auto kern, int T) -> int {
+  auto hash_count = [&](auto kern, int T, u64 items) -> int {
     int per_cu = 0;
     int r = blocks_per_cu(kern, T, &per_cu);
     if (r) return r;
-    hipLaunchKernelGGL(kern, dim3(std::max(1, per_cu) * n_cu), dim3(T), 0, st, ca);
+    hipLaunchKernelGGL(kern, dim3((u32)std::min<u64>((u64)std::max(1, per_cu) * n_cu, items)), dim3(T), 0, st, ca,
+                       ms ? md->n_buckets : P.B, P.cap);
     return KC_OK;
   };
-  {
-    constexpr int IT = WIDE ? 8 : 16, IT3 = WIDE ? 4 : 8;
-    if (P.variant == 2)
-      rc = ms ? block_sort(k_bucket_sort_count<K, 512, IT, true>, 512) : block_sort(k_bucket_sort_count<K, 512, IT>, 512);
-    else if (P.variant == 3)
-      rc = ms ? block_sort(k_bucket_sort_count<K, 256, IT3, true, true>, 256)
-              : block_sort(k_bucket_sort_count<K, 256, IT3, false, true>, 256);
-    else
-      rc = ms ? block_sort(k_bucket_sort_count<K, 256, IT, true>, 256) : block_sort(k_bucket_sort_count<K, 256, IT>, 256);
-    if (rc) return rc;
-  }
+  auto chunks = [&](auto shape) {
+    using H = decltype(shape);
+    return hash_count(k_hash_count<K, H::T, H::SLOTS, true, false>, H::T, P.chunk_cap);
+  };
+  auto buckets = [&](auto shape) {
+    using H = decltype(shape);
+    return ms ? hash_count(k_hash_count<K, H::T, H::SLOTS, false, true>, H::T, P.B)
+              : hash_count(k_hash_count<K, H::T, H::SLOTS, false, false>, H::T, P.B);
+  };
+  if ((rc = with_hash_shape<K>(P.variant, chunks))) return rc;
   if (marks) stage_mark(5, st);
-  {
-    constexpr u32 WC = WIDE ? WAVE_CAP_128 : WAVE_CAP_64;
-    auto wave_sort = [&](auto kern) -> int {
-      int per_cu = 0;
-      int r = blocks_per_cu(kern, WAVES_PER_BLOCK * 64, &per_cu);
-      if (r) return r;
-      hipLaunchKernelGGL(kern, dim3(std::max(1, per_cu) * n_cu), dim3(WAVES_PER_BLOCK * 64), 0, st, ca, W.tiny,
-                         W.meta + 5);
-      return KC_OK;
-    };
-    rc = ms ? wave_sort(k_wave_sort_count<K, WC, WAVES_PER_BLOCK, true>)
-            : wave_sort(k_wave_sort_count<K, WC, WAVES_PER_BLOCK>);
-    if (rc) return rc;
-  }
+  if ((rc = with_hash_shape<K>(P.variant, buckets))) return rc;
   if (marks) stage_mark(6, st);
   // merge the chunks' (k-mer, count) lists: compact, sort by k-mer, sum each run's counts
   scan_u32(W.klcnt, W.kloff, W.meta + 4, P.chunk_cap, W.kl_n, W.scanbuf, st, W.kl_nc, P.kl_cap);
-  hipLaunchKernelGGL((k_gather_segments<K>), grid_for(P.chunk_cap, 4, 4096), dim3(256), 0, st, W.lk0, W.klsc,
+  hipLaunchKernelGGL((k_gather_segments<K>), grid_for(P.chunk_cap, 4, 4096), dim3(256), 0, st, W.s0k, W.s0c,
                      W.chstart, (const u64*)nullptr, 0u, W.klcnt, W.kloff, W.meta + 4, P.chunk_cap, W.kl0k, W.kl0c,
                      (const u64*)nullptr, ~0ull);
   // each heavy bucket's lists are one segment, sorted on its own (in place)
@@ -947,7 +938,7 @@ int enqueue(const Plan& P, void* ws, const uint8_t* d_reads, const uint64_t* d_o
       er.rng = rng + q;
       launch_extract<EX_ROUND>(P, er, st);
       if ((rc = count_buckets<K>(P, W, bbase, lo, hi, hist_len, d_hist, d_tot, pool_k, pool_c, pool_n, P.pool_cap,
-                                 false, n_cu, st)))
+                                 false, n_cu, st, nullptr, rng + q)))
         return rc;
       hipLaunchKernelGGL(k_round_end, dim3(1), dim3(64), 0, st, W.counters, W.meta, W.surv_n, W.kl_n, P.rec_cap, acc,
                          pool_n, P.pool_cap, W.flags);
@@ -972,26 +963,20 @@ int enqueue(const Plan& P, void* ws, const uint8_t* d_reads, const uint64_t* d_o
 int warm_launch_facts() {
   int v = 0, rc;
   if ((rc = device_info(&v))) return rc;
-  if ((rc = blocks_per_cu(k_bucket_sort_count<u64, 256, 16>, 256, &v))) return rc;
-  if ((rc = blocks_per_cu(k_bucket_sort_count<u64, 512, 16>, 512, &v))) return rc;
-  if ((rc = blocks_per_cu(k_bucket_sort_count<k128, 256, 8>, 256, &v))) return rc;
-  if ((rc = blocks_per_cu(k_bucket_sort_count<k128, 512, 8>, 512, &v))) return rc;
-  if ((rc = blocks_per_cu(k_bucket_sort_count<u64, 256, 8, false, true>, 256, &v))) return rc;
-  if ((rc = blocks_per_cu(k_bucket_sort_count<k128, 256, 4, false, true>, 256, &v))) return rc;
-  if ((rc = blocks_per_cu(k_wave_sort_count<u64, WAVE_CAP_64, WAVES_PER_BLOCK>, WAVES_PER_BLOCK * 64, &v))) return rc;
-  if ((rc = blocks_per_cu(k_wave_sort_count<k128, WAVE_CAP_128, WAVES_PER_BLOCK>, WAVES_PER_BLOCK * 64, &v)))
-    return rc;
-  // the same kernels counting several read sets at once
-  if ((rc = blocks_per_cu(k_bucket_sort_count<u64, 256, 16, true>, 256, &v))) return rc;
-  if ((rc = blocks_per_cu(k_bucket_sort_count<u64, 512, 16, true>, 512, &v))) return rc;
-  if ((rc = blocks_per_cu(k_bucket_sort_count<k128, 256, 8, true>, 256, &v))) return rc;
-  if ((rc = blocks_per_cu(k_bucket_sort_count<k128, 512, 8, true>, 512, &v))) return rc;
-  if ((rc = blocks_per_cu(k_bucket_sort_count<u64, 256, 8, true, true>, 256, &v))) return rc;
-  if ((rc = blocks_per_cu(k_bucket_sort_count<k128, 256, 4, true, true>, 256, &v))) return rc;
-  if ((rc = blocks_per_cu(k_wave_sort_count<u64, WAVE_CAP_64, WAVES_PER_BLOCK, true>, WAVES_PER_BLOCK * 64, &v)))
-    return rc;
-  if ((rc = blocks_per_cu(k_wave_sort_count<k128, WAVE_CAP_128, WAVES_PER_BLOCK, true>, WAVES_PER_BLOCK * 64, &v)))
-    return rc;
+  for (u32 variant = 1; variant <= 3; ++variant) {
+    auto warm = [&](auto key) {
+      using K = decltype(key);
+      return with_hash_shape<K>(variant, [&](auto shape) -> int {
+        using H = decltype(shape);
+        int r;
+        if ((r = blocks_per_cu(k_hash_count<K, H::T, H::SLOTS, true, false>, H::T, &v))) return r;
+        if ((r = blocks_per_cu(k_hash_count<K, H::T, H::SLOTS, false, true>, H::T, &v))) return r;
+        return blocks_per_cu(k_hash_count<K, H::T, H::SLOTS, false, false>, H::T, &v);
+      });
+    };
+    if ((rc = warm(u64()))) return rc;
+    if ((rc = warm(k128()))) return rc;
+  }
   if ((rc = blocks_per_cu(k_seg_sort<u64, 256, 16>, 256, &v))) return rc;
   if ((rc = blocks_per_cu(k_seg_sort<k128, 256, 8>, 256, &v))) return rc;
   if ((rc = blocks_per_cu(k_seg_wave<u64, seg_wave_cap<u64>(), SEG_WAVES_PER_BLOCK>, SEG_WAVES_PER_BLOCK * 64, &v)))
@@ -1076,13 +1061,10 @@ bool make_multi_plan(const std::vector<MultiSet>& sets, int k, int m, u32 lo, u3
   while ((1u << mp->sbits) < S) ++mp->sbits;
   if (2 * k + (int)mp->sbits > 126) return false;
   const int kw = k <= 31 ? 1 : 2;
-  const u32 variant = (cfg && cfg->small_variant) ? cfg->small_variant : default_variant(kw);
+  const u32 variant = (cfg && cfg->small_variant) ? cfg->small_variant : DEFAULT_VARIANT;
   if (variant > 3) return false;
-  // mean bucket about a sixth of the on-chip capacity (a single count aims at a third):
-  // several counts of several sets overlap on the stream lanes, and smaller buckets (more
-  // of them sorted by one wave each) measured faster there -- the 5.6 Gbp batched workload
-  // took 167 ms against 184 ms at a third and 181 ms at a twelfth
-  const u64 target = std::max<u64>(1, bucket_target(kw, variant) / 2);
+  // mean bucket of at most half the table's slots (the sets are small: more buckets to spread)
+  const u64 target = hash_slots(kw, variant) / 2;
   mp->set_start.assign(S + 1, 0);
   mp->read_base.assign(S + 1, 0);
   mp->set_len.assign(S, 0);
@@ -1241,6 +1223,7 @@ int enqueue_multi(const MultiPlan& mp, void* ws, void* own, hipStream_t st) {
   u64* joff = at<u64>(ws, mp.o_joff);
   MultiDev md;
   md.n_sets = mp.n_sets;
+  md.n_buckets = mp.bbase.back() + (1u << mp.lb.back());
   md.bset = at<u32>(own, mp.o_bset);
   md.seg_bits = at<u32>(ws, mp.o_segbits);
   md.rset = at<u32>(ws, mp.o_rset);

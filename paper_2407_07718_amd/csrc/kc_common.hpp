@@ -87,6 +87,10 @@ __device__ __forceinline__ u32 lane_rot1(u32 v) {
 // v of lane `src` (a constant), as a wave-uniform value.
 __device__ __forceinline__ u32 lane_read(u32 v, int src) { return (u32)__builtin_amdgcn_readlane((int)v, src); }
 
+// A value that is the same in all lanes, as a scalar.
+__device__ __forceinline__ u32 uniform(u32 v) { return (u32)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ u64 uniform(u64 v) { return ((u64)uniform((u32)(v >> 32)) << 32) | uniform((u32)v); }
+
 // Inclusive prefix sum over the 64 lanes of a wave.
 template <typename T>
 __device__ __forceinline__ T wave_inclusive_scan(T v) {

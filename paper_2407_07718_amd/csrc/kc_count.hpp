@@ -31,12 +31,10 @@ struct CountArgs {
   const u32* rec;          // bucket-ordered supermer records
   const u32* rec_off;      // [B+1]
   const u64* bcnt;         // per bucket (records << 32) | k-mers
-  const u32* small_list;
   const u32* large_list;
-  const u64* large_koff;
   const u64* chunk_start;  // chunks of large buckets: first key in lkeys ...
   const u32* chunk_len;    // ... and length (<= cap)
-  const u64* meta;         // n_small, n_large, large k-mers, records, n_chunks, n_tiny
+  const u64* meta;         // see k_plan_scan
   const u64* kall_off;     // per bucket: first k-mer slot (prefix of k-mers over all buckets)
   int k;
   int rec_words;
@@ -47,14 +45,18 @@ struct CountArgs {
   void* surv_k;            // survivors of bucket b at slots kall_off[b] + i: keys ...
   u32* surv_c;             // ... and counts
   u32* surv_cnt;           // survivors per bucket
-  const void* lkeys;       // expanded keys of the large buckets
-  void* kl_k;              // (k-mer, count) list of chunk c at slots chunk_start[c] + i
+  const void* lkeys;       // expanded keys of the large buckets, at their buckets' k-mer slots
+  void* kl_k;              // (k-mer, count) list of chunk c at slots chunk_start[c] + i (an array of
+                           // its own: a chunk counted in classes reads its keys several times)
   u32* kl_c;
   u32* kl_cnt;             // list length per chunk
   // several read sets in one count: bucket b belongs to set bset[b], and hist / tot are
   // arrays over the sets ([n_sets][hist_len] bins, [n_sets] totals)
   const u32* bset;
   u32 n_sets;
+  // rounds: only the buckets of coarse groups [rng[0], rng[1]) hold k-mers (null: all)
+  const u32* rng;
+  int log_f;
 };
 
 // ---------------------------------------------------------------------------- key mixing
@@ -266,29 +268,577 @@ __device__ __forceinline__ void flush_stats(const RunSink& S, u64 ndist) {
   }
 }
 
-// ---------------------------------------------------------------------------- on-chip sort
-// Shared memory of one block of the bucket kernel.
-// With C16 the digit counts and offsets (at most CAP) are 16-bit, which saves LDS.
-template <typename K, int T, int ITEMS, bool C16 = false>
-struct BucketSmem {
-  static constexpr int W = T / 64, CAP = T * ITEMS;
-  using CntT = std::conditional_t<C16, u16, u32>;
-  static_assert(!C16 || CAP < 65536, "16-bit digit offsets");
-  K keys[CAP];
-  union {
-    struct {
-      u64 tbl[W][256];              // lane masks per digit; all zero between uses
-      CntT cnt[2][W][256];          // per-wave digit counts -> per-wave digit offsets
-    } r;
-    u16 hp[CAP];                    // run heads after the sort
-  } u;
-  u32 gtot[4];                      // digit-group totals of the current pass
-  u32 hist_s[256];
-  u32 wtot[W];
-  u32 item, lmax;
-  u64 scr[17];
+// ---------------------------------------------------------------------------- on-chip count
+// A bucket is counted in a hash table in LDS: its supermers are expanded key by key, each
+// key finds or claims its slot and adds one there, and the occupied slots are the bucket's
+// distinct k-mers with their counts.  (The survivors are sorted by key at the end, so the
+// order inside a bucket is free.)
+//
+// Table of SLOTS keys with 16-bit counts (an item holds at most 65,535 keys), probed by
+// aligned pairs: one 16-byte read sees two slots, a free slot is claimed by a compare and
+// swap, and a key whose pair is full goes on to the next pair.  A slot never becomes free
+// again and a key takes the first slot of its probe sequence that no other key holds, so a
+// key has one slot whatever the order of the lanes.  After PROBES full pairs the table is
+// given up as too full, and the item is counted in two halves, by the next bit of the
+// keys' mixed images (DFS over the bits; the images are a bijection, so a class at full
+// depth holds one key).  Only the distinct keys count against the table, so an item may
+// hold many times SLOTS keys.
+// One wave's scratch: the records it expands, one bit per unit of them (a unit is up to U
+// consecutive k-mers of one record, expanded by one lane) at each record's first unit, and
+// keys waiting for a slot; after the insertion, the list of its occupied slots.
+template <typename K>
+struct HashWave {
+  static constexpr int RW = sizeof(K) == 8 ? 4 : 8;
+  static constexpr u32 RECS = sizeof(K) == 8 ? 48 : 24, QUEUE = 64;
+  alignas(16) u32 rec[RECS * RW + 4];   // (+ words read past the last record)
+  u64 mark[16];
+  K queue[QUEUE];
 };
+template <typename K, int T, u32 SLOTS>
+struct HashSmem {
+  static constexpr int W = T / 64;
+  alignas(16) u64 lo[SLOTS];
+  alignas(16) u64 hi[sizeof(K) == 8 ? 2 : SLOTS];
+  u32 cnt[SLOTS / 2];              // two 16-bit counts per word, one word per pair
+  HashWave<K> w[W];
+  u32 hist_s[256];
+  u32 lmax, kept, full, dist[2];   // (dist: of this item and the next)
+  unsigned long long lover, ndist;
+};
+// No canonical k-mer has these words: 2k <= 62 bits for k <= 31; for k >= 32 a low word of
+// 32 T's has a smaller reverse complement, and the high word has at most 62 bits.
+constexpr u64 HASH_FREE = ~0ull;
+constexpr u32 HASH_PROBES = 16;
 
+// 24-bit products run at the full rate (32-bit ones at a quarter); the top bits of the sum
+// depend on every key bit.
+__device__ __forceinline__ u32 mul24(u32 a, u32 c) { return (a & 0xFFFFFFu) * c; }
+__device__ __forceinline__ u32 key_hash(u64 k) {
+  const u32 l = (u32)k, h = (u32)(k >> 32);
+  return mul24(l, 0x9E3779u) + mul24(__builtin_amdgcn_alignbit(h, l, 24), 0x85EBCBu) + mul24(h >> 16, 0xC2B2AFu);
+}
+__device__ __forceinline__ u32 key_hash(k128 k) {
+  const u32 l = (u32)k.hi, h = (u32)(k.hi >> 32);
+  return key_hash(k.lo) + mul24(l, 0x27D4EBu) + mul24(__builtin_amdgcn_alignbit(h, l, 24), 0x165667u) +
+         mul24(h >> 16, 0xB5297Bu);
+}
+
+// Classes of the DFS: keys whose mixed image has the low d bits p (d = 0: all keys).
+template <typename K> struct HashClass;
+template <> struct HashClass<u64> {
+  u32 d = 0;
+  u64 p = 0;
+  __device__ __forceinline__ bool has(u64 k) const {
+    const u64 y = mix_key(k);
+    return (d >= 64 ? y : y & ((1ull << d) - 1)) == p;
+  }
+  __device__ __forceinline__ bool bit() const { return (p >> (d - 1)) & 1; }
+  __device__ __forceinline__ void flip() { p ^= 1ull << (d - 1); }
+};
+template <> struct HashClass<k128> {
+  u32 d = 0;
+  k128 p = {0, 0};
+  __device__ __forceinline__ bool has(k128 k) const {
+    const k128 y = mix_key(k);
+    if (d < 64) return (y.lo & ((1ull << d) - 1)) == p.lo;
+    return y.lo == p.lo && (d >= 128 ? y.hi == p.hi : (y.hi & ((1ull << (d - 64)) - 1)) == p.hi);
+  }
+  __device__ __forceinline__ bool bit() const { return d <= 64 ? (p.lo >> (d - 1)) & 1 : (p.hi >> (d - 65)) & 1; }
+  __device__ __forceinline__ void flip() {
+    if (d <= 64) p.lo ^= 1ull << (d - 1);
+    else p.hi ^= 1ull << (d - 65);
+  }
+};
+// The next class after c is counted; false when all are.
+template <typename K>
+__device__ __forceinline__ bool next_class(HashClass<K>& c) {
+  while (c.d > 0 && c.bit()) {
+    c.flip();
+    --c.d;
+  }
+  if (c.d == 0) return false;
+  c.flip();
+  return true;
+}
+
+// The two words of a pair, read together.
+struct HashPair {
+  u64 x, y;
+};
+__device__ __forceinline__ HashPair hash_pair(const u64* p) {
+  typedef u32 u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 v = *reinterpret_cast<const u32x4*>(p);
+  return HashPair{((u64)v.y << 32) | v.x, ((u64)v.w << 32) | v.z};
+}
+
+// Each lane with `act` counts its key; false for a lane whose key found no slot.
+template <int T, u32 SLOTS>
+__device__ __forceinline__ bool hash_add(HashSmem<u64, T, SLOTS>& S, u64 key, bool act) {
+  constexpr int SH = 32 - __builtin_ctz(SLOTS / 2);
+  u32 i = (key_hash(key) >> SH) * 2;
+  u32 left = HASH_PROBES;
+  while (act) {
+    const HashPair t = hash_pair(&S.lo[i]);
+    u32 s = i + (t.x == key ? 0u : 1u);
+    bool done = t.x == key || t.y == key;
+    if (!done) {
+      if (t.x == HASH_FREE || t.y == HASH_FREE) {   // claim it, or look at the pair again
+        s = i + (t.x == HASH_FREE ? 0u : 1u);
+        const u64 old = atomicCAS((unsigned long long*)&S.lo[s], HASH_FREE, key);
+        done = old == HASH_FREE || old == key;
+      } else {
+        i = (i + 2) & (SLOTS - 1);
+        if (--left == 0) return false;
+      }
+    }
+    if (done) {
+      atomicAdd(&S.cnt[s >> 1], 1u << ((s & 1) * 16));
+      act = false;
+    }
+  }
+  return true;
+}
+// 128-bit keys claim a slot with their low word and then write its high word; a lane that
+// meets its low word in a slot whose high word is not there yet looks again (the claiming
+// lane writes it with its next instruction).
+template <int T, u32 SLOTS>
+__device__ __forceinline__ bool hash_add(HashSmem<k128, T, SLOTS>& S, k128 key, bool act) {
+  constexpr int SH = 32 - __builtin_ctz(SLOTS / 2);
+  u32 i = (key_hash(key) >> SH) * 2;
+  u32 left = HASH_PROBES;
+  while (act) {
+    const HashPair t = hash_pair(&S.lo[i]);
+    u32 s = i;
+    bool done = false, again = false;
+    if (t.x == key.lo) {
+      const u64 h = __hip_atomic_load(&S.hi[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      done = h == key.hi;
+      again = h == HASH_FREE;
+    }
+    if (!done && !again && t.y == key.lo) {
+      s = i + 1;
+      const u64 h = __hip_atomic_load(&S.hi[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      done = h == key.hi;
+      again = h == HASH_FREE;
+    }
+    if (!done && !again) {
+      if (t.x == HASH_FREE || t.y == HASH_FREE) {
+        s = i + (t.x == HASH_FREE ? 0u : 1u);
+        if (atomicCAS((unsigned long long*)&S.lo[s], HASH_FREE, key.lo) == HASH_FREE) {
+          __hip_atomic_store(&S.hi[s], key.hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          done = true;
+        }
+      } else {
+        i = (i + 2) & (SLOTS - 1);
+        if (--left == 0) return false;
+      }
+    }
+    if (done) {
+      atomicAdd(&S.cnt[s >> 1], 1u << ((s & 1) * 16));
+      act = false;
+    }
+  }
+  return true;
+}
+
+// Whether the key sits in the first / second slot of pair p.
+template <int T, u32 SLOTS>
+__device__ __forceinline__ void hash_find(const HashSmem<u64, T, SLOTS>& S, u64 key, u32 p, bool& in0, bool& in1) {
+  const HashPair t = hash_pair(&S.lo[2 * p]);
+  in0 = t.x == key;
+  in1 = t.y == key;
+}
+template <int T, u32 SLOTS>
+__device__ __forceinline__ void hash_find(const HashSmem<k128, T, SLOTS>& S, k128 key, u32 p, bool& in0, bool& in1) {
+  const HashPair t = hash_pair(&S.lo[2 * p]), h = hash_pair(&S.hi[2 * p]);
+  in0 = ((t.x ^ key.lo) | (h.x ^ key.hi)) == 0;
+  in1 = ((t.y ^ key.lo) | (h.y ^ key.hi)) == 0;
+}
+
+// The canonical k-mers at bases o and o + 1 of the record at rec.  One window of 64 (128)
+// bits holds both; it is read with funnel shifts, and its 2-bit reversal, brought down so
+// that the second k-mer's forward value starts at bit 0, gives the forward values.
+__device__ __forceinline__ void canon_two(const u32* rec, u32 o, int k, u64 (&out)[2]) {
+  const u64 mask = (1ull << (2 * k)) - 1;
+  const u64 V = rec_bits64(rec, 2 * o), R = rev2_64(V) >> (62 - 2 * k);
+  const u64 f0 = (R >> 2) & mask, c0 = ~V & mask, f1 = R & mask, c1 = ~(V >> 2) & mask;
+  out[0] = f0 < c0 ? f0 : c0;
+  out[1] = f1 < c1 ? f1 : c1;
+}
+__device__ __forceinline__ void canon_two(const u32* rec, u32 o, int k, k128 (&out)[2]) {
+  const u64 mhi = (1ull << (2 * k - 64)) - 1;
+  const u64 vl = rec_bits64(rec, 2 * o), vh = rec_bits64(rec, 2 * o + 64);
+  const u64 rl = rev2_64(vh), rh = rev2_64(vl);
+  const int s = 126 - 2 * k;                      // 0 .. 62
+  const u64 fl = (rl >> s) | ((rh << 1) << (63 - s)), fh = rh >> s;
+  const k128 f0{(fl >> 2) | (fh << 62), (fh >> 2) & mhi}, c0{~vl, ~vh & mhi};
+  const k128 f1{fl, fh & mhi}, c1{~((vl >> 2) | (vh << 62)), ~(vh >> 2) & mhi};
+  out[0] = key_lt(f0, c0) ? f0 : c0;
+  out[1] = key_lt(f1, c1) ? f1 : c1;
+}
+
+// Blocks take buckets (CHUNKS = false) or chunks of large buckets (whose keys are already
+// expanded in HBM) in turn.  A bucket's slots are final counts: statistics, and the
+// survivors to the bucket's own k-mer slots; a chunk's are the (k-mer, count) list of its
+// slots -- the paper's kmerlist form of a heavy-hitter task (Section 3.5) -- merged later
+// through HBM.  Several read sets (MS): a contiguous range of buckets per block (they are
+// numbered set by set), whose statistics are flushed when the set changes.
+//
+// Bound by VALU issue (on the 1 Gbp long reads, k = 31: 78% of the issue slots, 47% of the LDS
+// cycles; HBM is idle): about 85 vector instructions per 64 k-mers, half of them the
+// expansion.  Hence two k-mers per lane from one window of bits, 24-bit hash products, full
+// rows of 64 units, and a queue for the keys that need more than one look (10% there, but
+// nearly every row of 64 has some).  512 threads on 4,096 slots: 53 KB and at most 80 VGPRs, so
+// three blocks and 24 waves share a CU.  Measured there against the LSD radix passes in LDS
+// that it replaces (one wave per bucket up to 896 k-mers, one block up to 2,048, longer ones
+// expanded into HBM, cut and merged): 12.4 -> 3.7 ms at k = 31 (998 M k-mers), and at k = 51
+// 10.8 -> 3.2 ms (398 M).  256 threads on 2,048 slots: 4.0 ms; one key per lane, rows cut at
+// every 48 records and no queue: 5.7 ms.
+// Neighbouring buckets share a table while their distinct keys fill about a quarter of it,
+// which spares barriers and table scans (2^18 buckets: 4.15 -> 3.67 ms); at half full the first
+// pair misses too often (4.8 ms), at a tenth the scans show again (4.3 ms).
+template <typename K, int T, u32 SLOTS, bool CHUNKS, bool MS>
+__global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A, u32 B, u32 cap) {
+  using SM = HashSmem<K, T, SLOTS>;
+  using HW = HashWave<K>;
+  constexpr int W = SM::W, RW = HW::RW, U = 2;
+  constexpr u32 ROWS = SLOTS / T, SH = 32 - __builtin_ctz(SLOTS / 2);
+  static_assert(sizeof(HW) >= 2 * 64 * ROWS, "the list of a wave's occupied slots");
+  __shared__ SM S;
+  const u32 tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6);
+  HW& H = S.w[wave];
+  auto clear_table = [&]() {
+    for (u32 i = tid; i < SLOTS; i += T) {
+      S.lo[i] = HASH_FREE;
+      if (sizeof(K) == 16) S.hi[i] = HASH_FREE;
+    }
+    for (u32 i = tid; i < SLOTS / 2; i += T) S.cnt[i] = 0;
+  };
+  clear_table();
+  for (u32 i = tid; i < 256; i += T) S.hist_s[i] = 0;
+  if (lane < 4) H.rec[HW::RECS * RW + lane] = 0;
+  if (tid == 0) {
+    S.lmax = 0;
+    S.lover = 0;
+    S.ndist = 0;
+    S.kept = 0;
+    S.full = 0;
+    S.dist[0] = S.dist[1] = 0;
+  }
+  // the marks hold 1,024 units: records of up to 32 k-mers RECS at a time, longer ones 24
+  const u32 step = (RW == 4 && 52 - A.k <= 32) ? HW::RECS : 24u;
+  static_assert(HW::RECS >= 24 && HW::RECS <= 64, "one record per lane");
+  RunSink sink{S.hist_s, A.hist_len, A.hist, A.tot, &S.lmax, &S.lover};
+  const u64 lemask = lane == 63 ? ~0ull : ((2ull << lane) - 1);   // lanes <= this lane
+  const K* lkeys = reinterpret_cast<const K*>(A.lkeys);
+  // Many buckets per block: consecutive ones are counted together while they fit.  (Equal
+  // k-mers share a bucket, and the records and k-mer slots of neighbouring buckets adjoin.)
+  const u32 b0 = A.rng ? A.rng[0] << A.log_f : 0u, nb = (A.rng ? A.rng[1] << A.log_f : B) - b0;
+  const bool merge = !CHUNKS && nb >= 8 * gridDim.x;
+  const u32 stride = MS || merge ? 1u : gridDim.x;
+  u32 room = 0, parity = 0;
+  u32 learned = 0;   // class depth that the last full item ended at
+  u32 ndist = 0;     // distinct keys this wave saw
+  auto flush = [&]() {
+    if (lane == 0 && ndist) atomicAdd(&S.ndist, (unsigned long long)ndist);
+    ndist = 0;
+    __syncthreads();
+    flush_stats(sink, S.ndist);
+  };
+  // An item: its size and place, this wave's share of its records [ra, rb), the item after it.
+  struct Item {
+    u64 base;
+    u32 n, ra, rb, after;
+  };
+  // The plan's figures of the buckets from b on, one bucket per lane (a chunk's in lane 0),
+  // loaded an item ahead.
+  struct Ahead {
+    u64 c, ko;
+    u32 ro, st;
+  };
+  auto load_ahead = [&](u32 b, u32 end) {
+    Ahead R{0, 0, 0, 0};
+    if (b < end) {
+      const u32 i = merge ? min(b + lane, end - 1) : b;
+      if constexpr (CHUNKS) {
+        R.ko = A.chunk_start[i];
+        R.c = A.chunk_len[i];
+      } else {
+        R.c = A.bcnt[i];
+        R.ko = A.kall_off[i];
+        R.ro = A.rec_off[i];
+        if constexpr (MS) R.st = A.bset[i];
+      }
+    }
+    return R;
+  };
+  // The item that starts at bucket b: as many buckets up to `end` as hold at most `room`
+  // k-mers together, but one at least (a large bucket is an item with nothing to do).
+  auto look_up = [&](const Ahead& R, u32 b, u32 end) {
+    Item I{0, 0, 0, 0, b + stride};
+    if (b >= end) return I;
+    const u32 nk = (u32)R.c, nr = (u32)(R.c >> 32);
+    I.base = uniform(R.ko);
+    I.n = uniform(nk);
+    if constexpr (!CHUNKS) {
+      u32 m = 1;
+      if (merge) {
+        const bool fits =
+            b + lane < end && nk <= cap && R.ko + nk - I.base <= room && (!MS || R.st == uniform(R.st));
+        m = max(1u, (u32)__builtin_ctzll(~__ballot(fits) | (1ull << 63)));
+        I.after = b + m;
+      }
+      const u32 r0 = uniform(R.ro), r1 = lane_read(R.ro + nr, (int)m - 1), per = (r1 - r0 + W - 1) / W;
+      I.n = I.n > cap ? 0u : lane_read((u32)(R.ko - I.base) + nk, (int)m - 1);
+      if (I.n) {
+        I.ra = min(r1, r0 + wave * per);
+        I.rb = min(r1, I.ra + per);
+      }
+    }
+    return I;
+  };
+  // The first records of an item are on their way while the item before it is counted.
+  uint4 v[RW / 4];
+  auto load_records = [&](u32 c0, u32 rb) {
+#pragma unroll
+    for (int q = 0; q < RW / 4; ++q)
+      v[q] = lane < step && c0 + lane < rb ? reinterpret_cast<const uint4*>(A.rec)[(u64)(c0 + lane) * (RW / 4) + q]
+                                           : make_uint4(0u, 0u, 0u, 0u);
+  };
+  auto do_item = [&](u32 item, const Item& I, const Item& next) {
+    const u32 n = I.n;
+    const u64 base = I.base;
+    if (n == 0) {
+      load_records(next.ra, next.rb);
+      return;
+    }
+    K* const out_k = reinterpret_cast<K*>(CHUNKS ? A.kl_k : A.surv_k) + base;
+    u32* const out_c = (CHUNKS ? A.kl_c : A.surv_c) + base;
+    HashClass<K> cls;
+    cls.d = n > SLOTS / 2 ? learned : 0u;
+    u32 deepest = cls.d;
+    for (;;) {
+      bool ok = true;
+      u32 queued = 0;   // keys in the wave's queue
+      // The queue's keys claim their slots, one per lane.
+      auto drain = [&]() {
+        __builtin_amdgcn_wave_barrier();
+        const K key = H.queue[lane];
+        ok &= hash_add(S, key, lane < queued);
+        __builtin_amdgcn_wave_barrier();
+        queued = 0;
+      };
+      // One key per lane: counted at once where it sits in its first pair (the common case);
+      // the others wait in the queue until most lanes have one, because claiming a slot takes
+      // several LDS round trips whatever the number of lanes.
+      auto add_keys = [&](const K (&key)[U], const bool (&on)[U]) {
+        u32 p[U];
+        bool in0[U], in1[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          p[j] = key_hash(key[j]) >> SH;
+          hash_find(S, key[j], p[j], in0[j], in1[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+          if (on[j] & (in0[j] | in1[j])) atomicAdd(&S.cnt[p[j]], in0[j] ? 1u : 0x10000u);
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          const bool pend = on[j] & !(in0[j] | in1[j]);
+          const u64 m = __ballot(pend);
+          const u32 c = (u32)__popcll(m);
+          if (c > 24) {
+            ok &= hash_add(S, key[j], pend);
+          } else if (c) {
+            if (pend) H.queue[queued + mbcnt64(m)] = key[j];
+            queued += c;
+            if (queued >= 40) drain();
+          }
+        }
+      };
+      if constexpr (CHUNKS) {
+        for (u32 i0 = wave * 64 * U; i0 < n; i0 += T * U) {
+          K key[U];
+          bool on[U];
+#pragma unroll
+          for (int j = 0; j < U; ++j) {
+            const u32 i = i0 + 64 * j + lane;
+            key[j] = i < n ? lkeys[base + i] : key_zero<K>();
+            on[j] = i < n && (cls.d == 0 || cls.has(key[j]));
+          }
+          add_keys(key, on);
+        }
+      } else {
+        // each wave expands its records `step` at a time: lanes take the units in turn and find
+        // their record by the marks of the records' first units; the units past the last full
+        // row of 64 are left to the next step, which starts with their record (`skip` units of
+        // it done)
+        auto expand = [&](auto filtered) {
+          if (I.ra >= I.rb) load_records(next.ra, next.rb);
+          u32 skip = 0;
+          for (u32 c0 = I.ra; c0 < I.rb;) {
+            const u32 cnt = min(step, I.rb - c0);
+            const u32 g = lane < cnt ? (v[RW / 4 - 1].w >> 26) + 1u : 0u;
+            const u32 units = (g + U - 1) / U - (lane == 0 ? skip : 0u);
+            const u32 inc = wave_scan_u32(units), rel = inc - units;
+            const u32 G = lane_read(inc, 63);
+            const u32 full = c0 + cnt == I.rb || G < 64 ? G : G & ~63u;
+            const u32 before0 = skip ? 1u : 0u, first0 = 0u - skip;
+            u32 c1 = c0 + cnt;
+            skip = 0;
+            if (full < G) {   // unit `full` is in record c1
+              const u32 l = (u32)__popcll(__ballot(lane < cnt && rel <= full)) - 1u;
+              skip = full - lane_read(rel, (int)l) - (l == 0 ? first0 : 0u);
+              c1 = c0 + l;
+            }
+            __builtin_amdgcn_wave_barrier();
+            if (lane < HW::RECS) {
+#pragma unroll
+              for (int q = 0; q < RW / 4; ++q) *reinterpret_cast<uint4*>(&H.rec[RW * lane + 4 * q]) = v[q];
+            }
+            if (lane < 16) H.mark[lane] = 0;
+            if (g && lane >= before0) atomicOr((unsigned long long*)&H.mark[rel >> 6], 1ull << (rel & 63));
+            __builtin_amdgcn_wave_barrier();
+            if (c1 < I.rb) load_records(c1, I.rb);
+            else load_records(next.ra, next.rb);
+            const u64 mk = H.mark[lane & 15];   // lane j: the marks of units [64 j, 64 j + 64)
+            u32 first = first0, before = before0;   // records before this row, the last one's first unit
+            for (u32 q0 = 0, j = 0; q0 < full; q0 += 64, ++j) {
+              const u64 m = ((u64)lane_read((u32)(mk >> 32), (int)j) << 32) | lane_read((u32)mk, (int)j);
+              const u64 le = m & lemask;
+              const u32 q = q0 + lane;
+              const u32 st = le ? q0 + 63u - (u32)__clzll(le) : first;
+              const u32 o = U * (q - st);   // (lanes past the last unit read on inside H)
+              const u32* rec = &H.rec[RW * (before + (u32)__popcll(le) - 1u)];
+              const u32 left = (rec[RW - 1] >> 26) + 1u - o;   // k-mers from o on
+              K key[U];
+              canon_two(rec, o, A.k, key);
+              bool on[U] = {q < full, q < full && left > 1};
+              if constexpr (decltype(filtered)::value) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) on[u] = on[u] && cls.has(key[u]);
+              }
+              add_keys(key, on);
+              before += (u32)__popcll(m);
+              if (m) first = q0 + 63u - (u32)__clzll(m);
+            }
+            c0 = c1;
+          }
+        };
+        if (cls.d == 0) expand(std::false_type());
+        else expand(std::true_type());
+      }
+      if (queued) drain();
+      if (!ok) S.full = 1;
+      __syncthreads();
+      if (uniform(S.full)) {
+        __syncthreads();
+        clear_table();
+        if (tid == 0) S.full = 0;
+        __syncthreads();
+        ++cls.d;   // the class's first half
+        deepest = max(deepest, cls.d);
+        load_records(I.ra, I.rb);
+        continue;
+      }
+      // each wave lists the occupied slots of its rows, then counts, reports and frees them
+      u16* const list = reinterpret_cast<u16*>(&H);
+      u32 dist = 0;
+      {
+        u32 c[ROWS];
+#pragma unroll
+        for (u32 j = 0; j < ROWS; ++j) c[j] = reinterpret_cast<const u16*>(S.cnt)[j * T + tid];
+#pragma unroll
+        for (u32 j = 0; j < ROWS; ++j) {
+          const u64 occ = __ballot(c[j] != 0);
+          if (c[j]) list[dist + mbcnt64(occ)] = (u16)(j * T + tid);
+          dist += (u32)__popcll(occ);
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+      for (u32 e0 = 0; e0 < dist; e0 += 64) {
+        const bool act = e0 + lane < dist;
+        const u32 s = act ? list[e0 + lane] : 0u;
+        u16* const cs = reinterpret_cast<u16*>(S.cnt) + s;
+        const u32 c = act ? *cs : 0u;
+        bool emit = act;
+        if constexpr (!CHUNKS) {
+          emit = c >= A.min_freq && c <= A.max_freq;   // (min_freq >= 1)
+          run_stats_lanes(sink, c, act);
+        }
+        const u64 em = __ballot(emit);
+        if (em) {
+          u32 at = 0;
+          if (lane == 0) at = atomicAdd(&S.kept, (u32)__popcll(em));
+          at = lane_read(at, 0) + mbcnt64(em);
+          if (emit) {
+            if constexpr (sizeof(K) == 8) out_k[at] = S.lo[s];
+            else out_k[at] = K{S.lo[s], S.hi[s]};
+            out_c[at] = c;
+          }
+        }
+        if (act) {
+          *cs = 0;
+          S.lo[s] = HASH_FREE;
+          if (sizeof(K) == 16) S.hi[s] = HASH_FREE;
+        }
+      }
+      if (lane < 4) H.rec[HW::RECS * RW + lane] = 0;
+      ndist += dist;
+      if (lane == 0) atomicAdd(&S.dist[parity], dist);
+      if (tid == 0) S.dist[parity ^ 1] = 0;
+      __syncthreads();
+      if (!next_class(cls)) break;
+      load_records(I.ra, I.rb);
+    }
+    // what this item teaches: the class depth to start with, and how many k-mers fill about a
+    // quarter of a table
+    const u32 d = uniform(S.dist[parity]);
+    parity ^= 1;
+    learned = deepest && (d >> deepest) <= SLOTS / 4 ? deepest - 1 : deepest;
+    if (merge) room = (u32)min((float)cap, (float)n * (SLOTS / 4) / (float)max(d, 1u));
+    if (tid == 0) {   // (the next item adds to S.kept after its first barrier)
+      (CHUNKS ? A.kl_cnt : A.surv_cnt)[item] = S.kept;
+      S.kept = 0;
+    }
+  };
+  __syncthreads();
+  const bool ranges = MS || merge;
+  u32 item = CHUNKS ? blockIdx.x : b0 + (ranges ? (u32)((u64)nb * blockIdx.x / gridDim.x) : blockIdx.x);
+  const u32 end = CHUNKS ? (u32)A.meta[4] : b0 + (ranges ? (u32)((u64)nb * (blockIdx.x + 1) / gridDim.x) : nb);
+  Item I = look_up(load_ahead(item, end), item, end);
+  load_records(I.ra, I.rb);
+  Ahead ahead = load_ahead(I.after, end);
+  u32 cur = ~0u;
+  while (item < end) {
+    if constexpr (MS) {
+      const u32 st = A.bset[item];
+      if (st != cur) {
+        if (cur != ~0u) {
+          flush();
+          __syncthreads();
+          for (u32 i = tid; i < 256; i += T) S.hist_s[i] = 0;
+          if (tid == 0) {
+            S.lmax = 0;
+            S.lover = 0;
+            S.ndist = 0;
+          }
+          __syncthreads();
+        }
+        sink_to_set(sink, A.hist, A.tot, st);
+        cur = st;
+      }
+    }
+    const Item next = look_up(ahead, I.after, end);
+    ahead = load_ahead(next.after, end);
+    do_item(item, I, next);
+    item = I.after;
+    I = next;
+  }
+  if constexpr (!CHUNKS) flush();
+}
+
+// ---------------------------------------------------------------------------- LDS radix passes
 // Key above every canonical k-mer (which uses only the low 2k bits): pads a bucket to
 // whole waves.  Its digit is 0xFF in every pass, so a stable sort keeps the padding
 // after all real keys and the padded lanes need no masking.
@@ -435,12 +985,6 @@ __device__ __forceinline__ void lds_sort_passes(K* keys, u32* vals, u64* tbl, Cn
   }
 }
 
-template <typename K, int T, int ITEMS, bool C16>
-__device__ __forceinline__ void bucket_sort(BucketSmem<K, T, ITEMS, C16>& S, u32 n_pad, int p_begin, int p_end) {
-  lds_sort_passes<K, T, ITEMS, false>(S.keys, nullptr, &S.u.r.tbl[0][0], &S.u.r.cnt[0][0][0], S.gtot, n_pad, p_begin,
-                                      p_end, p_begin == 0);
-}
-
 // Counting needs equal keys adjacent, not ascending order (the survivors of all buckets
 // are sorted by key at the end).  After the LSD passes over the low `bits` bits the
 // keys are ordered by those bits, so equal keys already share one group of equal low
@@ -458,14 +1002,6 @@ __device__ __forceinline__ bool mixed_pair(const K* keys, u32 idx, u32 n, int bi
   return low_eq(a, b, bits) && !key_eq(a, b);
 }
 
-// Block-wide: does any group of equal low bits hold two distinct keys?
-template <typename K, int T, int ITEMS, bool C16>
-__device__ __forceinline__ bool mixed_groups(BucketSmem<K, T, ITEMS, C16>& S, u32 n, int bits) {
-  bool bad = false;
-  for (u32 idx = threadIdx.x; idx < n; idx += T) bad |= mixed_pair(S.keys, idx, n, bits);
-  return __syncthreads_or(bad) != 0;
-}
-
 // Passes sorted first: 3 digits (24 bits) for up to 1536 keys, else 4 digits (32 bits),
 // so a bucket of D distinct mixed keys needs the remaining passes with probability
 // about D^2 / 2^25 (D <= 1536: under 7%) or D^2 / 2^33 (D <= 4096: 0.2%).  Keys of at
@@ -474,393 +1010,6 @@ __device__ __forceinline__ int first_passes(u32 n) { return n <= 1536u ? 3 : 4; 
 template <typename K> __device__ __forceinline__ int sort_passes(int k);
 template <> __device__ __forceinline__ int sort_passes<u64>(int k) { return 2 * k <= 32 ? (2 * k + 7) / 8 : 8; }
 template <> __device__ __forceinline__ int sort_passes<k128>(int k) { return (2 * k + 7) / 8; }
-
-// Run heads of the sorted keys[0, n) -> S.u.hp[0, nruns) in order.  Returns nruns.
-template <typename K, int T, int ITEMS, bool C16>
-__device__ __forceinline__ u32 run_heads(BucketSmem<K, T, ITEMS, C16>& S, u32 n) {
-  constexpr int W = T / 64;
-  const u32 tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-  const int per = (int)((n + 64u * W - 1) / (64u * W));
-  u32 run = 0;
-  for (int j = 0; j < per; ++j) {
-    const u32 idx = (wave * (u32)per + (u32)j) * 64u + lane;
-    const bool head = idx < n && (idx == 0 || !key_eq(S.keys[idx], S.keys[idx - 1]));
-    run += (u32)__popcll(__ballot(head));
-  }
-  if (lane == 0) S.wtot[wave] = run;
-  __syncthreads();
-  u32 base = 0, all = 0;
-  for (u32 v = 0; v < (u32)W; ++v) {
-    const u32 t = S.wtot[v];
-    base += v < wave ? t : 0u;
-    all += t;
-  }
-  for (int j = 0; j < per; ++j) {
-    const u32 idx = (wave * (u32)per + (u32)j) * 64u + lane;
-    const bool head = idx < n && (idx == 0 || !key_eq(S.keys[idx], S.keys[idx - 1]));
-    const u64 m = __ballot(head);
-    if (head) S.u.hp[base + mbcnt64(m)] = (u16)idx;
-    base += (u32)__popcll(m);
-  }
-  __syncthreads();
-  return all;
-}
-
-// ---------------------------------------------------------------------------- bucket kernel
-// Emit the runs of a sorted block of keys.  Runs [0, nruns) with heads hp; a run is kept
-// when `final` and its count is in range (and feeds the statistics), or always for a
-// chunk list.  Kept runs go to dst_k/dst_c[0, kept) in run order; returns kept.
-// Block-wide (barriers inside).
-template <typename K>
-__device__ __forceinline__ u32 emit_runs_block(const K* keys, const u16* hp, u32 nruns, u32 n, bool final, u32 lo,
-                                               u32 hi, const RunSink& sink, K* dst_k, u32* dst_c, u64* scr,
-                                               bool mixed) {
-  u32 kept = 0;
-  for (u32 c0 = 0; c0 < nruns; c0 += blockDim.x) {
-    const u32 r = c0 + threadIdx.x;
-    bool emit = false;
-    u32 s = 0, c = 0;
-    if (r < nruns) {
-      s = hp[r];
-      c = ((r + 1 < nruns) ? (u32)hp[r + 1] : n) - s;
-      emit = final ? (c >= lo && c <= hi) : true;
-    }
-    if (final) run_stats_lanes(sink, c, r < nruns);
-    u64 tot;
-    const u64 ex = block_exclusive_scan<u64>(emit ? 1ull : 0ull, scr, &tot);
-    if (emit) {
-      dst_k[kept + ex] = mixed ? unmix_key(keys[s]) : keys[s];
-      dst_c[kept + ex] = c;
-    }
-    kept += (u32)tot;
-  }
-  return kept;
-}
-
-// Persistent blocks take work items round-robin (item = block, block + grid, ...).
-// Items [0, n_chunks) are chunks of large buckets: their keys (already expanded in HBM)
-// are sorted and run-counted on chip into (k-mer, count) lists -- the paper's kmerlist
-// form of a heavy-hitter task (Section 3.5) -- merged later through HBM.  Items after
-// that are small buckets: their supermers are expanded into LDS, sorted, and their runs
-// are final counts.  Every item writes its output to its own slot range.
-template <typename K, int T, int ITEMS, bool MS = false, bool C16 = false>
-__global__ __launch_bounds__(T) void k_bucket_sort_count(CountArgs A) {
-  using SM = BucketSmem<K, T, ITEMS, C16>;
-  constexpr int CAP = SM::CAP;
-  static_assert(sizeof(decltype(SM::u)) >= 4 * CAP, "expansion maps fit the rank tables");
-  __shared__ SM S;
-  __shared__ unsigned long long lover;
-  const u32 tid = threadIdx.x;
-  for (u32 i = tid; i < 256; i += T) S.hist_s[i] = 0;
-  if (tid == 0) {
-    S.lmax = 0;
-    lover = 0;
-  }
-  RunSink sink{S.hist_s, A.hist_len, A.hist, A.tot, &S.lmax, &lover};
-  const u64 n_small = A.meta[0], n_chunks = A.meta[4];
-  const int np = sort_passes<K>(A.k);
-  const bool mixed = 2 * A.k > 32;
-  u64 ndist = 0;
-  K* skeys = reinterpret_cast<K*>(A.surv_k);
-  const K* lkeys = reinterpret_cast<const K*>(A.lkeys);
-  K* klk = reinterpret_cast<K*>(A.kl_k);
-  auto do_item = [&](u64 item) {
-    __syncthreads();
-    const bool chunk = item < n_chunks;
-    u32 n, b = 0;
-    u64 ks = 0;
-    if (chunk) {
-      ks = A.chunk_start[item];
-      n = min(A.chunk_len[item], (u32)CAP);
-      for (u32 i = tid; i < n; i += T) S.keys[i] = mixed ? mix_key(lkeys[ks + i]) : lkeys[ks + i];
-    } else {
-      b = A.small_list[item - n_chunks];
-      const u32 r0 = A.rec_off[b], nr = A.rec_off[b + 1] - r0;
-      n = min((u32)A.bcnt[b], (u32)CAP);
-      // expand: thread t takes a contiguous range of records.  For u64 keys each thread
-      // rolls through its records' k-mers.  For 128-bit keys, whose rolling update is
-      // costly, the expansion is key-parallel: each record's first key index and, for each
-      // of its keys, the record index go to the (still unused) rank tables, then each
-      // thread computes keys o = tid, tid + T, ... straight from their records' bits.  (A
-      // small bucket has at most CAP k-mers, so at most CAP records.)
-      const u32 pr = (nr + T - 1) / T;
-      const u32 ra = min(nr, tid * pr), rb = min(nr, ra + pr);
-      u64 gsum = 0;
-      for (u32 r = ra; r < rb; ++r) gsum += record_g(A.rec, (u64)r0 + r, A.rec_words);
-      u64 gall;
-      u64 off = block_exclusive_scan<u64>(gsum, S.scr, &gall);
-      if constexpr (sizeof(K) == 8) {
-        for (u32 r = ra; r < rb; ++r) {
-          const u32 g = record_g(A.rec, (u64)r0 + r, A.rec_words);
-          if (off + g <= (u64)CAP) expand_record(A.rec, (u64)r0 + r, A.k, S.keys + off, g, mixed);
-          off += g;
-        }
-      } else {
-        u16* s_off = reinterpret_cast<u16*>(&S.u);   // [CAP] record -> its first key
-        u16* s_rid = s_off + CAP;                    // [CAP] key -> its record
-        for (u32 r = ra; r < rb; ++r) {
-          const u32 g = record_g(A.rec, (u64)r0 + r, A.rec_words);
-          s_off[r] = (u16)off;
-          for (u32 t = 0; t < g && off + t < (u64)CAP; ++t) s_rid[off + t] = (u16)r;
-          off += g;
-        }
-        __syncthreads();
-        for (u32 o = tid; o < n; o += T) {
-          const u32 r = s_rid[o];
-          const K key = canon_at<K>(A.rec + ((u64)r0 + r) * 8, 2u * (o - s_off[r]), A.k);
-          S.keys[o] = mixed ? mix_key(key) : key;
-        }
-      }
-    }
-    // pad to whole waves of every wave of the block
-    constexpr u32 WB = 64u * (T / 64);
-    const u32 n_pad = (n + WB - 1) / WB * WB;
-    for (u32 i = n + tid; i < n_pad; i += T) S.keys[i] = key_pad<K>();
-    __syncthreads();
-    const int p0 = mixed ? first_passes(n) : np;
-    bucket_sort(S, n_pad, 0, p0);
-    if (p0 < np && mixed_groups(S, n, 8 * p0)) bucket_sort(S, n_pad, p0, np);
-    const u32 nruns = run_heads(S, n);
-    if (chunk) {
-      const u32 kept =
-          emit_runs_block<K>(S.keys, S.u.hp, nruns, n, false, 0, 0, sink, klk + ks, A.kl_c + ks, S.scr, mixed);
-      if (tid == 0) A.kl_cnt[item] = kept;
-    } else {
-      const u64 so = A.kall_off[b];
-      const u32 kept = emit_runs_block<K>(S.keys, S.u.hp, nruns, n, true, A.min_freq, A.max_freq, sink, skeys + so,
-                                          A.surv_c + so, S.scr, mixed);
-      if (tid == 0) A.surv_cnt[b] = kept;
-      ndist += nruns;
-    }
-  };
-  if constexpr (!MS) {
-    for (u64 item = blockIdx.x; item < n_chunks + n_small; item += gridDim.x) do_item(item);
-  } else {
-    // Several read sets: chunks (no statistics) round-robin, then the small buckets in one
-    // contiguous range per block.  Buckets are numbered set by set, so a block meets few
-    // sets and flushes its statistics only when the set changes.
-    for (u64 item = blockIdx.x; item < n_chunks; item += gridDim.x) do_item(item);
-    const u64 per = (n_small + gridDim.x - 1) / gridDim.x;
-    const u64 ia = n_chunks + min(n_small, (u64)blockIdx.x * per), ie = n_chunks + min(n_small, (u64)(blockIdx.x + 1) * per);
-    u32 cur = ~0u;
-    for (u64 item = ia; item < ie; ++item) {
-      const u32 st = A.bset[A.small_list[item - n_chunks]];
-      if (st != cur) {
-        if (cur != ~0u) {
-          __syncthreads();
-          flush_stats(sink, tid == 0 ? ndist : 0);
-          __syncthreads();
-          for (u32 i = tid; i < 256; i += T) S.hist_s[i] = 0;
-          if (tid == 0) {
-            S.lmax = 0;
-            lover = 0;
-          }
-          ndist = 0;
-        }
-        sink_to_set(sink, A.hist, A.tot, st);
-        cur = st;
-      }
-      do_item(item);
-    }
-  }
-  __syncthreads();
-  flush_stats(sink, tid == 0 ? ndist : 0);
-}
-
-// ---------------------------------------------------------------------------- wave kernel
-// Small buckets (at most WCAP k-mers) are sorted by one wave each, in the wave's own
-// slice of LDS, with no block barriers: the waves of a block are independent and hide
-// each other's LDS latency.
-template <typename K, int WCAP>
-struct WaveSmem {
-  K keys[WCAP];
-  union {
-    struct {
-      u64 tbl[256];                 // lane masks per digit; all zero between uses
-      u16 cnt[256];                 // digit counts -> digit offsets (at most WCAP)
-    } r;
-    u16 hp[WCAP];                   // run heads after the sort
-  } u;
-};
-
-template <typename K, int WCAP>
-__device__ __forceinline__ void wave_sort(WaveSmem<K, WCAP>& S, u32 n_pad, int p_begin, int p_end) {
-  constexpr int ITEMS = WCAP / 64;
-  const u32 lane = lane_id();
-  const u64 ge = ~((1ull << lane) - 1ull);
-  const int per = (int)(n_pad / 64);
-  for (int p = p_begin; p < p_end; ++p) {
-    K kr[ITEMS];
-    u32 rk[ITEMS];
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j)
-      if (j < per) kr[j] = S.keys[(u32)j * 64u + lane];
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-      if (j < per) {
-        const u32 d = key_digit(kr[j], 8 * p);
-        const u64 mask = digit_peers_full(S.u.r.tbl, d, ge);
-        const u32 base = S.u.r.cnt[d];
-        const u32 lr = mbcnt64(mask);
-        if (lr == 0) {
-          S.u.r.cnt[d] = (u16)(base + (u32)__popcll(mask));
-          S.u.r.tbl[d] = 0;
-        }
-        rk[j] = base + lr;
-      }
-    }
-    // counts -> exclusive digit offsets; lane l owns digits 4l..4l+3
-    const u32 c0 = S.u.r.cnt[4 * lane], c1 = S.u.r.cnt[4 * lane + 1], c2 = S.u.r.cnt[4 * lane + 2],
-              c3 = S.u.r.cnt[4 * lane + 3];
-    const u32 s4 = c0 + c1 + c2 + c3;
-    const u32 ex = wave_scan_u32(s4) - s4;
-    S.u.r.cnt[4 * lane] = (u16)ex;
-    S.u.r.cnt[4 * lane + 1] = (u16)(ex + c0);
-    S.u.r.cnt[4 * lane + 2] = (u16)(ex + c0 + c1);
-    S.u.r.cnt[4 * lane + 3] = (u16)(ex + c0 + c1 + c2);
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-      if (j < per) S.keys[S.u.r.cnt[key_digit(kr[j], 8 * p)] + rk[j]] = kr[j];
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) S.u.r.cnt[4 * lane + i] = 0;
-  }
-}
-
-template <typename K, int WCAP, int WPB, bool MS = false>
-__global__ __launch_bounds__(WPB * 64) void k_wave_sort_count(CountArgs A, const u32* __restrict__ tiny_list,
-                                                               const u64* __restrict__ n_tiny_ptr) {
-  static_assert(sizeof(u16) * WCAP <= sizeof(WaveSmem<K, WCAP>::u), "run heads reuse the rank tables");
-  constexpr int NS = MS ? WPB : 1;   // statistics slices: per block, or per wave for several sets
-  __shared__ WaveSmem<K, WCAP> WS[WPB];
-  __shared__ u32 hist_s[NS][256];
-  __shared__ u32 lmax[NS];
-  __shared__ unsigned long long lover[NS];
-  __shared__ u64 ndb;
-  const u32 tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-  for (u32 i = tid; i < NS * 256; i += blockDim.x) (&hist_s[0][0])[i] = 0;
-  if (tid < NS) { lmax[tid] = 0; lover[tid] = 0; }
-  if (tid == 0) ndb = 0;
-  __syncthreads();
-  const u32 sl = MS ? wave : 0u;
-  RunSink sink{hist_s[sl], A.hist_len, A.hist, A.tot, &lmax[sl], &lover[sl]};
-  WaveSmem<K, WCAP>& S = WS[wave];
-  const u64 n_tiny = *n_tiny_ptr;
-  const int np = sort_passes<K>(A.k);
-  const bool mixed = 2 * A.k > 32;
-  K* skeys = reinterpret_cast<K*>(A.surv_k);
-  u64 ndist = 0;
-  const u64 gw = (u64)blockIdx.x * WPB + wave, nw = (u64)gridDim.x * WPB;
-  // key -> record map of a 64-record chunk, and each record's first key, in the rank
-  // tables' region (cleared for the sort only after the expansion)
-  constexpr u32 MAPB = sizeof(S.u) - 128;
-  u8* const rid = reinterpret_cast<u8*>(&S.u);
-  u16* const roff = reinterpret_cast<u16*>(rid + MAPB);
-  constexpr int RW = sizeof(K) == 8 ? 4 : 8;
-  // Several read sets: one contiguous range of tiny buckets per wave (buckets are
-  // numbered set by set, so a wave meets few sets and flushes its statistics only when
-  // the set changes).  One set: round-robin.
-  u64 item = gw, i_end = n_tiny, i_step = nw;
-  if constexpr (MS) {
-    const u64 per = (n_tiny + nw - 1) / nw;
-    item = min(n_tiny, gw * per);
-    i_end = min(n_tiny, item + per);
-    i_step = 1;
-  }
-  u32 cur = ~0u;
-  for (; item < i_end; item += i_step) {
-    const u32 b = tiny_list[item];
-    if constexpr (MS) {
-      const u32 st = A.bset[b];
-      if (st != cur) {
-        if (cur != ~0u) flush_stats_wave(sink, ndist);
-        ndist = 0;
-        sink_to_set(sink, A.hist, A.tot, st);
-        cur = st;
-      }
-    }
-    const u32 r0 = A.rec_off[b], nr = A.rec_off[b + 1] - r0;
-    const u32 n = min((u32)A.bcnt[b], (u32)WCAP);
-    // expand 64 records at a time.  For 128-bit keys key-parallel: lanes take the chunk's
-    // keys in turn and compute each from its record's bits (a chunk too large for the
-    // map, possible only for very small k, is expanded by its records' lanes instead).
-    // For u64 keys each lane rolls through its record's k-mers (measured faster there).
-    u32 off = 0;
-    for (u32 c0 = 0; c0 < nr; c0 += 64) {
-      const u32 r = c0 + lane;
-      const u32 g = r < nr ? record_g(A.rec, (u64)r0 + r, A.rec_words) : 0u;
-      const u32 inc = wave_scan_u32(g);
-      const u32 rel = inc - g;
-      const u32 G = lane_read(inc, 63);
-      if (sizeof(K) == 16 && G <= MAPB) {
-        roff[lane] = (u16)rel;
-        for (u32 t = 0; t < g; ++t) rid[rel + t] = (u8)lane;
-        for (u32 q = lane; q < G && off + q < (u32)WCAP; q += 64) {
-          const u32 l = rid[q];
-          const K key = canon_at<K>(A.rec + ((u64)r0 + c0 + l) * RW, 2u * (q - roff[l]), A.k);
-          S.keys[off + q] = mixed ? mix_key(key) : key;
-        }
-      } else {
-        const u32 o = off + rel;
-        if (g && o + g <= (u32)WCAP) expand_record(A.rec, (u64)r0 + r, A.k, S.keys + o, g, mixed);
-      }
-      off += G;
-    }
-    for (u32 i = lane; i < 256; i += 64) {
-      S.u.r.tbl[i] = 0;
-      S.u.r.cnt[i] = 0;
-    }
-    const u32 n_pad = (n + 63u) & ~63u;
-    for (u32 i = n + lane; i < n_pad; i += 64) S.keys[i] = key_pad<K>();
-    const int p0 = mixed ? first_passes(n) : np;
-    wave_sort<K, WCAP>(S, n_pad, 0, p0);
-    if (p0 < np) {
-      bool bad = false;
-      for (u32 idx = lane; idx < n; idx += 64) bad |= mixed_pair(S.keys, idx, n, 8 * p0);
-      if (__ballot(bad) != 0) wave_sort<K, WCAP>(S, n_pad, p0, np);
-    }
-    // run heads
-    const int per = (int)((n + 63) / 64);
-    u32 nruns = 0;
-    for (int j = 0; j < per; ++j) {
-      const u32 idx = (u32)j * 64u + lane;
-      const bool head = idx < n && (idx == 0 || !key_eq(S.keys[idx], S.keys[idx - 1]));
-      const u64 m = __ballot(head);
-      if (head) S.u.hp[nruns + mbcnt64(m)] = (u16)idx;
-      nruns += (u32)__popcll(m);
-    }
-    // runs: statistics, survivors to this bucket's slots
-    const u64 so = A.kall_off[b];
-    u32 kept = 0;
-    for (u32 c0 = 0; c0 < nruns; c0 += 64) {
-      const u32 r = c0 + lane;
-      bool emit = false;
-      u32 s = 0, c = 0;
-      if (r < nruns) {
-        s = S.u.hp[r];
-        c = ((r + 1 < nruns) ? (u32)S.u.hp[r + 1] : n) - s;
-        emit = c >= A.min_freq && c <= A.max_freq;
-      }
-      run_stats_lanes(sink, c, r < nruns);
-      const u64 m = __ballot(emit);
-      if (emit) {
-        const u64 dst = so + kept + mbcnt64(m);
-        skeys[dst] = mixed ? unmix_key(S.keys[s]) : S.keys[s];
-        A.surv_c[dst] = c;
-      }
-      kept += (u32)__popcll(m);
-    }
-    if (lane == 0) A.surv_cnt[b] = kept;
-    ndist += nruns;
-  }
-  if constexpr (MS) {
-    flush_stats_wave(sink, ndist);
-  } else {
-    if (lane == 0 && ndist) atomicAdd((unsigned long long*)&ndb, (unsigned long long)ndist);
-    __syncthreads();
-    flush_stats(sink, tid == 0 ? ndb : 0);
-  }
-}
 
 // ---------------------------------------------------------------------------- large buckets
 // Expand the records of every large bucket into one HBM key array.  Equal k-mers share
@@ -889,7 +1038,7 @@ __global__ __launch_bounds__(T) void k_expand_large(CountArgs A, K* __restrict__
   for (u64 item = blockIdx.x; item < n_large; item += gridDim.x) {
     const u32 b = A.large_list[item];
     const u32 r0 = A.rec_off[b], nr = A.rec_off[b + 1] - r0;
-    u64 base = A.large_koff[b];
+    u64 base = A.kall_off[b];
     for (u32 c0 = 0; c0 < nr; c0 += T) {
       const u32 r = c0 + tid;
       uint4 v[RW / 4];

@@ -431,9 +431,9 @@ __global__ __launch_bounds__(256) void k_extract(ExtractArgs A) {
 }
 
 // ---------------------------------------------------------------------------- bucket plan
-// The plan classifies buckets by k-mer count n: tiny (n <= cap_tiny, one wave each),
-// small (n <= cap_small, one block each) -- both sorted on chip from their records --
-// and large (cut into chunks of at most cap_chunk k-mers, see the counting stage).  It
+// The plan classifies buckets by k-mer count n: tiny (n <= cap_tiny) and small (n <=
+// cap_small), counted on chip from their records, and large (cut into chunks of at most
+// cap_chunk k-mers, see the counting stage).  It
 // is three kernels: per-block sums, one scan of the block sums, then the writes (one
 // kernel when the buckets fit one block).
 // Quantities per bucket: q0 records, q1 k-mers, q2 classes packed (tiny | small << 21 |
@@ -448,12 +448,8 @@ struct PlanArgs {
   const u64* bcnt;
   u32 B, cap_tiny, cap_small, cap_chunk;
   u64* bsum;             // [nblocks][PLAN_Q] block sums -> block offsets
-  u32* tiny_list;
   u32* rec_off;          // [B + 1]
-  u32* cursor;
-  u32* small_list;
   u32* large_list;
-  u64* large_koff;
   u64* chunk_start;
   u32* chunk_len;
   u64 chunk_cap;
@@ -541,34 +537,27 @@ __global__ __launch_bounds__(PLAN_T) void k_plan_write(PlanArgs P) {
   for (int j = 0; j < PLAN_Q; ++j)
     off[j] = block_exclusive_scan<u64>(sum[j], scr, &tot[j]) + (ONE ? 0ull : P.bsum[(u64)blockIdx.x * PLAN_Q + j]);
   if (ONE && threadIdx.x == 0) plan_meta(P, tot);
-  u64 prec = off[0], pk = off[1], plk = off[3], pch = off[4];
-  u64 ptiny = off[2] & ((1ull << 21) - 1), psmall = (off[2] >> 21) & ((1ull << 21) - 1), plarge = off[2] >> 42;
+  u64 prec = off[0], pk = off[1], pch = off[4];
+  u64 plarge = off[2] >> 42;
   for (u32 i = 0; i < PLAN_PER_THREAD; ++i) {
     const u32 b = b0 + i;
     if (b >= P.B) break;
     const u32 nk = (u32)c[i], nr = (u32)(c[i] >> 32);
     P.rec_off[b] = (u32)prec;
-    P.cursor[b] = (u32)prec;
     prec += nr;
     P.kall_off[b] = pk;
-    pk += nk;
     if (nk > P.cap_small) {
       P.large_ch0[plarge] = (u32)pch;
       P.large_list[plarge++] = b;
-      P.large_koff[b] = plk;
-      for (u32 o = 0; o < nk; o += P.cap_chunk) {
+      for (u32 o = 0; o < nk; o += P.cap_chunk) {   // at the bucket's own k-mer slots
         if (pch < P.chunk_cap) {
-          P.chunk_start[pch] = plk + o;
+          P.chunk_start[pch] = pk + o;
           P.chunk_len[pch] = min(P.cap_chunk, nk - o);
         }
         ++pch;
       }
-      plk += nk;
-    } else if (nk > P.cap_tiny) {
-      P.small_list[psmall++] = b;
-    } else if (nk > 0) {
-      P.tiny_list[ptiny++] = b;
     }
+    pk += nk;
   }
 }
 

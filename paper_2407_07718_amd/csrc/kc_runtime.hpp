@@ -77,13 +77,6 @@ struct TuneVal {
 std::mutex g_tune_mu;
 std::map<TuneKey, TuneVal> g_tune;
 
-int auto_log_b(u64 n_max, int key_words, u32 variant) {
-  const u64 target = bucket_target(key_words, variant);
-  int lb = 1;
-  while (lb < 20 && (n_max >> lb) > target) ++lb;
-  return lb;
-}
-
 TuneKey tune_key(const JobInfo& ji, int k, u64 n_reads) {
   int sc = 0;
   while (sc < 40 && (ji.R >> (sc + 1)) > 0) ++sc;
@@ -94,7 +87,7 @@ TuneKey tune_key(const JobInfo& ji, int k, u64 n_reads) {
 kc_config tuned_config(const kc_config& base, const JobInfo& ji, const TuneVal& tv) {
   kc_config c = base;
   c.small_variant = tv.variant;
-  c.log2_buckets = (u32)std::min(20, std::max(1, auto_log_b(ji.n_max, ji.key_words, tv.variant) + tv.log_b_delta));
+  c.log2_buckets = (u32)std::min(20, std::max(1, auto_log_b(ji.n_max, hash_slots(ji.key_words, tv.variant)) + tv.log_b_delta));
   return c;
 }
 
