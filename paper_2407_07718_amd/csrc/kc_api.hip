@@ -622,7 +622,7 @@ ExtractArgs extract_args(const Plan& P, const Ws<K>& W, const uint64_t* d_offset
   ea.m = P.m;
   ea.log_b = P.log_b;
   ea.gmax = P.gmax;
-  ea.gmax_magic = (u32)(((1ull << 32) + (u64)P.gmax - 1) / (u64)P.gmax);
+  ea.gmax_magic = ((1u << 17) + (u32)P.gmax - 1) / (u32)P.gmax;
   ea.rec_words = P.rec_words;
   ea.span = P.span;
   ea.spb = P.part_spb;

@@ -116,9 +116,10 @@ __device__ __forceinline__ u32 wave_scan_u32(u32 x) {
   return x;
 }
 
-// q / d and q % d for q < 2^26, 1 <= d <= 64, with magic = ceil(2^32 / d): exact because
-// the rounding error of magic stays below 1/d over that range.
-__device__ __forceinline__ u32 div_small(u32 q, u32 magic) { return __umulhi(q, magic); }
+// q / d for q < 2048, 1 <= d <= 64, with magic = ceil(2^17 / d): the rounding error of magic
+// adds less than q / 2^17 <= 1/64 <= 1/d.  (24-bit products run at the full rate, 32-bit ones at
+// a quarter.)
+__device__ __forceinline__ u32 div_small(u32 q, u32 magic) { return ((q & 0xFFFFFFu) * (magic & 0xFFFFFFu)) >> 17; }
 
 // Exclusive prefix sum over a whole block (blockDim.x a multiple of 64, <= 1024).
 // `scratch` holds at least 17 values of T.  Returns the exclusive prefix; *total is
