@@ -339,7 +339,8 @@ __global__ __launch_bounds__(256) void k_extract(ExtractArgs A) {
   const u64 kmask_cut = ((1ull << k) - 1) & ~1ull;   // no read may start inside (p, p + k)
   const u32 bmask = (1u << A.log_b) - 1u;
 
-  const u64 n_sp = min(n_spans, A.n_span_cap);
+  // a round past the last one has no groups: nothing to look for
+  const u64 n_sp = g_n == 0 ? 0 : min(n_spans, A.n_span_cap);
   const u64 s_end = min(n_sp, (u64)(blockIdx.x + 1) * A.spb);
   // records of this block: slot0 + [0, blk_n)
   const u64 slot0 = MODE == EX_ROUND ? (u64)uniform(A.blk_base[blockIdx.x]) : (u64)blockIdx.x * A.blk_slots;
