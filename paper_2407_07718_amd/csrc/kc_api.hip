@@ -263,7 +263,7 @@ void plan_layout(Plan* p) {
   p->o_scanbuf = take(8ull * 1024);
   p->o_phist = take(4ull * ((u64)1 << p->log_c) * p->nblk_cap);
   p->o_lch0 = take(4ull * p->B);
-  p->o_seg = take(8ull * (std::max<u64>(p->B, (u64)256 << 8) + 2));
+  p->o_seg = take(8ull * (std::max<u64>(p->B, (u64)256 << MSD_G2_MAX) + 2));
   p->o_mhist = take(4ull * 256 * MSD_NB);
   if (rounds) {
     const u64 C = 1ull << p->log_c;
@@ -445,21 +445,23 @@ inline dim3 grid_for(u64 n, u32 block, u32 max_blocks = 1u << 20) {
 }
 
 // Queue one full count on `st`.
-constexpr u32 SEG_CAP_64 = 256 * 16, SEG_CAP_128 = 256 * 8;   // pairs sorted on chip per segment
+constexpr int SEG_T = 512;                                    // threads of k_seg_sort ...
+constexpr u32 SEG_CAP_64 = SEG_T * 8, SEG_CAP_128 = SEG_T * 4;   // ... and pairs sorted on chip per segment
 // Segments of at most seg_wave_cap pairs are sorted by one wave each (k_seg_wave); the
-// survivors' key ranges aim at half that so that most of them are.
-template <typename K> constexpr u32 seg_wave_cap() { return sizeof(K) == 8 ? 1024u : 512u; }
-template <typename K> constexpr u32 seg_range_target() { return seg_wave_cap<K>() / 2; }
+// survivors' key ranges aim below that on average so that nearly all of them are (ranges by
+// powers of two average between half the target and the target).
+template <typename K> constexpr u32 seg_wave_cap() { return sizeof(K) == 8 ? 768u : 448u; }
+template <typename K> constexpr u32 seg_range_target() { return seg_wave_cap<K>() - (sizeof(K) == 8 ? 112u : 80u); }
 
 // max_seg: a host-side bound on the number of segments (the grids need no more blocks).
 template <typename K>
 int seg_sort(K* keys, u32* vals, K* tmp_k, u32* tmp_v, K* out_k, u32* out_v, u64 out_cap, const u64* seg,
-             const u64* n_seg, u64 max_seg, int nbits, bool group_only, const u64* msd_n, u32 msd_target, int n_cu,
+             const u64* n_seg, u64 max_seg, int nbits, bool canonical, bool group_only, const u64* msd_n, u32 msd_target, int n_cu,
              hipStream_t st, int* grid) {
-  constexpr int IT = sizeof(K) == 8 ? 16 : 8;
-  static_assert(256 * IT == (sizeof(K) == 8 ? SEG_CAP_64 : SEG_CAP_128), "segment capacity");
+  constexpr int IT = sizeof(K) == 8 ? 8 : 4;
+  static_assert(SEG_T * IT == (sizeof(K) == 8 ? SEG_CAP_64 : SEG_CAP_128), "segment capacity");
   int per_cu = 0, per_cu_w = 0, rc;
-  if ((rc = blocks_per_cu(k_seg_sort<K, 256, IT>, 256, &per_cu))) return rc;
+  if ((rc = blocks_per_cu(k_seg_sort<K, SEG_T, IT>, SEG_T, &per_cu))) return rc;
   if ((rc = blocks_per_cu(k_seg_wave<K, seg_wave_cap<K>(), SEG_WAVES_PER_BLOCK>, SEG_WAVES_PER_BLOCK * 64,
                           &per_cu_w)))
     return rc;
@@ -477,13 +479,14 @@ int seg_sort(K* keys, u32* vals, K* tmp_k, u32* tmp_v, K* out_k, u32* out_v, u64
   a.seg = seg;
   a.n_seg_ptr = n_seg;
   a.nbits = nbits;
+  a.canonical = canonical ? 1 : 0;
   a.group_only = group_only ? 1 : 0;
   a.msd_n = msd_n;
   a.msd_target = msd_target;
   a.wave_cap = seg_wave_cap<K>();
   hipLaunchKernelGGL((k_seg_wave<K, seg_wave_cap<K>(), SEG_WAVES_PER_BLOCK>), dim3(grid_w),
                      dim3(SEG_WAVES_PER_BLOCK * 64), 0, st, a);
-  hipLaunchKernelGGL((k_seg_sort<K, 256, IT>), dim3(*grid), dim3(256), 0, st, a);
+  hipLaunchKernelGGL((k_seg_sort<K, SEG_T, IT>), dim3(*grid), dim3(SEG_T), 0, st, a);
   return KC_OK;
 }
 
@@ -777,7 +780,7 @@ int count_buckets(const Plan& P, const Ws<K>& W, const u32* blk_base, uint32_t l
                      W.meta + 4, P.chunk_cap, W.kl_nc, W.seg);
   int seg_grid = 0;
   if ((rc = seg_sort<K>(W.kl0k, W.kl0c, W.kl1k, W.kl1c, W.kl0k, W.kl0c, ~0ull, W.seg, W.meta + 1,
-                        std::min<u64>(P.B, P.chunk_cap), 2 * P.k, true, nullptr, 0, n_cu, st, &seg_grid)))
+                        std::min<u64>(P.B, P.chunk_cap), 2 * P.k, true, true, nullptr, 0, n_cu, st, &seg_grid)))
     return rc;
   K* lks = W.kl0k;
   u32* lvs = W.kl0c;
@@ -851,6 +854,7 @@ int sort_survivors(const Plan& P, const Ws<K>& W, K* in_k, u32* in_c, K* mid_k, 
   ma.seg = W.seg;
   ma.n_seg = W.ctrl + C_NSEG;
   ma.nbits = nbits;
+  ma.canonical = key_bits == 0;
   ma.target = seg_range_target<K>();
   // blocks of the coarse pass: about 16K survivors each at most, up to MSD_NB
   ma.nb = (u32)std::min<u64>(MSD_NB, std::max<u64>(1, ceil_div(n_cap, 16384)));
@@ -859,10 +863,10 @@ int sort_survivors(const Plan& P, const Ws<K>& W, K* in_k, u32* in_c, K* mid_k, 
   hipLaunchKernelGGL((k_msd_scatter<K>), dim3(ma.nb), dim3(512), 0, st, ma);
   hipLaunchKernelGGL((k_msd_fine<K>), dim3(256), dim3(1024), 0, st, ma);
   // the key ranges number 256 << g2, g2 growing with the survivor count (at most n_cap)
-  const u64 max_ranges = 256ull << msd_g2(n_cap, nbits, seg_range_target<K>());
+  const u64 max_ranges = 256ull << msd_g2(n_cap, seg_range_target<K>());
   int seg_grid = 0;
   return seg_sort<K>(in_k, in_c, mid_k, mid_c, reinterpret_cast<K*>(d_kmers), d_counts, pair_cap, W.seg,
-                     W.ctrl + C_NSEG, max_ranges, nbits, false, n_ptr, seg_range_target<K>(), n_cu, st, &seg_grid);
+                     W.ctrl + C_NSEG, max_ranges, nbits, key_bits == 0, false, n_ptr, seg_range_target<K>(), n_cu, st, &seg_grid);
 }
 
 template <typename K>
@@ -977,8 +981,8 @@ int warm_launch_facts() {
     if ((rc = warm(u64()))) return rc;
     if ((rc = warm(k128()))) return rc;
   }
-  if ((rc = blocks_per_cu(k_seg_sort<u64, 256, 16>, 256, &v))) return rc;
-  if ((rc = blocks_per_cu(k_seg_sort<k128, 256, 8>, 256, &v))) return rc;
+  if ((rc = blocks_per_cu(k_seg_sort<u64, SEG_T, 8>, SEG_T, &v))) return rc;
+  if ((rc = blocks_per_cu(k_seg_sort<k128, SEG_T, 4>, SEG_T, &v))) return rc;
   if ((rc = blocks_per_cu(k_seg_wave<u64, seg_wave_cap<u64>(), SEG_WAVES_PER_BLOCK>, SEG_WAVES_PER_BLOCK * 64, &v)))
     return rc;
   if ((rc = blocks_per_cu(k_seg_wave<k128, seg_wave_cap<k128>(), SEG_WAVES_PER_BLOCK>, SEG_WAVES_PER_BLOCK * 64, &v)))

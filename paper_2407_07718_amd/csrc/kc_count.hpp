@@ -870,34 +870,6 @@ __device__ __forceinline__ u64 digit_peers_full(u64* tbl, u32 d, u64 ge_mask) {
   return tbl[d];
 }
 
-// Lanes of one wave that share digit d with this lane, as a lane mask.  Every active lane
-// ORs its bit into the wave's table entry of its digit and reads the entry back; when
-// neighbouring lanes hold equal digits (frequent once equal keys cluster) only the
-// first lane of each such run ORs the bits of the whole run, so that the LDS atomics
-// of a wave do not pile up on one address.
-__device__ __forceinline__ u64 digit_peers(u64* tbl, u32 d, bool act) {
-  const u32 lane = lane_id();
-  const u32 dp = (u32)__shfl_up((int)d, 1, 64);
-  const bool ap = __shfl_up((int)act, 1, 64) != 0;
-  const bool same = act && lane > 0 && ap && dp == d;
-  const u64 S = __ballot(same);
-  if (S == 0) {
-    if (act) atomicOr((unsigned long long*)&tbl[d], (unsigned long long)(1ull << lane));
-  } else {
-    // run starts: active lanes not continuing the previous lane's digit
-    const u64 L = __ballot(act && !same);
-    const u64 actm = __ballot(act);   // (ballots stay outside divergent branches)
-    if (act && !same) {
-      const u64 above = L & ~((lane == 63) ? ~0ull : ((2ull << lane) - 1));   // starts after this lane
-      const u32 nl = above ? (u32)__builtin_ctzll(above) : 64u;
-      const u64 upto = (nl == 64) ? ~0ull : ((1ull << nl) - 1);
-      const u64 run = upto & ~((1ull << lane) - 1) & actm;
-      atomicOr((unsigned long long*)&tbl[d], (unsigned long long)run);
-    }
-  }
-  return act ? tbl[d] : 0ull;
-}
-
 // LSD radix passes [p_begin, p_end) over 8-bit digits of keys[0, n_pad) in LDS (with
 // vals moving alongside when HASV).  Per pass: each item is ranked among the equal
 // digits of its wave (digit_peers_full + mbcnt; the lowest lane adds the group size to
@@ -1002,11 +974,7 @@ __device__ __forceinline__ bool mixed_pair(const K* keys, u32 idx, u32 n, int bi
   return low_eq(a, b, bits) && !key_eq(a, b);
 }
 
-// Passes sorted first: 3 digits (24 bits) for up to 1536 keys, else 4 digits (32 bits),
-// so a bucket of D distinct mixed keys needs the remaining passes with probability
-// about D^2 / 2^25 (D <= 1536: under 7%) or D^2 / 2^33 (D <= 4096: 0.2%).  Keys of at
-// most 32 bits are sorted in full without mixing.
-__device__ __forceinline__ int first_passes(u32 n) { return n <= 1536u ? 3 : 4; }
+// Passes that order the keys in full; keys of at most 32 bits are not mixed.
 template <typename K> __device__ __forceinline__ int sort_passes(int k);
 template <> __device__ __forceinline__ int sort_passes<u64>(int k) { return 2 * k <= 32 ? (2 * k + 7) / 8 : 8; }
 template <> __device__ __forceinline__ int sort_passes<k128>(int k) { return (2 * k + 7) / 8; }

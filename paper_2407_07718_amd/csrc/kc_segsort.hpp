@@ -5,8 +5,11 @@
 //     sorted on their own and summed per run;
 //   * the survivors, split by their top key bits into key ranges (two scatter passes),
 //     each range then sorted on its own -- ascending order of the whole output.
-// A segment that fits the block's LDS is sorted there in one read and one write; a
-// longer one is sorted by its block through HBM (stable LSD passes over LDS tiles).
+// A segment that fits on chip is sorted there in one read and one write, by one digit of about
+// log2(length) bits and a ranking inside the digit's bin: keys of a segment spread over the
+// bins, so a bin holds one or two keys and each key's rank is its bin's start plus the smaller
+// keys of its bin.  A longer segment is sorted by its block through HBM (stable LSD passes
+// over LDS tiles).
 #pragma once
 #include "kc_common.hpp"
 #include "kc_count.hpp"
@@ -26,11 +29,30 @@ __device__ __forceinline__ u32 key_field(k128 k, int sh, int nb) {
 
 constexpr u32 MSD_NB = 1024;   // blocks of the coarse pass at most
 
+// The leading 32 bits of a key of nbits bits (fewer bits: moved up).
+__device__ __forceinline__ u32 key_top32(u64 k, int nbits) {
+  return nbits >= 32 ? (u32)(k >> (nbits - 32)) : (u32)k << (32 - nbits);
+}
+__device__ __forceinline__ u32 key_top32(k128 k, int nbits) {   // nbits >= 64
+  const int sh = nbits - 32;
+  return sh >= 64 ? (u32)(k.hi >> (sh - 64)) : (u32)(k.lo >> sh) | (u32)(k.hi << (64 - sh));
+}
+// Where a key falls among all keys, as a 32-bit fraction that never decreases with the key.
+// Canonical k-mers are the smaller of two strands, so their density falls linearly from twice
+// the mean to nothing and the share of keys below x is 1 - (1 - x)^2: that spreads them
+// evenly over ranges and bins (split by their leading bits the first ranges hold twice the
+// mean, which a third of the blocks then waits for).  Wide keys start with the set: as they are.
+template <typename K>
+__device__ __forceinline__ u32 key_place(K k, int nbits, int canonical) {
+  const u32 t = key_top32(k, nbits);
+  return canonical ? ~__umulhi(~t, ~t) : t;
+}
+
 struct MsdArgs {
   const void* in_k;        // dense survivors
   const u32* in_v;
   const u64* n_ptr;        // survivors
-  void* mid_k;             // grouped by the top 8 bits
+  void* mid_k;             // grouped by the top 8 bits of their places
   u32* mid_v;
   void* out_k;             // grouped by the top 8 + g2 bits
   u32* out_v;
@@ -39,22 +61,16 @@ struct MsdArgs {
   u64* seg;                // [(256 << g2) + 1] range starts
   u64* n_seg;              // ranges
   int nbits;               // key bits (2k)
+  int canonical;           // see key_place
   u32 target;              // keys per range wanted
 };
 
-__host__ __device__ __forceinline__ int msd_shift1(int nbits) { return nbits > 8 ? nbits - 8 : 0; }
-__device__ __forceinline__ int msd_bits1(int nbits) { return nbits < 8 ? nbits : 8; }
-// Fine field width: the fewest bits that bring a range to about `target` keys, then
-// rounded up (within 8 and the key) until the bits left below the fields are a whole
-// number of 8-bit passes -- the extra bits save a pass -- unless that would leave ranges
-// of under target / 8 keys on average (then the per-range costs outweigh the pass).
-__host__ __device__ __forceinline__ int msd_g2(u64 n, int nbits, u32 target) {
-  const int room = msd_shift1(nbits);
+// Fine field width: the fewest bits that bring a range to `target` keys on average.
+constexpr int MSD_G2_MAX = 10;
+__host__ __device__ __forceinline__ int msd_g2(u64 n, u32 target) {
   int g2 = 0;
-  while (g2 < 8 && g2 < room && (n >> (8 + g2)) > (u64)target) ++g2;
-  int up = g2;
-  while (up < 8 && up < room && (room - up) % 8 != 0) ++up;
-  return (n >> (8 + up)) >= (u64)(target / 8) ? up : g2;
+  while (g2 < MSD_G2_MAX && (n >> (8 + g2)) > (u64)target) ++g2;
+  return g2;
 }
 
 struct SegArgs {
@@ -68,29 +84,55 @@ struct SegArgs {
   const u64* seg;          // segment i = [seg[i], seg[i + 1])
   const u64* n_seg_ptr;    // number of segments
   int nbits;               // key bits (2k)
+  int canonical;           // see key_place
   int group_only;          // equal keys adjacent suffices (segments of a count's lists)
-  const u64* msd_n;        // when set: segments are key ranges of k_msd_fine over *msd_n keys,
-  u32 msd_target;          //   so only the bits below the range fields are sorted
+  const u64* msd_n;        // when set: segments are key ranges of k_msd_fine over *msd_n keys
+  u32 msd_target;
   u32 wave_cap;            // segments of at most this many pairs are left to k_seg_wave
 };
 
-// Passes of a segment sort: the bits to order are all 2k, or those below the key-range
-// fields when the segments are key ranges.  Grouping only (a count's lists): mixed keys,
-// early exit as in the bucket kernels.
-__device__ __forceinline__ int seg_sort_bits(const SegArgs& A) {
-  return A.msd_n ? msd_shift1(A.nbits) - msd_g2(*A.msd_n, A.nbits, A.msd_target) : A.nbits;
+// Bits of the keys' places that a segment's keys share: those of its range.
+__device__ __forceinline__ int seg_place_bits(const SegArgs& A) {
+  return A.msd_n ? 8 + msd_g2(*A.msd_n, A.msd_target) : 0;
+}
+
+// Bins of a segment of m keys: a power of two of at least m and 64.
+__device__ __forceinline__ int seg_bin_bits(u32 m) { return max(6, 32 - __builtin_clz((m - 1) | 1)); }
+// The bin of a key: the bits of its place below its segment's, or, where equal keys need only
+// be adjacent, bits of its mixed image (a heavy bucket's k-mers share their minimizer).
+template <typename K>
+__device__ __forceinline__ u32 seg_bin(const SegArgs& A, K key, int pbits, int db) {
+  if (A.group_only) return key_field(mix_key(key), 0, db);
+  return (key_place(key, A.nbits, A.canonical) << pbits) >> (32 - db);
+}
+// Keys of the bin [b0, b1) that come before the key at slot `at` (equal keys by their slot).
+template <typename K>
+__device__ __forceinline__ u32 seg_rank(const K* keys, K key, u32 at, u32 b0, u32 b1) {
+  u32 r = b0;
+  if (b1 - b0 > 1)
+    for (u32 i = b0; i < b1; ++i) {
+      const K x = keys[i];
+      r += (key_lt(x, key) || (key_eq(x, key) && i < at)) ? 1u : 0u;
+    }
+  return r;
 }
 
 template <typename K, int T, int ITEMS>
 struct SegSmem {
   static constexpr int W = T / 64, CAP = T * ITEMS;
   K keys[CAP];
-  u32 vals[CAP];
+  union {
+    u32 bins[CAP + 4];                // counts, then first slots; [bins] = keys
+    u32 vals[CAP];
+  } b;
+  // long segments
   u64 tbl[W * 256];
   u32 cnt[2 * W * 256];
   u32 gtot[4];
   u32 dcnt[256], dstart[256], drun[256];
   u64 scr[17];
+  u16 lng[T];                         // the long ones among T segments
+  u32 n_long;
 };
 
 template <typename K, int T, int ITEMS>
@@ -100,41 +142,87 @@ __global__ __launch_bounds__(T) void k_seg_sort(SegArgs A) {
   __shared__ SM S;
   const u32 tid = threadIdx.x;
   const u64 n_seg = *A.n_seg_ptr;
-  const int np = (seg_sort_bits(A) + 7) / 8;
-  // grouping only: mixed keys, early exit as in the bucket kernels
+  const int pbits = seg_place_bits(A);
+  const int np = (A.nbits + 7) / 8;
+  // long segments, grouping only: mixed keys, early exit
   const bool mixed = A.group_only && A.nbits > 32;
   const int np_mixed = sort_passes<K>(A.nbits / 2);
   K* in_k = reinterpret_cast<K*>(A.keys);
   K* tmp_k = reinterpret_cast<K*>(A.tmp_k);
   K* out_k = reinterpret_cast<K*>(A.out_k);
-  for (u64 sgi = blockIdx.x; sgi < n_seg; sgi += gridDim.x) {
+  // the block's segments (block, + grid, ...) are looked through T at a time: most are short
+  for (u64 c0 = blockIdx.x; c0 < n_seg; c0 += (u64)gridDim.x * T) {
+   __syncthreads();
+   if (tid == 0) S.n_long = 0;
+   __syncthreads();
+   {
+    const u64 sgi = c0 + (u64)tid * gridDim.x;
+    if (sgi < n_seg && A.seg[sgi + 1] > A.seg[sgi] + A.wave_cap) S.lng[atomicAdd(&S.n_long, 1u)] = (u16)tid;
+   }
+   __syncthreads();
+   const u32 n_long = S.n_long;
+   for (u32 li = 0; li < n_long; ++li) {
+    const u64 sgi = c0 + (u64)S.lng[li] * gridDim.x;
     const u64 s0 = A.seg[sgi], s1 = A.seg[sgi + 1];
-    if (s1 <= s0 || s1 - s0 <= A.wave_cap) continue;   // uniform over the block
     const u64 n = s1 - s0;
     __syncthreads();                             // LDS of the previous segment is free
     if (n <= CAP) {
-      const u32 m = (u32)n, m_pad = (m + WB - 1) / WB * WB;
-      for (u32 i = tid; i < m_pad; i += T) {
-        K key = key_pad<K>();
-        if (i < m) key = mixed ? mix_key(in_k[s0 + i]) : in_k[s0 + i];
-        S.keys[i] = key;
-        S.vals[i] = i < m ? A.vals[s0 + i] : 0u;
+      const u32 m = (u32)n;
+      const int db = seg_bin_bits(m);
+      const u32 per = (1u << db) / T;              // bins per thread (m > wave_cap >= T: at least 1)
+      for (u32 i = tid; i < 1u << db; i += T) S.b.bins[i] = 0;
+      __syncthreads();
+      K kr[ITEMS];
+      u32 vr[ITEMS], rk[ITEMS];
+#pragma unroll
+      for (int j = 0; j < ITEMS; ++j) {
+        const u32 i = tid + (u32)j * T;
+        if (i < m) {
+          kr[j] = in_k[s0 + i];
+          vr[j] = A.vals[s0 + i];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < ITEMS; ++j)
+        if (tid + (u32)j * T < m) rk[j] = atomicAdd(&S.b.bins[seg_bin(A, kr[j], pbits, db)], 1u);
+      __syncthreads();
+      {
+        u64 sum = 0, tot;
+        for (u32 q = 0; q < per; ++q) sum += S.b.bins[tid * per + q];
+        u32 run = (u32)block_exclusive_scan<u64>(sum, S.scr, &tot);
+        for (u32 q = 0; q < per; ++q) {
+          const u32 c = S.b.bins[tid * per + q];
+          S.b.bins[tid * per + q] = run;
+          run += c;
+        }
+        if (tid == 0) S.b.bins[1u << db] = m;
       }
       __syncthreads();
-      if (mixed) {
-        const int p0 = first_passes(m);
-        lds_sort_passes<K, T, ITEMS, true>(S.keys, S.vals, S.tbl, S.cnt, S.gtot, m_pad, 0, p0, true);
-        bool bad = false;
-        for (u32 i = tid; i < m; i += T) bad |= mixed_pair(S.keys, i, m, 8 * p0);
-        if (__syncthreads_or(bad))
-          lds_sort_passes<K, T, ITEMS, true>(S.keys, S.vals, S.tbl, S.cnt, S.gtot, m_pad, p0, np_mixed, false);
-      } else {
-        lds_sort_passes<K, T, ITEMS, true>(S.keys, S.vals, S.tbl, S.cnt, S.gtot, m_pad, 0, np, true);
-      }
+#pragma unroll
+      for (int j = 0; j < ITEMS; ++j)
+        if (tid + (u32)j * T < m) {
+          rk[j] += S.b.bins[seg_bin(A, kr[j], pbits, db)];
+          S.keys[rk[j]] = kr[j];
+        }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < ITEMS; ++j)
+        if (tid + (u32)j * T < m) {
+          const u32 d = seg_bin(A, kr[j], pbits, db);
+          rk[j] = seg_rank(S.keys, kr[j], rk[j], S.b.bins[d], S.b.bins[d + 1]);
+        }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < ITEMS; ++j)
+        if (tid + (u32)j * T < m) {
+          S.keys[rk[j]] = kr[j];
+          S.b.vals[rk[j]] = vr[j];
+        }
+      __syncthreads();
       for (u32 i = tid; i < m; i += T) {
         if (s0 + i < A.out_cap) {
-          out_k[s0 + i] = mixed ? unmix_key(S.keys[i]) : S.keys[i];
-          A.out_v[s0 + i] = S.vals[i];
+          out_k[s0 + i] = S.keys[i];
+          A.out_v[s0 + i] = S.b.vals[i];
         }
       }
       continue;
@@ -165,12 +253,12 @@ __global__ __launch_bounds__(T) void k_seg_sort(SegArgs A) {
         const u32 m = (u32)min((u64)CAP, n - t0), m_pad = (m + WB - 1) / WB * WB;
         for (u32 i = tid; i < m_pad; i += T) {
           S.keys[i] = i < m ? ld(src_k, s0 + t0 + i, p) : key_pad<K>();
-          S.vals[i] = i < m ? src_v[s0 + t0 + i] : 0u;
+          S.b.vals[i] = i < m ? src_v[s0 + t0 + i] : 0u;
         }
         for (u32 d = tid; d < 256; d += T) S.dcnt[d] = 0;
         __syncthreads();
         // one stable pass on digit p orders the tile by that digit (padding last)
-        lds_sort_passes<K, T, ITEMS, true>(S.keys, S.vals, S.tbl, S.cnt, S.gtot, m_pad, p, p + 1, true);
+        lds_sort_passes<K, T, ITEMS, true>(S.keys, S.b.vals, S.tbl, S.cnt, S.gtot, m_pad, p, p + 1, true);
         for (u32 i = tid; i < m; i += T) {
           const u32 d = key_digit(S.keys[i], 8 * p);
           if (i == 0 || key_digit(S.keys[i - 1], 8 * p) != d) S.dstart[d] = i;
@@ -181,7 +269,7 @@ __global__ __launch_bounds__(T) void k_seg_sort(SegArgs A) {
           const u32 d = key_digit(S.keys[i], 8 * p);
           const u64 at = s0 + S.drun[d] + (i - S.dstart[d]);
           dst_k[at] = S.keys[i];
-          dst_v[at] = S.vals[i];
+          dst_v[at] = S.b.vals[i];
         }
         __syncthreads();
         for (u32 d = tid; d < 256; d += T) S.drun[d] += S.dcnt[d];
@@ -219,116 +307,103 @@ __global__ __launch_bounds__(T) void k_seg_sort(SegArgs A) {
       for (u64 i = tid; i < n; i += T)
         if (s0 + i < A.out_cap) A.out_v[s0 + i] = src_v[s0 + i];
     }
+   }
   }
 }
 
 // ---------------------------------------------------------------------------- short segments
-// Segments of at most WCAP pairs are sorted by one wave each in its own slice of LDS, with
-// no block barriers (the waves of a block are independent), by the same stable LSD
-// passes as the block sort: each item ranked among the equal digits of its row
-// (lane-mask table + mbcnt), rows in order, then the digit counts turned into offsets by
-// one wave scan.
+// Segments of at most WCAP pairs are sorted by one wave each in its own slice of LDS, with no
+// block barriers (the waves of a block are independent).  Bound by LDS round trips: per pair
+// one counter, one staged key, the one or two keys of its bin and the output staging, against
+// nine operations in each of the 5 to 12 LSD passes it replaces.
+// Measured, survivors' segment sorts (all kernels): 43 M u64 pairs 1.24 -> 0.46 ms, 18.6 M 128-bit
+// pairs 1.25 -> 0.35 ms; with LSD passes the longer half of the ranges (split by leading bits)
+// also went to k_seg_sort.
 template <typename K, int WCAP>
 struct SegWaveSmem {
+  static constexpr int BINS = WCAP <= 512 ? 512 : 1024;
+  static_assert(WCAP <= 1024, "bins");
   K keys[WCAP];
-  u32 vals[WCAP];
-  u64 tbl[256];                     // lane masks per digit; all zero between uses
-  u32 cnt[256];                     // digit counts -> digit offsets; zero between passes
+  union {
+    u32 bins[BINS + 4];               // counts, then first slots; [bins] = keys
+    u32 vals[WCAP];
+  } b;
 };
-
-template <typename K, int WCAP>
-__device__ __forceinline__ void wave_sort_pairs(SegWaveSmem<K, WCAP>& S, u32 n_pad, int p_begin, int p_end) {
-  constexpr int ITEMS = WCAP / 64;
-  const u32 lane = lane_id();
-  const u64 ge = ~((1ull << lane) - 1ull);
-  const int per = (int)(n_pad / 64);
-  for (int p = p_begin; p < p_end; ++p) {
-    K kr[ITEMS];
-    u32 vr[ITEMS], rk[ITEMS];
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-      if (j < per) {
-        kr[j] = S.keys[(u32)j * 64u + lane];
-        vr[j] = S.vals[(u32)j * 64u + lane];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-      if (j < per) {
-        const u32 d = key_digit(kr[j], 8 * p);
-        const u64 mask = digit_peers_full(S.tbl, d, ge);
-        const u32 base = S.cnt[d];
-        const u32 lr = mbcnt64(mask);
-        if (lr == 0) {
-          S.cnt[d] = base + (u32)__popcll(mask);
-          S.tbl[d] = 0;
-        }
-        rk[j] = base + lr;
-      }
-    }
-    // counts -> exclusive digit offsets; lane l owns digits 4l..4l+3
-    const u32 c0 = S.cnt[4 * lane], c1 = S.cnt[4 * lane + 1], c2 = S.cnt[4 * lane + 2], c3 = S.cnt[4 * lane + 3];
-    const u32 s4 = c0 + c1 + c2 + c3;
-    const u32 ex = wave_scan_u32(s4) - s4;
-    S.cnt[4 * lane] = ex;
-    S.cnt[4 * lane + 1] = ex + c0;
-    S.cnt[4 * lane + 2] = ex + c0 + c1;
-    S.cnt[4 * lane + 3] = ex + c0 + c1 + c2;
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-      if (j < per) {
-        const u32 at = S.cnt[key_digit(kr[j], 8 * p)] + rk[j];
-        S.keys[at] = kr[j];
-        S.vals[at] = vr[j];
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) S.cnt[4 * lane + i] = 0;
-  }
-}
 
 // Waves take segments in turn (segment = global wave index, + all waves of the grid, ...);
 // a segment longer than WCAP is left to k_seg_sort.
 template <typename K, int WCAP, int WPB>
 __global__ __launch_bounds__(WPB * 64) void k_seg_wave(SegArgs A) {
+  constexpr int ITEMS = WCAP / 64;
   __shared__ SegWaveSmem<K, WCAP> WS[WPB];
-  const u32 lane = lane_id(), wave = threadIdx.x >> 6;
+  const u32 lane = lane_id(), wave = uniform(threadIdx.x >> 6);
   SegWaveSmem<K, WCAP>& S = WS[wave];
-  for (u32 i = lane; i < 256; i += 64) {
-    S.tbl[i] = 0;
-    S.cnt[i] = 0;
-  }
   const u64 n_seg = *A.n_seg_ptr;
-  const int np = (seg_sort_bits(A) + 7) / 8;
-  const bool mixed = A.group_only && A.nbits > 32;
-  const int np_mixed = sort_passes<K>(A.nbits / 2);
+  const int pbits = seg_place_bits(A);
   const K* in_k = reinterpret_cast<const K*>(A.keys);
   K* out_k = reinterpret_cast<K*>(A.out_k);
   for (u64 sgi = (u64)blockIdx.x * WPB + wave; sgi < n_seg; sgi += (u64)gridDim.x * WPB) {
-    const u64 s0 = A.seg[sgi], s1 = A.seg[sgi + 1];
+    const u64 s0 = uniform(A.seg[sgi]), s1 = uniform(A.seg[sgi + 1]);
     if (s1 <= s0 || s1 - s0 > WCAP) continue;    // uniform over the wave
-    const u32 m = (u32)(s1 - s0), m_pad = (m + 63u) & ~63u;
-    for (u32 i = lane; i < m_pad; i += 64) {
-      K key = key_pad<K>();
-      if (i < m) key = mixed ? mix_key(in_k[s0 + i]) : in_k[s0 + i];
-      S.keys[i] = key;
-      S.vals[i] = i < m ? A.vals[s0 + i] : 0u;
-    }
-    if (mixed) {
-      const int p0 = first_passes(m);
-      wave_sort_pairs<K, WCAP>(S, m_pad, 0, p0);
-      bool bad = false;
-      for (u32 i = lane; i < m; i += 64) bad |= mixed_pair(S.keys, i, m, 8 * p0);
-      if (__ballot(bad)) wave_sort_pairs<K, WCAP>(S, m_pad, p0, np_mixed);
-    } else {
-      wave_sort_pairs<K, WCAP>(S, m_pad, 0, np);
-    }
-    for (u32 i = lane; i < m; i += 64) {
-      if (s0 + i < A.out_cap) {
-        out_k[s0 + i] = mixed ? unmix_key(S.keys[i]) : S.keys[i];
-        A.out_v[s0 + i] = S.vals[i];
+    const u32 m = (u32)(s1 - s0), rows = (m + 63) / 64;
+    const int db = seg_bin_bits(m);
+    const u32 per = (1u << db) / 64;             // bins per lane, a power of two
+    K kr[ITEMS];
+    u32 vr[ITEMS], rk[ITEMS];
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+      const u32 i = (u32)j * 64 + lane;
+      if ((u32)j < rows && i < m) {
+        kr[j] = in_k[s0 + i];
+        vr[j] = A.vals[s0 + i];
       }
     }
+    for (u32 q = 0; q < per; ++q) S.b.bins[q * 64 + lane] = 0;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j)
+      if ((u32)j < rows && (u32)j * 64 + lane < m) rk[j] = atomicAdd(&S.b.bins[seg_bin(A, kr[j], pbits, db)], 1u);
+    __builtin_amdgcn_wave_barrier();
+    {
+      u32 sum = 0;
+      for (u32 q = 0; q < per; ++q) sum += S.b.bins[lane * per + q];
+      u32 run = wave_scan_u32(sum) - sum;
+      for (u32 q = 0; q < per; ++q) {
+        const u32 c = S.b.bins[lane * per + q];
+        S.b.bins[lane * per + q] = run;
+        run += c;
+      }
+      if (lane == 0) S.b.bins[1u << db] = m;
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j)
+      if ((u32)j < rows && (u32)j * 64 + lane < m) {
+        rk[j] += S.b.bins[seg_bin(A, kr[j], pbits, db)];
+        S.keys[rk[j]] = kr[j];
+      }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j)
+      if ((u32)j < rows && (u32)j * 64 + lane < m) {
+        const u32 d = seg_bin(A, kr[j], pbits, db);
+        rk[j] = seg_rank(S.keys, kr[j], rk[j], S.b.bins[d], S.b.bins[d + 1]);
+      }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j)
+      if ((u32)j < rows && (u32)j * 64 + lane < m) {
+        S.keys[rk[j]] = kr[j];
+        S.b.vals[rk[j]] = vr[j];
+      }
+    __builtin_amdgcn_wave_barrier();
+    for (u32 i = lane; i < m; i += 64) {
+      if (s0 + i < A.out_cap) {
+        out_k[s0 + i] = S.keys[i];
+        A.out_v[s0 + i] = S.b.vals[i];
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
@@ -350,7 +425,7 @@ __global__ __launch_bounds__(256) void k_merge_segs(const u32* __restrict__ klof
 // The survivors are split into key ranges by their top bits: a coarse pass on the top 8
 // bits (per-block LDS histograms, one scan, a scatter staged through LDS) and a fine
 // pass, one block per coarse group, on the next g2 bits, g2 chosen from the survivor
-// count so that a range averages about `target` keys.  The fine pass writes the range
+// count so that a range averages at most `target` keys.  The fine pass writes the range
 // table in key order.
 template <typename K>
 __global__ __launch_bounds__(256) void k_msd_hist(MsdArgs A) {
@@ -358,26 +433,26 @@ __global__ __launch_bounds__(256) void k_msd_hist(MsdArgs A) {
   const u64 n = *A.n_ptr;
   const u64 per = (n + A.nb - 1) / A.nb;
   const u64 a = min(n, blockIdx.x * per), b = min(n, a + per);
-  const int sh = msd_shift1(A.nbits), nb = msd_bits1(A.nbits);
   const K* in = reinterpret_cast<const K*>(A.in_k);
   h[threadIdx.x] = 0;
   __syncthreads();
-  for (u64 i = a + threadIdx.x; i < b; i += 256) atomicAdd(&h[key_field(in[i], sh, nb)], 1u);
+  for (u64 i = a + threadIdx.x; i < b; i += 256) atomicAdd(&h[key_place(in[i], A.nbits, A.canonical) >> 24], 1u);
   __syncthreads();
   A.hist[(u64)threadIdx.x * A.nb + blockIdx.x] = h[threadIdx.x];
 }
 
 // Elements [a, b) of in moved to out in rounds of R staged through LDS: each round is
-// ranked by its field (bits [sh, sh + nbits) of the key, nbits <= 8) with LDS counters,
+// ranked by its field (fb bits of its place below the leading `pb`, 2^fb <= F) with LDS counters,
 // staged in field order and written so that consecutive threads write consecutive slots
 // of a field's range; gpos[f] is the next output slot of field f (advanced per round).
-// cnt, lbase and gpos have 256 entries.  Block-wide (barriers inside).
-template <typename K, u32 T>
+// cnt, lbase and gpos have F <= T entries.  Block-wide (barriers inside).
+template <typename K, u32 T, u32 F>
 __device__ __forceinline__ void msd_rounds(const K* __restrict__ in, const u32* __restrict__ in_v, u64 a, u64 b,
-                                           int sh, int nbits, K* __restrict__ out, u32* __restrict__ out_v, K* sk,
+                                           const MsdArgs& A, int pb, int fb, K* __restrict__ out, u32* __restrict__ out_v, K* sk,
                                            u32* sv, u32* cnt, u32* lbase, u32* gpos, u64* scr) {
   constexpr u32 R = sizeof(K) == 8 ? 4096u : 2048u, IT = R / T;
   const u32 tid = threadIdx.x;
+  auto field = [&](K k) { return fb ? (key_place(k, A.nbits, A.canonical) << pb) >> (32 - fb) : 0u; };
   for (u64 r0 = a; r0 < b; r0 += R) {
     const u32 nr = (u32)min((u64)R, b - r0);
     K kr[IT];
@@ -393,14 +468,15 @@ __device__ __forceinline__ void msd_rounds(const K* __restrict__ in, const u32* 
 #pragma unroll
     for (u32 j = 0; j < IT; ++j) {
       if (tid + j * T < nr) {
-        cc[j] = key_field(kr[j], sh, nbits);
+        cc[j] = field(kr[j]);
         rk[j] = atomicAdd(&cnt[cc[j]], 1u);
       }
     }
     __syncthreads();
     u64 tot;
-    const u32 ex = (u32)block_exclusive_scan<u64>(tid < 256 ? (u64)cnt[tid] : 0ull, scr, &tot);
-    if (tid < 256) lbase[tid] = ex;
+    static_assert(F <= T, "one thread per field");
+    const u32 ex = (u32)block_exclusive_scan<u64>(tid < F ? (u64)cnt[tid] : 0ull, scr, &tot);
+    if (tid < F) lbase[tid] = ex;
     __syncthreads();
 #pragma unroll
     for (u32 j = 0; j < IT; ++j) {
@@ -412,13 +488,13 @@ __device__ __forceinline__ void msd_rounds(const K* __restrict__ in, const u32* 
     }
     __syncthreads();
     for (u32 i = tid; i < nr; i += T) {
-      const u32 c = key_field(sk[i], sh, nbits);
+      const u32 c = field(sk[i]);
       const u64 d = (u64)gpos[c] + (i - lbase[c]);
       out[d] = sk[i];
       out_v[d] = sv[i];
     }
     __syncthreads();
-    if (tid < 256) {
+    if (tid < F) {
       gpos[tid] += cnt[tid];
       cnt[tid] = 0;
     }
@@ -443,47 +519,37 @@ __global__ __launch_bounds__(512) void k_msd_scatter(MsdArgs A) {
     gpos[tid] = A.hist[(u64)tid * A.nb + blockIdx.x];
   }
   __syncthreads();
-  msd_rounds<K, T>(reinterpret_cast<const K*>(A.in_k), A.in_v, a, b, msd_shift1(A.nbits), msd_bits1(A.nbits),
+  msd_rounds<K, T, 256>(reinterpret_cast<const K*>(A.in_k), A.in_v, a, b, A, 0, 8,
                    reinterpret_cast<K*>(A.mid_k), A.mid_v, sk, sv, cnt, lbase, gpos, scr);
 }
 
-// Fine pass: one block per coarse group; counts its sub-ranges, writes the range table,
+// Fine pass (43 M pairs: 0.69 ms with groups by leading bits, the first twice as long as the
+// mean; 0.50 ms by place): one block per coarse group; counts its sub-ranges, writes the range table,
 // then moves the group's elements into their sub-ranges in staged rounds.
 template <typename K>
 __global__ __launch_bounds__(1024) void k_msd_fine(MsdArgs A) {
   constexpr u32 T = 1024, R = sizeof(K) == 8 ? 4096u : 2048u;
   __shared__ K sk[R];
   __shared__ u32 sv[R];
-  __shared__ u32 cnt[256], lbase[256], cur[256];
+  __shared__ u32 cnt[1 << MSD_G2_MAX], lbase[1 << MSD_G2_MAX], cur[1 << MSD_G2_MAX];
   __shared__ u64 scr[17];
   const u32 g = blockIdx.x, tid = threadIdx.x;
   const u64 n = *A.n_ptr;
-  const int sh1 = msd_shift1(A.nbits), g2 = msd_g2(n, A.nbits, A.target), sh2 = sh1 - g2;
+  const int g2 = msd_g2(n, A.target);
   const u32 F = 1u << g2;
   const u64 a = A.hist[(u64)g * A.nb];
   const u64 b = g + 1 < 256 ? (u64)A.hist[(u64)(g + 1) * A.nb] : n;
   const K* mid = reinterpret_cast<const K*>(A.mid_k);
-  if (tid < 256) cnt[tid] = 0;
+  cnt[tid] = 0;
   __syncthreads();
-  for (u64 i = a + tid; i < b; i += T) atomicAdd(&cnt[key_field(mid[i], sh2, g2)], 1u);
+  for (u64 i = a + tid; i < b; i += T) atomicAdd(&cnt[g2 ? (key_place(mid[i], A.nbits, A.canonical) << 8) >> (32 - g2) : 0u], 1u);
   __syncthreads();
-  if (tid < 64) {
-    // exclusive prefix over the F <= 256 sub-ranges: lane l owns sub-ranges 4l..4l+3
-    u32 c[4], s = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      c[q] = 4 * tid + q < F ? cnt[4 * tid + q] : 0u;
-      s += c[q];
-    }
-    u32 run = wave_scan_u32(s) - s;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const u32 f = 4 * tid + q;
-      if (f < F) {
-        cur[f] = (u32)a + run;
-        A.seg[((u64)g << g2) + f] = a + run;
-      }
-      run += c[q];
+  {
+    u64 tot;
+    const u32 run = (u32)block_exclusive_scan<u64>(tid < F ? (u64)cnt[tid] : 0ull, scr, &tot);
+    if (tid < F) {
+      cur[tid] = (u32)a + run;
+      A.seg[((u64)g << g2) + tid] = a + run;
     }
   }
   if (g == 0 && tid == 0) {
@@ -491,7 +557,7 @@ __global__ __launch_bounds__(1024) void k_msd_fine(MsdArgs A) {
     *A.n_seg = (u64)256 << g2;
   }
   __syncthreads();
-  if (tid < 256) cnt[tid] = 0;
+  cnt[tid] = 0;
   __syncthreads();
-  msd_rounds<K, T>(mid, A.mid_v, a, b, sh2, g2, reinterpret_cast<K*>(A.out_k), A.out_v, sk, sv, cnt, lbase, cur, scr);
+  msd_rounds<K, T, 1u << MSD_G2_MAX>(mid, A.mid_v, a, b, A, 8, g2, reinterpret_cast<K*>(A.out_k), A.out_v, sk, sv, cnt, lbase, cur, scr);
 }
