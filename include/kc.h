@@ -193,7 +193,8 @@ int kc_count_device_noalloc(const uint8_t *d_reads, uint64_t total_bases, const 
  * Pairs, counts, histogram and totals are exactly those of kc_count; m plays no part.
  * Internally each window travels as (canonical key, 32-bit base offset) through one
  * stable LSD radix sort; the offset is decoded into (read, position) only for the
- * reported k-mers.  Read indices and in-read offsets are 32-bit: n_reads < 2^32. */
+ * reported k-mers.  Larger counts with min_freq >= 2 run the plain count first and look
+ * each window up in its pairs (same results).  Read indices and in-read offsets are 32-bit: n_reads < 2^32. */
 typedef struct kc_ext_result {
   kc_result pairs;         /* k-mers, counts, histogram, totals (totals.n_occ = n_occ) */
   uint64_t n_occ;          /* sum of the reported counts */
@@ -214,7 +215,9 @@ int kc_count_ext(const uint8_t *reads, const uint64_t *offsets, uint64_t n_reads
 void kc_ext_result_free(kc_ext_result *res);
 
 /* Bytes of device workspace kc_count_ext_device needs (0 on bad arguments, total_bases
- * or n_reads >= 2^32 included, or when cfg->hbm_budget is set and no plan fits it).
+ * or n_reads >= 2^32 included, or when cfg->hbm_budget is set and no plan fits it).  About
+ * 29 bytes per base (k >= 32: 45), or 49 (89) where the count may go through its pairs; a
+ * workspace that holds only the former is accepted too, and the windows are sorted.
  *
  * Memory-bounded counting (Section 3.1: with too little memory for an out-of-place sort
  * the paper switches to an in-place one; Section 3.3: the exchange runs in rounds of

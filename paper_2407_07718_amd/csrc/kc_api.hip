@@ -394,10 +394,12 @@ void radix_passes(K*& src, K*& dst, u32*& vs, u32*& vd, const u64* n_ptr, u32* c
                   int nbits, hipStream_t st, int* passes) {
   constexpr int ITEMS = sizeof(K) == 8 ? RADIX_ITEMS_64 : RADIX_ITEMS_128;
   for (int sh = 0; sh < nbits; sh += DB) {
-    hipLaunchKernelGGL((k_radix_upsweep<K, DB>), dim3(nb), dim3(256), 0, st, src, n_ptr, counts, sh);
+    DigitSel D;
+    D.sh = sh;
+    hipLaunchKernelGGL((k_radix_upsweep<K, DB>), dim3(nb), dim3(256), 0, st, src, n_ptr, counts, D);
     hipLaunchKernelGGL(k_radix_rowscan, dim3(1u << DB), dim3(256), 0, st, counts, nb, totals);
-    hipLaunchKernelGGL((k_radix_downsweep<K, HASV, RADIX_T, ITEMS, KC_RADIX_SHARED != 0, DB>), dim3(nb),
-                       dim3(RADIX_T), 0, st, src, dst, vs, vd, n_ptr, counts, totals, sh);
+    hipLaunchKernelGGL((k_radix_downsweep<K, HASV, RADIX_T, ITEMS, KC_RADIX_SHARED != 0, DB, StorePairs<K>>), dim3(nb),
+                       dim3(RADIX_T), 0, st, src, vs, StorePairs<K>{dst, vd}, n_ptr, counts, totals, D);
     std::swap(src, dst);
     std::swap(vs, vd);
     ++*passes;
@@ -1336,6 +1338,11 @@ struct ExtPlan {
   u32 nb = 1;                      // radix blocks
   u64 o_packed, o_nmask, o_starts, o_k0, o_k1, o_v0, o_v1, o_hp, o_blk, o_bp, o_bo, o_rid, o_ctrl, o_cnt, o_tot,
       o_scan, o_bins, o_rb, bytes = 0;
+  // one pass by count (see kc_ext.hpp): the plain count's plan, and the regions after it
+  bool by_count = false;
+  u64 bytes_sort = 0;              // workspace that the sort of all windows needs
+  Plan cp;
+  u64 o_c_rid = 0, o_c_blk = 0, o_c_off = 0, o_c_cnt = 0, o_c_tot = 0, o_c_ctrl = 0;
 };
 
 enum ExtCtrl : int {
@@ -1395,6 +1402,56 @@ void ext_layout(ExtPlan* p, u64 cap) {
   p->bytes = o;
 }
 
+// A one-pass extension count by the plain count, where that is the faster way.  Sorting all
+// windows costs a pass over them per digit of the k-mer; counting costs about 55 launches, one
+// random read per window and three passes over 8-byte pairs, whatever k.  Measured with 150-base
+// reads that cover their genome 5 and 40 times, by count against sorted:
+//   k = 51: 2^22 bases 547 and 458 us against 805 and 859 (2^21: 483 and 440 against 507 and 526)
+//   k = 31: 2^26 bases 4838 and 3504 us against 5584 and 5604 (2^24: 1459 and 1092 against 1410
+//           and 1490, 2^22: 526 and 425 against 433 and 467)
+//   k = 26: 2^26 bases 4999 and 3666 us against 5150 and 5158 (2^28: 21.3 and 13.7 ms against
+//           19.0 and 19.3), k = 22: 5165 and 3823 us against 4714 and 4707
+// so from k = 29 (eight 8-bit digits) on 2^25 bases, from k = 32 (16-byte keys) on 2^22; up to
+// 2^30, beyond which the workspace -- the plain count's, 49 bytes per base against 29 (k >= 32:
+// 89 against 45) -- leaves too little of the HBM.  Used when min_freq >= 2: half as many pairs as
+// windows at most, so that their table fits one region.
+constexpr u64 EXT_COUNT_MAX = 1ull << 30;
+constexpr int EXT_COUNT_K = 29;
+inline u64 ext_count_min(int k) { return k <= 31 ? 1ull << 25 : 1ull << 22; }
+constexpr int EXT_COUNT_DB = 9;    // digits of the passes by pair index: at most 9 bits
+
+bool ext_plan_by_count(ExtPlan* p, u64 budget) {
+  p->by_count = false;
+  p->bytes_sort = p->bytes;
+  if (p->k < EXT_COUNT_K || p->R < ext_count_min(p->k) || p->R > EXT_COUNT_MAX) return false;
+  const int m = std::min(21, std::max((p->k + 1) / 2, p->k - 14));
+  if (!make_plan(p->R, p->n_reads, p->R, p->k, m, 2, nullptr, &p->cp)) return false;
+  u64 o = align_up(p->cp.bytes, 256);
+  auto take = [&](u64 bytes) {
+    u64 r = o;
+    o = align_up(o + bytes, 256);
+    return r;
+  };
+  p->o_c_rid = take(4 * p->n_blk);
+  p->o_c_blk = take(4 * p->n_tiles);
+  p->o_c_off = take(4 * p->n_tiles);
+  p->o_c_cnt = take(4ull * (1u << EXT_COUNT_DB) * 1024);
+  p->o_c_tot = take(4ull * (1u << EXT_COUNT_DB));
+  p->o_c_ctrl = take(8ull * X_WORDS);
+  if (budget && o > budget) return false;
+  p->bytes = std::max(p->bytes, o);
+  p->by_count = true;
+  return true;
+}
+
+// Where the memory at hand is less than the count needs, all windows are sorted instead if
+// that fits.
+void ext_fit(ExtPlan* p, u64 bytes) {
+  if (!p->by_count || bytes >= p->bytes || bytes < p->bytes_sort) return;
+  p->by_count = false;
+  p->bytes = p->bytes_sort;
+}
+
 // budget 0: no limit.  Returns false when the input is too large or the budget cannot
 // hold even small rounds.
 bool make_ext_plan(u64 R, u64 n_reads, int k, u64 budget, ExtPlan* p) {
@@ -1413,6 +1470,7 @@ bool make_ext_plan(u64 R, u64 n_reads, int k, u64 budget, ExtPlan* p) {
   p->n_blk = (R >> p->blk_sh) + 2;
   p->rounds = 1;
   ext_layout(p, p->N);
+  if (ext_plan_by_count(p, budget)) return true;
   if (!budget || p->bytes <= budget) return true;
   // rounds: sort buffers sized from what the budget leaves after the fixed part
   ExtPlan q = *p;
@@ -1481,7 +1539,7 @@ int enqueue_ext(const ExtPlan& P, void* ws, const uint8_t* d_reads, const uint64
   if (P.n_reads) {
     hipLaunchKernelGGL(k_read_starts, grid_for(P.n_reads, 256), dim3(256), 0, st, d_offsets, P.n_reads, P.R, starts,
                        flags);
-    hipLaunchKernelGGL(k_ext_read_blocks, grid_for(P.n_reads, 256), dim3(256), 0, st, d_offsets, P.n_reads, P.R, rid,
+    hipLaunchKernelGGL(k_ext_read_blocks, grid_for(P.n_reads, 256, 512), dim3(256), 0, st, d_offsets, P.n_reads, P.R, rid,
                        P.n_blk, P.blk_sh, ctrl + X_MAXLEN);
   }
   // window positions: every base of the buffer; the kernels keep the windows inside
@@ -1614,6 +1672,125 @@ int ext_check(int k, uint32_t lo, uint32_t hi, uint64_t hist_len, uint64_t total
   return KC_OK;
 }
 
+// The extension count by the plain count (see kc_ext.hpp).
+template <typename K>
+int enqueue_ext_by_count(const ExtPlan& E, void* ws, const uint8_t* d_reads, const uint64_t* d_offsets, uint32_t lo,
+                         uint32_t hi, uint64_t hist_len, uint64_t* d_kmers, uint32_t* d_counts, uint64_t pair_cap,
+                         uint64_t* d_occ_off, uint32_t* d_occ_read, uint32_t* d_occ_pos, uint64_t occ_cap,
+                         uint64_t* d_hist, DevTotals* d_tot, hipStream_t st) {
+  const Plan& P = E.cp;
+  int n_cu = 0;
+  int rc = device_info(&n_cu);
+  if (rc) return rc;
+  const Ws<K> W = ws_ptrs<K>(P, ws);
+  u32* rid = at<u32>(ws, E.o_c_rid);
+  u32* blk = at<u32>(ws, E.o_c_blk);
+  u32* off = at<u32>(ws, E.o_c_off);
+  u32* cnt = at<u32>(ws, E.o_c_cnt);
+  u32* tot = at<u32>(ws, E.o_c_tot);
+  u64* ctrl = at<u64>(ws, E.o_c_ctrl);
+  stage_mark(0, st);
+  launch_clear<K>(P, W, d_hist, hist_len, d_tot, st);
+  {
+    FillList fl{};
+    fl.p[0] = rid;
+    fl.n[0] = E.n_blk;
+    fl.v[0] = 0xFFFFFFFFu;
+    fl.p[1] = (u32*)ctrl;
+    fl.n[1] = 2ull * X_WORDS;
+    fl.cnt = 2;
+    hipLaunchKernelGGL(k_fill_multi, grid_for(E.n_blk, 256, 4096), dim3(256), 0, st, fl);
+  }
+  launch_encode<K>(P, W, d_reads, d_offsets, st);
+  if (P.n_reads)
+    hipLaunchKernelGGL(k_ext_read_blocks, grid_for(P.n_reads, 256, 512), dim3(256), 0, st, d_offsets, P.n_reads, P.R, rid,
+                       E.n_blk, E.blk_sh, ctrl + X_MAXLEN);
+  stage_mark(1, st);
+  launch_extract<EX_ONE>(P, extract_args<K>(P, W, d_offsets), st);
+  // the pairs in key order at Z (the sort's second buffer doubles as its output: a range is
+  // read from X and written to its own place)
+  if ((rc = count_buckets<K>(P, W, nullptr, lo, hi, hist_len, d_hist, d_tot, W.kl0k, W.kl0c, nullptr, ~0ull, false,
+                             n_cu, st)))
+    return rc;
+  K* const pk = W.s0k;
+  u32* const pc = W.s0c;
+  if ((rc = sort_survivors<K>(P, W, W.kl0k, W.kl0c, pk, pc, W.surv_nc, P.surv_cap, reinterpret_cast<uint64_t*>(pk), pc,
+                              P.surv_cap, n_cu, st)))
+    return rc;
+  const u64 n_cap = P.surv_cap / lo + 1;         // pairs at most
+  const u64* n_ptr = W.surv_nc;
+  hipLaunchKernelGGL((k_copy_pairs<K>), grid_for(std::min<u64>(n_cap, std::max<u64>(1, pair_cap)), 256, 4096), dim3(256),
+                     0, st, pk, pc, n_ptr, pair_cap, reinterpret_cast<K*>(d_kmers), d_counts);
+  const u64 otiles = std::min<u64>(E.n_tiles, ceil_div(n_cap, EXT_TILE));
+  hipLaunchKernelGGL(k_ext_offsets<false>, dim3((u32)otiles), dim3(EXT_T), 0, st, pc, n_ptr, off, d_occ_off, pair_cap);
+  scan_u32(off, off, (const u64*)nullptr, otiles, ctrl + X_NOCC, W.scanbuf, st);
+  hipLaunchKernelGGL(k_ext_offsets<true>, dim3((u32)otiles), dim3(EXT_T), 0, st, pc, n_ptr, off, d_occ_off, pair_cap);
+  stage_mark(2, st);
+  // the pairs' table at X, the windows found at Y
+  u32* tab = W.recA;
+  u32* found = W.hp;
+  const u64 slot_cap = P.slots;   // (the region holds that many records of a slot's size)
+  hipLaunchKernelGGL((k_ext_table_clear<K>), dim3(2048), dim3(256), 0, st, n_ptr, slot_cap,
+                     reinterpret_cast<uint4*>(tab));
+  hipLaunchKernelGGL((k_ext_table_insert<K>), grid_for(n_cap, 256, 4096), dim3(256), 0, st, pk, n_ptr,
+                     slot_cap, tab);
+  ExtWinArgs wa{};
+  wa.packed = W.packed;
+  wa.nmask = W.nmask;
+  wa.starts = W.starts;
+  wa.offsets = d_offsets;
+  wa.n_reads = P.n_reads;
+  wa.R = P.R;
+  wa.n_pos = P.R >= (u64)P.k ? P.R - (u64)P.k + 1 : 0;
+  wa.k = P.k;
+  wa.blk = blk;
+  wa.rid = rid;
+  wa.n_blk = E.n_blk;
+  wa.blk_sh = E.blk_sh;
+  wa.rbits = read_bits(P.n_reads);
+  wa.max_len = ctrl + X_MAXLEN;
+  wa.n_packed = P.n_packed;
+  wa.n_mask = P.n_mask;
+  hipLaunchKernelGGL((k_ext_lookup<K>), dim3((u32)E.n_tiles), dim3(EXT_T), 0, st, wa, n_ptr, slot_cap,
+                     reinterpret_cast<const uint4*>(tab), found);
+  stage_mark(3, st);
+  scan_u32(blk, blk, (const u64*)nullptr, E.n_tiles, ctrl + X_NWIN, W.scanbuf, st);
+  const u64 N = P.kl_cap;
+  u32* i0 = W.ptmp_rec;
+  u32 *v0 = i0 + N, *i1 = i0 + 2 * N, *v1 = i0 + 3 * N;
+  hipLaunchKernelGGL(k_ext_compact, dim3((u32)E.n_tiles), dim3(EXT_T), 0, st, wa, found, i0, v0);
+  stage_mark(4, st);
+  // sorted by pair index: the fewest passes of at most 9 bits that the most pairs would need
+  int ibits = 1;
+  while (ibits < 32 && (n_cap >> ibits)) ++ibits;
+  DigitSel D;
+  D.n_idx = n_ptr;
+  D.passes = (ibits + EXT_COUNT_DB - 1) / EXT_COUNT_DB;
+  constexpr int ITEMS = 16;
+  const u32 nb = (u32)std::min<u64>(1024, std::max<u64>(1, ceil_div(N, 2ull * RADIX_T * ITEMS)));
+  const u64* nw = ctrl + X_NWIN;
+  for (D.pass = 0; D.pass < D.passes; ++D.pass) {
+    hipLaunchKernelGGL((k_radix_upsweep<u32, EXT_COUNT_DB>), dim3(nb), dim3(256), 0, st, i0, nw, cnt, D);
+    hipLaunchKernelGGL(k_radix_rowscan, dim3(1u << EXT_COUNT_DB), dim3(256), 0, st, cnt, nb, tot);
+    if (D.pass + 1 < D.passes) {
+      hipLaunchKernelGGL((k_radix_downsweep<u32, true, RADIX_T, ITEMS, false, EXT_COUNT_DB, StorePairs<u32>>), dim3(nb),
+                         dim3(RADIX_T), 0, st, i0, v0, StorePairs<u32>{i1, v1}, nw, cnt, tot, D);
+    } else {
+      const StoreOcc out{d_occ_read, d_occ_pos, occ_cap, wa.rbits, wa.max_len, d_offsets, P.n_reads, rid, E.n_blk,
+                         E.blk_sh};
+      hipLaunchKernelGGL((k_radix_downsweep<u32, true, RADIX_T, ITEMS, false, EXT_COUNT_DB, StoreOcc>), dim3(nb),
+                         dim3(RADIX_T), 0, st, i0, v0, out, nw, cnt, tot, D);
+    }
+    std::swap(i0, i1);
+    std::swap(v0, v1);
+  }
+  hipLaunchKernelGGL(k_ext_count_totals, dim3(1), dim3(64), 0, st, d_tot, W.meta, W.surv_n, ctrl + X_NOCC, W.flags,
+                     d_occ_off, pair_cap);
+  stage_mark(5, st);
+  HIP_TRY(hipGetLastError());
+  return KC_OK;
+}
+
 int enqueue_ext_any(const ExtPlan& P, void* ws, const uint8_t* d_reads, const uint64_t* d_offsets, uint32_t lo,
                     uint32_t hi, uint64_t hist_len, uint64_t* d_kmers, uint32_t* d_counts, uint64_t pair_cap,
                     uint64_t* d_occ_off, uint32_t* d_occ_read, uint32_t* d_occ_pos, uint64_t occ_cap,
@@ -1628,7 +1805,12 @@ int enqueue_ext_any(const ExtPlan& P, void* ws, const uint8_t* d_reads, const ui
     g_ev_cur = &g_ev_pool[g_ev_used++];
   }
   int rc;
-  if (P.key_words == 1)
+  if (P.by_count && lo >= 2)
+    rc = P.key_words == 1 ? enqueue_ext_by_count<u64>(P, ws, d_reads, d_offsets, lo, hi, hist_len, d_kmers, d_counts,
+                                                      pair_cap, d_occ_off, d_occ_read, d_occ_pos, occ_cap, d_hist, d_tot, st)
+                          : enqueue_ext_by_count<k128>(P, ws, d_reads, d_offsets, lo, hi, hist_len, d_kmers, d_counts,
+                                                       pair_cap, d_occ_off, d_occ_read, d_occ_pos, occ_cap, d_hist, d_tot, st);
+  else if (P.key_words == 1)
     rc = enqueue_ext<u64>(P, ws, d_reads, d_offsets, lo, hi, hist_len, d_kmers, d_counts, pair_cap, d_occ_off,
                           d_occ_read, d_occ_pos, occ_cap, d_hist, d_tot, st);
   else
@@ -1962,6 +2144,7 @@ static int ext_device_common(const uint8_t* d_reads, uint64_t total_bases, const
     return budget ? fail(KC_ENOMEM, "no plan fits a workspace budget of %llu bytes", (unsigned long long)budget)
                   : fail(KC_EINVAL, "input too large");
   if (!ext_radix_bits(cfg, &P.rbits)) return fail(KC_EINVAL, "radix_bits=%u outside [8, 9]", cfg->radix_bits);
+  ext_fit(&P, ws_bytes);
   if (ws_bytes < P.bytes)
     return fail(KC_EINVAL, "workspace of %zu bytes < %llu needed", ws_bytes, (unsigned long long)P.bytes);
   return enqueue_ext_any(P, ws, d_reads, d_offsets, lo, hi, hist_len, d_kmers, d_counts, pair_cap, d_occ_off,
@@ -2044,6 +2227,7 @@ int kc_count_ext(const uint8_t* reads, const uint64_t* offsets, uint64_t n_reads
             out_bytes = o_h + align_up(8 * hist_len, 256);
   size_t free_b = 0, total_b = 0;
   HIP_TRY(hipMemGetInfo(&free_b, &total_b));
+  ext_fit(&P, min_freq < 2 ? P.bytes_sort : free_b - std::min<u64>(free_b, in_bytes + out_bytes));
   if (P.bytes + in_bytes + out_bytes > free_b)
     return fail(KC_ENOMEM, "needs %llu bytes of HBM, %zu free", (unsigned long long)(P.bytes + in_bytes + out_bytes),
                 free_b);

@@ -25,6 +25,7 @@ __device__ __forceinline__ u32 key_digit(k128 k, int sh) {
   return sh >= 64 ? (u32)(k.hi >> (sh - 64)) & 0xFFu : (u32)(k.lo >> sh) & 0xFFu;
 }
 template <typename K> __device__ __forceinline__ K key_zero();
+template <> __device__ __forceinline__ u32 key_zero<u32>() { return 0; }
 template <> __device__ __forceinline__ u64 key_zero<u64>() { return 0; }
 template <> __device__ __forceinline__ k128 key_zero<k128>() { return k128{0, 0}; }
 

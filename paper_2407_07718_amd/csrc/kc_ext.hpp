@@ -11,7 +11,8 @@
 // run of equal keys holds its occurrences in ascending (read, position) order, and one
 // scan over the runs counts them (Section 3.1).  Under an HBM budget the same steps run
 // in rounds over consecutive key ranges (Section 3.1: the paper's memory-tight sort;
-// Section 3.3: exchange rounds of bounded size).
+// Section 3.3: exchange rounds of bounded size).  Larger one-pass counts sort the windows by
+// the index of their pair instead, after a plain count (below, "by count").
 #pragma once
 #include "kc_common.hpp"
 #include "kc_count.hpp"
@@ -33,15 +34,25 @@ constexpr u32 EXT_WAVE = EXT_PER * 64;
 // inside a read; other entries keep the fill value ~0.  The block size follows the mean
 // read length, so that a block spans few reads and the table stays small for long reads.
 // Reads whose offsets are out of order or out of range are skipped (the count reports
-// them through its flags).  Also raises *max_len to the longest read.
+// them through its flags).  Also raises *max_len to the longest read, a block at a time: the
+// atomics on it queue (a read at a time, 300,000 reads of 150 bases took 58 us).
 __global__ __launch_bounds__(256) void k_ext_read_blocks(const u64* __restrict__ offsets, u64 n_reads, u64 R,
                                                          u32* __restrict__ rid, u64 n_blk, u32 sh,
                                                          u64* __restrict__ max_len) {
+  __shared__ u64 top[4];
+  u64 longest = 0;
   for (u64 r = blockIdx.x * (u64)blockDim.x + threadIdx.x; r < n_reads; r += (u64)gridDim.x * blockDim.x) {
     const u64 a = offsets[r], b = offsets[r + 1];
     if (b <= a || b > R) continue;
     for (u64 q = (a + ((1ull << sh) - 1)) >> sh; (q << sh) < b && q < n_blk; ++q) rid[q] = (u32)r;
-    if (b - a > *(volatile u64*)max_len) atomicMax((unsigned long long*)max_len, (unsigned long long)(b - a));
+    longest = max(longest, b - a);
+  }
+  for (int d = 32; d; d >>= 1) longest = max(longest, (u64)__shfl_xor((unsigned long long)longest, d, 64));
+  if (lane_id() == 0) top[threadIdx.x >> 6] = longest;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    longest = max(max(top[0], top[1]), max(top[2], top[3]));
+    if (longest > *(volatile u64*)max_len) atomicMax((unsigned long long*)max_len, (unsigned long long)longest);
   }
 }
 
@@ -479,6 +490,263 @@ __global__ __launch_bounds__(EXT_T) void k_ext_occ(ExtRunArgs A) {
   }
 }
 
+// ---------------------------------------------------------------------------- by count
+// Larger one-pass extension counts (min_freq >= 2) do not sort the windows: the plain count
+// gives the reported pairs in key order, each window looks its k-mer up in a hash table of
+// them, and the windows found are sorted by pair index -- a 32-bit key of about 21 bits where
+// the k-mer has 2k, in position order to begin with, so that each pair's occurrences stay
+// ascending.
+//
+// Table of pair indices: four slots per pair where the region allows it (slot_cap), two at
+// least, 16 bytes for u64 keys, 32 for 128-bit keys, probed linearly: key words, then the
+// index (EXT_NONE: free).  Fewer probes are worth the larger table: at four slots per pair
+// the lookups of 40 Mbp of 150-base reads take 677 us (k = 31), at two 703 us.
+constexpr u32 EXT_NONE = 0xFFFFFFFFu;
+template <typename K> constexpr u32 ext_slot_words() { return sizeof(K) == 8 ? 4u : 8u; }
+__device__ __forceinline__ u32 ext_slots(u64 n, u64 slot_cap) { return (u32)min(max(4 * n, (u64)64), slot_cap); }
+__device__ __forceinline__ u32 ext_slot_of(u64 k, u32 slots) { return __umulhi((u32)(mix64(k) >> 32), slots); }
+__device__ __forceinline__ u32 ext_slot_of(k128 k, u32 slots) {
+  return __umulhi((u32)((mix64(k.lo) ^ mix64(k.hi + MIX_C)) >> 32), slots);
+}
+
+template <typename K>
+__global__ __launch_bounds__(256) void k_ext_table_clear(const u64* __restrict__ n_ptr, u64 slot_cap, uint4* __restrict__ tab) {
+  constexpr u32 Q = ext_slot_words<K>() / 4;     // the index is in the slot's last uint4
+  const u32 slots = ext_slots(*n_ptr, slot_cap);
+  for (u64 i = blockIdx.x * (u64)blockDim.x + threadIdx.x; i < slots; i += (u64)gridDim.x * blockDim.x)
+    tab[i * Q + Q - 1] = make_uint4(0u, 0u, EXT_NONE, 0u);
+}
+
+// Pairs are distinct: a slot is claimed through its index, and its key is read only by later
+// kernels.
+__device__ __forceinline__ void ext_slot_key(u32* s, u64 k) { *reinterpret_cast<u64*>(s) = k; }
+__device__ __forceinline__ void ext_slot_key(u32* s, k128 k) {
+  *reinterpret_cast<uint4*>(s) = make_uint4((u32)k.lo, (u32)(k.lo >> 32), (u32)k.hi, (u32)(k.hi >> 32));
+}
+template <typename K>
+__global__ __launch_bounds__(256) void k_ext_table_insert(const K* __restrict__ keys, const u64* __restrict__ n_ptr,
+                                                          u64 slot_cap, u32* __restrict__ tab) {
+  constexpr u32 SW = ext_slot_words<K>();
+  const u64 n = *n_ptr;
+  const u32 slots = ext_slots(n, slot_cap);
+  for (u64 i = blockIdx.x * (u64)blockDim.x + threadIdx.x; i < n; i += (u64)gridDim.x * blockDim.x) {
+    const K key = keys[i];
+    u32 s = ext_slot_of(key, slots);
+    while (atomicCAS(&tab[(u64)s * SW + SW - 2], EXT_NONE, (u32)i) != EXT_NONE) s = s + 1 == slots ? 0u : s + 1;
+    ext_slot_key(&tab[(u64)s * SW], key);
+  }
+}
+
+// One slot as read by a lookup.
+template <typename K> struct ExtSlot;
+template <> struct ExtSlot<u64> {
+  uint4 a;
+  __device__ __forceinline__ void load(const uint4* tab, u32 s) { a = tab[s]; }
+  __device__ __forceinline__ u32 idx() const { return a.z; }
+  __device__ __forceinline__ bool is(u64 k) const { return a.x == (u32)k && a.y == (u32)(k >> 32); }
+};
+template <> struct ExtSlot<k128> {
+  uint4 a, b;
+  __device__ __forceinline__ void load(const uint4* tab, u32 s) {
+    a = tab[2 * (u64)s];
+    b = tab[2 * (u64)s + 1];
+  }
+  __device__ __forceinline__ u32 idx() const { return b.z; }
+  __device__ __forceinline__ bool is(k128 k) const {
+    return a.x == (u32)k.lo && a.y == (u32)(k.lo >> 32) && a.z == (u32)k.hi && a.w == (u32)(k.hi >> 32);
+  }
+};
+
+// Pair index of every window position (EXT_NONE: no window there, or a k-mer that is not
+// reported) and the windows found per tile.  Bound by the table's random reads:
+// eight positions per lane have theirs in flight together, the first and each further probe
+// (one position's probes after the other: 821 us where this takes 677, as above).  Slots
+// picked by minimizer, so that neighbouring windows share lines, took 793 us: more probes.
+template <typename K>
+__global__ __launch_bounds__(EXT_T) void k_ext_lookup(ExtWinArgs A, const u64* __restrict__ n_ptr, u64 slot_cap,
+                                                      const uint4* __restrict__ tab, u32* __restrict__ found) {
+  __shared__ u32 wtot[EXT_T / 64];
+  __shared__ u32 s_pk[EXT_T / 64][EXT_PK], s_nm[EXT_T / 64][EXT_MK], s_ct[EXT_T / 64][EXT_MK];
+  const u32 lane = lane_id(), wave = uniform(threadIdx.x >> 6);
+  const u64 e0 = (u64)blockIdx.x * EXT_TILE + (u64)wave * EXT_WAVE;
+  const u64 lo = A.n_reads ? min(A.offsets[0], A.R) : 0;
+  const u64 hi = A.n_reads ? min(A.offsets[A.n_reads], A.R) : 0;
+  const u32 slots = ext_slots(*n_ptr, slot_cap);
+  u32* const pk = s_pk[wave];
+  u32* const nm = s_nm[wave];
+  u32* const ct = s_ct[wave];
+  const u32 offp = (u32)(e0 & 15), offm = (u32)(e0 & 31);
+  {
+    const u64 pw0 = e0 >> 4, mw0 = e0 >> 5;
+    const u64 i0 = pw0 + lane, i1 = pw0 + 64 + lane, jm = mw0 + lane;
+    const u32 a0 = i0 < A.n_packed ? A.packed[i0] : 0u;
+    const u32 a1 = i1 < A.n_packed ? A.packed[i1] : 0u;
+    const u32 b0 = jm < A.n_mask ? A.nmask[jm] : 0u;
+    const u32 c0 = b0 | (jm < A.n_mask ? A.starts[jm] : 0u);
+    pk[lane] = a0;
+    pk[64 + lane] = a1;
+    nm[lane] = b0;
+    ct[lane] = c0;
+    __builtin_amdgcn_wave_barrier();
+  }
+  const u64 kmask_cut = ((1ull << A.k) - 1) & ~1ull;   // no read may start inside
+  constexpr int U = sizeof(K) == 8 ? 8 : 4;
+  u32 cnt = 0;
+  for (int j0 = 0; j0 < (int)EXT_PER; j0 += U) {
+    K key[U];
+    ExtSlot<K> e[U];
+    u32 at[U];
+    bool v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const u32 q = (u32)(j0 + u) * 64 + lane;   // position e0 + q
+      const u64 i = e0 + q;
+      v[u] = i < A.n_pos && i >= lo && i + (u64)A.k <= hi;
+      const u32 x = v[u] ? q + offm : 0u;
+      v[u] = v[u] && (lds_bits64(ct, x) & kmask_cut) == 0 && ((nm[x >> 5] >> (x & 31)) & 1u) == 0;
+      ext_canon_lds(pk, q + offp, A.k, &key[u]);
+      at[u] = ext_slot_of(key[u], slots);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (v[u]) e[u].load(tab, at[u]);
+    for (bool more = true; __any(more);) {   // the next probes of all positions together
+      more = false;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool go = v[u] && e[u].idx() != EXT_NONE && !e[u].is(key[u]);
+        if (go) {
+          at[u] = at[u] + 1 == slots ? 0u : at[u] + 1;
+          e[u].load(tab, at[u]);
+        }
+        more |= go;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const u32 idx = v[u] ? e[u].idx() : EXT_NONE;
+      const u64 i = e0 + (u64)(j0 + u) * 64 + lane;
+      if (i < A.R) found[i] = idx;
+      cnt += (u32)__popcll(__ballot(idx != EXT_NONE));
+    }
+  }
+  if (lane == 0) wtot[wave] = cnt;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    u32 s = 0;
+    for (u32 w = 0; w < EXT_T / 64; ++w) s += wtot[w];
+    A.blk[blockIdx.x] = s;
+  }
+}
+
+// The windows found, densely in position order: pair index and (read, position) value (see
+// ext_packed).
+__global__ __launch_bounds__(EXT_T) void k_ext_compact(ExtWinArgs A, const u32* __restrict__ found,
+                                                       u32* __restrict__ out_idx, u32* __restrict__ out_val) {
+  __shared__ u32 wtot[EXT_T / 64];
+  const u32 lane = lane_id(), wave = threadIdx.x >> 6;
+  const u64 e0 = (u64)blockIdx.x * EXT_TILE + (u64)wave * EXT_WAVE;
+  u32 idx[EXT_PER];
+  u32 cnt = 0;
+#pragma unroll
+  for (int j = 0; j < (int)EXT_PER; ++j) {
+    const u64 i = e0 + (u64)j * 64 + lane;
+    idx[j] = i < A.R ? found[i] : EXT_NONE;
+    cnt += (u32)__popcll(__ballot(idx[j] != EXT_NONE));
+  }
+  if (lane == 0) wtot[wave] = cnt;
+  __syncthreads();
+  u64 base = A.blk[blockIdx.x];
+  for (u32 w = 0; w < wave; ++w) base += wtot[w];
+  const u64 ml = *A.max_len;
+  const bool packed_v = ext_packed(A.rbits, ml);
+  const u32 pb = ext_pos_bits(ml);
+#pragma unroll
+  for (int j = 0; j < (int)EXT_PER; ++j) {
+    const u64 m = __ballot(idx[j] != EXT_NONE);
+    if (idx[j] != EXT_NONE) {
+      const u64 p = e0 + (u64)j * 64 + lane, o = base + mbcnt64(m);
+      u32 v = (u32)p;
+      if (packed_v) {
+        const u32 rd = ext_find_read(A.offsets, A.n_reads, A.rid, A.n_blk, A.blk_sh, p);
+        v = (pb < 32 ? (rd << pb) : 0u) | (u32)(p - A.offsets[rd]);
+      }
+      out_idx[o] = idx[j];
+      out_val[o] = v;
+    }
+    base += (u32)__popcll(m);
+  }
+}
+
+// The last pass by pair index writes the occurrences, decoded.
+struct StoreOcc {
+  u32 *occ_read, *occ_pos;
+  u64 occ_cap;
+  u32 rbits;
+  const u64* max_len;
+  const u64* offsets;
+  u64 n_reads;
+  const u32* rid;
+  u64 n_blk;
+  u32 blk_sh;
+  __device__ __forceinline__ void key(u64, u32) const {}
+  __device__ __forceinline__ void val(u64 o, u32 v) const {
+    if (o >= occ_cap) return;
+    const u64 ml = *max_len;
+    const u32 pb = ext_pos_bits(ml);
+    u32 rd, ps;
+    if (ext_packed(rbits, ml)) {
+      rd = pb < 32 ? (v >> pb) : 0u;
+      ps = v & (u32)((1ull << pb) - 1);
+    } else {
+      rd = ext_find_read(offsets, n_reads, rid, n_blk, blk_sh, v);
+      ps = (u32)(v - offsets[rd]);
+    }
+    occ_read[o] = rd;
+    occ_pos[o] = ps;
+  }
+};
+
+// Summed counts per tile of EXT_TILE pairs; then (scanned) each pair's first occurrence.
+template <bool WRITE>
+__global__ __launch_bounds__(EXT_T) void k_ext_offsets(const u32* __restrict__ counts, const u64* __restrict__ n_ptr,
+                                                       u32* __restrict__ blk, u64* __restrict__ occ_off,
+                                                       u64 pair_cap) {
+  __shared__ u64 scr[17];
+  const u64 n = *n_ptr, i0 = (u64)blockIdx.x * EXT_TILE + (u64)threadIdx.x * EXT_PER;
+  u32 c[EXT_PER];
+  u64 sum = 0;
+#pragma unroll
+  for (u32 q = 0; q < EXT_PER; ++q) {
+    c[q] = i0 + q < n ? counts[i0 + q] : 0u;
+    sum += c[q];
+  }
+  u64 tot;
+  u64 run = block_exclusive_scan<u64>(sum, scr, &tot);
+  if (!WRITE) {
+    if (threadIdx.x == 0) blk[blockIdx.x] = (u32)tot;
+    return;
+  }
+  run += blk[blockIdx.x];
+#pragma unroll
+  for (u32 q = 0; q < EXT_PER; ++q) {
+    if (i0 + q < n && i0 + q < pair_cap) occ_off[i0 + q] = run;
+    run += c[q];
+  }
+}
+
+// Totals of such a count (the bucket figures stay 0, as for a sorted one).
+__global__ void k_ext_count_totals(DevTotals* tot, const u64* meta, const u64* n_pairs, const u64* n_occ,
+                                   const u32* flags, u64* occ_off, u64 pair_cap) {
+  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+  tot->n_windows = meta[2] + meta[6] + meta[7];
+  tot->n_pairs = *n_pairs;
+  tot->n_occ = *n_occ;
+  tot->flags = *flags & 1u;
+  if (*n_pairs <= pair_cap) occ_off[*n_pairs] = *n_occ;
+}
+
+// ---------------------------------------------------------------------------- rounds
 // Windows per key prefix, over all valid windows: the waves of persistent blocks take
 // spans of EXT_WAVE positions in turn (staged in LDS as in k_ext_windows), count into the
 // block's LDS bins and add them to the global bins once at the end.

@@ -179,6 +179,7 @@ std::map<TuneKey, u32> g_tune_bits;
 int tune_radix_bits(const kc_job& j, const JobInfo& ji, u32* best_bits) {
   ExtPlan P;
   if (!make_ext_plan(ji.R, j.n_reads, j.k, 0, &P)) return fail(KC_EINVAL, "job too large for the extension version");
+  P.by_count = false;   // (the digit width matters only where the windows are sorted)
   const u64 w = 8ull * ji.key_words, cap = std::max<u64>(1, ji.n_max), pcap = ji.pair_cap;
   const u64 o_k = align_up(P.bytes, 256), o_c = o_k + align_up(w * pcap, 256), o_off = o_c + align_up(4 * pcap, 256),
             o_rd = o_off + align_up(8 * (pcap + 1), 256), o_ps = o_rd + align_up(4 * cap, 256),

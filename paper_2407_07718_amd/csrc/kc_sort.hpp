@@ -27,6 +27,34 @@ template <int DB> __device__ __forceinline__ u32 key_digit_w(k128 k, int sh) {
   return (u32)v & ((1u << DB) - 1u);
 }
 
+template <int DB> __device__ __forceinline__ u32 key_digit_w(u32 k, int sh) { return (k >> sh) & ((1u << DB) - 1u); }
+
+// The digit of a pass: the DB bits from bit `sh` on, or, for 32-bit keys, the pass-th of
+// `passes` equal digits (of at most DB bits) of an index below *n_idx.
+struct DigitSel {
+  int sh = 0;
+  const u64* n_idx = nullptr;
+  int pass = 0, passes = 1;
+};
+struct Digit {
+  int sh;
+  u32 mask;
+};
+template <typename K, int DB> __device__ __forceinline__ Digit digit_of(const DigitSel& D) {
+  if constexpr (sizeof(K) != 4) return Digit{D.sh, (1u << DB) - 1u};
+  const u64 n = max(*D.n_idx, (u64)2) - 1;       // the largest index
+  const int w = (64 - __builtin_clzll(n) + D.passes - 1) / D.passes;
+  return Digit{min(31, w * D.pass), (1u << min(w, DB)) - 1u};
+}
+// Where a downsweep's pairs go: two arrays.
+template <typename K>
+struct StorePairs {
+  K* k;
+  u32* v;
+  __device__ __forceinline__ void key(u64 i, K x) const { k[i] = x; }
+  __device__ __forceinline__ void val(u64 i, u32 x) const { v[i] = x; }
+};
+
 template <int W, int DB = 8>
 struct RankSmem {
   static constexpr int NB = 1 << DB;
@@ -108,8 +136,9 @@ __device__ __forceinline__ void block_range(u64 n, u32 nb, u64* s, u64* e) {
 // counts[d * nb + b] = number of keys of block b with digit d (DB-bit digits).
 template <typename K, int DB = 8>
 __global__ __launch_bounds__(256) void k_radix_upsweep(const K* __restrict__ keys, const u64* __restrict__ n_ptr,
-                                                       u32* __restrict__ counts, int sh) {
+                                                       u32* __restrict__ counts, DigitSel D) {
   constexpr u32 NB = 1u << DB;
+  const Digit dg = digit_of<K, DB>(D);
   __shared__ u32 h[4][NB];
   const u32 nb = gridDim.x, tid = threadIdx.x, wave = tid >> 6;
   for (u32 i = tid; i < 4 * NB; i += 256) (&h[0][0])[i] = 0;
@@ -132,7 +161,7 @@ __global__ __launch_bounds__(256) void k_radix_upsweep(const K* __restrict__ key
     if (i0 + 256 * U < e) load(kb, i0 + 256 * U);
 #pragma unroll
     for (u32 u = 0; u < U; ++u)
-      if (i0 + (u64)u * 256 < e) atomicAdd(&h[wave][key_digit_w<DB>(ka[u], sh)], 1u);
+      if (i0 + (u64)u * 256 < e) atomicAdd(&h[wave][key_digit_w<DB>(ka[u], dg.sh) & dg.mask], 1u);
 #pragma unroll
     for (u32 u = 0; u < U; ++u) ka[u] = kb[u];
   }
@@ -238,13 +267,13 @@ __global__ __launch_bounds__(256) void k_radix_rowscan(u32* __restrict__ counts,
 // Stable scatter of one pass.  Each tile of T*ITEMS keys is ranked by digit, staged in
 // LDS in digit order and written out as one run per digit.  With SHARED the values are
 // staged after the keys in the same LDS buffer (less LDS per block, one more barrier).
-template <typename K, bool HASV, int T, int ITEMS, bool SHARED = false, int DB = 8>
-__global__ __launch_bounds__(T) void k_radix_downsweep(const K* __restrict__ kin, K* __restrict__ kout,
-                                                       const u32* __restrict__ vin, u32* __restrict__ vout,
+template <typename K, bool HASV, int T, int ITEMS, bool SHARED, int DB, typename Out>
+__global__ __launch_bounds__(T) void k_radix_downsweep(const K* __restrict__ kin, const u32* __restrict__ vin, Out out,
                                                        const u64* __restrict__ n_ptr, const u32* __restrict__ counts,
-                                                       const u32* __restrict__ totals, int sh) {
+                                                       const u32* __restrict__ totals, DigitSel D) {
   constexpr int W = T / 64, TILE = T * ITEMS, NB = 1 << DB;
   static_assert(NB <= T, "one thread per digit");
+  const Digit digit = digit_of<K, DB>(D);
   __shared__ RankSmem<W, DB> S;
   __shared__ K stage_k[TILE];
   __shared__ u32 stage_v[(HASV && !SHARED) ? TILE : 1];
@@ -296,7 +325,7 @@ __global__ __launch_bounds__(T) void k_radix_downsweep(const K* __restrict__ kin
     if (t0 + TILE < e) load_tile(t0 + TILE);
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
-      if (j < per) dg[j] = key_digit_w<DB>(kr[j], sh);
+      if (j < per) dg[j] = key_digit_w<DB>(kr[j], digit.sh) & digit.mask;
     }
     rank_by_digit<T, ITEMS, DB>(dg, rk, per, nt, S);
 #pragma unroll
@@ -318,9 +347,9 @@ __global__ __launch_bounds__(T) void k_radix_downsweep(const K* __restrict__ kin
         const u32 i = tid + (u32)j * T;
         if (i < nt) {
           const K key = stage_k[i];
-          const u32 d = key_digit_w<DB>(key, sh);
+          const u32 d = key_digit_w<DB>(key, digit.sh) & digit.mask;
           dsts[j] = run_base[d] + (i - S.dstart[d]);
-          kout[dsts[j]] = key;
+          out.key(dsts[j], key);
         }
       }
       __syncthreads();
@@ -336,15 +365,15 @@ __global__ __launch_bounds__(T) void k_radix_downsweep(const K* __restrict__ kin
 #pragma unroll
       for (int j = 0; j < ITEMS; ++j) {
         const u32 i = tid + (u32)j * T;
-        if (i < nt) vout[dsts[j]] = sv[i];
+        if (i < nt) out.val(dsts[j], sv[i]);
       }
     } else {
       for (u32 i = tid; i < nt; i += T) {
         const K key = stage_k[i];
-        const u32 d = key_digit_w<DB>(key, sh);
+        const u32 d = key_digit_w<DB>(key, digit.sh) & digit.mask;
         const u64 dst = (u64)run_base[d] + (i - S.dstart[d]);
-        kout[dst] = key;
-        if (HASV) vout[dst] = stage_v[i];
+        out.key(dst, key);
+        if (HASV) out.val(dst, stage_v[i]);
       }
     }
     __syncthreads();
