@@ -107,6 +107,8 @@ const char *kc_last_error(void);
  *   k in [1, 63]; m in [1, min(k-1, 32)]; 1 <= min_freq <= max_freq; hist_len >= 2.
  *   cfg may be NULL; cfg->hbm_budget bounds the device workspace (rounds, see
  *   kc_workspace_size).  On KC_OK, *out owns host arrays that kc_result_free releases.
+ *   Without a budget, up to 4 GiB of a call's device memory stay with the library for the
+ *   next host call (of any thread) and go back when an allocation of the library runs short.
  *   Errors: KC_EINVAL (arguments, non-monotone offsets, more than 2^32-1 windows),
  *   KC_ENOMEM (no plan fits the budget or free HBM; a count in rounds that could not
  *   finish), KC_EDEVICE. */

@@ -126,6 +126,127 @@ enum Ctrl : int {
 };
 static_assert(C_META + 8 <= C_FLAGS, "meta overlaps the flags");
 
+// ---------------------------------------------------------------- device memory of host calls
+// A host call (kc_count, kc_count_ext, kc_partition_inspect) needs about 62 bytes of HBM per
+// base for as long as it runs.  Handing them back to the driver costs more than the count: the
+// next allocation may wait until the pages are cleared (16 Mbp: 30 ms a call, 2.7 ms without; 60
+// Mbp: 28.5 and 27.5 ms, the rest being the result's pages on the host).  So up
+// to KEEP_MAX bytes (1.5 % of the HBM) of blocks stay here for the next call, and go back to the
+// driver when newer ones take their place or an allocation of this library runs short.  A block
+// is kept only after its call's work on it has completed, and a call with a budget of its own
+// neither takes nor leaves one.  (Never destroyed: at the process's end the driver is gone first.)
+constexpr u64 KEEP_MAX = 4ull << 30;
+struct DevBlock {
+  char* p = nullptr;
+  u64 bytes = 0;
+  int dev = 0;
+};
+class KeptBlocks {
+  static constexpr int N = 8;
+  std::mutex mu_;
+  DevBlock b_[N];   // oldest first
+  int n_ = 0;
+  u64 total_ = 0;
+  DevBlock remove(int i) {
+    const DevBlock b = b_[i];
+    for (int j = i + 1; j < n_; ++j) b_[j - 1] = b_[j];
+    --n_;
+    total_ -= b.bytes;
+    return b;
+  }
+
+ public:
+  // the smallest kept block of the device that holds `bytes`
+  bool take(int dev, u64 bytes, DevBlock* out) {
+    std::lock_guard<std::mutex> g(mu_);
+    int best = -1;
+    for (int i = 0; i < n_; ++i)
+      if (b_[i].dev == dev && b_[i].bytes >= bytes && (best < 0 || b_[i].bytes < b_[best].bytes)) best = i;
+    if (best < 0) return false;
+    *out = remove(best);
+    return true;
+  }
+  void put(const DevBlock& b) {
+    DevBlock old[N + 1];
+    int n_old = 0;
+    {
+      std::lock_guard<std::mutex> g(mu_);
+      if (b.bytes > KEEP_MAX) {
+        old[n_old++] = b;
+      } else {
+        while (n_ == N || total_ + b.bytes > KEEP_MAX) old[n_old++] = remove(0);
+        b_[n_++] = b;
+        total_ += b.bytes;
+      }
+    }
+    for (int i = 0; i < n_old; ++i) (void)hipFree(old[i].p);
+  }
+  // all kept blocks of the device back to the driver; false: there were none
+  bool drop(int dev) {
+    DevBlock old[N];
+    int n_old = 0;
+    {
+      std::lock_guard<std::mutex> g(mu_);
+      for (int i = n_ - 1; i >= 0; --i)
+        if (b_[i].dev == dev) old[n_old++] = remove(i);
+    }
+    for (int i = 0; i < n_old; ++i) (void)hipFree(old[i].p);
+    return n_old > 0;
+  }
+  u64 held(int dev) {
+    std::lock_guard<std::mutex> g(mu_);
+    u64 t = 0;
+    for (int i = 0; i < n_; ++i)
+      if (b_[i].dev == dev) t += b_[i].bytes;
+    return t;
+  }
+};
+KeptBlocks& kept_blocks() {
+  static KeptBlocks* k = new KeptBlocks();
+  return *k;
+}
+
+// Free HBM of the current device, kept blocks included.
+int free_hbm(u64* bytes) {
+  int dev = 0;
+  size_t free_b = 0, total_b = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  HIP_TRY(hipMemGetInfo(&free_b, &total_b));
+  *bytes = free_b + kept_blocks().held(dev);
+  return KC_OK;
+}
+// hipMalloc, with the kept blocks given back where it runs short.
+template <typename T>
+hipError_t dev_malloc(T** p, u64 bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  int dev = 0;
+  if (e == hipSuccess || hipGetDevice(&dev) != hipSuccess || !kept_blocks().drop(dev)) return e;
+  (void)hipGetLastError();
+  return hipMalloc(p, bytes);
+}
+// A host call's block of `bytes`; release(true) once all work on it has completed.
+struct HostBlock {
+  DevBlock b;
+  bool keep = false;
+  int take(u64 bytes, const kc_config* cfg) {
+    keep = !(cfg && cfg->hbm_budget);
+    HIP_TRY(hipGetDevice(&b.dev));
+    if (keep && kept_blocks().take(b.dev, bytes, &b)) return KC_OK;
+    u64 free_b = 0;
+    const int rc = free_hbm(&free_b);
+    if (rc) return rc;
+    if (bytes > free_b)
+      return fail(KC_ENOMEM, "needs %llu bytes of HBM, %llu free", (unsigned long long)bytes, (unsigned long long)free_b);
+    HIP_TRY(dev_malloc(&b.p, bytes));
+    b.bytes = bytes;
+    return KC_OK;
+  }
+  void release(bool done) {
+    if (keep && done) kept_blocks().put(b);
+    else (void)hipFree(b.p);
+  }
+};
+
 // On-chip shapes of the bucket count, as slots of the block's hash table (half as many for
 // 128-bit keys): 1 = 4,096 (the default: the most that leaves three blocks of 512 threads per
 // CU), 2 = 8,192, 3 = 2,048.
@@ -1991,13 +2112,9 @@ int kc_count(const uint8_t* reads, const uint64_t* offsets, uint64_t n_reads, in
   const u64 in_bytes = align_up(R + 16, 256) + align_up(8 * (n_reads + 1), 256);
   const u64 out_bytes = align_up(w * pcap, 256) + align_up(4 * pcap, 256) + align_up(sizeof(kc_totals), 256) +
                         align_up(8 * hist_len, 256);
-  size_t free_b = 0, total_b = 0;
-  HIP_TRY(hipMemGetInfo(&free_b, &total_b));
-  if (P.bytes + in_bytes + out_bytes > free_b)
-    return fail(KC_ENOMEM, "needs %llu bytes of HBM, %zu free", (unsigned long long)(P.bytes + in_bytes + out_bytes),
-                free_b);
-  char* dmem = nullptr;
-  HIP_TRY(hipMalloc(&dmem, P.bytes + in_bytes + out_bytes));
+  HostBlock block;
+  if ((rc = block.take(P.bytes + in_bytes + out_bytes, cfg))) return rc;
+  char* const dmem = block.b.p;
   void* ws = dmem;
   uint8_t* d_reads = reinterpret_cast<uint8_t*>(dmem + P.bytes);
   uint64_t* d_offsets = reinterpret_cast<uint64_t*>(dmem + P.bytes + align_up(R + 16, 256));
@@ -2008,7 +2125,7 @@ int kc_count(const uint8_t* reads, const uint64_t* offsets, uint64_t n_reads, in
   uint64_t* d_hist = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(d_tot) + align_up(sizeof(kc_totals), 256));
   hipStream_t st = nullptr;
   auto cleanup = [&](int code) {
-    (void)hipFree(dmem);
+    block.release(code == KC_OK);
     if (code) kc_result_free(out);
     return code;
   };
@@ -2072,17 +2189,14 @@ int kc_partition_inspect(const uint8_t* reads, const uint64_t* offsets, uint64_t
   Plan P;
   if (!make_plan(R, n_reads, n_max, k, m, 1, &one, &P)) return fail(KC_EINVAL, "bad kc_config");
   const u64 in_bytes = align_up(R + 16, 256) + align_up(8 * (n_reads + 1), 256);
-  size_t free_b = 0, total_b = 0;
-  HIP_TRY(hipMemGetInfo(&free_b, &total_b));
-  if (P.bytes + in_bytes > free_b)
-    return fail(KC_ENOMEM, "needs %llu bytes of HBM, %zu free", (unsigned long long)(P.bytes + in_bytes), free_b);
-  char* dmem = nullptr;
-  HIP_TRY(hipMalloc(&dmem, P.bytes + in_bytes));
+  HostBlock block;
+  if ((rc = block.take(P.bytes + in_bytes, cfg))) return rc;
+  char* const dmem = block.b.p;
   uint8_t* d_reads = reinterpret_cast<uint8_t*>(dmem + P.bytes);
   uint64_t* d_offsets = reinterpret_cast<uint64_t*>(dmem + P.bytes + align_up(R + 16, 256));
   hipStream_t st = nullptr;
   auto cleanup = [&](int code) {
-    (void)hipFree(dmem);
+    block.release(code == KC_OK);
     if (code) kc_partition_free(out);
     return code;
   };
@@ -2225,14 +2339,12 @@ int kc_count_ext(const uint8_t* reads, const uint64_t* offsets, uint64_t n_reads
             o_rd = o_off + align_up(8 * (cap + 1), 256), o_ps = o_rd + align_up(4 * cap, 256),
             o_tot = o_ps + align_up(4 * cap, 256), o_h = o_tot + align_up(sizeof(kc_totals), 256),
             out_bytes = o_h + align_up(8 * hist_len, 256);
-  size_t free_b = 0, total_b = 0;
-  HIP_TRY(hipMemGetInfo(&free_b, &total_b));
+  u64 free_b = 0;
+  if ((rc = free_hbm(&free_b))) return rc;
   ext_fit(&P, min_freq < 2 ? P.bytes_sort : free_b - std::min<u64>(free_b, in_bytes + out_bytes));
-  if (P.bytes + in_bytes + out_bytes > free_b)
-    return fail(KC_ENOMEM, "needs %llu bytes of HBM, %zu free", (unsigned long long)(P.bytes + in_bytes + out_bytes),
-                free_b);
-  char* dmem = nullptr;
-  HIP_TRY(hipMalloc(&dmem, P.bytes + in_bytes + out_bytes));
+  HostBlock block;
+  if ((rc = block.take(P.bytes + in_bytes + out_bytes, cfg))) return rc;
+  char* const dmem = block.b.p;
   void* ws = dmem;
   uint8_t* d_reads = reinterpret_cast<uint8_t*>(dmem + P.bytes);
   uint64_t* d_offsets = reinterpret_cast<uint64_t*>(dmem + P.bytes + align_up(R + 16, 256));
@@ -2246,7 +2358,7 @@ int kc_count_ext(const uint8_t* reads, const uint64_t* offsets, uint64_t n_reads
   uint64_t* d_hist = reinterpret_cast<uint64_t*>(ob + o_h);
   hipStream_t st = nullptr;
   auto cleanup = [&](int code) {
-    (void)hipFree(dmem);
+    block.release(code == KC_OK);
     if (code) kc_ext_result_free(out);
     return code;
   };

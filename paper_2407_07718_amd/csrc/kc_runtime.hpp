@@ -145,7 +145,7 @@ int autotune_device(const kc_job& j, const JobInfo& ji, const kc_config* base, k
   }
   const u64 ob = outputs_bytes(ji, j.hist_len);
   char* mem = nullptr;
-  HIP_TRY(hipMalloc(&mem, ws_bytes + ob));
+  HIP_TRY(dev_malloc(&mem, ws_bytes + ob));
   hipStream_t st;
   if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) {
     (void)hipFree(mem);
@@ -179,14 +179,14 @@ std::map<TuneKey, u32> g_tune_bits;
 int tune_radix_bits(const kc_job& j, const JobInfo& ji, u32* best_bits) {
   ExtPlan P;
   if (!make_ext_plan(ji.R, j.n_reads, j.k, 0, &P)) return fail(KC_EINVAL, "job too large for the extension version");
-  P.by_count = false;   // (the digit width matters only where the windows are sorted)
+  ext_fit(&P, P.bytes_sort);   // (the digit width matters only where the windows are sorted)
   const u64 w = 8ull * ji.key_words, cap = std::max<u64>(1, ji.n_max), pcap = ji.pair_cap;
   const u64 o_k = align_up(P.bytes, 256), o_c = o_k + align_up(w * pcap, 256), o_off = o_c + align_up(4 * pcap, 256),
             o_rd = o_off + align_up(8 * (pcap + 1), 256), o_ps = o_rd + align_up(4 * cap, 256),
             o_h = o_ps + align_up(4 * cap, 256), o_t = o_h + align_up(8 * j.hist_len, 256),
             total = o_t + align_up(sizeof(DevTotals), 256);
   char* mem = nullptr;
-  HIP_TRY(hipMalloc(&mem, total));
+  HIP_TRY(dev_malloc(&mem, total));
   hipStream_t st;
   if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) {
     (void)hipFree(mem);
@@ -235,13 +235,31 @@ int tune_radix_bits(const kc_job& j, const JobInfo& ji, u32* best_bits) {
   return KC_OK;
 }
 
-// Copy one job's result (device outputs) to a host kc_result.
+// Device arrays to pinned host memory in one launch (a copy call each costs about 15 us).
+struct CopyOut {
+  const u32* src[3];
+  u32* dst[3];
+  u64 n[3];   // words
+};
+__global__ __launch_bounds__(256) void k_copy_out(CopyOut C) {
+  const u64 t0 = blockIdx.x * (u64)blockDim.x + threadIdx.x, stride = (u64)gridDim.x * blockDim.x;
+  for (int r = 0; r < 3; ++r)
+    for (u64 i = t0; i < C.n[r]; i += stride) C.dst[r][i] = C.src[r][i];
+}
+
+// Copy one job's result (device outputs) to a host kc_result.  `head`: its totals, if they are on
+// the host already; `pin`: pinned memory of pin_bytes to copy it through, if it fits.
 int fetch_result(const DevTotals* d_tot, const uint64_t* d_kmers, const uint32_t* d_counts, const uint64_t* d_hist,
-                 u64 pair_cap, u64 hist_len, int key_words, hipStream_t st, kc_result* out) {
+                 u64 pair_cap, u64 hist_len, int key_words, hipStream_t st, kc_result* out,
+                 const kc_totals* head = nullptr, char* pin = nullptr, u64 pin_bytes = 0) {
   memset(out, 0, sizeof(*out));
   kc_totals t;
-  HIP_TRY(hipMemcpyAsync(&t, d_tot, sizeof(t), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
+  if (head) {
+    t = *head;
+  } else {
+    HIP_TRY(hipMemcpyAsync(&t, d_tot, sizeof(t), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+  }
   if (t.flags & 1) return fail(KC_EINVAL, "offsets are not non-decreasing or exceed the reads");
   if (t.flags & 24) return fail(KC_ENOMEM, "%s", rounds_failure(t.flags));
   if (t.flags) return fail(KC_EDEVICE, "internal capacity exceeded (flags=%llu)", (unsigned long long)t.flags);
@@ -256,6 +274,20 @@ int fetch_result(const DevTotals* d_tot, const uint64_t* d_kmers, const uint32_t
   if (!out->kmers || !out->counts || !out->hist) {
     kc_result_free(out);
     return fail(KC_ENOMEM, "host allocation failed");
+  }
+  const u64 kb = t.n_pairs * key_words * 8, cb = t.n_pairs * 4, hb = hist_len * 8;
+  if (pin && kb + cb + hb <= pin_bytes) {
+    CopyOut C{{(const u32*)d_kmers, d_counts, (const u32*)d_hist},
+              {(u32*)pin, (u32*)(pin + kb), (u32*)(pin + kb + cb)},
+              {kb / 4, cb / 4, hb / 4}};
+    const u64 most = std::max(kb, hb) / 4;
+    hipLaunchKernelGGL(k_copy_out, grid_for(most, 256, 256), dim3(256), 0, st, C);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(st));
+    memcpy(out->kmers, pin, kb);
+    memcpy(out->counts, pin + kb, cb);
+    memcpy(out->hist, pin + kb + cb, hb);
+    return KC_OK;
   }
   if (t.n_pairs) {
     HIP_TRY(hipMemcpyAsync(out->kmers, d_kmers, t.n_pairs * key_words * 8, hipMemcpyDeviceToHost, st));
@@ -288,6 +320,10 @@ struct kc_batch {
     MultiPlan mp;
     int lane = 0;
     char* own = nullptr;
+    // on the host since the last run's first result: first pair and totals of every set
+    std::vector<u64> first;
+    std::vector<kc_totals> tot;
+    bool on_host = false;
   };
   std::vector<Job> jobs;
   std::vector<Group> groups;
@@ -298,6 +334,11 @@ struct kc_batch {
   std::vector<char*> ws;
   char* out_mem = nullptr;
   char* owned_inputs = nullptr;
+  // results pass through pinned memory from a batch's third on (a batch may be made for one)
+  static constexpr u64 PIN_BYTES = 4ull << 20;
+  std::mutex result_mu;
+  u32 n_results = 0;
+  char* pin = nullptr;
   u64 device_bytes = 0;   // workspaces, tables and outputs (not the caller's inputs)
   hipEvent_t fork = nullptr;
   std::vector<hipEvent_t> join;
@@ -315,6 +356,7 @@ struct kc_batch {
     for (auto& G : groups)
       if (G.own) (void)hipFree(G.own);
     if (out_mem) (void)hipFree(out_mem);
+    if (pin) (void)hipHostFree(pin);
     if (owned_inputs) (void)hipFree(owned_inputs);
   }
 
@@ -468,9 +510,12 @@ int batch_build(std::vector<kc_batch::Job>&& jobs, const kc_config* cfg, kc_batc
   }
   for (auto& G : b->groups) own_total += G.mp.own_bytes;
   b->lanes = (int)std::max<size_t>(1, std::min<size_t>((size_t)b->lanes, sizes.size()));
-  size_t free_b = 0, total_b = 0;
-  HIP_TRY(hipMemGetInfo(&free_b, &total_b));
-  const u64 limit = cfg && cfg->hbm_budget ? std::min<u64>(cfg->hbm_budget, free_b) : (u64)free_b;
+  u64 free_b = 0;
+  {
+    const int rc = free_hbm(&free_b);
+    if (rc) return rc;
+  }
+  const u64 limit = cfg && cfg->hbm_budget ? std::min<u64>(cfg->hbm_budget, free_b) : free_b;
   // fewer lanes while the lanes' workspaces do not fit
   std::vector<int> lane;
   std::vector<u64> ws_bytes;
@@ -487,7 +532,8 @@ int batch_build(std::vector<kc_batch::Job>&& jobs, const kc_config* cfg, kc_batc
   if (cfg && cfg->hbm_budget && need > cfg->hbm_budget)
     return fail(KC_ENOMEM, "batch needs %llu bytes > budget %llu", (unsigned long long)need,
                 (unsigned long long)cfg->hbm_budget);
-  if (need > free_b) return fail(KC_ENOMEM, "batch needs %llu bytes of HBM, %zu free", (unsigned long long)need, free_b);
+  if (need > free_b) return fail(KC_ENOMEM, "batch needs %llu bytes of HBM, %llu free", (unsigned long long)need,
+                             (unsigned long long)free_b);
   b->device_bytes = need;
   for (size_t i = 0; i < sizes.size(); ++i) {
     if (item_group[i] >= 0) b->groups[item_group[i]].lane = lane[i];
@@ -495,18 +541,20 @@ int batch_build(std::vector<kc_batch::Job>&& jobs, const kc_config* cfg, kc_batc
   }
   for (int l = 0; l < b->lanes; ++l) {
     char* p = nullptr;
-    HIP_TRY(hipMalloc(&p, ws_bytes[l]));
+    HIP_TRY(dev_malloc(&p, ws_bytes[l]));
     b->ws.push_back(p);
   }
   for (auto& G : b->groups) {   // tables written once, before any capture
-    HIP_TRY(hipMalloc(&G.own, std::max<u64>(256, G.mp.own_bytes)));
+    HIP_TRY(dev_malloc(&G.own, std::max<u64>(256, G.mp.own_bytes)));
+    G.first.resize(G.mp.n_sets + 1);
+    G.tot.resize(G.mp.n_sets);
     std::vector<char> tab;
     std::vector<u32> bset;
     multi_tables(G.mp, &tab, &bset);
     HIP_TRY(hipMemcpy(G.own + G.mp.o_tab, tab.data(), tab.size(), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(G.own + G.mp.o_bset, bset.data(), 4 * bset.size(), hipMemcpyHostToDevice));
   }
-  HIP_TRY(hipMalloc(&b->out_mem, std::max<u64>(256, out_total)));
+  HIP_TRY(dev_malloc(&b->out_mem, std::max<u64>(256, out_total)));
   char* o = b->out_mem;
   for (auto& J : b->jobs) {
     if (J.group >= 0) continue;
@@ -572,6 +620,10 @@ int kc_batch_run(kc_batch* b, void* stream) {
   g_err.clear();
   if (!b) return fail(KC_EINVAL, "NULL batch");
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  {
+    std::lock_guard<std::mutex> g(b->result_mu);
+    for (auto& G : b->groups) G.on_host = false;
+  }
   if (b->use_graph) {
     HIP_TRY(hipGraphLaunch(b->exec, st));
   } else {
@@ -586,16 +638,27 @@ int kc_batch_result(kc_batch* b, uint32_t job, kc_result* out) {
   g_err.clear();
   if (!b || !out || job >= b->jobs.size()) return fail(KC_EINVAL, "bad batch result request");
   auto& J = b->jobs[job];
-  if (J.group >= 0) {
-    const auto& G = b->groups[J.group];
-    const MultiOut O = multi_out(G.mp, G.own);
-    u64 fr[2];
-    HIP_TRY(hipMemcpy(fr, O.first + J.set, 16, hipMemcpyDeviceToHost));
-    const int kw = G.mp.P.key_words;
-    return fetch_result(O.tot + J.set, reinterpret_cast<const uint64_t*>(O.kmers) + fr[0] * kw, O.counts + fr[0],
-                        O.hist + (u64)J.set * G.mp.hist_len, fr[1] - fr[0], G.mp.hist_len, kw, b->origin, out);
+  std::lock_guard<std::mutex> g(b->result_mu);
+  if (!b->pin && ++b->n_results >= 3 && hipHostMalloc(&b->pin, kc_batch::PIN_BYTES, hipHostMallocDefault) != hipSuccess) {
+    b->pin = nullptr;   // (copied straight to the result then)
+    (void)hipGetLastError();
   }
-  return fetch_result(J.tot, J.kmers, J.counts, J.hist, J.ji.pair_cap, J.j.hist_len, J.ji.key_words, b->origin, out);
+  if (J.group >= 0) {
+    auto& G = b->groups[J.group];
+    const MultiOut O = multi_out(G.mp, G.own);
+    if (!G.on_host) {
+      HIP_TRY(hipMemcpy(G.first.data(), O.first, 8 * G.first.size(), hipMemcpyDeviceToHost));
+      HIP_TRY(hipMemcpy(G.tot.data(), O.tot, sizeof(kc_totals) * G.tot.size(), hipMemcpyDeviceToHost));
+      G.on_host = true;
+    }
+    const u64 f0 = G.first[J.set], f1 = G.first[J.set + 1];
+    const int kw = G.mp.P.key_words;
+    return fetch_result(O.tot + J.set, reinterpret_cast<const uint64_t*>(O.kmers) + f0 * kw, O.counts + f0,
+                        O.hist + (u64)J.set * G.mp.hist_len, f1 - f0, G.mp.hist_len, kw, b->origin, out, &G.tot[J.set],
+                        b->pin, kc_batch::PIN_BYTES);
+  }
+  return fetch_result(J.tot, J.kmers, J.counts, J.hist, J.ji.pair_cap, J.j.hist_len, J.ji.key_words, b->origin, out,
+                      nullptr, b->pin, kc_batch::PIN_BYTES);
 }
 
 int kc_batch_info(const kc_batch* b, uint32_t* n_counts, uint32_t* n_shared, uint32_t* lanes,
@@ -634,7 +697,7 @@ int kc_count_batch(uint32_t n_jobs, const kc_job* jobs, kc_result* outs, const k
     in_bytes += align_up(bj[i].ji.R + 16, 256) + align_up(8 * (jobs[i].n_reads + 1), 256);
   }
   char* in = nullptr;
-  HIP_TRY(hipMalloc(&in, std::max<u64>(256, in_bytes)));
+  HIP_TRY(dev_malloc(&in, std::max<u64>(256, in_bytes)));
   char* p = in;
   for (u32 i = 0; i < n_jobs; ++i) {
     bj[i].j = jobs[i];
@@ -1193,7 +1256,7 @@ int kc_server_create(const kc_server_cfg* cfg, kc_server** out) {
   int rc = warm_launch_facts();
   if (rc) return rc;
   HIP_TRY(hipGetDevice(&s->device));
-  HIP_TRY(hipMalloc(&s->arena_mem, s->cfg.arena_bytes));
+  HIP_TRY(dev_malloc(&s->arena_mem, s->cfg.arena_bytes));
   s->arena.init(s->arena_mem, s->cfg.arena_bytes);
   for (u32 i = 0; i < s->cfg.slots; ++i) {
     Slot sl;
