@@ -895,12 +895,9 @@ int count_buckets(const Plan& P, const Ws<K>& W, const u32* blk_base, uint32_t l
   if (marks) stage_mark(6, st);
   // merge the chunks' (k-mer, count) lists: compact, sort by k-mer, sum each run's counts
   scan_u32(W.klcnt, W.kloff, W.meta + 4, P.chunk_cap, W.kl_n, W.scanbuf, st, W.kl_nc, P.kl_cap);
-  hipLaunchKernelGGL((k_gather_segments<K>), grid_for(P.chunk_cap, 4, 4096), dim3(256), 0, st, W.s0k, W.s0c,
-                     W.chstart, (const u64*)nullptr, 0u, W.klcnt, W.kloff, W.meta + 4, P.chunk_cap, W.kl0k, W.kl0c,
-                     (const u64*)nullptr, ~0ull);
-  // each heavy bucket's lists are one segment, sorted on its own (in place)
-  hipLaunchKernelGGL(k_merge_segs, grid_for(P.B + 1, 256, 1024), dim3(256), 0, st, W.kloff, W.lch0, W.meta + 1,
-                     W.meta + 4, P.chunk_cap, W.kl_nc, W.seg);
+  // (each heavy bucket's lists are one segment, sorted on its own, in place)
+  hipLaunchKernelGGL((k_gather_lists<K>), grid_for(P.chunk_cap, 4, 4096), dim3(256), 0, st, W.s0k, W.s0c, W.chstart,
+                     W.klcnt, W.kloff, W.lch0, W.meta + 1, W.meta + 4, P.chunk_cap, W.kl_nc, W.kl0k, W.kl0c, W.seg);
   int seg_grid = 0;
   if ((rc = seg_sort<K>(W.kl0k, W.kl0c, W.kl1k, W.kl1c, W.kl0k, W.kl0c, ~0ull, W.seg, W.meta + 1,
                         std::min<u64>(P.B, P.chunk_cap), 2 * P.k, true, true, nullptr, 0, n_cu, st, &seg_grid)))
@@ -916,9 +913,8 @@ int count_buckets(const Plan& P, const Ws<K>& W, const u32* blk_base, uint32_t l
     seg_bits = md->seg_bits;
   }
   hipLaunchKernelGGL((k_rle_count<K>), dim3(P.nb_large), dim3(256), 0, st, lks, W.kl_nc, W.bc, seg_bits);
-  hipLaunchKernelGGL(k_scan_u32, dim3(1), dim3(1024), 0, st, W.bc, W.bc, (const u64*)nullptr, (u64)P.nb_large,
-                     W.nruns, (u64*)nullptr, 0ull);
-  hipLaunchKernelGGL((k_rle_heads<K>), dim3(P.nb_large), dim3(256), 0, st, lks, W.kl_nc, W.bc, W.hp, seg_bits);
+  hipLaunchKernelGGL((k_rle_heads<K>), dim3(P.nb_large), dim3(256), 0, st, lks, W.kl_nc, W.bc, W.hp, W.nruns,
+                     seg_bits);
   if (ms)
     hipLaunchKernelGGL((k_rle_runs<K, true>), dim3(RUN_BLOCKS), dim3(256), 0, st, ca, lks, lvs, W.kl_nc, W.hp,
                        W.nruns, fk, fc, W.scnt + P.B, (const u64*)W.seg, md->rset);
@@ -927,6 +923,7 @@ int count_buckets(const Plan& P, const Ws<K>& W, const u32* blk_base, uint32_t l
                        fc, W.scnt + P.B, (const u64*)nullptr, (u32*)nullptr);
 
   if (marks) stage_mark(7, st);
+  if (!ms && !out_k) return KC_OK;   // (sorted from where they are: see surv_segs)
   // ---- compact the survivors (buckets, then merged runs)
   scan_u32(W.scnt, W.soff, (const u64*)nullptr, (u64)P.B + RUN_BLOCKS, W.surv_n, W.scanbuf, st, W.surv_nc,
            P.surv_cap);
@@ -950,22 +947,29 @@ int count_buckets(const Plan& P, const Ws<K>& W, const u32* blk_base, uint32_t l
     return KC_OK;
   }
   hipLaunchKernelGGL((k_gather_segments<K>), grid_for(P.B, 4, 4096), dim3(256), 0, st, W.s0k, W.s0c, W.kall,
-                     (const u64*)nullptr, 0u, W.scnt, W.soff, (const u64*)nullptr, (u64)P.B, out_k, out_c, out_base,
+                     (const u64*)nullptr, 0u, W.scnt, W.soff, (u64)P.B, out_k, out_c, out_base,
                      out_cap);
   hipLaunchKernelGGL((k_gather_segments<K>), grid_for(RUN_BLOCKS, 4, 4096), dim3(256), 0, st, fk, fc,
-                     (const u64*)nullptr, W.nruns, RUN_BLOCKS, W.scnt + P.B, W.soff + P.B, (const u64*)nullptr,
-                     (u64)RUN_BLOCKS, out_k, out_c, out_base, out_cap);
+                     (const u64*)nullptr, W.nruns, RUN_BLOCKS, W.scnt + P.B, W.soff + P.B, (u64)RUN_BLOCKS, out_k, out_c, out_base, out_cap);
   return KC_OK;
 }
 
+// The survivors of a one-pass count where count_buckets left them.
+template <typename K>
+SurvSegs surv_segs(const Plan& P, const Ws<K>& W) {
+  return SurvSegs{W.s0k, W.s0c, W.kall, W.scnt, P.B, RUN_BLOCKS, W.kl1k, W.kl1c, W.nruns};
+}
+
 // Survivors in[0, *n_ptr) (their count at most n_cap) -> split into key ranges by their
-// top bits (in -> mid -> in), then each range sorted on chip into the caller's buffers.
+// top bits (in -> mid -> in), then each range sorted on chip into the caller's buffers.  With
+// `segs` the survivors are read from there (then in only holds the ranges, and may be segs'
+// bucket slots) and their number is set.
 template <typename K>
 int sort_survivors(const Plan& P, const Ws<K>& W, K* in_k, u32* in_c, K* mid_k, u32* mid_c, const u64* n_ptr,
                    u64 n_cap, uint64_t* d_kmers, uint32_t* d_counts, uint64_t pair_cap, int n_cu, hipStream_t st,
-                   int key_bits = 0) {
+                   int key_bits = 0, const SurvSegs* segs = nullptr) {
   const int nbits = key_bits ? key_bits : 2 * P.k;   // significant bits of the keys
-  MsdArgs ma;
+  MsdArgs ma{};
   ma.in_k = in_k;
   ma.in_v = in_c;
   ma.n_ptr = n_ptr;
@@ -981,9 +985,16 @@ int sort_survivors(const Plan& P, const Ws<K>& W, K* in_k, u32* in_c, K* mid_k, 
   ma.target = seg_range_target<K>();
   // blocks of the coarse pass: about 16K survivors each at most, up to MSD_NB
   ma.nb = (u32)std::min<u64>(MSD_NB, std::max<u64>(1, ceil_div(n_cap, 16384)));
-  hipLaunchKernelGGL((k_msd_hist<K>), dim3(ma.nb), dim3(256), 0, st, ma);
-  scan_u32(ma.hist, ma.hist, (const u64*)nullptr, 256ull * ma.nb, (u64*)nullptr, W.scanbuf, st);
-  hipLaunchKernelGGL((k_msd_scatter<K>), dim3(ma.nb), dim3(512), 0, st, ma);
+  if (segs) {
+    ma.sv = *segs;
+    hipLaunchKernelGGL((k_msd_hist<K, true>), dim3(ma.nb), dim3(256), 0, st, ma);
+    scan_u32(ma.hist, ma.hist, (const u64*)nullptr, 256ull * ma.nb, W.surv_n, W.scanbuf, st, W.surv_nc, n_cap);
+    hipLaunchKernelGGL((k_msd_scatter<K, true>), dim3(ma.nb), dim3(512), 0, st, ma);
+  } else {
+    hipLaunchKernelGGL((k_msd_hist<K, false>), dim3(ma.nb), dim3(256), 0, st, ma);
+    scan_u32(ma.hist, ma.hist, (const u64*)nullptr, 256ull * ma.nb, (u64*)nullptr, W.scanbuf, st);
+    hipLaunchKernelGGL((k_msd_scatter<K, false>), dim3(ma.nb), dim3(512), 0, st, ma);
+  }
   hipLaunchKernelGGL((k_msd_fine<K>), dim3(256), dim3(1024), 0, st, ma);
   // the key ranges number 256 << g2, g2 growing with the survivor count (at most n_cap)
   const u64 max_ranges = 256ull << msd_g2(n_cap, seg_range_target<K>());
@@ -1009,17 +1020,17 @@ int enqueue(const Plan& P, void* ws, const uint8_t* d_reads, const uint64_t* d_o
   // ---- stage 1: encode, read starts, minimizers and supermers, bucket partition
   launch_encode<K>(P, W, d_reads, d_offsets, st);
   const ExtractArgs ea = extract_args<K>(P, W, d_offsets);
-  K* s1k = W.kl0k;   // dense survivors of a one-pass count: where the sorted lists were
-  u32* s1c = W.kl0c;
   stage_mark(1, st);
   if (!rounds) {
     launch_extract<EX_ONE>(P, ea, st);
-    if ((rc = count_buckets<K>(P, W, nullptr, lo, hi, hist_len, d_hist, d_tot, s1k, s1c, nullptr, ~0ull, true, n_cu,
-                               st)))
+    if ((rc = count_buckets<K>(P, W, nullptr, lo, hi, hist_len, d_hist, d_tot, nullptr, nullptr, nullptr, ~0ull, true,
+                               n_cu, st)))
       return rc;
     // ---- output: the survivors sorted by key straight into the caller's buffers
-    if ((rc = sort_survivors<K>(P, W, s1k, s1c, W.s0k, W.s0c, W.surv_nc, P.surv_cap, d_kmers, d_counts, pair_cap, n_cu,
-                                st)))
+    // (first to where the sorted lists were)
+    const SurvSegs segs = surv_segs<K>(P, W);
+    if ((rc = sort_survivors<K>(P, W, W.s0k, W.s0c, W.kl0k, W.kl0c, W.surv_nc, P.surv_cap, d_kmers, d_counts, pair_cap,
+                                n_cu, st, 0, &segs)))
       return rc;
     hipLaunchKernelGGL(k_finalize, dim3(1), dim3(64), 0, st, d_tot, W.counters, W.surv_n, P.rec_cap, P.surv_cap,
                        W.flags, W.meta, W.kl_n, P.B);
@@ -1828,15 +1839,16 @@ int enqueue_ext_by_count(const ExtPlan& E, void* ws, const uint8_t* d_reads, con
                        E.n_blk, E.blk_sh, ctrl + X_MAXLEN);
   stage_mark(1, st);
   launch_extract<EX_ONE>(P, extract_args<K>(P, W, d_offsets), st);
-  // the pairs in key order at Z (the sort's second buffer doubles as its output: a range is
-  // read from X and written to its own place)
-  if ((rc = count_buckets<K>(P, W, nullptr, lo, hi, hist_len, d_hist, d_tot, W.kl0k, W.kl0c, nullptr, ~0ull, false,
+  // the pairs in key order at X (the sort's second buffer doubles as its output: a range is
+  // read from Z and written to its own place)
+  if ((rc = count_buckets<K>(P, W, nullptr, lo, hi, hist_len, d_hist, d_tot, nullptr, nullptr, nullptr, ~0ull, false,
                              n_cu, st)))
     return rc;
-  K* const pk = W.s0k;
-  u32* const pc = W.s0c;
-  if ((rc = sort_survivors<K>(P, W, W.kl0k, W.kl0c, pk, pc, W.surv_nc, P.surv_cap, reinterpret_cast<uint64_t*>(pk), pc,
-                              P.surv_cap, n_cu, st)))
+  K* const pk = W.kl0k;
+  u32* const pc = W.kl0c;
+  const SurvSegs segs = surv_segs<K>(P, W);
+  if ((rc = sort_survivors<K>(P, W, W.s0k, W.s0c, pk, pc, W.surv_nc, P.surv_cap, reinterpret_cast<uint64_t*>(pk), pc,
+                              P.surv_cap, n_cu, st, 0, &segs)))
     return rc;
   const u64 n_cap = P.surv_cap / lo + 1;         // pairs at most
   const u64* n_ptr = W.surv_nc;
@@ -1847,10 +1859,11 @@ int enqueue_ext_by_count(const ExtPlan& E, void* ws, const uint8_t* d_reads, con
   scan_u32(off, off, (const u64*)nullptr, otiles, ctrl + X_NOCC, W.scanbuf, st);
   hipLaunchKernelGGL(k_ext_offsets<true>, dim3((u32)otiles), dim3(EXT_T), 0, st, pc, n_ptr, off, d_occ_off, pair_cap);
   stage_mark(2, st);
-  // the pairs' table at X, the windows found at Y
-  u32* tab = W.recA;
+  // the pairs' table at Y, the windows found at Z (the last of the four arrays where the pair
+  // index of every position was)
+  u32* tab = W.ptmp_rec;
   u32* found = W.hp;
-  const u64 slot_cap = P.slots;   // (the region holds that many records of a slot's size)
+  const u64 slot_cap = P.rec_cap;   // (the region holds that many records of a slot's size)
   hipLaunchKernelGGL((k_ext_table_clear<K>), dim3(2048), dim3(256), 0, st, n_ptr, slot_cap,
                      reinterpret_cast<uint4*>(tab));
   hipLaunchKernelGGL((k_ext_table_insert<K>), grid_for(n_cap, 256, 4096), dim3(256), 0, st, pk, n_ptr,
@@ -1877,8 +1890,8 @@ int enqueue_ext_by_count(const ExtPlan& E, void* ws, const uint8_t* d_reads, con
   stage_mark(3, st);
   scan_u32(blk, blk, (const u64*)nullptr, E.n_tiles, ctrl + X_NWIN, W.scanbuf, st);
   const u64 N = P.kl_cap;
-  u32* i0 = W.ptmp_rec;
-  u32 *v0 = i0 + N, *i1 = i0 + 2 * N, *v1 = i0 + 3 * N;
+  u32* i0 = reinterpret_cast<u32*>(W.s0k);
+  u32 *v0 = i0 + N, *i1 = i0 + 2 * N, *v1 = found;
   hipLaunchKernelGGL(k_ext_compact, dim3((u32)E.n_tiles), dim3(EXT_T), 0, st, wa, found, i0, v0);
   stage_mark(4, st);
   // sorted by pair index: the fewest passes of at most 9 bits that the most pairs would need

@@ -85,7 +85,7 @@ __device__ __forceinline__ u32 lane_next(u32 v, u32 fill) {
 __device__ __forceinline__ u32 lane_rot1(u32 v) {
   return (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x13C, 0xF, 0xF, false);
 }
-// v of lane `src` (a constant), as a wave-uniform value.
+// v of lane `src` (the same in all lanes), as a wave-uniform value.
 __device__ __forceinline__ u32 lane_read(u32 v, int src) { return (u32)__builtin_amdgcn_readlane((int)v, src); }
 
 // A value that is the same in all lanes, as a scalar.

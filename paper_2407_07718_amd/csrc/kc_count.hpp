@@ -1064,15 +1064,18 @@ __global__ __launch_bounds__(256) void k_rle_count(const K* __restrict__ keys, c
   if (threadIdx.x == 0) bc[blockIdx.x] = (u32)tot;
 }
 
-// Head positions in order: hp[r] = index of the first key of run r.
+// Head positions in order: hp[r] = index of the first key of run r; and the number of runs.
+// (Each block adds up the heads before its own: at most 1024 counts, less than a scan's launch.)
 template <typename K>
 __global__ __launch_bounds__(256) void k_rle_heads(const K* __restrict__ keys, const u64* __restrict__ n_ptr,
                                                    const u32* __restrict__ bc, u32* __restrict__ hp,
-                                                   const u32* __restrict__ seg_bits = nullptr) {
+                                                   u64* __restrict__ n_runs, const u32* __restrict__ seg_bits = nullptr) {
   __shared__ u64 scr[17];
   u64 s, e;
   block_range(*n_ptr, gridDim.x, &s, &e);
-  u64 base = bc[blockIdx.x];
+  u64 base, before = 0;
+  for (u32 i = threadIdx.x; i < blockIdx.x; i += 256) before += bc[i];
+  block_exclusive_scan<u64>(before, scr, &base);
   for (u64 c0 = s; c0 < e; c0 += 256) {
     const u64 i = c0 + threadIdx.x;
     const bool head = i < e && (i == 0 || !key_eq(keys[i], keys[i - 1]) || seg_start(seg_bits, i));
@@ -1081,6 +1084,7 @@ __global__ __launch_bounds__(256) void k_rle_heads(const K* __restrict__ keys, c
     if (head) hp[base + ex] = (u32)i;
     base += tot;
   }
+  if (blockIdx.x + 1 == gridDim.x && threadIdx.x == 0) *n_runs = base;
 }
 
 // Several read sets: the set of the list entry at position i, through its segment (one
@@ -1192,11 +1196,10 @@ __global__ __launch_bounds__(256) void k_gather_segments(const K* __restrict__ s
                                                          const u64* __restrict__ base_arr,
                                                          const u64* __restrict__ base_range_n, u32 base_range_nb,
                                                          const u32* __restrict__ cnt, const u32* __restrict__ off,
-                                                         const u64* __restrict__ n_seg_ptr, u64 n_seg_max,
+                                                         u64 n_seg,
                                                          K* __restrict__ dst_k, u32* __restrict__ dst_c,
                                                          const u64* __restrict__ dst_base = nullptr,
                                                          u64 dst_cap = ~0ull) {
-  const u64 n_seg = n_seg_ptr ? min(*n_seg_ptr, n_seg_max) : n_seg_max;
   const u64 db = dst_base ? *dst_base : 0ull;   // rounds: the pool's fill so far
   const u64 wave = (blockIdx.x * (u64)blockDim.x + threadIdx.x) >> 6;
   const u64 n_waves = ((u64)gridDim.x * blockDim.x) >> 6;

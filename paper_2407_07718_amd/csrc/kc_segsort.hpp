@@ -48,9 +48,23 @@ __device__ __forceinline__ u32 key_place(K k, int nbits, int canonical) {
   return canonical ? ~__umulhi(~t, ~t) : t;
 }
 
+// Survivors where the count left them: bucket i's s_cnt[i] at s_base[i] of (s_k, s_c), i <
+// n_buckets, and block j of k_rle_runs' s_cnt[n_buckets + j] at its first run of *n_runs in
+// (r_k, r_c), j < n_rblk.
+struct SurvSegs {
+  const void* s_k;
+  const u32* s_c;
+  const u64* s_base;
+  const u32* s_cnt;
+  u32 n_buckets, n_rblk;
+  const void* r_k;
+  const u32* r_c;
+  const u64* n_runs;
+};
 struct MsdArgs {
-  const void* in_k;        // dense survivors
+  const void* in_k;        // dense survivors ...
   const u32* in_v;
+  SurvSegs sv;             // ... or as the count left them
   const u64* n_ptr;        // survivors
   void* mid_k;             // grouped by the top 8 bits of their places
   u32* mid_v;
@@ -407,17 +421,30 @@ __global__ __launch_bounds__(WPB * 64) void k_seg_wave(SegArgs A) {
   }
 }
 
-// Segment table of the heavy buckets' lists: lists are compacted in chunk order and the
-// chunks of one bucket are consecutive, so bucket i spans the scanned list offsets of its
-// first chunk up to those of the next bucket's first chunk.
-__global__ __launch_bounds__(256) void k_merge_segs(const u32* __restrict__ kloff, const u32* __restrict__ large_ch0,
-                                                    const u64* __restrict__ n_large_ptr,
-                                                    const u64* __restrict__ n_chunks_ptr, u64 chunk_cap,
-                                                    const u64* __restrict__ n_entries_ptr, u64* __restrict__ seg) {
+// The chunks' lists gathered into one array, and the segment table of the heavy buckets: lists
+// are compacted in chunk order and the chunks of one bucket are consecutive, so bucket i spans
+// the scanned list offsets of its first chunk up to those of the next bucket's first chunk.
+template <typename K>
+__global__ __launch_bounds__(256) void k_gather_lists(const K* __restrict__ src_k, const u32* __restrict__ src_c,
+                                                      const u64* __restrict__ chunk_start, const u32* __restrict__ cnt,
+                                                      const u32* __restrict__ kloff, const u32* __restrict__ large_ch0,
+                                                      const u64* __restrict__ n_large_ptr,
+                                                      const u64* __restrict__ n_chunks_ptr, u64 chunk_cap,
+                                                      const u64* __restrict__ n_entries_ptr, K* __restrict__ dst_k,
+                                                      u32* __restrict__ dst_c, u64* __restrict__ seg) {
   const u64 n_large = *n_large_ptr, n_chunks = min(*n_chunks_ptr, chunk_cap), n_ent = *n_entries_ptr;
-  for (u64 i = blockIdx.x * (u64)blockDim.x + threadIdx.x; i <= n_large; i += (u64)gridDim.x * blockDim.x) {
+  const u64 t = blockIdx.x * (u64)blockDim.x + threadIdx.x, n_t = (u64)gridDim.x * blockDim.x;
+  for (u64 i = t; i <= n_large; i += n_t) {
     const u64 c = i < n_large ? (u64)large_ch0[i] : n_chunks;
     seg[i] = c < n_chunks ? min((u64)kloff[c], n_ent) : n_ent;
+  }
+  for (u64 i = t >> 6; i < n_chunks; i += n_t >> 6) {
+    const u32 c = cnt[i];
+    const u64 from = chunk_start[i], to = kloff[i];
+    for (u32 j = lane_id(); j < c; j += 64) {
+      dst_k[to + j] = src_k[from + j];
+      dst_c[to + j] = src_c[from + j];
+    }
   }
 }
 
@@ -427,47 +454,161 @@ __global__ __launch_bounds__(256) void k_merge_segs(const u32* __restrict__ klof
 // pass, one block per coarse group, on the next g2 bits, g2 chosen from the survivor
 // count so that a range averages at most `target` keys.  The fine pass writes the range
 // table in key order.
-template <typename K>
+//
+// The coarse pass of a one-pass count reads the survivors from where the count left them: a
+// block takes an equal share of the buckets and of the runs' blocks, its waves their segments
+// in turn, one row of up to 64 at a time.  (Gathered into one dense array first, 1 Gbp with 43 M
+// survivors took 13.19 ms instead of 12.87, 60 Mbp with 20 M 1.76 instead of 1.65, and every
+// count five launches more.)
+template <typename K, u32 NW>
+struct SegRows {
+  const SurvSegs& V;
+  u32 b0, nb, r0, n;   // the block's buckets [b0, b0 + nb), runs' blocks from r0 on, segments in all
+  u32 i0;              // the wave's current 64 segments: i0 + NW * lane
+  u32 c;               // lane: its segment's survivors ...
+  u64 base;            // ... and place
+  bool run;
+  u64 left;            // lanes whose segments are still to do
+  u32 off;             // done of the first of them
+
+  __device__ __forceinline__ SegRows(const SurvSegs& v, u32 n_blk) : V(v) {
+    const u32 pb = (v.n_buckets + n_blk - 1) / n_blk, pr = (v.n_rblk + n_blk - 1) / n_blk;
+    b0 = min(v.n_buckets, blockIdx.x * pb);
+    nb = min(v.n_buckets - b0, pb);
+    r0 = min(v.n_rblk, blockIdx.x * pr);
+    n = nb + min(v.n_rblk - r0, pr);
+    i0 = uniform(threadIdx.x >> 6);
+    load();
+  }
+  __device__ __forceinline__ void load() {
+    const u32 i = i0 + NW * lane_id();
+    c = 0;
+    base = 0;
+    run = i >= nb;
+    if (i < n) {
+      if (run) {
+        const u32 j = r0 + i - nb;
+        const u64 nr = *V.n_runs, per = (nr + V.n_rblk - 1) / V.n_rblk;
+        c = V.s_cnt[V.n_buckets + j];
+        base = min(nr, j * per);
+      } else {
+        c = V.s_cnt[b0 + i];
+        base = V.s_base[b0 + i];
+      }
+    }
+    left = __ballot(c != 0);
+    off = 0;
+  }
+  // The next row's keys, one per lane: true where the lane has one.  (Past the last row: none.)
+  __device__ __forceinline__ bool row(const K** k, const u32** v) {
+    while (!left) {
+      if (i0 + 64 * NW >= n) return false;
+      i0 += 64 * NW;
+      load();
+    }
+    const int l = __builtin_ctzll(left);
+    const u32 cl = lane_read(c, l), o = off + lane_id();
+    const u64 at = (((u64)lane_read((u32)(base >> 32), l) << 32) | lane_read((u32)base, l)) + o;
+    const bool rn = i0 + NW * (u32)l >= nb;
+    *k = reinterpret_cast<const K*>(rn ? V.r_k : V.s_k) + at;
+    *v = (rn ? V.r_c : V.s_c) + at;
+    off += 64;
+    if (off >= cl) {
+      off = 0;
+      left &= left - 1;
+    }
+    return o < cl;
+  }
+  __device__ __forceinline__ bool done() const { return !left && i0 + 64 * NW >= n; }
+};
+
+template <typename K, bool SEGS>
 __global__ __launch_bounds__(256) void k_msd_hist(MsdArgs A) {
   __shared__ u32 h[256];
-  const u64 n = *A.n_ptr;
-  const u64 per = (n + A.nb - 1) / A.nb;
-  const u64 a = min(n, blockIdx.x * per), b = min(n, a + per);
-  const K* in = reinterpret_cast<const K*>(A.in_k);
   h[threadIdx.x] = 0;
   __syncthreads();
-  for (u64 i = a + threadIdx.x; i < b; i += 256) atomicAdd(&h[key_place(in[i], A.nbits, A.canonical) >> 24], 1u);
+  if constexpr (SEGS) {
+    constexpr int U = 8;   // rows in flight
+    SegRows<K, 4> S(A.sv, A.nb);
+    while (!S.done()) {
+      K k[U];
+      bool on[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const K* pk;
+        const u32* pv;
+        on[u] = S.row(&pk, &pv);
+        k[u] = on[u] ? *pk : key_zero<K>();
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (on[u]) atomicAdd(&h[key_place(k[u], A.nbits, A.canonical) >> 24], 1u);
+    }
+  } else {
+    const u64 n = *A.n_ptr;
+    const u64 per = (n + A.nb - 1) / A.nb;
+    const u64 a = min(n, blockIdx.x * per), b = min(n, a + per);
+    const K* in = reinterpret_cast<const K*>(A.in_k);
+    for (u64 i = a + threadIdx.x; i < b; i += 256) atomicAdd(&h[key_place(in[i], A.nbits, A.canonical) >> 24], 1u);
+  }
   __syncthreads();
   A.hist[(u64)threadIdx.x * A.nb + blockIdx.x] = h[threadIdx.x];
 }
 
-// Elements [a, b) of in moved to out in rounds of R staged through LDS: each round is
+// Pairs for msd_rounds, up to IT per thread at a time: those of [a, b) of an array ...
+template <typename K, u32 T, u32 IT>
+struct DensePairs {
+  const K* in;
+  const u32* in_v;
+  u64 r0, b;
+  __device__ __forceinline__ bool more() const { return r0 < b; }
+  __device__ __forceinline__ void get(K (&k)[IT], u32 (&v)[IT], bool (&on)[IT]) {
+#pragma unroll
+    for (u32 j = 0; j < IT; ++j) {
+      const u64 i = r0 + threadIdx.x + j * T;
+      on[j] = i < b;
+      k[j] = on[j] ? in[i] : key_zero<K>();
+      v[j] = on[j] ? in_v[i] : 0u;
+    }
+    r0 += (u64)IT * T;
+  }
+};
+// ... or the block's share of the survivors as the count left them.
+template <typename K, u32 T, u32 IT>
+struct SegPairs {
+  SegRows<K, T / 64> S;
+  __device__ __forceinline__ bool more() const { return __syncthreads_or(!S.done()); }
+  __device__ __forceinline__ void get(K (&k)[IT], u32 (&v)[IT], bool (&on)[IT]) {
+#pragma unroll
+    for (u32 j = 0; j < IT; ++j) {
+      const K* pk;
+      const u32* pv;
+      on[j] = S.row(&pk, &pv);
+      k[j] = on[j] ? *pk : key_zero<K>();
+      v[j] = on[j] ? *pv : 0u;
+    }
+  }
+};
+
+// The pairs of `in` moved to out in rounds of at most R staged through LDS: each round is
 // ranked by its field (fb bits of its place below the leading `pb`, 2^fb <= F) with LDS counters,
 // staged in field order and written so that consecutive threads write consecutive slots
 // of a field's range; gpos[f] is the next output slot of field f (advanced per round).
 // cnt, lbase and gpos have F <= T entries.  Block-wide (barriers inside).
-template <typename K, u32 T, u32 F>
-__device__ __forceinline__ void msd_rounds(const K* __restrict__ in, const u32* __restrict__ in_v, u64 a, u64 b,
-                                           const MsdArgs& A, int pb, int fb, K* __restrict__ out, u32* __restrict__ out_v, K* sk,
-                                           u32* sv, u32* cnt, u32* lbase, u32* gpos, u64* scr) {
-  constexpr u32 R = sizeof(K) == 8 ? 4096u : 2048u, IT = R / T;
+template <typename K, u32 T, u32 F, u32 IT, typename In>
+__device__ __forceinline__ void msd_rounds(In& in, const MsdArgs& A, int pb, int fb, K* __restrict__ out,
+                                           u32* __restrict__ out_v, K* sk, u32* sv, u32* cnt, u32* lbase, u32* gpos,
+                                           u64* scr) {
   const u32 tid = threadIdx.x;
   auto field = [&](K k) { return fb ? (key_place(k, A.nbits, A.canonical) << pb) >> (32 - fb) : 0u; };
-  for (u64 r0 = a; r0 < b; r0 += R) {
-    const u32 nr = (u32)min((u64)R, b - r0);
+  while (in.more()) {
     K kr[IT];
     u32 vr[IT], cc[IT], rk[IT];
+    bool on[IT];
+    in.get(kr, vr, on);
 #pragma unroll
     for (u32 j = 0; j < IT; ++j) {
-      const u32 i = tid + j * T;
-      if (i < nr) {
-        kr[j] = in[r0 + i];
-        vr[j] = in_v[r0 + i];
-      }
-    }
-#pragma unroll
-    for (u32 j = 0; j < IT; ++j) {
-      if (tid + j * T < nr) {
+      if (on[j]) {
         cc[j] = field(kr[j]);
         rk[j] = atomicAdd(&cnt[cc[j]], 1u);
       }
@@ -480,14 +621,14 @@ __device__ __forceinline__ void msd_rounds(const K* __restrict__ in, const u32* 
     __syncthreads();
 #pragma unroll
     for (u32 j = 0; j < IT; ++j) {
-      if (tid + j * T < nr) {
+      if (on[j]) {
         const u32 at = lbase[cc[j]] + rk[j];
         sk[at] = kr[j];
         sv[at] = vr[j];
       }
     }
     __syncthreads();
-    for (u32 i = tid; i < nr; i += T) {
+    for (u32 i = tid; i < (u32)tot; i += T) {
       const u32 c = field(sk[i]);
       const u64 d = (u64)gpos[c] + (i - lbase[c]);
       out[d] = sk[i];
@@ -503,7 +644,7 @@ __device__ __forceinline__ void msd_rounds(const K* __restrict__ in, const u32* 
 }
 
 // Coarse scatter: the block's range in rounds staged through LDS, written group by group.
-template <typename K>
+template <typename K, bool SEGS>
 __global__ __launch_bounds__(512) void k_msd_scatter(MsdArgs A) {
   constexpr u32 T = 512, R = sizeof(K) == 8 ? 4096u : 2048u;
   __shared__ K sk[R];
@@ -511,16 +652,24 @@ __global__ __launch_bounds__(512) void k_msd_scatter(MsdArgs A) {
   __shared__ u32 cnt[256], lbase[256], gpos[256];
   __shared__ u64 scr[17];
   const u32 tid = threadIdx.x;
-  const u64 n = *A.n_ptr;
-  const u64 per = (n + A.nb - 1) / A.nb;
-  const u64 a = min(n, blockIdx.x * per), b = min(n, a + per);
   if (tid < 256) {
     cnt[tid] = 0;
     gpos[tid] = A.hist[(u64)tid * A.nb + blockIdx.x];
   }
   __syncthreads();
-  msd_rounds<K, T, 256>(reinterpret_cast<const K*>(A.in_k), A.in_v, a, b, A, 0, 8,
-                   reinterpret_cast<K*>(A.mid_k), A.mid_v, sk, sv, cnt, lbase, gpos, scr);
+  auto move = [&](auto& in) {
+    msd_rounds<K, T, 256, R / T>(in, A, 0, 8, reinterpret_cast<K*>(A.mid_k), A.mid_v, sk, sv, cnt, lbase, gpos, scr);
+  };
+  if constexpr (SEGS) {
+    SegPairs<K, T, R / T> in{SegRows<K, T / 64>(A.sv, A.nb)};
+    move(in);
+  } else {
+    const u64 n = *A.n_ptr;
+    const u64 per = (n + A.nb - 1) / A.nb;
+    const u64 a = min(n, blockIdx.x * per), b = min(n, a + per);
+    DensePairs<K, T, R / T> in{reinterpret_cast<const K*>(A.in_k), A.in_v, a, b};
+    move(in);
+  }
 }
 
 // Fine pass (43 M pairs: 0.69 ms with groups by leading bits, the first twice as long as the
@@ -559,5 +708,7 @@ __global__ __launch_bounds__(1024) void k_msd_fine(MsdArgs A) {
   __syncthreads();
   cnt[tid] = 0;
   __syncthreads();
-  msd_rounds<K, T, 1u << MSD_G2_MAX>(mid, A.mid_v, a, b, A, 8, g2, reinterpret_cast<K*>(A.out_k), A.out_v, sk, sv, cnt, lbase, cur, scr);
+  DensePairs<K, T, R / T> in{mid, A.mid_v, a, b};
+  msd_rounds<K, T, 1u << MSD_G2_MAX, R / T>(in, A, 8, g2, reinterpret_cast<K*>(A.out_k), A.out_v, sk, sv, cnt, lbase,
+                                            cur, scr);
 }
