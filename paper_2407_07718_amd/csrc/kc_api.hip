@@ -110,7 +110,7 @@ struct Plan {
 // Control words (all zeroed at the start of a count).
 enum Ctrl : int {
   C_COUNTERS = 0,   // [0] records, [1] windows
-  C_META = 2,       // 8 words, see k_plan_scan
+  C_META = 2,       // 8 words, see plan_meta
   C_FLAGS = 10,
   C_SURV_N = 11,
   C_NRUNS = 12,
@@ -547,20 +547,17 @@ int radix_sort(K* k0, K* k1, u32* v0, u32* v1, const u64* n_ptr, u32* counts, u3
   return KC_OK;
 }
 
-// Device-wide exclusive scan (see k_scan_reduce); n_max must be <= 1024 * SCAN_BLOCK.
-// Short inputs take one single-block launch instead of three.
-constexpr u64 SCAN_ONE_BLOCK_MAX = 32768;
-// With `clamped`, min(total, cap) is also written there.
+// Device-wide exclusive scan (see k_scan_u32); n_max must be <= 1024 * SCAN_BLOCK, and bsum holds
+// ceil(n_max / SCAN_BLOCK) values.
 void scan_u32(const u32* in, u32* out, const u64* n_ptr, u64 n_max, u64* total, u64* bsum, hipStream_t st,
               u64* clamped = nullptr, u64 cap = 0) {
-  if (n_max <= SCAN_ONE_BLOCK_MAX) {
-    hipLaunchKernelGGL(k_scan_u32, dim3(1), dim3(1024), 0, st, in, out, n_ptr, n_max, total, clamped, cap);
+  if (n_max <= SCAN_ONE_MAX) {
+    hipLaunchKernelGGL(k_scan_u32, dim3(1), dim3(SCAN_ONE_T), 0, st, in, out, n_ptr, n_max, total, clamped, cap);
     return;
   }
-  const u32 nb = (u32)std::max<u64>(1, (n_max + SCAN_BLOCK - 1) / SCAN_BLOCK);
+  const u32 nb = (u32)((n_max + SCAN_BLOCK - 1) / SCAN_BLOCK);
   hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(SCAN_T), 0, st, in, n_ptr, n_max, bsum);
-  hipLaunchKernelGGL(k_scan_mid, dim3(1), dim3(1024), 0, st, bsum, nb, total, clamped, cap);
-  hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(SCAN_T), 0, st, in, out, n_ptr, n_max, bsum);
+  hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(SCAN_T), 0, st, in, out, n_ptr, n_max, bsum, total, clamped, cap);
 }
 
 inline dim3 grid_for(u64 n, u32 block, u32 max_blocks = 1u << 20) {
@@ -835,7 +832,6 @@ int count_buckets(const Plan& P, const Ws<K>& W, const u32* blk_base, uint32_t l
       hipLaunchKernelGGL(k_plan_write<true>, dim3(1), dim3(PLAN_T), 0, st, pa);
     } else {
       hipLaunchKernelGGL(k_plan_reduce, dim3(nbp), dim3(PLAN_T), 0, st, pa);
-      hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(1024), 0, st, pa, nbp);
       hipLaunchKernelGGL(k_plan_write<false>, dim3(nbp), dim3(PLAN_T), 0, st, pa);
     }
   }

@@ -117,6 +117,12 @@ __device__ __forceinline__ u32 wave_scan_u32(u32 x) {
   return x;
 }
 
+// Sum over the 64 lanes of a wave, in every lane.
+__device__ __forceinline__ u64 wave_sum(u64 v) {
+  for (int d = 32; d; d >>= 1) v += (u64)__shfl_xor((unsigned long long)v, d, 64);
+  return v;
+}
+
 // q / d for q < 2048, 1 <= d <= 64, with magic = ceil(2^17 / d): the rounding error of magic
 // adds less than q / 2^17 <= 1/64 <= 1/d.  (24-bit products run at the full rate, 32-bit ones at
 // a quarter.)

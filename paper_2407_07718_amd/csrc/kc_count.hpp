@@ -34,7 +34,7 @@ struct CountArgs {
   const u32* large_list;
   const u64* chunk_start;  // chunks of large buckets: first key in lkeys ...
   const u32* chunk_len;    // ... and length (<= cap)
-  const u64* meta;         // see k_plan_scan
+  const u64* meta;         // see plan_meta
   const u64* kall_off;     // per bucket: first k-mer slot (prefix of k-mers over all buckets)
   int k;
   int rec_words;

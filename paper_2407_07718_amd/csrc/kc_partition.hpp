@@ -531,21 +531,47 @@ __device__ __forceinline__ void plan_quantities(const PlanArgs& P, u64 c, u64 q[
   q[6] = (nk > P.cap_tiny && nk <= P.cap_small) ? nk : 0;
 }
 
+// Block sums of the quantities (in every thread), and with `excl` each thread's exclusive
+// prefixes; one barrier for all of them.
+__device__ __forceinline__ void plan_block_scan(const u64 (&v)[PLAN_Q], u64 (*ws)[PLAN_Q], u64 (&excl)[PLAN_Q],
+                                                u64 (&tot)[PLAN_Q]) {
+  const u32 lane = lane_id(), wave = uniform(threadIdx.x >> 6);
+  u64 inc[PLAN_Q];
+#pragma unroll
+  for (int j = 0; j < PLAN_Q; ++j) inc[j] = wave_inclusive_scan<u64>(v[j]);
+  if (lane == 63) {
+#pragma unroll
+    for (int j = 0; j < PLAN_Q; ++j) ws[wave][j] = inc[j];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < PLAN_Q; ++j) {
+    excl[j] = inc[j] - v[j];
+    tot[j] = 0;
+    for (u32 w = 0; w < PLAN_T / 64; ++w) {
+      if (w == wave) excl[j] += tot[j];
+      tot[j] += ws[w][j];
+    }
+  }
+}
+
 __global__ __launch_bounds__(PLAN_T) void k_plan_reduce(PlanArgs P) {
-  __shared__ u64 scr[17];
-  const u32 b0 = blockIdx.x * PLAN_BLOCK + threadIdx.x * PLAN_PER_THREAD;
+  __shared__ u64 ws[PLAN_T / 64][PLAN_Q];
+  const u32 b0 = blockIdx.x * PLAN_BLOCK + threadIdx.x;
   u64 sum[PLAN_Q] = {0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
   for (u32 i = 0; i < PLAN_PER_THREAD; ++i) {
-    if (b0 + i < P.B) {
+    if (b0 + i * PLAN_T < P.B) {
       u64 q[PLAN_Q];
-      plan_quantities(P, P.bcnt[b0 + i], q);
+      plan_quantities(P, P.bcnt[b0 + i * PLAN_T], q);
       for (int j = 0; j < PLAN_Q; ++j) sum[j] += q[j];
     }
   }
-  for (int j = 0; j < PLAN_Q; ++j) {
-    u64 tot;
-    block_exclusive_scan<u64>(sum[j], scr, &tot);
-    if (threadIdx.x == 0) P.bsum[(u64)blockIdx.x * PLAN_Q + j] = tot;
+  u64 excl[PLAN_Q], tot[PLAN_Q];
+  plan_block_scan(sum, ws, excl, tot);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int j = 0; j < PLAN_Q; ++j) P.bsum[(u64)blockIdx.x * PLAN_Q + j] = tot[j];
   }
 }
 
@@ -562,30 +588,12 @@ __device__ __forceinline__ void plan_meta(const PlanArgs& P, const u64 (&tot)[PL
   P.meta[7] = tot[6];
 }
 
-// One block: exclusive scan of the block sums (in place) and the totals.
-__global__ __launch_bounds__(1024) void k_plan_scan(PlanArgs P, u32 nblocks) {
-  __shared__ u64 scr[17];
-  const u32 per = (nblocks + blockDim.x - 1) / blockDim.x;
-  const u32 s = min(nblocks, threadIdx.x * per), e = min(nblocks, s + per);
-  u64 tot[PLAN_Q];
-  for (int j = 0; j < PLAN_Q; ++j) {
-    u64 sum = 0;
-    for (u32 i = s; i < e; ++i) sum += P.bsum[(u64)i * PLAN_Q + j];
-    u64 run = block_exclusive_scan<u64>(sum, scr, &tot[j]);
-    for (u32 i = s; i < e; ++i) {
-      const u64 v = P.bsum[(u64)i * PLAN_Q + j];
-      P.bsum[(u64)i * PLAN_Q + j] = run;
-      run += v;
-    }
-  }
-  if (threadIdx.x == 0) plan_meta(P, tot);
-}
-
-// With ONE (B <= PLAN_BLOCK, a single block) the block's own sums are the totals: the
-// reduce and scan kernels are not needed.
+// With ONE (B <= PLAN_BLOCK, a single block) the block's own sums are the totals: the reduce
+// kernel is not needed.  Else each block adds up the sums of the blocks before it (at most 1023)
+// itself, and the last one has the totals.
 template <bool ONE>
 __global__ __launch_bounds__(PLAN_T) void k_plan_write(PlanArgs P) {
-  __shared__ u64 scr[17];
+  __shared__ u64 ws[2][PLAN_T / 64][PLAN_Q];
   const u32 b0 = blockIdx.x * PLAN_BLOCK + threadIdx.x * PLAN_PER_THREAD;
   u64 c[PLAN_PER_THREAD];
   u64 sum[PLAN_Q] = {0, 0, 0, 0, 0, 0, 0};
@@ -596,9 +604,21 @@ __global__ __launch_bounds__(PLAN_T) void k_plan_write(PlanArgs P) {
     for (int j = 0; j < PLAN_Q; ++j) sum[j] += q[j];
   }
   u64 off[PLAN_Q], tot[PLAN_Q];
-  for (int j = 0; j < PLAN_Q; ++j)
-    off[j] = block_exclusive_scan<u64>(sum[j], scr, &tot[j]) + (ONE ? 0ull : P.bsum[(u64)blockIdx.x * PLAN_Q + j]);
-  if (ONE && threadIdx.x == 0) plan_meta(P, tot);
+  plan_block_scan(sum, ws[0], off, tot);
+  if constexpr (!ONE) {
+    u64 part[PLAN_Q] = {0, 0, 0, 0, 0, 0, 0}, unused[PLAN_Q], before[PLAN_Q];
+    for (u32 i = threadIdx.x; i < blockIdx.x; i += PLAN_T) {
+#pragma unroll
+      for (int j = 0; j < PLAN_Q; ++j) part[j] += P.bsum[(u64)i * PLAN_Q + j];
+    }
+    plan_block_scan(part, ws[1], unused, before);
+#pragma unroll
+    for (int j = 0; j < PLAN_Q; ++j) {
+      off[j] += before[j];
+      tot[j] += before[j];
+    }
+  }
+  if (blockIdx.x + 1 == gridDim.x && threadIdx.x == 0) plan_meta(P, tot);
   u64 prec = off[0], pk = off[1], pch = off[4];
   u64 plarge = off[2] >> 42;
   for (u32 i = 0; i < PLAN_PER_THREAD; ++i) {

@@ -169,79 +169,135 @@ __global__ __launch_bounds__(256) void k_radix_upsweep(const K* __restrict__ key
   for (u32 d = tid; d < NB; d += 256) counts[(u64)d * nb + blockIdx.x] = h[0][d] + h[1][d] + h[2][d] + h[3][d];
 }
 
-// Exclusive scan out[i] = sum of in[0, i) for i < n by one block; n = min(*n_ptr, n_max)
-// when n_ptr is given, else n_max; *total = sum (if non-null).  in and out may alias.
-__global__ __launch_bounds__(1024) void k_scan_u32(const u32* __restrict__ in, u32* __restrict__ out,
-                                                   const u64* __restrict__ n_ptr, u64 n_max, u64* __restrict__ total,
-                                                   u64* __restrict__ clamped = nullptr, u64 cap = 0) {
-  __shared__ u64 scr[17];
-  const u64 n = n_ptr ? min(*n_ptr, n_max) : n_max;
-  const u32 T = blockDim.x, t = threadIdx.x;
-  const u64 per = (n + T - 1) / T;
-  const u64 s = min(n, (u64)t * per), e = min(n, s + per);
-  u64 sum = 0;
-  for (u64 i = s; i < e; ++i) sum += in[i];
-  u64 all;
-  u64 run = block_exclusive_scan<u64>(sum, scr, &all);
-  for (u64 i = s; i < e; ++i) {
-    const u32 v = in[i];
-    out[i] = (u32)run;
-    run += v;
+// ---------------------------------------------------------------------------- scan
+// Exclusive scans out[i] = sum of in[0, i) for i < n; n = min(*n_ptr, n_max) when n_ptr is given,
+// else n_max; *total = sum, *clamped = min(sum, cap) (where non-null).  in and out may be the
+// same array; it starts and, padded, ends at 256-byte boundaries.
+//
+// Four consecutive values from element i of n on (i a multiple of 4; those past the end: 0), and
+// the same to be written.
+__device__ __forceinline__ uint4 load4(const u32* __restrict__ p, u64 i, u64 n) {
+  if (i >= n) return make_uint4(0u, 0u, 0u, 0u);
+  uint4 v = *reinterpret_cast<const uint4*>(p + i);
+  if (i + 1 >= n) v.y = 0;
+  if (i + 2 >= n) v.z = 0;
+  if (i + 3 >= n) v.w = 0;
+  return v;
+}
+__device__ __forceinline__ void store4(u32* __restrict__ p, u64 i, u64 n, uint4 v) {
+  if (i + 3 < n) {
+    *reinterpret_cast<uint4*>(p + i) = v;
+  } else {
+    if (i < n) p[i] = v.x;
+    if (i + 1 < n) p[i + 1] = v.y;
+    if (i + 2 < n) p[i + 2] = v.z;
   }
-  if (t == 0 && total) *total = all;
-  if (t == 0 && clamped) *clamped = min(all, cap);
+}
+__device__ __forceinline__ u64 sum4(uint4 v) { return (u64)v.x + v.y + v.z + v.w; }
+
+// ROWS rows of 256 values from element i0 on, one wave: their exclusive prefixes after `base`
+// (sums modulo 2^32, as the array holds them).
+template <int ROWS>
+__device__ __forceinline__ void wave_scan_rows(const uint4 (&v)[ROWS], u32 base, u32* __restrict__ out, u64 i0, u64 n) {
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r) {
+    const u32 s = v[r].x + v[r].y + v[r].z + v[r].w, inc = wave_scan_u32(s), a = base + inc - s;
+    store4(out, i0 + 256 * r + 4 * lane_id(), n, make_uint4(a, a + v[r].x, a + v[r].x + v[r].y, a + v[r].x + v[r].y + v[r].z));
+    base += lane_read(inc, 63);
+  }
 }
 
-// Device-wide exclusive scan of u32 counts in three kernels (block sums, scan of the
-// block sums, apply): n = min(*n_ptr, n_max) (n_max alone if n_ptr is null); blocks of
-// SCAN_T threads take SCAN_BLOCK consecutive elements.  bsum holds ceil(n_max /
-// SCAN_BLOCK) <= 1024 entries.  *total = sum (and *clamped = min(sum, cap) when given).
-// in and out may alias.
-constexpr u32 SCAN_T = 256, SCAN_PER = 16, SCAN_BLOCK = SCAN_T * SCAN_PER;
+// By one block, n_max at most SCAN_ONE_MAX: each wave holds its share, a whole number of rows of
+// 256, in registers.  (10,000 values: 5 us; thread by
+// thread over consecutive values, read twice, 9.)
+constexpr u32 SCAN_ONE_T = 1024, SCAN_ONE_ROWS = 8;
+constexpr u64 SCAN_ONE_MAX = SCAN_ONE_T / 64 * SCAN_ONE_ROWS * 256;
+__global__ __launch_bounds__(SCAN_ONE_T) void k_scan_u32(const u32* __restrict__ in, u32* __restrict__ out,
+                                                         const u64* __restrict__ n_ptr, u64 n_max,
+                                                         u64* __restrict__ total, u64* __restrict__ clamped = nullptr,
+                                                         u64 cap = 0) {
+  constexpr u32 W = SCAN_ONE_T / 64;
+  __shared__ u64 wsum[W];
+  const u64 n = n_ptr ? min(*n_ptr, n_max) : n_max;
+  const u32 lane = lane_id(), wave = uniform(threadIdx.x >> 6);
+  const u32 rows = (u32)((n + W * 256 - 1) / (W * 256));   // of each wave
+  const u64 i0 = (u64)wave * rows * 256, end = min(n, i0 + (u64)rows * 256);
+  uint4 v[SCAN_ONE_ROWS];
+  u64 sum = 0;
+#pragma unroll
+  for (u32 r = 0; r < SCAN_ONE_ROWS; ++r) {
+    v[r] = load4(in, i0 + 256 * r + 4 * lane, end);
+    sum += sum4(v[r]);
+  }
+  sum = wave_sum(sum);
+  if (lane == 0) wsum[wave] = sum;
+  __syncthreads();
+  u64 base = 0, all = 0;
+  for (u32 w = 0; w < W; ++w) {
+    if (w == wave) base = all;
+    all += wsum[w];
+  }
+  wave_scan_rows<SCAN_ONE_ROWS>(v, (u32)base, out, i0, end);
+  if (threadIdx.x == 0 && total) *total = all;
+  if (threadIdx.x == 0 && clamped) *clamped = min(all, cap);
+}
 
+// Larger arrays (up to 1024 * SCAN_BLOCK), in two launches: each block's sum, then each block's
+// prefixes after the sum of the blocks before it, which it adds up itself (at most 1023: less
+// than a third launch).  The last block writes the total.  (A count of 6 Mbp, with the plan's sums
+// the same way: 325 us with the third launches and values read one by one, 288 so.)
+constexpr u32 SCAN_T = 256, SCAN_ROWS = 4, SCAN_BLOCK = SCAN_T / 64 * SCAN_ROWS * 256;
+__device__ __forceinline__ u64 scan_wave_load(const u32* __restrict__ in, u64 i0, u64 n, uint4 (&v)[SCAN_ROWS]) {
+  u64 sum = 0;
+#pragma unroll
+  for (u32 r = 0; r < SCAN_ROWS; ++r) {
+    v[r] = load4(in, i0 + 256 * r + 4 * lane_id(), n);
+    sum += sum4(v[r]);
+  }
+  return wave_sum(sum);
+}
 __global__ __launch_bounds__(SCAN_T) void k_scan_reduce(const u32* __restrict__ in, const u64* __restrict__ n_ptr,
                                                         u64 n_max, u64* __restrict__ bsum) {
-  __shared__ u64 scr[17];
+  __shared__ u64 wsum[SCAN_T / 64];
   const u64 n = n_ptr ? min(*n_ptr, n_max) : n_max;
-  const u64 i0 = (u64)blockIdx.x * SCAN_BLOCK + (u64)threadIdx.x * SCAN_PER;
-  u64 sum = 0;
-  for (u32 i = 0; i < SCAN_PER; ++i)
-    if (i0 + i < n) sum += in[i0 + i];
-  u64 tot;
-  block_exclusive_scan<u64>(sum, scr, &tot);
-  if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+  const u32 wave = uniform(threadIdx.x >> 6);
+  uint4 v[SCAN_ROWS];
+  const u64 sum = scan_wave_load(in, (u64)blockIdx.x * SCAN_BLOCK + (u64)wave * SCAN_ROWS * 256, n, v);
+  if (lane_id() == 0) wsum[wave] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    u64 t = 0;
+    for (u32 w = 0; w < SCAN_T / 64; ++w) t += wsum[w];
+    bsum[blockIdx.x] = t;
+  }
 }
-
-__global__ __launch_bounds__(1024) void k_scan_mid(u64* __restrict__ bsum, u32 nb, u64* __restrict__ total,
-                                                   u64* __restrict__ clamped, u64 cap) {
-  __shared__ u64 scr[17];
-  const u64 v = threadIdx.x < nb ? bsum[threadIdx.x] : 0ull;
-  u64 tot;
-  const u64 ex = block_exclusive_scan<u64>(v, scr, &tot);
-  if (threadIdx.x < nb) bsum[threadIdx.x] = ex;
-  if (threadIdx.x == 0 && total) *total = tot;
-  if (threadIdx.x == 0 && clamped) *clamped = min(tot, cap);
-}
-
 __global__ __launch_bounds__(SCAN_T) void k_scan_apply(const u32* __restrict__ in, u32* __restrict__ out,
                                                        const u64* __restrict__ n_ptr, u64 n_max,
-                                                       const u64* __restrict__ bsum) {
-  __shared__ u64 scr[17];
+                                                       const u64* __restrict__ bsum, u64* __restrict__ total,
+                                                       u64* __restrict__ clamped, u64 cap) {
+  __shared__ u64 wsum[SCAN_T / 64], wbefore[SCAN_T / 64];
   const u64 n = n_ptr ? min(*n_ptr, n_max) : n_max;
-  const u64 i0 = (u64)blockIdx.x * SCAN_BLOCK + (u64)threadIdx.x * SCAN_PER;
-  u32 v[SCAN_PER];
-  u64 sum = 0;
-#pragma unroll
-  for (u32 i = 0; i < SCAN_PER; ++i) {
-    v[i] = (i0 + i < n) ? in[i0 + i] : 0u;
-    sum += v[i];
+  const u32 wave = uniform(threadIdx.x >> 6);
+  const u64 i0 = (u64)blockIdx.x * SCAN_BLOCK + (u64)wave * SCAN_ROWS * 256;
+  u64 before = 0;
+  for (u32 i = threadIdx.x; i < blockIdx.x; i += SCAN_T) before += bsum[i];
+  uint4 v[SCAN_ROWS];
+  const u64 sum = scan_wave_load(in, i0, n, v);
+  before = wave_sum(before);
+  if (lane_id() == 0) {
+    wsum[wave] = sum;
+    wbefore[wave] = before;
   }
-  u64 tot;
-  u64 run = block_exclusive_scan<u64>(sum, scr, &tot) + bsum[blockIdx.x];
-#pragma unroll
-  for (u32 i = 0; i < SCAN_PER; ++i) {
-    if (i0 + i < n) out[i0 + i] = (u32)run;
-    run += v[i];
+  __syncthreads();
+  u64 base = 0, all = 0;
+  for (u32 w = 0; w < SCAN_T / 64; ++w) {
+    base += wbefore[w] + (w < wave ? wsum[w] : 0ull);
+    all += wbefore[w] + wsum[w];
+  }
+  wave_scan_rows<SCAN_ROWS>(v, (u32)base, out, i0, n);
+  if (blockIdx.x + 1 == gridDim.x && threadIdx.x == 0) {
+    if (total) *total = all;
+    if (clamped) *clamped = min(all, cap);
   }
 }
 
