@@ -69,7 +69,6 @@ int fail(int code, const char* fmt, ...) {
 #endif
 constexpr int RADIX_T = KC_RADIX_T;   // HBM radix passes: threads per block ...
 constexpr int SEG_WAVES_PER_BLOCK = 2;   // k_seg_wave: more, smaller blocks measured slightly faster
-constexpr u32 RUN_BLOCKS = 1024;   // blocks of the merged-run kernel
 #ifndef KC_RADIX_ITEMS_64
 #define KC_RADIX_ITEMS_64 16
 #endif
@@ -91,11 +90,10 @@ struct Plan {
   u64 rec_cap = 0, surv_cap = 0;
   u64 slots = 0, n_span_cap = 0;   // record slots of the extract blocks (a bound over m), spans
   u32 span = 0;
-  u32 nb_large = 1, nb_surv = 1;        // radix blocks
   // offsets into the workspace
   u64 o_packed, o_nmask, o_starts, o_X, o_Y, o_Z, o_bcnt, o_recoff, o_large,
-      o_ctrl, o_cnt_large, o_cnt_surv, o_tot_large, o_tot_surv, o_bc, o_hp, o_blkcnt, o_chstart, o_chlen,
-      o_kall, o_klcnt, o_kloff, o_scnt, o_soff, o_bsum, o_scanbuf, o_phist, o_lch0, o_seg, o_mhist;
+      o_ctrl, o_blkcnt, o_chstart, o_chlen,
+      o_kall, o_klcnt, o_scnt, o_soff, o_bsum, o_scanbuf, o_phist, o_lch0, o_seg, o_mhist;
   int log_c = 0, log_f = 0;
   u32 part_nblk = 1, part_spb = 1, nblk_cap = 1;   // extract blocks: this count's, and the bound over m
   u64 n_packed, n_mask, bytes = 0;
@@ -113,10 +111,8 @@ enum Ctrl : int {
   C_META = 2,       // 8 words, see plan_meta
   C_FLAGS = 10,
   C_SURV_N = 11,
-  C_NRUNS = 12,
   C_SURV_NC = 13,   // survivors, clamped to capacity
   C_KL_N = 14,      // (k-mer, count) list entries
-  C_KL_NC = 15,     // ... clamped to capacity
   C_NSEG = 16,      // key ranges of the survivors
   C_ROUND_END = 17, // words [0, C_ROUND_END) but C_FLAGS start over in every round
   C_ACC = 17,       // rounds: 10 running totals (see k_round_end)
@@ -127,7 +123,7 @@ enum Ctrl : int {
 static_assert(C_META + 8 <= C_FLAGS, "meta overlaps the flags");
 
 // ---------------------------------------------------------------- device memory of host calls
-// A host call (kc_count, kc_count_ext, kc_partition_inspect) needs about 62 bytes of HBM per
+// A host call (kc_count, kc_count_ext, kc_partition_inspect) needs about 58 bytes of HBM per
 // base for as long as it runs.  Handing them back to the driver costs more than the count: the
 // next allocation may wait until the pages are cleared (16 Mbp: 30 ms a call, 2.7 ms without; 60
 // Mbp: 28.5 and 27.5 ms, the rest being the result's pages on the host).  So up
@@ -335,9 +331,6 @@ void plan_layout(Plan* p) {
   p->rec_cap = rounds ? std::max<u64>(1, p->cap_r) : n_k;
   p->surv_cap = n_k;   // a count's (or round's) survivors sit at their bucket's k-mer slots first
   const u64 w = 8ull * p->key_words;
-  const u64 tile = (u64)RADIX_T * (p->key_words == 1 ? RADIX_ITEMS_64 : RADIX_ITEMS_128);
-  p->nb_large = (u32)std::min<u64>(1024, std::max<u64>(1, ceil_div(n_k, tile * 2)));
-  p->nb_surv = (u32)std::min<u64>(1024, std::max<u64>(1, ceil_div(p->surv_cap, tile * 2)));
   u64 o = 0;
   auto take = [&](u64 bytes) {
     u64 r = o;
@@ -372,18 +365,11 @@ void plan_layout(Plan* p) {
   p->o_large = take(4ull * p->B);
   p->o_kall = take(8ull * p->B);
   p->o_ctrl = take(8ull * C_WORDS);
-  p->o_cnt_large = take(4ull * 256 * p->nb_large);
-  p->o_cnt_surv = take(4ull * 256 * p->nb_surv);
-  p->o_tot_large = take(4ull * 256);
-  p->o_tot_surv = take(4ull * 256);
-  p->o_bc = take(4ull * 1024);
-  p->o_hp = take(4 * N);
   p->o_chstart = take(8 * p->chunk_cap);
   p->o_chlen = take(4 * p->chunk_cap);
   p->o_klcnt = take(4 * p->chunk_cap);
-  p->o_kloff = take(4 * p->chunk_cap);
-  p->o_scnt = take(4ull * (p->B + RUN_BLOCKS));
-  p->o_soff = take(4ull * (p->B + RUN_BLOCKS));
+  p->o_scnt = take(4ull * p->B);
+  p->o_soff = take(4ull * p->B);
   p->o_bsum = take(8ull * PLAN_Q * (p->B / PLAN_BLOCK + 1));
   p->o_scanbuf = take(8ull * 1024);
   p->o_phist = take(4ull * ((u64)1 << p->log_c) * p->nblk_cap);
@@ -407,13 +393,13 @@ void plan_layout(Plan* p) {
 // (packed reads and masks, bucket tables, histograms) leaves of the budget goes a quarter to
 // the survivor pool (pool_cap pairs) and the rest to the rounds (per k-mer of a round: three
 // regions of a (k-mer, count) pair, which the key-range split of the pool uses as its second
-// buffer afterwards, plus a run head): each round costs a pass over the reads, so they are as
+// buffer afterwards): each round costs a pass over the reads, so they are as
 // large as fits (200 Mbp at 10 bytes per base: 7 instead of the 10 that half the budget gave,
 // 9.2 ms instead of 12.1).  False when half of it cannot hold a round of at least 16 on-chip
 // chunks.
 bool plan_rounds(Plan* p, u64 budget) {
   const u64 w = 8ull * p->key_words, rb = 4ull * p->rec_words;
-  const u64 per_k = 3 * (w + 4) + 4, per_pool = w + 4;
+  const u64 per_k = 3 * (w + 4), per_pool = w + 4;
   Plan q = *p;
   q.rounds = 2;
   q.cap_k = q.cap_r = 1;
@@ -424,7 +410,7 @@ bool plan_rounds(Plan* p, u64 budget) {
   if (budget <= q.bytes + 1024 * 1024) return false;
   const u64 free_b = budget - q.bytes - 1024 * 1024;   // (slack for alignment and the round table)
   const u64 pool = std::max<u64>(1, std::min<u64>(p->n_max + 1, free_b / 4 / per_pool));
-  if ((free_b - std::min(free_b, 2 * pool * per_pool)) / per_k < min_cap) return false;
+  if ((free_b - std::min(free_b, 2 * pool * per_pool)) / (per_k + 4) < min_cap) return false;
   u64 cap = (free_b - std::min(free_b, pool * per_pool)) / per_k;
   for (; cap >= min_cap; cap -= std::max<u64>(1, cap / 64)) {
     q = *p;
@@ -582,7 +568,7 @@ template <typename K> constexpr u32 seg_range_target() { return seg_wave_cap<K>(
 // max_seg: a host-side bound on the number of segments (the grids need no more blocks).
 template <typename K>
 int seg_sort(K* keys, u32* vals, K* tmp_k, u32* tmp_v, K* out_k, u32* out_v, u64 out_cap, const u64* seg,
-             const u64* n_seg, u64 max_seg, int nbits, bool canonical, bool group_only, const u64* msd_n, u32 msd_target, int n_cu,
+             const u64* n_seg, u64 max_seg, int nbits, bool canonical, const u64* msd_n, u32 msd_target, int n_cu,
              hipStream_t st, int* grid) {
   constexpr int IT = sizeof(K) == 8 ? 8 : 4;
   static_assert(SEG_T * IT == (sizeof(K) == 8 ? SEG_CAP_64 : SEG_CAP_128), "segment capacity");
@@ -606,7 +592,6 @@ int seg_sort(K* keys, u32* vals, K* tmp_k, u32* tmp_v, K* out_k, u32* out_v, u64
   a.n_seg_ptr = n_seg;
   a.nbits = nbits;
   a.canonical = canonical ? 1 : 0;
-  a.group_only = group_only ? 1 : 0;
   a.msd_n = msd_n;
   a.msd_target = msd_target;
   a.wave_cap = seg_wave_cap<K>();
@@ -616,16 +601,21 @@ int seg_sort(K* keys, u32* vals, K* tmp_k, u32* tmp_v, K* out_k, u32* out_v, u64
   return KC_OK;
 }
 
+// Threads of k_merge_lists, and entries of a large bucket's lists that they merge on chip, each: one
+// block per CU, but a large bucket is done sooner (400 Mbp of long reads, k = 51: 301 us; 512
+// threads with 8 entries 360, with 4 416).
+constexpr int MERGE_T = 1024, MERGE_ITEMS = 4;
+
 // Pointers of one count's workspace regions.
 template <typename K>
 struct Ws {
   u32 *packed, *nmask, *starts, *recA, *ptmp_rec, *recB, *s0c, *kl0c, *kl1c;
   K *lk0, *s0k, *kl0k, *kl1k;
   u64* bcnt;
-  u32 *recoff, *klcnt, *kloff, *scnt, *soff, *large, *blkcnt, *chlen, *bc, *hp, *lch0, *phist,
+  u32 *recoff, *klcnt, *scnt, *soff, *large, *blkcnt, *chlen, *lch0, *phist,
       *mhist;
   u64 *kall, *bsum, *scanbuf, *ctrl, *chstart, *seg;
-  u64 *counters, *meta, *surv_n, *nruns, *surv_nc, *kl_n, *kl_nc;
+  u64 *counters, *meta, *surv_n, *surv_nc, *kl_n;
   u32* flags;
 };
 
@@ -653,7 +643,6 @@ Ws<K> ws_ptrs(const Plan& P, void* ws) {
   W.recoff = at<u32>(ws, P.o_recoff);
   W.kall = at<u64>(ws, P.o_kall);
   W.klcnt = at<u32>(ws, P.o_klcnt);
-  W.kloff = at<u32>(ws, P.o_kloff);
   W.scnt = at<u32>(ws, P.o_scnt);
   W.soff = at<u32>(ws, P.o_soff);
   W.bsum = at<u64>(ws, P.o_bsum);
@@ -663,8 +652,6 @@ Ws<K> ws_ptrs(const Plan& P, void* ws) {
   W.blkcnt = at<u32>(ws, P.o_blkcnt);
   W.chstart = at<u64>(ws, P.o_chstart);
   W.chlen = at<u32>(ws, P.o_chlen);
-  W.bc = at<u32>(ws, P.o_bc);
-  W.hp = at<u32>(ws, P.o_hp);
   W.lch0 = at<u32>(ws, P.o_lch0);
   W.phist = at<u32>(ws, P.o_phist);
   W.seg = at<u64>(ws, P.o_seg);
@@ -673,10 +660,8 @@ Ws<K> ws_ptrs(const Plan& P, void* ws) {
   W.meta = W.ctrl + C_META;
   W.flags = reinterpret_cast<u32*>(W.ctrl + C_FLAGS);
   W.surv_n = W.ctrl + C_SURV_N;
-  W.nruns = W.ctrl + C_NRUNS;
   W.surv_nc = W.ctrl + C_SURV_NC;
   W.kl_n = W.ctrl + C_KL_N;
-  W.kl_nc = W.ctrl + C_KL_NC;
   return W;
 }
 
@@ -691,8 +676,6 @@ Ws<K> ws_ptrs(const Plan& P, void* ws) {
 struct MultiDev {
   u32 n_sets = 0, n_buckets = 0;   // (the sets' buckets; the plan's number is a power of two)
   const u32* bset = nullptr;
-  u32* seg_bits = nullptr;
-  u32* rset = nullptr;
   k128* wide_k = nullptr;     // wide keys (set << 2k | k-mer) ...
   void* pair_k = nullptr;     // ... or k-mers with value = count | set << cbits (cbits >= 0)
   u32* wide_c = nullptr;
@@ -704,7 +687,7 @@ struct MultiDev {
 // launch).  d_hist / d_tot may be null (the partition inspection has none).
 template <typename K>
 void launch_clear(const Plan& P, const Ws<K>& W, uint64_t* d_hist, uint64_t hist_len, DevTotals* d_tot,
-                  hipStream_t st, u64 n_tot = 1, u32* extra = nullptr, u64 extra_words = 0) {
+                  hipStream_t st, u64 n_tot = 1) {
   const u64 n32 = ceil_div(P.R, 32);
   FillList fl{};
   u64 most = 0;
@@ -718,7 +701,6 @@ void launch_clear(const Plan& P, const Ws<K>& W, uint64_t* d_hist, uint64_t hist
   add(W.ctrl, 2ull * C_WORDS);
   if (d_hist) add(d_hist, 2ull * hist_len);
   if (d_tot) add(d_tot, n_tot * sizeof(DevTotals) / 4);
-  if (extra) add(extra, extra_words);
   add(W.starts, P.n_mask);
   add(W.scnt, P.B);
   add(W.packed + 2 * n32, P.n_packed - 2 * n32);
@@ -895,71 +877,40 @@ int count_buckets(const Plan& P, const Ws<K>& W, const u32* blk_base, uint32_t l
   if (marks) stage_mark(5, st);
   if ((rc = with_hash_shape<K>(P.variant, buckets))) return rc;
   if (marks) stage_mark(6, st);
-  // merge the chunks' (k-mer, count) lists: compact, sort by k-mer, sum each run's counts
-  scan_u32(W.klcnt, W.kloff, W.meta + 4, P.chunk_cap, W.kl_n, W.scanbuf, st, W.kl_nc, P.kl_cap);
-  // (each heavy bucket's lists are one segment, sorted on its own, in place)
-  hipLaunchKernelGGL((k_gather_lists<K>), grid_for(P.chunk_cap, 4, 4096), dim3(256), 0, st, W.s0k, W.s0c, W.chstart,
-                     W.klcnt, W.kloff, W.lch0, W.meta + 1, W.meta + 4, P.chunk_cap, W.kl_nc, W.kl0k, W.kl0c, W.seg);
-  int seg_grid = 0;
-  if ((rc = seg_sort<K>(W.kl0k, W.kl0c, W.kl1k, W.kl1c, W.kl0k, W.kl0c, ~0ull, W.seg, W.meta + 1,
-                        std::min<u64>(P.B, P.chunk_cap), 2 * P.k, true, true, nullptr, 0, n_cu, st, &seg_grid)))
-    return rc;
-  K* lks = W.kl0k;
-  u32* lvs = W.kl0c;
-  K* fk = W.kl1k;                    // the free buffer holds the merged runs' survivors
-  u32* fc = W.kl1c;
-  const u32* seg_bits = nullptr;
-  if (ms) {   // a heavy bucket's segment always starts a run (two sets may share a k-mer)
-    hipLaunchKernelGGL(k_seg_bits, grid_for(std::min<u64>(P.B, P.chunk_cap), 256, 1024), dim3(256), 0, st, W.seg,
-                       W.meta + 1, W.kl_nc, md->seg_bits);
-    seg_bits = md->seg_bits;
+  // merge the large buckets' chunks' (k-mer, count) lists
+  {
+    MergeArgs ma{ca, W.lch0, P.chunk_cap, W.kl0k, W.kl1k, W.kl0c, W.kl1c, W.kl_n};
+    auto merge = [&](auto kern) -> int {
+      int per_cu = 0;
+      const int r = blocks_per_cu(kern, MERGE_T, &per_cu);
+      if (r) return r;
+      hipLaunchKernelGGL(kern, dim3((u32)std::min<u64>((u64)std::max(1, per_cu) * n_cu, std::min<u64>(P.B, P.chunk_cap))),
+                         dim3(MERGE_T), 0, st, ma);
+      return KC_OK;
+    };
+    if ((rc = ms ? merge(k_merge_lists<K, MERGE_T, MERGE_ITEMS, true>) : merge(k_merge_lists<K, MERGE_T, MERGE_ITEMS, false>))) return rc;
   }
-  hipLaunchKernelGGL((k_rle_count<K>), dim3(P.nb_large), dim3(256), 0, st, lks, W.kl_nc, W.bc, seg_bits);
-  hipLaunchKernelGGL((k_rle_heads<K>), dim3(P.nb_large), dim3(256), 0, st, lks, W.kl_nc, W.bc, W.hp, W.nruns,
-                     seg_bits);
-  if (ms)
-    hipLaunchKernelGGL((k_rle_runs<K, true>), dim3(RUN_BLOCKS), dim3(256), 0, st, ca, lks, lvs, W.kl_nc, W.hp,
-                       W.nruns, fk, fc, W.scnt + P.B, (const u64*)W.seg, md->rset);
-  else
-    hipLaunchKernelGGL((k_rle_runs<K>), dim3(RUN_BLOCKS), dim3(256), 0, st, ca, lks, lvs, W.kl_nc, W.hp, W.nruns, fk,
-                       fc, W.scnt + P.B, (const u64*)nullptr, (u32*)nullptr);
 
   if (marks) stage_mark(7, st);
   if (!ms && !out_k) return KC_OK;   // (sorted from where they are: see surv_segs)
-  // ---- compact the survivors (buckets, then merged runs)
-  scan_u32(W.scnt, W.soff, (const u64*)nullptr, (u64)P.B + RUN_BLOCKS, W.surv_n, W.scanbuf, st, W.surv_nc,
-           P.surv_cap);
-  if (ms && md->cbits >= 0) {   // k-mers with count | set << cbits, sorted by k-mer then set
-    K* pk = reinterpret_cast<K*>(md->pair_k);
-    hipLaunchKernelGGL((k_gather_packed<K>), grid_for(P.B, 4, 4096), dim3(256), 0, st, W.s0k, W.s0c, W.kall,
-                       (const u64*)nullptr, 0u, md->bset, (const u32*)nullptr, W.scnt, W.soff, (u64)P.B, md->cbits,
-                       pk, md->wide_c, md->wide_cap);
-    hipLaunchKernelGGL((k_gather_packed<K>), grid_for(RUN_BLOCKS, 4, 4096), dim3(256), 0, st, fk, fc,
-                       (const u64*)nullptr, W.nruns, RUN_BLOCKS, (const u32*)nullptr, (const u32*)md->rset,
-                       W.scnt + P.B, W.soff + P.B, (u64)RUN_BLOCKS, md->cbits, pk, md->wide_c, md->wide_cap);
-    return KC_OK;
-  }
-  if (ms) {   // as wide keys (set << 2k | k-mer), sorted once by set and k-mer afterwards
-    hipLaunchKernelGGL((k_gather_wide<K>), grid_for(P.B, 4, 4096), dim3(256), 0, st, W.s0k, W.s0c, W.kall,
-                       (const u64*)nullptr, 0u, md->bset, (const u32*)nullptr, W.scnt, W.soff, (u64)P.B, P.k,
-                       md->wide_k, md->wide_c, md->wide_cap);
-    hipLaunchKernelGGL((k_gather_wide<K>), grid_for(RUN_BLOCKS, 4, 4096), dim3(256), 0, st, fk, fc,
-                       (const u64*)nullptr, W.nruns, RUN_BLOCKS, (const u32*)nullptr, (const u32*)md->rset,
-                       W.scnt + P.B, W.soff + P.B, (u64)RUN_BLOCKS, P.k, md->wide_k, md->wide_c, md->wide_cap);
-    return KC_OK;
-  }
-  hipLaunchKernelGGL((k_gather_segments<K>), grid_for(P.B, 4, 4096), dim3(256), 0, st, W.s0k, W.s0c, W.kall,
-                     (const u64*)nullptr, 0u, W.scnt, W.soff, (u64)P.B, out_k, out_c, out_base,
-                     out_cap);
-  hipLaunchKernelGGL((k_gather_segments<K>), grid_for(RUN_BLOCKS, 4, 4096), dim3(256), 0, st, fk, fc,
-                     (const u64*)nullptr, W.nruns, RUN_BLOCKS, W.scnt + P.B, W.soff + P.B, (u64)RUN_BLOCKS, out_k, out_c, out_base, out_cap);
+  // ---- compact the survivors
+  scan_u32(W.scnt, W.soff, (const u64*)nullptr, (u64)P.B, W.surv_n, W.scanbuf, st, W.surv_nc, P.surv_cap);
+  if (ms && md->cbits >= 0)   // k-mers with count | set << cbits, sorted by k-mer then set
+    hipLaunchKernelGGL((k_gather_packed<K>), grid_for(P.B, 4, 4096), dim3(256), 0, st, W.s0k, W.s0c, W.kall, md->bset,
+                       W.scnt, W.soff, (u64)P.B, md->cbits, reinterpret_cast<K*>(md->pair_k), md->wide_c, md->wide_cap);
+  else if (ms)   // as wide keys (set << 2k | k-mer), sorted once by set and k-mer afterwards
+    hipLaunchKernelGGL((k_gather_wide<K>), grid_for(P.B, 4, 4096), dim3(256), 0, st, W.s0k, W.s0c, W.kall, md->bset,
+                       W.scnt, W.soff, (u64)P.B, P.k, md->wide_k, md->wide_c, md->wide_cap);
+  else
+    hipLaunchKernelGGL((k_gather_segments<K>), grid_for(P.B, 4, 4096), dim3(256), 0, st, W.s0k, W.s0c, W.kall, W.scnt,
+                       W.soff, (u64)P.B, out_k, out_c, out_base, out_cap);
   return KC_OK;
 }
 
 // The survivors of a one-pass count where count_buckets left them.
 template <typename K>
 SurvSegs surv_segs(const Plan& P, const Ws<K>& W) {
-  return SurvSegs{W.s0k, W.s0c, W.kall, W.scnt, P.B, RUN_BLOCKS, W.kl1k, W.kl1c, W.nruns};
+  return SurvSegs{W.s0k, W.s0c, W.kall, W.scnt, P.B};
 }
 
 // Survivors in[0, *n_ptr) (their count at most n_cap) -> split into key ranges by their
@@ -1002,7 +953,7 @@ int sort_survivors(const Plan& P, const Ws<K>& W, K* in_k, u32* in_c, K* mid_k, 
   const u64 max_ranges = 256ull << msd_g2(n_cap, seg_range_target<K>());
   int seg_grid = 0;
   return seg_sort<K>(in_k, in_c, mid_k, mid_c, reinterpret_cast<K*>(d_kmers), d_counts, pair_cap, W.seg,
-                     W.ctrl + C_NSEG, max_ranges, nbits, key_bits == 0, false, n_ptr, seg_range_target<K>(), n_cu, st, &seg_grid);
+                     W.ctrl + C_NSEG, max_ranges, nbits, key_bits == 0, n_ptr, seg_range_target<K>(), n_cu, st, &seg_grid);
 }
 
 template <typename K>
@@ -1117,6 +1068,10 @@ int warm_launch_facts() {
     if ((rc = warm(u64()))) return rc;
     if ((rc = warm(k128()))) return rc;
   }
+  if ((rc = blocks_per_cu(k_merge_lists<u64, MERGE_T, MERGE_ITEMS, false>, MERGE_T, &v))) return rc;
+  if ((rc = blocks_per_cu(k_merge_lists<u64, MERGE_T, MERGE_ITEMS, true>, MERGE_T, &v))) return rc;
+  if ((rc = blocks_per_cu(k_merge_lists<k128, MERGE_T, MERGE_ITEMS, false>, MERGE_T, &v))) return rc;
+  if ((rc = blocks_per_cu(k_merge_lists<k128, MERGE_T, MERGE_ITEMS, true>, MERGE_T, &v))) return rc;
   if ((rc = blocks_per_cu(k_seg_sort<u64, SEG_T, 8>, SEG_T, &v))) return rc;
   if ((rc = blocks_per_cu(k_seg_sort<k128, SEG_T, 4>, SEG_T, &v))) return rc;
   if ((rc = blocks_per_cu(k_seg_wave<u64, seg_wave_cap<u64>(), SEG_WAVES_PER_BLOCK>, SEG_WAVES_PER_BLOCK * 64, &v)))
@@ -1177,7 +1132,7 @@ struct MultiPlan {
   u32 radix_nb = 1;
   // scratch (reusable by the next count on the same stream): the joint count's workspace,
   // then these regions
-  u64 o_segbits = 0, segbits_words = 0, o_rset = 0, o_joff = 0, o_wk[3] = {}, o_wc[3] = {}, o_rcnt = 0, o_rtot = 0,
+  u64 o_joff = 0, o_wk[3] = {}, o_wc[3] = {}, o_rcnt = 0, o_rtot = 0,
       scratch_bytes = 0;
   // the count's own memory (tables and outputs, kept until the results are read)
   u64 o_tab = 0, tab_bytes = 0, o_bset = 0, o_first = 0, o_hist = 0, o_tot = 0, o_outk = 0, o_outc = 0, own_bytes = 0;
@@ -1265,9 +1220,6 @@ bool make_multi_plan(const std::vector<MultiSet>& sets, int k, int m, u32 lo, u3
     o = align_up(o + bytes, 256);
     return r;
   };
-  mp->segbits_words = mp->P.kl_cap / 32 + 2;
-  mp->o_segbits = take(4ull * mp->segbits_words);
-  mp->o_rset = take(4ull * mp->P.kl_cap);
   mp->o_joff = take(8ull * (reads + 1));
   mp->cbits = 32 - __builtin_clz(std::max<u32>(1, hi));
   mp->packed = mp->cbits + (int)mp->sbits <= 32;
@@ -1365,15 +1317,13 @@ int enqueue_multi(const MultiPlan& mp, void* ws, void* own, hipStream_t st) {
   md.n_sets = mp.n_sets;
   md.n_buckets = mp.bbase.back() + (1u << mp.lb.back());
   md.bset = at<u32>(own, mp.o_bset);
-  md.seg_bits = at<u32>(ws, mp.o_segbits);
-  md.rset = at<u32>(ws, mp.o_rset);
   md.wide_k = at<k128>(ws, mp.o_wk[0]);
   md.pair_k = at<char>(ws, mp.o_wk[0]);
   md.wide_c = at<u32>(ws, mp.o_wc[0]);
   md.wide_cap = mp.wide_cap;
   md.cbits = mp.packed ? mp.cbits : -1;
   stage_mark(0, st);
-  launch_clear<K>(P, W, O.hist, mp.hist_len * mp.n_sets, O.tot, st, mp.n_sets, md.seg_bits, mp.segbits_words);
+  launch_clear<K>(P, W, O.hist, mp.hist_len * mp.n_sets, O.tot, st, mp.n_sets);
   // joint offsets, then the encode straight from each set's buffer
   hipLaunchKernelGGL(k_join_offsets, grid_for(mp.n_reads + 1, 256), dim3(256), 0, st, T, mp.n_reads, mp.R, joff);
   if (mp.R)
@@ -1476,7 +1426,7 @@ struct ExtPlan {
   bool by_count = false;
   u64 bytes_sort = 0;              // workspace that the sort of all windows needs
   Plan cp;
-  u64 o_c_rid = 0, o_c_blk = 0, o_c_off = 0, o_c_cnt = 0, o_c_tot = 0, o_c_ctrl = 0;
+  u64 o_c_found = 0, o_c_rid = 0, o_c_blk = 0, o_c_off = 0, o_c_cnt = 0, o_c_tot = 0, o_c_ctrl = 0;
 };
 
 enum ExtCtrl : int {
@@ -1566,6 +1516,7 @@ bool ext_plan_by_count(ExtPlan* p, u64 budget) {
     o = align_up(o + bytes, 256);
     return r;
   };
+  p->o_c_found = take(4 * p->cp.kl_cap);
   p->o_c_rid = take(4 * p->n_blk);
   p->o_c_blk = take(4 * p->n_tiles);
   p->o_c_off = take(4 * p->n_tiles);
@@ -1864,7 +1815,7 @@ int enqueue_ext_by_count(const ExtPlan& E, void* ws, const uint8_t* d_reads, con
   // the pairs' table at Y, the windows found at Z (the last of the four arrays where the pair
   // index of every position was)
   u32* tab = W.ptmp_rec;
-  u32* found = W.hp;
+  u32* found = at<u32>(ws, E.o_c_found);
   const u64 slot_cap = P.rec_cap;   // (the region holds that many records of a slot's size)
   hipLaunchKernelGGL((k_ext_table_clear<K>), dim3(2048), dim3(256), 0, st, n_ptr, slot_cap,
                      reinterpret_cast<uint4*>(tab));

@@ -243,16 +243,6 @@ __device__ __forceinline__ void flush_stats_wave(const RunSink& S, u64 ndist) {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Statistics of one run straight to the global targets (runs of several sets in one
-// step; rare).
-__device__ __forceinline__ void run_stats_global(u64* hist, u64 hist_len, DevTotals* tot, u64 c) {
-  const u64 last = hist_len - 1;
-  atomicAdd((unsigned long long*)&hist[c < last ? c : last], 1ull);
-  if (c >= last) atomicAdd((unsigned long long*)&tot->overflow_sum, (unsigned long long)c);
-  atomicMax((unsigned long long*)&tot->max_count, (unsigned long long)c);
-  atomicAdd((unsigned long long*)&tot->n_distinct, 1ull);
-}
-
 __device__ __forceinline__ void flush_stats(const RunSink& S, u64 ndist) {
   const u32 H = (u32)min(S.hist_len, (u64)256);
   for (u32 i = threadIdx.x; i < H; i += blockDim.x) {
@@ -1041,186 +1031,28 @@ __global__ __launch_bounds__(T) void k_expand_large(CountArgs A, K* __restrict__
   }
 }
 
-// Head counts per block range of the sorted large-key array.
-// Several read sets in one count: the merged lists of two heavy buckets of different
-// sets may hold the same k-mer, so a segment's first entry always starts a run
-// (seg_bits: one bit per entry; null for one set, where neighbouring buckets never
-// share a key).
-__device__ __forceinline__ bool seg_start(const u32* seg_bits, u64 i) {
-  return seg_bits && ((seg_bits[i >> 5] >> (i & 31)) & 1u);
-}
-
-template <typename K>
-__global__ __launch_bounds__(256) void k_rle_count(const K* __restrict__ keys, const u64* __restrict__ n_ptr,
-                                                   u32* __restrict__ bc, const u32* __restrict__ seg_bits = nullptr) {
-  __shared__ u64 scr[17];
-  u64 s, e;
-  block_range(*n_ptr, gridDim.x, &s, &e);
-  u64 c = 0;
-  for (u64 i = s + threadIdx.x; i < e; i += 256)
-    c += (i == 0 || !key_eq(keys[i], keys[i - 1]) || seg_start(seg_bits, i)) ? 1 : 0;
-  u64 tot;
-  block_exclusive_scan<u64>(c, scr, &tot);
-  if (threadIdx.x == 0) bc[blockIdx.x] = (u32)tot;
-}
-
-// Head positions in order: hp[r] = index of the first key of run r; and the number of runs.
-// (Each block adds up the heads before its own: at most 1024 counts, less than a scan's launch.)
-template <typename K>
-__global__ __launch_bounds__(256) void k_rle_heads(const K* __restrict__ keys, const u64* __restrict__ n_ptr,
-                                                   const u32* __restrict__ bc, u32* __restrict__ hp,
-                                                   u64* __restrict__ n_runs, const u32* __restrict__ seg_bits = nullptr) {
-  __shared__ u64 scr[17];
-  u64 s, e;
-  block_range(*n_ptr, gridDim.x, &s, &e);
-  u64 base, before = 0;
-  for (u32 i = threadIdx.x; i < blockIdx.x; i += 256) before += bc[i];
-  block_exclusive_scan<u64>(before, scr, &base);
-  for (u64 c0 = s; c0 < e; c0 += 256) {
-    const u64 i = c0 + threadIdx.x;
-    const bool head = i < e && (i == 0 || !key_eq(keys[i], keys[i - 1]) || seg_start(seg_bits, i));
-    u64 tot;
-    const u64 ex = block_exclusive_scan<u64>(head ? 1ull : 0ull, scr, &tot);
-    if (head) hp[base + ex] = (u32)i;
-    base += tot;
-  }
-  if (blockIdx.x + 1 == gridDim.x && threadIdx.x == 0) *n_runs = base;
-}
-
-// Several read sets: the set of the list entry at position i, through its segment (one
-// per heavy bucket, in large-list order; seg[0..n_large] are their starts).
-__device__ __forceinline__ u32 entry_set(const CountArgs& A, const u64* seg, u64 n_large, u64 i) {
-  u64 lo = 0, hi = n_large;   // seg[lo] <= i < seg[hi]
-  while (hi - lo > 1) {
-    const u64 mid = (lo + hi) >> 1;
-    if (seg[mid] <= i) lo = mid;
-    else hi = mid;
-  }
-  return A.bset[A.large_list[lo]];
-}
-
-// Runs of the sorted (k-mer, count) list: a run's count is the sum of its entries'
-// counts (the merge of the chunks' lists).  Block b takes a contiguous range of runs
-// [rs, re); its survivors go to slots rs + i and their number to blk_cnt[b].
-// Several read sets (MS): each run's set comes from its segment; the statistics of a
-// step of 256 runs of one set go through LDS (flushed when the set changes), those of a
-// step that crosses sets straight to the global targets; survivors' sets go to out_s.
-template <typename K, bool MS = false>
-__global__ __launch_bounds__(256) void k_rle_runs(CountArgs A, const K* __restrict__ keys, const u32* __restrict__ vals,
-                                                  const u64* __restrict__ n_ptr, const u32* __restrict__ hp,
-                                                  const u64* __restrict__ nruns_ptr, K* __restrict__ out_k,
-                                                  u32* __restrict__ out_c, u32* __restrict__ blk_cnt,
-                                                  const u64* __restrict__ seg = nullptr, u32* __restrict__ out_s = nullptr) {
-  __shared__ u32 hist_s[256];
-  __shared__ u32 lmax;
-  __shared__ unsigned long long lover;
-  __shared__ u64 scr[17];
-  __shared__ u32 step_set[2];
-  for (u32 i = threadIdx.x; i < 256; i += blockDim.x) hist_s[i] = 0;
-  if (threadIdx.x == 0) { lmax = 0; lover = 0; }
-  __syncthreads();
-  RunSink sink{hist_s, A.hist_len, A.hist, A.tot, &lmax, &lover};
-  const u64 n = *n_ptr, nruns = *nruns_ptr;
-  const u64 n_large = MS ? A.meta[1] : 0;
-  u64 rs, re;
-  block_range(nruns, gridDim.x, &rs, &re);
-  u64 kept = 0, ndist = 0;
-  u32 cur = ~0u;
-  for (u64 c0 = rs; c0 < re; c0 += blockDim.x) {
-    const u64 r = c0 + threadIdx.x;
-    bool surv = false;
-    u64 c = 0, s = 0;
-    if (r < re) {
-      s = hp[r];
-      const u64 e = (r + 1 < nruns) ? hp[r + 1] : n;
-      for (u64 i = s; i < e; ++i) c += vals[i];
-      surv = c >= A.min_freq && c <= A.max_freq;
-    }
-    u32 my_set = 0;
-    if constexpr (MS) {
-      if (threadIdx.x == 0) {
-        step_set[0] = entry_set(A, seg, n_large, hp[c0]);
-        step_set[1] = entry_set(A, seg, n_large, hp[min(re, c0 + blockDim.x) - 1]);
-      }
-      __syncthreads();
-      const u32 s0 = step_set[0], s1 = step_set[1];
-      if (s0 == s1) {
-        if (s0 != cur) {
-          if (cur != ~0u) {
-            flush_stats(sink, threadIdx.x == 0 ? ndist : 0);
-            __syncthreads();
-            for (u32 i = threadIdx.x; i < 256; i += blockDim.x) hist_s[i] = 0;
-            if (threadIdx.x == 0) { lmax = 0; lover = 0; }
-            __syncthreads();
-          }
-          ndist = 0;
-          sink_to_set(sink, A.hist, A.tot, s0);
-          cur = s0;
-        }
-        my_set = s0;
-        run_stats_lanes(sink, c, r < re);
-        ndist += min(re, c0 + blockDim.x) - c0;
-      } else {
-        if (r < re) {
-          my_set = entry_set(A, seg, n_large, s);
-          run_stats_global(A.hist + (u64)my_set * A.hist_len, A.hist_len, A.tot + my_set, c);
-        }
-      }
-    } else {
-      run_stats_lanes(sink, c, r < re);
-    }
-    u64 tot;
-    const u64 ex = block_exclusive_scan<u64>(surv ? 1ull : 0ull, scr, &tot);
-    if (surv) {
-      out_k[rs + kept + ex] = keys[s];
-      out_c[rs + kept + ex] = (u32)c;
-      if constexpr (MS) out_s[rs + kept + ex] = my_set;
-    }
-    kept += tot;
-  }
-  if (threadIdx.x == 0) blk_cnt[blockIdx.x] = (u32)kept;
-  if constexpr (MS) {
-    __syncthreads();
-    flush_stats(sink, threadIdx.x == 0 ? ndist : 0);
-  } else {
-    flush_stats(sink, threadIdx.x == 0 ? (re - rs) : 0);
-  }
-}
-
+// ---------------------------------------------------------------------------- gather
 // Gather of sparse segments into one dense array: segment i holds cnt[i] entries at
-// src + base, base = base_arr[i] -- or, when base_arr is null, the first run of block i
-// of k_rle_runs over *base_range_n runs -- and lands at dst + off[i], off being the
-// exclusive scan of cnt.  One wave per segment.
+// src + base[i] and lands at dst + off[i] (after *dst_base entries), off being the exclusive scan
+// of cnt.  One wave per segment.
 template <typename K>
 __global__ __launch_bounds__(256) void k_gather_segments(const K* __restrict__ src_k, const u32* __restrict__ src_c,
-                                                         const u64* __restrict__ base_arr,
-                                                         const u64* __restrict__ base_range_n, u32 base_range_nb,
-                                                         const u32* __restrict__ cnt, const u32* __restrict__ off,
-                                                         u64 n_seg,
+                                                         const u64* __restrict__ base, const u32* __restrict__ cnt,
+                                                         const u32* __restrict__ off, u64 n_seg,
                                                          K* __restrict__ dst_k, u32* __restrict__ dst_c,
-                                                         const u64* __restrict__ dst_base = nullptr,
-                                                         u64 dst_cap = ~0ull) {
-  const u64 db = dst_base ? *dst_base : 0ull;   // rounds: the pool's fill so far
+                                                         const u64* __restrict__ dst_base, u64 dst_cap) {
+  const u64 db = *dst_base;   // rounds: the pool's fill so far
   const u64 wave = (blockIdx.x * (u64)blockDim.x + threadIdx.x) >> 6;
   const u64 n_waves = ((u64)gridDim.x * blockDim.x) >> 6;
   const u32 lane = lane_id();
   for (u64 i = wave; i < n_seg; i += n_waves) {
     const u32 c = cnt[i];
     if (!c) continue;
-    u64 base;
-    if (base_arr) {
-      base = base_arr[i];
-    } else {
-      // block ranges of k_rle_runs over base_range_n runs
-      const u64 nr = *base_range_n;
-      const u64 per = (nr + base_range_nb - 1) / base_range_nb;
-      base = min(nr, i * per);
-    }
-    const u64 o = db + off[i];
+    const u64 from = base[i], o = db + off[i];
     for (u32 j = lane; j < c; j += 64) {
       if (o + j < dst_cap) {
-        dst_k[o + j] = src_k[base + j];
-        dst_c[o + j] = src_c[base + j];
+        dst_k[o + j] = src_k[from + j];
+        dst_c[o + j] = src_c[from + j];
       }
     }
   }
@@ -1245,25 +1077,10 @@ __device__ __forceinline__ void wide_key(k128 w, int k, k128* out) {
   *out = k128{w.lo, 2 * k == 64 ? 0ull : (w.hi & ((1ull << (2 * k - 64)) - 1ull))};
 }
 
-// One bit per merged-list entry at the start of each heavy bucket's segment (bits zeroed
-// before).
-__global__ __launch_bounds__(256) void k_seg_bits(const u64* __restrict__ seg, const u64* __restrict__ n_large_ptr,
-                                                  const u64* __restrict__ n_ent_ptr, u32* __restrict__ bits) {
-  const u64 n_large = *n_large_ptr, n_ent = *n_ent_ptr;
-  for (u64 i = blockIdx.x * (u64)blockDim.x + threadIdx.x; i < n_large; i += (u64)gridDim.x * blockDim.x) {
-    const u64 p = seg[i];
-    if (p < n_ent) atomicOr(&bits[p >> 5], 1u << (p & 31));
-  }
-}
-
-// k_gather_segments for several sets: the same segments, written as wide keys.  The set
-// of segment i is bset[i] (bucket survivors), else that of each entry (src_set: merged
-// runs).
+// k_gather_segments for several sets: the same segments, of set bset[i], written as wide keys.
 template <typename K>
 __global__ __launch_bounds__(256) void k_gather_wide(const K* __restrict__ src_k, const u32* __restrict__ src_c,
-                                                     const u64* __restrict__ base_arr,
-                                                     const u64* __restrict__ base_range_n, u32 base_range_nb,
-                                                     const u32* __restrict__ bset, const u32* __restrict__ src_set,
+                                                     const u64* __restrict__ base, const u32* __restrict__ bset,
                                                      const u32* __restrict__ cnt, const u32* __restrict__ off,
                                                      u64 n_seg, int k, k128* __restrict__ dst_k,
                                                      u32* __restrict__ dst_c, u64 dst_cap) {
@@ -1273,20 +1090,13 @@ __global__ __launch_bounds__(256) void k_gather_wide(const K* __restrict__ src_k
   for (u64 i = wave; i < n_seg; i += n_waves) {
     const u32 c = cnt[i];
     if (!c) continue;
-    u64 base;
-    if (base_arr) {
-      base = base_arr[i];
-    } else {
-      const u64 nr = *base_range_n;
-      const u64 per = (nr + base_range_nb - 1) / base_range_nb;
-      base = min(nr, i * per);
-    }
+    const u64 from = base[i];
+    const u32 st = bset[i];
     const u64 o = off[i];
     for (u32 j = lane; j < c; j += 64) {
       if (o + j < dst_cap) {
-        const u32 st = bset ? bset[i] : src_set[base + j];
-        dst_k[o + j] = wide_of(src_k[base + j], st, k);
-        dst_c[o + j] = src_c[base + j];
+        dst_k[o + j] = wide_of(src_k[from + j], st, k);
+        dst_c[o + j] = src_c[from + j];
       }
     }
   }
@@ -1296,9 +1106,7 @@ __global__ __launch_bounds__(256) void k_gather_wide(const K* __restrict__ src_k
 // value = count | set << cbits (the count is at most max_freq < 2^cbits).
 template <typename K>
 __global__ __launch_bounds__(256) void k_gather_packed(const K* __restrict__ src_k, const u32* __restrict__ src_c,
-                                                       const u64* __restrict__ base_arr,
-                                                       const u64* __restrict__ base_range_n, u32 base_range_nb,
-                                                       const u32* __restrict__ bset, const u32* __restrict__ src_set,
+                                                       const u64* __restrict__ base, const u32* __restrict__ bset,
                                                        const u32* __restrict__ cnt, const u32* __restrict__ off,
                                                        u64 n_seg, int cbits, K* __restrict__ dst_k,
                                                        u32* __restrict__ dst_c, u64 dst_cap) {
@@ -1308,20 +1116,13 @@ __global__ __launch_bounds__(256) void k_gather_packed(const K* __restrict__ src
   for (u64 i = wave; i < n_seg; i += n_waves) {
     const u32 c = cnt[i];
     if (!c) continue;
-    u64 base;
-    if (base_arr) {
-      base = base_arr[i];
-    } else {
-      const u64 nr = *base_range_n;
-      const u64 per = (nr + base_range_nb - 1) / base_range_nb;
-      base = min(nr, i * per);
-    }
+    const u64 from = base[i];
+    const u32 st = bset[i];
     const u64 o = off[i];
     for (u32 j = lane; j < c; j += 64) {
       if (o + j < dst_cap) {
-        const u32 st = bset ? bset[i] : src_set[base + j];
-        dst_k[o + j] = src_k[base + j];
-        dst_c[o + j] = src_c[base + j] | (st << cbits);
+        dst_k[o + j] = src_k[from + j];
+        dst_c[o + j] = src_c[from + j] | (st << cbits);
       }
     }
   }

@@ -48,18 +48,13 @@ __device__ __forceinline__ u32 key_place(K k, int nbits, int canonical) {
   return canonical ? ~__umulhi(~t, ~t) : t;
 }
 
-// Survivors where the count left them: bucket i's s_cnt[i] at s_base[i] of (s_k, s_c), i <
-// n_buckets, and block j of k_rle_runs' s_cnt[n_buckets + j] at its first run of *n_runs in
-// (r_k, r_c), j < n_rblk.
+// Survivors where the count left them: bucket i's s_cnt[i] at s_base[i] of (s_k, s_c).
 struct SurvSegs {
   const void* s_k;
   const u32* s_c;
   const u64* s_base;
   const u32* s_cnt;
-  u32 n_buckets, n_rblk;
-  const void* r_k;
-  const u32* r_c;
-  const u64* n_runs;
+  u32 n_buckets;
 };
 struct MsdArgs {
   const void* in_k;        // dense survivors ...
@@ -99,7 +94,6 @@ struct SegArgs {
   const u64* n_seg_ptr;    // number of segments
   int nbits;               // key bits (2k)
   int canonical;           // see key_place
-  int group_only;          // equal keys adjacent suffices (segments of a count's lists)
   const u64* msd_n;        // when set: segments are key ranges of k_msd_fine over *msd_n keys
   u32 msd_target;
   u32 wave_cap;            // segments of at most this many pairs are left to k_seg_wave
@@ -112,11 +106,9 @@ __device__ __forceinline__ int seg_place_bits(const SegArgs& A) {
 
 // Bins of a segment of m keys: a power of two of at least m and 64.
 __device__ __forceinline__ int seg_bin_bits(u32 m) { return max(6, 32 - __builtin_clz((m - 1) | 1)); }
-// The bin of a key: the bits of its place below its segment's, or, where equal keys need only
-// be adjacent, bits of its mixed image (a heavy bucket's k-mers share their minimizer).
+// The bin of a key: the bits of its place below its segment's.
 template <typename K>
 __device__ __forceinline__ u32 seg_bin(const SegArgs& A, K key, int pbits, int db) {
-  if (A.group_only) return key_field(mix_key(key), 0, db);
   return (key_place(key, A.nbits, A.canonical) << pbits) >> (32 - db);
 }
 // Keys of the bin [b0, b1) that come before the key at slot `at` (equal keys by their slot).
@@ -149,18 +141,135 @@ struct SegSmem {
   u32 n_long;
 };
 
+// The block's m pairs (kr, vr; thread t holds pairs t, t + T, ...) sorted into S.keys and
+// S.b.vals by bin(key), below 2^db, then by key.  db: 2^db of at least T and m.
+template <int T, int ITEMS, typename K, typename SM, typename Bin>
+__device__ __forceinline__ void seg_sort_chip(SM& S, u32 m, int db, const K (&kr)[ITEMS], const u32 (&vr)[ITEMS], Bin bin) {
+  const u32 tid = threadIdx.x, per = (1u << db) / T;   // bins per thread
+  for (u32 i = tid; i < 1u << db; i += T) S.b.bins[i] = 0;
+  __syncthreads();
+  u32 rk[ITEMS];
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j)
+    if (tid + (u32)j * T < m) rk[j] = atomicAdd(&S.b.bins[bin(kr[j])], 1u);
+  __syncthreads();
+  {
+    u64 sum = 0, tot;
+    for (u32 q = 0; q < per; ++q) sum += S.b.bins[tid * per + q];
+    u32 run = (u32)block_exclusive_scan<u64>(sum, S.scr, &tot);
+    for (u32 q = 0; q < per; ++q) {
+      const u32 c = S.b.bins[tid * per + q];
+      S.b.bins[tid * per + q] = run;
+      run += c;
+    }
+    if (tid == 0) S.b.bins[1u << db] = m;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j)
+    if (tid + (u32)j * T < m) {
+      rk[j] += S.b.bins[bin(kr[j])];
+      S.keys[rk[j]] = kr[j];
+    }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j)
+    if (tid + (u32)j * T < m) {
+      const u32 d = bin(kr[j]);
+      rk[j] = seg_rank(S.keys, kr[j], rk[j], S.b.bins[d], S.b.bins[d + 1]);
+    }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j)
+    if (tid + (u32)j * T < m) {
+      S.keys[rk[j]] = kr[j];
+      S.b.vals[rk[j]] = vr[j];
+    }
+  __syncthreads();
+}
+
+// A segment [s0, s0 + n) longer than a block holds: stable LSD passes through HBM, ping-pong
+// between src and dst (which end with the sorted pairs in src).  With `mixed` (keys of more than
+// 32 bits), where equal keys
+// need only be adjacent, the keys are mixed as they are first read, the low 8 * p0 bits are
+// sorted first (p0 from the length, so that two distinct keys share those bits with a chance of
+// about 1%), and the remaining passes run only if some group of equal low bits holds two keys;
+// the keys stay mixed.
+template <int T, int ITEMS, typename K, typename SM>
+__device__ __forceinline__ void seg_sort_long(SM& S, K*& src_k, u32*& src_v, K*& dst_k, u32*& dst_v, u64 s0, u64 n,
+                                              int nbits, bool mixed) {
+  constexpr u32 CAP = SM::CAP, WB = 64u * (T / 64);
+  const u32 tid = threadIdx.x;
+  auto ld = [&](const K* src, u64 i, int p) { return (mixed && p == 0) ? mix_key(src[i]) : src[i]; };
+  auto pass = [&](int p) {
+    for (u32 d = tid; d < 256; d += T) S.dcnt[d] = 0;
+    __syncthreads();
+    for (u64 i = tid; i < n; i += T) atomicAdd(&S.dcnt[key_digit(ld(src_k, s0 + i, p), 8 * p)], 1u);
+    __syncthreads();
+    {
+      u64 tot;
+      const u64 v = tid < 256 ? (u64)S.dcnt[tid] : 0ull;
+      const u64 ex = block_exclusive_scan<u64>(v, S.scr, &tot);
+      if (tid < 256) S.drun[tid] = (u32)ex;
+    }
+    __syncthreads();
+    for (u64 t0 = 0; t0 < n; t0 += CAP) {
+      const u32 m = (u32)min((u64)CAP, n - t0), m_pad = (m + WB - 1) / WB * WB;
+      for (u32 i = tid; i < m_pad; i += T) {
+        S.keys[i] = i < m ? ld(src_k, s0 + t0 + i, p) : key_pad<K>();
+        S.b.vals[i] = i < m ? src_v[s0 + t0 + i] : 0u;
+      }
+      for (u32 d = tid; d < 256; d += T) S.dcnt[d] = 0;
+      __syncthreads();
+      // one stable pass on digit p orders the tile by that digit (padding last)
+      lds_sort_passes<K, T, ITEMS, true>(S.keys, S.b.vals, S.tbl, S.cnt, S.gtot, m_pad, p, p + 1, true);
+      for (u32 i = tid; i < m; i += T) {
+        const u32 d = key_digit(S.keys[i], 8 * p);
+        if (i == 0 || key_digit(S.keys[i - 1], 8 * p) != d) S.dstart[d] = i;
+        atomicAdd(&S.dcnt[d], 1u);
+      }
+      __syncthreads();
+      for (u32 i = tid; i < m; i += T) {
+        const u32 d = key_digit(S.keys[i], 8 * p);
+        const u64 at = s0 + S.drun[d] + (i - S.dstart[d]);
+        dst_k[at] = S.keys[i];
+        dst_v[at] = S.b.vals[i];
+      }
+      __syncthreads();
+      for (u32 d = tid; d < 256; d += T) S.drun[d] += S.dcnt[d];
+      __syncthreads();
+    }
+    K* tk = src_k;
+    src_k = dst_k;
+    dst_k = tk;
+    u32* tv = src_v;
+    src_v = dst_v;
+    dst_v = tv;
+  };
+  const int np = mixed ? sort_passes<K>(nbits / 2) : (nbits + 7) / 8;
+  // 8 * p0 >= 2 log2(n) + 7 bits (one pass loop, so that the pass is inlined once)
+  int p_end = mixed ? min((2 * (64 - __builtin_clzll(n)) + 14) / 8, np) : np;
+  bool checked = !mixed;
+  for (int p = 0;;) {
+    const int p0 = p_end;
+    for (; p < p_end; ++p) pass(p);
+    if (checked) break;
+    checked = true;
+    bool bad = false;
+    for (u64 i = tid; i < n; i += T) bad |= mixed_pair(src_k + s0, (u32)i, (u32)n, 8 * p0);
+    if (!__syncthreads_or(bad)) break;
+    p_end = np;
+  }
+}
+
 template <typename K, int T, int ITEMS>
 __global__ __launch_bounds__(T) void k_seg_sort(SegArgs A) {
   using SM = SegSmem<K, T, ITEMS>;
-  constexpr u32 CAP = SM::CAP, WB = 64u * (T / 64);
+  constexpr u32 CAP = SM::CAP;
   __shared__ SM S;
   const u32 tid = threadIdx.x;
   const u64 n_seg = *A.n_seg_ptr;
   const int pbits = seg_place_bits(A);
-  const int np = (A.nbits + 7) / 8;
-  // long segments, grouping only: mixed keys, early exit
-  const bool mixed = A.group_only && A.nbits > 32;
-  const int np_mixed = sort_passes<K>(A.nbits / 2);
   K* in_k = reinterpret_cast<K*>(A.keys);
   K* tmp_k = reinterpret_cast<K*>(A.tmp_k);
   K* out_k = reinterpret_cast<K*>(A.out_k);
@@ -182,57 +291,16 @@ __global__ __launch_bounds__(T) void k_seg_sort(SegArgs A) {
     __syncthreads();                             // LDS of the previous segment is free
     if (n <= CAP) {
       const u32 m = (u32)n;
-      const int db = seg_bin_bits(m);
-      const u32 per = (1u << db) / T;              // bins per thread (m > wave_cap >= T: at least 1)
-      for (u32 i = tid; i < 1u << db; i += T) S.b.bins[i] = 0;
-      __syncthreads();
+      const int db = seg_bin_bits(m);              // (m > wave_cap >= T: at least T bins)
       K kr[ITEMS];
-      u32 vr[ITEMS], rk[ITEMS];
+      u32 vr[ITEMS];
 #pragma unroll
       for (int j = 0; j < ITEMS; ++j) {
         const u32 i = tid + (u32)j * T;
-        if (i < m) {
-          kr[j] = in_k[s0 + i];
-          vr[j] = A.vals[s0 + i];
-        }
+        kr[j] = i < m ? in_k[s0 + i] : key_zero<K>();
+        vr[j] = i < m ? A.vals[s0 + i] : 0u;
       }
-#pragma unroll
-      for (int j = 0; j < ITEMS; ++j)
-        if (tid + (u32)j * T < m) rk[j] = atomicAdd(&S.b.bins[seg_bin(A, kr[j], pbits, db)], 1u);
-      __syncthreads();
-      {
-        u64 sum = 0, tot;
-        for (u32 q = 0; q < per; ++q) sum += S.b.bins[tid * per + q];
-        u32 run = (u32)block_exclusive_scan<u64>(sum, S.scr, &tot);
-        for (u32 q = 0; q < per; ++q) {
-          const u32 c = S.b.bins[tid * per + q];
-          S.b.bins[tid * per + q] = run;
-          run += c;
-        }
-        if (tid == 0) S.b.bins[1u << db] = m;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < ITEMS; ++j)
-        if (tid + (u32)j * T < m) {
-          rk[j] += S.b.bins[seg_bin(A, kr[j], pbits, db)];
-          S.keys[rk[j]] = kr[j];
-        }
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < ITEMS; ++j)
-        if (tid + (u32)j * T < m) {
-          const u32 d = seg_bin(A, kr[j], pbits, db);
-          rk[j] = seg_rank(S.keys, kr[j], rk[j], S.b.bins[d], S.b.bins[d + 1]);
-        }
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < ITEMS; ++j)
-        if (tid + (u32)j * T < m) {
-          S.keys[rk[j]] = kr[j];
-          S.b.vals[rk[j]] = vr[j];
-        }
-      __syncthreads();
+      seg_sort_chip<T, ITEMS>(S, m, db, kr, vr, [&](K k) { return seg_bin(A, k, pbits, db); });
       for (u32 i = tid; i < m; i += T) {
         if (s0 + i < A.out_cap) {
           out_k[s0 + i] = S.keys[i];
@@ -241,81 +309,12 @@ __global__ __launch_bounds__(T) void k_seg_sort(SegArgs A) {
       }
       continue;
     }
-    // Long segment: stable LSD passes through HBM, ping-pong between in and tmp.  When only
-    // grouping is needed the keys are mixed as they are first read, the low 8 * p0 bits
-    // are sorted first (p0 from the length, so that two distinct keys share those bits
-    // with a chance of about 1%), and the remaining passes run only if some group of
-    // equal low bits holds two keys; the keys are unmixed as they are written out.
-    K* src_k = in_k;
-    u32* src_v = A.vals;
-    K* dst_k = tmp_k;
-    u32* dst_v = A.tmp_v;
-    auto ld = [&](const K* src, u64 i, int p) { return (mixed && p == 0) ? mix_key(src[i]) : src[i]; };
-    auto pass = [&](int p) {
-      for (u32 d = tid; d < 256; d += T) S.dcnt[d] = 0;
-      __syncthreads();
-      for (u64 i = tid; i < n; i += T) atomicAdd(&S.dcnt[key_digit(ld(src_k, s0 + i, p), 8 * p)], 1u);
-      __syncthreads();
-      {
-        u64 tot;
-        const u64 v = tid < 256 ? (u64)S.dcnt[tid] : 0ull;
-        const u64 ex = block_exclusive_scan<u64>(v, S.scr, &tot);
-        if (tid < 256) S.drun[tid] = (u32)ex;
-      }
-      __syncthreads();
-      for (u64 t0 = 0; t0 < n; t0 += CAP) {
-        const u32 m = (u32)min((u64)CAP, n - t0), m_pad = (m + WB - 1) / WB * WB;
-        for (u32 i = tid; i < m_pad; i += T) {
-          S.keys[i] = i < m ? ld(src_k, s0 + t0 + i, p) : key_pad<K>();
-          S.b.vals[i] = i < m ? src_v[s0 + t0 + i] : 0u;
-        }
-        for (u32 d = tid; d < 256; d += T) S.dcnt[d] = 0;
-        __syncthreads();
-        // one stable pass on digit p orders the tile by that digit (padding last)
-        lds_sort_passes<K, T, ITEMS, true>(S.keys, S.b.vals, S.tbl, S.cnt, S.gtot, m_pad, p, p + 1, true);
-        for (u32 i = tid; i < m; i += T) {
-          const u32 d = key_digit(S.keys[i], 8 * p);
-          if (i == 0 || key_digit(S.keys[i - 1], 8 * p) != d) S.dstart[d] = i;
-          atomicAdd(&S.dcnt[d], 1u);
-        }
-        __syncthreads();
-        for (u32 i = tid; i < m; i += T) {
-          const u32 d = key_digit(S.keys[i], 8 * p);
-          const u64 at = s0 + S.drun[d] + (i - S.dstart[d]);
-          dst_k[at] = S.keys[i];
-          dst_v[at] = S.b.vals[i];
-        }
-        __syncthreads();
-        for (u32 d = tid; d < 256; d += T) S.drun[d] += S.dcnt[d];
-        __syncthreads();
-      }
-      K* tk = src_k;
-      src_k = dst_k;
-      dst_k = tk;
-      u32* tv = src_v;
-      src_v = dst_v;
-      dst_v = tv;
-    };
-    // 8 * p0 >= 2 log2(n) + 7 bits (one pass loop, so that the pass is inlined once)
-    const int p0 = mixed ? min((2 * (64 - __builtin_clzll(n)) + 14) / 8, np_mixed) : np;
-    int p_end = p0;
-    bool checked = !mixed;
-    for (int p = 0;;) {
-      for (; p < p_end; ++p) pass(p);
-      if (checked) break;
-      checked = true;
-      bool bad = false;
-      for (u64 i = tid; i < n; i += T) bad |= mixed_pair(src_k + s0, (u32)i, (u32)n, 8 * p0);
-      if (!__syncthreads_or(bad)) break;
-      p_end = np_mixed;
-    }
-    if (src_k != out_k || mixed) {
-      for (u64 i = tid; i < n; i += T) {
-        if (s0 + i < A.out_cap) {
-          const K key = src_k[s0 + i];
-          out_k[s0 + i] = mixed ? unmix_key(key) : key;
-        }
-      }
+    K *src_k = in_k, *dst_k = tmp_k;
+    u32 *src_v = A.vals, *dst_v = A.tmp_v;
+    seg_sort_long<T, ITEMS>(S, src_k, src_v, dst_k, dst_v, s0, n, A.nbits, false);
+    if (src_k != out_k) {
+      for (u64 i = tid; i < n; i += T)
+        if (s0 + i < A.out_cap) out_k[s0 + i] = src_k[s0 + i];
     }
     if (src_v != A.out_v) {
       for (u64 i = tid; i < n; i += T)
@@ -323,6 +322,205 @@ __global__ __launch_bounds__(T) void k_seg_sort(SegArgs A) {
     }
    }
   }
+}
+
+// ---------------------------------------------------------------------------- heavy buckets
+// A large bucket's chunks left (k-mer, count) lists with distinct k-mers each; one block brings a
+// bucket's lists together, sorts them so that equal k-mers adjoin, adds up each run's counts and
+// leaves the bucket's survivors, like any other's, at its k-mer slots.  (The steps by kernels of
+// their own, over all buckets' lists at once, were seven launches, which most counts made for
+// nothing: a count of 240 kbp took 188 us with them, 166 without.)
+struct MergeArgs {
+  CountArgs c;
+  const u32* ch0;          // first chunk of each large bucket
+  u64 chunk_cap;
+  void *k0, *k1;           // two buffers for lists that a block does not hold, at the k-mer slots
+  u32 *v0, *v1;
+  u64* n_entries;          // list entries, added up
+};
+
+template <typename K, int T, int ITEMS, bool MS>
+__global__ __launch_bounds__(T) void k_merge_lists(MergeArgs M) {
+  using SM = SegSmem<K, T, ITEMS>;
+  constexpr u32 CAP = SM::CAP;
+  __shared__ SM S;
+  __shared__ u32 hist_s[256], lmax, cursor, kept;
+  __shared__ unsigned long long lover, nd;
+  const CountArgs& A = M.c;
+  const u32 tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6);
+  const u64 n_large = A.meta[1], n_chunks = min(A.meta[4], M.chunk_cap);
+  if (blockIdx.x >= n_large) return;
+  auto clear_stats = [&]() {
+    for (u32 i = tid; i < 256; i += T) hist_s[i] = 0;
+    if (tid == 0) {
+      lmax = 0;
+      lover = 0;
+      nd = 0;
+      kept = 0;
+    }
+  };
+  clear_stats();
+  RunSink sink{hist_s, A.hist_len, A.hist, A.tot, &lmax, &lover};
+  const K* lists_k = reinterpret_cast<const K*>(A.kl_k);
+  const bool mixed = 2 * A.k > 32;
+  u64 entries = 0;
+  u32 cur = ~0u;
+  for (u64 b = blockIdx.x; b < n_large; b += gridDim.x) {
+    const u32 bucket = A.large_list[b];
+    const u64 base = A.kall_off[bucket];
+    const u64 c0 = min((u64)M.ch0[b], n_chunks), c1 = b + 1 < n_large ? min((u64)M.ch0[b + 1], n_chunks) : n_chunks;
+    __syncthreads();                             // (the previous bucket is done with LDS)
+    if constexpr (MS) {
+      const u32 st = A.bset[bucket];
+      if (st != cur) {
+        if (cur != ~0u) {
+          flush_stats(sink, nd);
+          __syncthreads();
+          clear_stats();
+        }
+        sink_to_set(sink, A.hist, A.tot, st);
+        cur = st;
+      }
+    }
+    if (tid == 0) cursor = 0;
+    u64 n;
+    {
+      u64 sum = 0;
+      for (u64 c = c0 + tid; c < c1; c += T) sum += A.kl_cnt[c];
+      block_exclusive_scan<u64>(sum, S.scr, &n);
+    }
+    entries += n;
+    // the lists into LDS or the first buffer, 64 chunks per wave at a time: short ones one per
+    // lane, others one after the other
+    const bool chip = n <= CAP;
+    K* src_k = reinterpret_cast<K*>(M.k0);
+    u32* src_v = M.v0;
+    auto bring = [&](auto put) {
+      for (u64 g = c0 + wave * 64; g < c1; g += T) {
+        const u32 cnt = g + lane < c1 ? A.kl_cnt[g + lane] : 0u;
+        const u64 from = g + lane < c1 ? A.chunk_start[g + lane] : 0ull;
+        const u32 inc = wave_scan_u32(cnt);
+        u32 at = 0;
+        if (lane == 63) at = atomicAdd(&cursor, inc);
+        at = lane_read(at, 63) + inc - cnt;
+        if (!__ballot(cnt > 8)) {
+          for (u32 j = 0; j < cnt; ++j) put(at + j, from + j);
+        } else {
+          for (u64 left = __ballot(cnt != 0); left; left &= left - 1) {
+            const int l = __builtin_ctzll(left);
+            const u32 cl = lane_read(cnt, l), al = lane_read(at, l);
+            const u64 fl = ((u64)lane_read((u32)(from >> 32), l) << 32) | lane_read((u32)from, l);
+            for (u32 j = lane; j < cl; j += 64) put(al + j, fl + j);
+          }
+        }
+      }
+    };
+    if (chip)
+      bring([&](u32 at, u64 from) {
+        S.keys[at] = lists_k[from];
+        S.b.vals[at] = A.kl_c[from];
+      });
+    else
+      bring([&](u32 at, u64 from) {
+        src_k[base + at] = lists_k[from];
+        src_v[base + at] = A.kl_c[from];
+      });
+    __syncthreads();
+    // equal k-mers together
+    if (chip) {
+      const u32 m = (u32)n;
+      const int db = max(__builtin_ctz(T), seg_bin_bits(m));
+      K kr[ITEMS];
+      u32 vr[ITEMS];
+#pragma unroll
+      for (int j = 0; j < ITEMS; ++j) {
+        const u32 i = tid + (u32)j * T;
+        kr[j] = i < m ? S.keys[i] : key_zero<K>();
+        vr[j] = i < m ? S.b.vals[i] : 0u;
+      }
+      __syncthreads();
+      seg_sort_chip<T, ITEMS>(S, m, db, kr, vr, [&](K k) { return key_field(mix_key(k), 0, db); });
+    } else {
+      K* dst_k = reinterpret_cast<K*>(M.k1);
+      u32* dst_v = M.v1;
+      seg_sort_long<T, ITEMS>(S, src_k, src_v, dst_k, dst_v, base, n, 2 * A.k, mixed);
+    }
+    // Runs, a block's hold of entries at a time (up to the last run that may go on behind it): the
+    // thread of a run's first entry adds up its counts.
+    K* const out_k = reinterpret_cast<K*>(A.surv_k) + base;
+    u32* const out_c = A.surv_c + base;
+    u32 distinct = 0;
+    auto report = [&](K key, u64 c, bool head) {
+      run_stats_lanes(sink, c, head);
+      distinct += (u32)__popcll(__ballot(head));
+      const bool emit = head && c >= A.min_freq && c <= A.max_freq;
+      const u64 em = __ballot(emit);
+      if (!em) return;
+      u32 at = 0;
+      if (lane == 0) at = atomicAdd(&kept, (u32)__popcll(em));
+      at = lane_read(at, 0) + mbcnt64(em);
+      if (emit) {
+        out_k[at] = chip || !mixed ? key : unmix_key(key);
+        out_c[at] = (u32)c;
+      }
+    };
+    for (u64 t0 = 0; t0 < n;) {
+      const u32 m = (u32)min((u64)CAP, n - t0);
+      if (!chip) {
+        __syncthreads();
+        for (u32 i = tid; i < m; i += T) {
+          S.keys[i] = src_k[base + t0 + i];
+          S.b.vals[i] = src_v[base + t0 + i];
+        }
+        if (tid == 0) cursor = 0;
+        __syncthreads();
+      }
+      u32 last = m;
+      if (t0 + m < n) {
+        u32 h = 0;
+        for (u32 i = tid; i < m; i += T)
+          if (i && !key_eq(S.keys[i], S.keys[i - 1])) h = i;
+        if (h) atomicMax(&cursor, h);
+        __syncthreads();
+        last = cursor;
+      }
+      if (last == 0) {   // one run, all of it and more
+        const K key = S.keys[0];
+        u64 sum = 0, c, pos = t0;
+        for (;;) {
+          const u64 i = pos + tid;
+          const bool on = i < n && key_eq(src_k[base + i], key);
+          sum += on ? src_v[base + i] : 0u;
+          const u32 got = (u32)__syncthreads_count(on);
+          pos += got;
+          if (got < T) break;
+        }
+        block_exclusive_scan<u64>(sum, S.scr, &c);
+        report(key, c, tid == 0);
+        t0 = pos;
+        continue;
+      }
+      for (u32 r0 = 0; r0 < last; r0 += T) {
+        const u32 i = r0 + tid;
+        const K key = S.keys[min(i, last - 1)];
+        const bool head = i < last && (i == 0 || !key_eq(key, S.keys[i - 1]));
+        u64 c = 0;
+        if (head)
+          for (u32 j = i; j < last && key_eq(S.keys[j], key); ++j) c += S.b.vals[j];
+        report(key, c, head);
+      }
+      t0 += last;
+    }
+    if (lane == 0 && distinct) atomicAdd(&nd, (unsigned long long)distinct);
+    __syncthreads();
+    if (tid == 0) {
+      A.surv_cnt[bucket] = kept;
+      kept = 0;
+    }
+  }
+  __syncthreads();
+  flush_stats(sink, nd);
+  if (tid == 0) atomicAdd((unsigned long long*)M.n_entries, (unsigned long long)entries);
 }
 
 // ---------------------------------------------------------------------------- short segments
@@ -421,33 +619,6 @@ __global__ __launch_bounds__(WPB * 64) void k_seg_wave(SegArgs A) {
   }
 }
 
-// The chunks' lists gathered into one array, and the segment table of the heavy buckets: lists
-// are compacted in chunk order and the chunks of one bucket are consecutive, so bucket i spans
-// the scanned list offsets of its first chunk up to those of the next bucket's first chunk.
-template <typename K>
-__global__ __launch_bounds__(256) void k_gather_lists(const K* __restrict__ src_k, const u32* __restrict__ src_c,
-                                                      const u64* __restrict__ chunk_start, const u32* __restrict__ cnt,
-                                                      const u32* __restrict__ kloff, const u32* __restrict__ large_ch0,
-                                                      const u64* __restrict__ n_large_ptr,
-                                                      const u64* __restrict__ n_chunks_ptr, u64 chunk_cap,
-                                                      const u64* __restrict__ n_entries_ptr, K* __restrict__ dst_k,
-                                                      u32* __restrict__ dst_c, u64* __restrict__ seg) {
-  const u64 n_large = *n_large_ptr, n_chunks = min(*n_chunks_ptr, chunk_cap), n_ent = *n_entries_ptr;
-  const u64 t = blockIdx.x * (u64)blockDim.x + threadIdx.x, n_t = (u64)gridDim.x * blockDim.x;
-  for (u64 i = t; i <= n_large; i += n_t) {
-    const u64 c = i < n_large ? (u64)large_ch0[i] : n_chunks;
-    seg[i] = c < n_chunks ? min((u64)kloff[c], n_ent) : n_ent;
-  }
-  for (u64 i = t >> 6; i < n_chunks; i += n_t >> 6) {
-    const u32 c = cnt[i];
-    const u64 from = chunk_start[i], to = kloff[i];
-    for (u32 j = lane_id(); j < c; j += 64) {
-      dst_k[to + j] = src_k[from + j];
-      dst_c[to + j] = src_c[from + j];
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------- key ranges
 // The survivors are split into key ranges by their top bits: a coarse pass on the top 8
 // bits (per-block LDS histograms, one scan, a scatter staged through LDS) and a fine
@@ -456,46 +627,30 @@ __global__ __launch_bounds__(256) void k_gather_lists(const K* __restrict__ src_
 // table in key order.
 //
 // The coarse pass of a one-pass count reads the survivors from where the count left them: a
-// block takes an equal share of the buckets and of the runs' blocks, its waves their segments
-// in turn, one row of up to 64 at a time.  (Gathered into one dense array first, 1 Gbp with 43 M
+// block takes an equal share of the buckets, its waves their segments in turn, one row of up to 64 at a time.  (Gathered into one dense array first, 1 Gbp with 43 M
 // survivors took 13.19 ms instead of 12.87, 60 Mbp with 20 M 1.76 instead of 1.65, and every
 // count five launches more.)
 template <typename K, u32 NW>
 struct SegRows {
   const SurvSegs& V;
-  u32 b0, nb, r0, n;   // the block's buckets [b0, b0 + nb), runs' blocks from r0 on, segments in all
-  u32 i0;              // the wave's current 64 segments: i0 + NW * lane
-  u32 c;               // lane: its segment's survivors ...
+  u32 b0, n;           // the block's buckets [b0, b0 + n)
+  u32 i0;              // the wave's current 64 buckets: i0 + NW * lane
+  u32 c;               // lane: its bucket's survivors ...
   u64 base;            // ... and place
-  bool run;
-  u64 left;            // lanes whose segments are still to do
+  u64 left;            // lanes whose buckets are still to do
   u32 off;             // done of the first of them
 
   __device__ __forceinline__ SegRows(const SurvSegs& v, u32 n_blk) : V(v) {
-    const u32 pb = (v.n_buckets + n_blk - 1) / n_blk, pr = (v.n_rblk + n_blk - 1) / n_blk;
-    b0 = min(v.n_buckets, blockIdx.x * pb);
-    nb = min(v.n_buckets - b0, pb);
-    r0 = min(v.n_rblk, blockIdx.x * pr);
-    n = nb + min(v.n_rblk - r0, pr);
+    const u32 per = (v.n_buckets + n_blk - 1) / n_blk;
+    b0 = min(v.n_buckets, blockIdx.x * per);
+    n = min(v.n_buckets - b0, per);
     i0 = uniform(threadIdx.x >> 6);
     load();
   }
   __device__ __forceinline__ void load() {
     const u32 i = i0 + NW * lane_id();
-    c = 0;
-    base = 0;
-    run = i >= nb;
-    if (i < n) {
-      if (run) {
-        const u32 j = r0 + i - nb;
-        const u64 nr = *V.n_runs, per = (nr + V.n_rblk - 1) / V.n_rblk;
-        c = V.s_cnt[V.n_buckets + j];
-        base = min(nr, j * per);
-      } else {
-        c = V.s_cnt[b0 + i];
-        base = V.s_base[b0 + i];
-      }
-    }
+    c = i < n ? V.s_cnt[b0 + i] : 0u;
+    base = i < n ? V.s_base[b0 + i] : 0ull;
     left = __ballot(c != 0);
     off = 0;
   }
@@ -509,9 +664,8 @@ struct SegRows {
     const int l = __builtin_ctzll(left);
     const u32 cl = lane_read(c, l), o = off + lane_id();
     const u64 at = (((u64)lane_read((u32)(base >> 32), l) << 32) | lane_read((u32)base, l)) + o;
-    const bool rn = i0 + NW * (u32)l >= nb;
-    *k = reinterpret_cast<const K*>(rn ? V.r_k : V.s_k) + at;
-    *v = (rn ? V.r_c : V.s_c) + at;
+    *k = reinterpret_cast<const K*>(V.s_k) + at;
+    *v = V.s_c + at;
     off += 64;
     if (off >= cl) {
       off = 0;
