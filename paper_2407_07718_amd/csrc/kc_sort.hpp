@@ -201,6 +201,7 @@ template <int ROWS>
 __device__ __forceinline__ void wave_scan_rows(const uint4 (&v)[ROWS], u32 base, u32* __restrict__ out, u64 i0, u64 n) {
 #pragma unroll
   for (int r = 0; r < ROWS; ++r) {
+    if (i0 + 256 * r >= n) break;   // (the same in all lanes)
     const u32 s = v[r].x + v[r].y + v[r].z + v[r].w, inc = wave_scan_u32(s), a = base + inc - s;
     store4(out, i0 + 256 * r + 4 * lane_id(), n, make_uint4(a, a + v[r].x, a + v[r].x + v[r].y, a + v[r].x + v[r].y + v[r].z));
     base += lane_read(inc, 63);
@@ -225,18 +226,20 @@ __global__ __launch_bounds__(SCAN_ONE_T) void k_scan_u32(const u32* __restrict__
   uint4 v[SCAN_ONE_ROWS];
   u64 sum = 0;
 #pragma unroll
+  for (u32 r = 0; r < SCAN_ONE_ROWS; ++r) v[r] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
   for (u32 r = 0; r < SCAN_ONE_ROWS; ++r) {
+    if (i0 + 256 * r >= end) break;
     v[r] = load4(in, i0 + 256 * r + 4 * lane, end);
     sum += sum4(v[r]);
   }
   sum = wave_sum(sum);
   if (lane == 0) wsum[wave] = sum;
   __syncthreads();
-  u64 base = 0, all = 0;
-  for (u32 w = 0; w < W; ++w) {
-    if (w == wave) base = all;
-    all += wsum[w];
-  }
+  // (the first 16 lanes hold the waves' sums)
+  u64 base = lane < W ? wsum[lane] : 0ull;
+  const u64 all = wave_sum(base);
+  base = wave_sum(lane < wave ? base : 0ull);
   wave_scan_rows<SCAN_ONE_ROWS>(v, (u32)base, out, i0, end);
   if (threadIdx.x == 0 && total) *total = all;
   if (threadIdx.x == 0 && clamped) *clamped = min(all, cap);
