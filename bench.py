@@ -143,23 +143,22 @@ def kernel_roofline(dom: str, per: dict, tot: dict, k: int, traffic) -> dict:
     n_win = max(1, tot["n_windows"])
     s_avg = rb * tot["n_records"] / n_win          # record bytes per k-mer
     surv = tot["n_pairs"]
-    name = {"extract": "k_extract", "block_sort": "k_bucket_sort_count", "wave_sort": "k_wave_sort_count"}[dom]
+    # (the stage names are those of the profile's slots: the chunks' and the buckets' count)
+    name = {"extract": "k_extract", "block_sort": "k_hash_count", "wave_sort": "k_hash_count"}[dom]
     if dom == "extract":
         # 2-bit bases + invalid-base mask + cut mask read once (0.5 B per base), records
         # written once
         algo = 0.5 * tot["bases"] + rb * tot["n_records"]
         basis = "0.5 B per base read + one record write"
     elif dom == "block_sort":
-        # small buckets: their records read once; large-bucket chunks: keys read, (k-mer,
-        # count) lists written; survivors written (their share of the k-mers)
-        keys = tot["small_kmers"]
-        algo = (keys * s_avg + tot["large_keys"] * w + tot["list_entries"] * (w + 4)
-                + surv * keys / n_win * (w + 4))
-        basis = "small-bucket k-mers x record bytes per k-mer + large keys x w + lists x (w+4) + survivors x (w+4)"
+        # large-bucket chunks: keys read, (k-mer, count) lists written
+        algo = tot["large_keys"] * w + tot["list_entries"] * (w + 4)
+        basis = "large keys x w + lists x (w+4)"
     else:
-        keys = tot["tiny_kmers"]
+        # buckets: their records read once, their survivors (their share of the k-mers) written
+        keys = tot["tiny_kmers"] + tot["small_kmers"]
         algo = keys * s_avg + surv * keys / n_win * (w + 4)
-        basis = "tiny-bucket k-mers x record bytes per k-mer + survivors x (w+4)"
+        basis = "on-chip buckets' k-mers x record bytes per k-mer + survivors x (w+4)"
     ms = per[dom]
     achieved = algo / (ms * 1e-3) / 1e9
     tr = None
