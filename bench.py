@@ -164,7 +164,8 @@ def kernel_roofline(dom: str, per: dict, tot: dict, k: int, traffic) -> dict:
     tr = None
     if traffic:
         rec = traffic["kernels"].get(name)
-        tr = rec["traffic_bytes_per_launch"] if rec else None
+        # (per count: the chunks' and the buckets' launches of k_hash_count share a name)
+        tr = int(rec["traffic_bytes_per_launch"] * rec["dispatches"] / traffic["counts_profiled"]) if rec else None
     return {"bound": "hbm", "kernel": name, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": tr, "algo_bytes_per_launch": int(algo),
             "avg_launch_ms": round(ms, 4), "algo_basis": basis}
