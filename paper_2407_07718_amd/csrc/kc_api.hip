@@ -95,6 +95,8 @@ struct Plan {
       o_ctrl, o_blkcnt, o_chstart, o_chlen,
       o_kall, o_klcnt, o_scnt, o_soff, o_bsum, o_scanbuf, o_phist, o_lch0, o_seg, o_mhist;
   int log_c = 0, log_f = 0;
+  u32 B_cap = 0;         // buckets (and their coarse bits) that the regions are sized for
+  int log_c_cap = 0;
   u32 part_nblk = 1, part_spb = 1, nblk_cap = 1;   // extract blocks: this count's, and the bound over m
   u64 n_packed, n_mask, bytes = 0;
   // Memory-bounded counting (rounds > 1): the coarse bucket groups are counted in rounds
@@ -261,6 +263,17 @@ int auto_log_b(u64 n_max, u64 slots) {
   while (few < 10 && (n_max >> few) > 512) ++few;
   return std::max(lb, few);
 }
+// The same where minimizers of at least 9 bases (2^17 of them) spread the k-mers evenly over few
+// buckets: from 64 buckets on only as many as bring the mean to half the slots, because each costs
+// its share of an empty table.  (240,000 k-mers of 31 bases, 6x: 87 us of kernels in 128 buckets,
+// 100 in 512; 500,000: 103 us in 256, 120 in 1,024; 800,000 in 64 210 us, in 128 123.  With
+// minimizers of 5 bases 500,000 k-mers seen once take 1.33 ms in 256 buckets, 0.79 in 1,024, with 8
+// bases 240,000 of 51 bases 158 us in 256 and 147 in 512.)
+int even_log_b(u64 n_max, u64 slots) {
+  int lb = auto_log_b(n_max, slots), few = 6;
+  while (few < lb && (n_max >> few) > slots / 2) ++few;
+  return std::min(lb, few);
+}
 
 void plan_layout(Plan* p);
 
@@ -287,9 +300,13 @@ bool make_plan(u64 R, u64 n_reads, u64 n_max, int k, int m, uint32_t min_freq, c
     if (cfg->log2_buckets > 20) return false;
     p->log_b = (int)cfg->log2_buckets;
   } else {
-    p->log_b = auto_log_b(n_max, slots);
+    p->log_b = m >= 9 ? even_log_b(n_max, slots) : auto_log_b(n_max, slots);
   }
   p->B = 1u << p->log_b;
+  // (the workspace may not depend on m, see below)
+  const int log_b_cap = cfg && cfg->log2_buckets ? p->log_b : auto_log_b(n_max, slots);
+  p->B_cap = 1u << log_b_cap;
+  p->log_c_cap = std::min(9, log_b_cap);
   p->log_c = std::min(9, p->log_b);
   p->log_f = p->log_b - p->log_c;
   p->rec_cap = std::max<u64>(1, n_max);
@@ -339,7 +356,7 @@ void plan_layout(Plan* p) {
   };
   const u64 rb = 4ull * p->rec_words;
   const u64 N = n_k;
-  p->chunk_cap = N / p->cap_chunk + p->B + 1;
+  p->chunk_cap = N / p->cap_chunk + p->B_cap + 1;
   p->kl_cap = N;
   p->o_packed = take(4 * p->n_packed);
   p->o_nmask = take(4 * p->n_mask);
@@ -360,24 +377,24 @@ void plan_layout(Plan* p) {
   p->o_Z = take(std::max((w + 4) * N, mid - std::min(mid, o - p->o_X)));
   p->o_pmid = p->o_X;
   p->o_blkcnt = take(4ull * p->nblk_cap);
-  p->o_bcnt = take(8ull * p->B);
-  p->o_recoff = take(4ull * (p->B + 1));
-  p->o_large = take(4ull * p->B);
-  p->o_kall = take(8ull * p->B);
+  p->o_bcnt = take(8ull * p->B_cap);
+  p->o_recoff = take(4ull * (p->B_cap + 1));
+  p->o_large = take(4ull * p->B_cap);
+  p->o_kall = take(8ull * p->B_cap);
   p->o_ctrl = take(8ull * C_WORDS);
   p->o_chstart = take(8 * p->chunk_cap);
   p->o_chlen = take(4 * p->chunk_cap);
   p->o_klcnt = take(4 * p->chunk_cap);
-  p->o_scnt = take(4ull * p->B);
-  p->o_soff = take(4ull * p->B);
-  p->o_bsum = take(8ull * PLAN_Q * (p->B / PLAN_BLOCK + 1));
+  p->o_scnt = take(4ull * p->B_cap);
+  p->o_soff = take(4ull * p->B_cap);
+  p->o_bsum = take(8ull * PLAN_Q * (p->B_cap / PLAN_BLOCK + 1));
   p->o_scanbuf = take(8ull * 1024);
-  p->o_phist = take(4ull * ((u64)1 << p->log_c) * p->nblk_cap);
-  p->o_lch0 = take(4ull * p->B);
-  p->o_seg = take(8ull * (std::max<u64>(p->B, (u64)256 << MSD_G2_MAX) + 2));
+  p->o_phist = take(4ull * ((u64)1 << p->log_c_cap) * p->nblk_cap);
+  p->o_lch0 = take(4ull * p->B_cap);
+  p->o_seg = take(8ull * (std::max<u64>(p->B_cap, (u64)256 << MSD_G2_MAX) + 2));
   p->o_mhist = take(4ull * 256 * MSD_NB);
   if (rounds) {
-    const u64 C = 1ull << p->log_c;
+    const u64 C = 1ull << p->log_c_cap;
     p->o_hrec = take(4ull * C * p->nblk_cap);
     p->o_hkm = take(4ull * C * p->nblk_cap);
     p->o_gsum = take(16ull * C);
@@ -400,6 +417,10 @@ void plan_layout(Plan* p) {
 bool plan_rounds(Plan* p, u64 budget) {
   const u64 w = 8ull * p->key_words, rb = 4ull * p->rec_words;
   const u64 per_k = 3 * (w + 4), per_pool = w + 4;
+  p->B = p->B_cap;   // (more coarse groups to fill rounds with)
+  p->log_b = __builtin_ctz(p->B_cap);
+  p->log_c = p->log_c_cap;
+  p->log_f = p->log_b - p->log_c;
   Plan q = *p;
   q.rounds = 2;
   q.cap_k = q.cap_r = 1;
