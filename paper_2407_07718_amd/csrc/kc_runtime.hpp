@@ -320,7 +320,7 @@ struct kc_batch {
     MultiPlan mp;
     int lane = 0;
     char* own = nullptr;
-    // on the host since the last run's first result: first pair and totals of every set
+    // on the host since the first result after the last run: first pair and totals of every set
     std::vector<u64> first;
     std::vector<kc_totals> tot;
     bool on_host = false;
@@ -338,6 +338,7 @@ struct kc_batch {
   static constexpr u64 PIN_BYTES = 4ull << 20;
   std::mutex result_mu;
   u32 n_results = 0;
+  u32 running = 0;   // runs under way: what a result copies beside one is not kept for the next
   char* pin = nullptr;
   u64 device_bytes = 0;   // workspaces, tables and outputs (not the caller's inputs)
   hipEvent_t fork = nullptr;
@@ -620,10 +621,18 @@ int kc_batch_run(kc_batch* b, void* stream) {
   g_err.clear();
   if (!b) return fail(KC_EINVAL, "NULL batch");
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  {
-    std::lock_guard<std::mutex> g(b->result_mu);
-    for (auto& G : b->groups) G.on_host = false;
-  }
+  struct Running {
+    kc_batch* b;
+    explicit Running(kc_batch* b_) : b(b_) {
+      std::lock_guard<std::mutex> g(b->result_mu);
+      ++b->running;
+      for (auto& G : b->groups) G.on_host = false;
+    }
+    ~Running() {
+      std::lock_guard<std::mutex> g(b->result_mu);
+      --b->running;
+    }
+  } running(b);
   if (b->use_graph) {
     HIP_TRY(hipGraphLaunch(b->exec, st));
   } else {
@@ -649,9 +658,10 @@ int kc_batch_result(kc_batch* b, uint32_t job, kc_result* out) {
     if (!G.on_host) {
       HIP_TRY(hipMemcpy(G.first.data(), O.first, 8 * G.first.size(), hipMemcpyDeviceToHost));
       HIP_TRY(hipMemcpy(G.tot.data(), O.tot, sizeof(kc_totals) * G.tot.size(), hipMemcpyDeviceToHost));
-      G.on_host = true;
+      G.on_host = b->running == 0;
     }
     const u64 f0 = G.first[J.set], f1 = G.first[J.set + 1];
+    if (f0 > f1 || f1 > G.mp.wide_cap) return fail(KC_EDEVICE, "the batch has no complete run to read");
     const int kw = G.mp.P.key_words;
     return fetch_result(O.tot + J.set, reinterpret_cast<const uint64_t*>(O.kmers) + f0 * kw, O.counts + f0,
                         O.hist + (u64)J.set * G.mp.hist_len, f1 - f0, G.mp.hist_len, kw, b->origin, out, &G.tot[J.set],
