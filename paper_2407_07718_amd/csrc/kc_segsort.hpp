@@ -30,11 +30,14 @@ __device__ __forceinline__ u32 key_field(k128 k, int sh, int nb) {
 constexpr u32 MSD_NB = 1024;   // blocks of the coarse pass at most
 
 // The leading 32 bits of a key of nbits bits (fewer bits: moved up).
-__device__ __forceinline__ u32 key_top32(u64 k, int nbits) {
+__host__ __device__ __forceinline__ u32 key_top32(u64 k, int nbits) {
   return nbits >= 32 ? (u32)(k >> (nbits - 32)) : (u32)k << (32 - nbits);
 }
-__device__ __forceinline__ u32 key_top32(k128 k, int nbits) {   // nbits >= 64
+// (wide keys, set << 2k | k-mer, may have as few bits as a set and a base)
+__host__ __device__ __forceinline__ u32 key_top32(k128 k, int nbits) {
   const int sh = nbits - 32;
+  if (sh < 0) return (u32)k.lo << -sh;
+  if (sh <= 32) return (u32)(k.lo >> sh);
   return sh >= 64 ? (u32)(k.hi >> (sh - 64)) : (u32)(k.lo >> sh) | (u32)(k.hi << (64 - sh));
 }
 // Where a key falls among all keys, as a 32-bit fraction that never decreases with the key.
@@ -43,9 +46,9 @@ __device__ __forceinline__ u32 key_top32(k128 k, int nbits) {   // nbits >= 64
 // evenly over ranges and bins (split by their leading bits the first ranges hold twice the
 // mean, which a third of the blocks then waits for).  Wide keys start with the set: as they are.
 template <typename K>
-__device__ __forceinline__ u32 key_place(K k, int nbits, int canonical) {
+__host__ __device__ __forceinline__ u32 key_place(K k, int nbits, int canonical) {
   const u32 t = key_top32(k, nbits);
-  return canonical ? ~__umulhi(~t, ~t) : t;
+  return canonical ? ~(u32)(((u64)~t * ~t) >> 32) : t;
 }
 
 // Survivors where the count left them: bucket i's s_cnt[i] at s_base[i] of (s_k, s_c).
