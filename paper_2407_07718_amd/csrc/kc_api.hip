@@ -104,6 +104,8 @@ struct Plan {
   // pool of pool_cap pairs, sorted by key at the end.  max_rounds rounds are enqueued.
   u32 rounds = 1, max_rounds = 1;
   u64 cap_k = 0, cap_r = 0, pool_cap = 0;
+  u64 min_round = 0;     // k-mers that a round holds at least
+  int log_b_min = 1;     // buckets (log2) that a small budget makes do with
   u64 o_hrec = 0, o_hkm = 0, o_gsum = 0, o_rng = 0, o_bbase = 0, o_bcnt_r = 0, o_pool = 0, o_pmid = 0;
 };
 
@@ -275,7 +277,23 @@ int even_log_b(u64 n_max, u64 slots) {
   return std::min(lb, few);
 }
 
+// Segments of at most seg_wave_cap pairs are sorted by one wave each (k_seg_wave); the
+// survivors' key ranges aim below that on average so that nearly all of them are (ranges by
+// powers of two average between half the target and the target).
+template <typename K> constexpr u32 seg_wave_cap() { return sizeof(K) == 8 ? 768u : 448u; }
+template <typename K> constexpr u32 seg_range_target() { return seg_wave_cap<K>() - (sizeof(K) == 8 ? 112u : 80u); }
+
 void plan_layout(Plan* p);
+
+// 2^log_b buckets, in regions for 2^log_b_cap.
+void plan_buckets(Plan* p, int log_b, int log_b_cap) {
+  p->log_b = log_b;
+  p->B = 1u << log_b;
+  p->log_c = std::min(9, log_b);
+  p->log_f = log_b - p->log_c;
+  p->B_cap = 1u << log_b_cap;
+  p->log_c_cap = std::min(9, log_b_cap);
+}
 
 bool make_plan(u64 R, u64 n_reads, u64 n_max, int k, int m, uint32_t min_freq, const kc_config* cfg,
                Plan* p) {
@@ -302,13 +320,15 @@ bool make_plan(u64 R, u64 n_reads, u64 n_max, int k, int m, uint32_t min_freq, c
   } else {
     p->log_b = m >= 9 ? even_log_b(n_max, slots) : auto_log_b(n_max, slots);
   }
-  p->B = 1u << p->log_b;
   // (the workspace may not depend on m, see below)
   const int log_b_cap = cfg && cfg->log2_buckets ? p->log_b : auto_log_b(n_max, slots);
-  p->B_cap = 1u << log_b_cap;
-  p->log_c_cap = std::min(9, log_b_cap);
-  p->log_c = std::min(9, p->log_b);
-  p->log_f = p->log_b - p->log_c;
+  plan_buckets(p, p->log_b, log_b_cap);
+  p->min_round = 16ull * (cfg && cfg->small_variant ? slots : 2048u);
+  p->log_b_min = log_b_cap;
+  if (!(cfg && cfg->log2_buckets)) {
+    const u64 most = hash_slots(p->key_words, p->variant == 3 ? 1u : p->variant) / 3;
+    for (p->log_b_min = 1; p->log_b_min < log_b_cap && (n_max >> p->log_b_min) > most;) ++p->log_b_min;
+  }
   p->rec_cap = std::max<u64>(1, n_max);
   // each wave span of the extract stage covers `span` k-mer positions, 64 * tiles - (w - 1):
   // 16 tiles of 64 m-mer positions, or fewer (at least 4) for small inputs so that there
@@ -337,6 +357,13 @@ bool make_plan(u64 R, u64 n_reads, u64 n_max, int k, int m, uint32_t min_freq, c
   p->rounds = 1;
   plan_layout(p);
   return true;
+}
+
+// Key ranges that up to n survivors are split into: with the smaller of the two key types' targets,
+// as several sets' survivors may be sorted as wide keys.  (A table for 2^18 ranges, whatever n,
+// made the smallest workspaces, and so the smallest budgets, 1.5 MB larger.)
+u64 max_ranges(u64 n) {
+  return 256ull << msd_g2(n, std::min(seg_range_target<u64>(), seg_range_target<k128>()));
 }
 
 // Byte offsets of every region.  One pass: regions sized for all k-mers.  Rounds: regions
@@ -391,7 +418,7 @@ void plan_layout(Plan* p) {
   p->o_scanbuf = take(8ull * 1024);
   p->o_phist = take(4ull * ((u64)1 << p->log_c_cap) * p->nblk_cap);
   p->o_lch0 = take(4ull * p->B_cap);
-  p->o_seg = take(8ull * (std::max<u64>(p->B_cap, (u64)256 << MSD_G2_MAX) + 2));
+  p->o_seg = take(8ull * (max_ranges(rounds ? std::max<u64>(1, p->pool_cap) : n_k) + 2));
   p->o_mhist = take(4ull * 256 * MSD_NB);
   if (rounds) {
     const u64 C = 1ull << p->log_c_cap;
@@ -412,29 +439,26 @@ void plan_layout(Plan* p) {
 // regions of a (k-mer, count) pair, which the key-range split of the pool uses as its second
 // buffer afterwards): each round costs a pass over the reads, so they are as
 // large as fits (200 Mbp at 10 bytes per base: 7 instead of the 10 that half the budget gave,
-// 9.2 ms instead of 12.1).  False when half of it cannot hold a round of at least 16 on-chip
-// chunks.
-bool plan_rounds(Plan* p, u64 budget) {
+// 9.2 ms instead of 12.1).  False when half of it cannot hold a round of min_round k-mers.
+bool plan_rounds_at(Plan* p, u64 budget, int log_b) {
   const u64 w = 8ull * p->key_words, rb = 4ull * p->rec_words;
   const u64 per_k = 3 * (w + 4), per_pool = w + 4;
-  p->B = p->B_cap;   // (more coarse groups to fill rounds with)
-  p->log_b = __builtin_ctz(p->B_cap);
-  p->log_c = p->log_c_cap;
-  p->log_f = p->log_b - p->log_c;
-  Plan q = *p;
+  Plan base = *p;
+  plan_buckets(&base, log_b, log_b);
+  Plan q = base;
   q.rounds = 2;
   q.cap_k = q.cap_r = 1;
   q.pool_cap = 1;
   q.max_rounds = 1;
   plan_layout(&q);
-  const u64 min_cap = 16ull * 2048;
+  const u64 min_cap = p->min_round;
   if (budget <= q.bytes + 1024 * 1024) return false;
   const u64 free_b = budget - q.bytes - 1024 * 1024;   // (slack for alignment and the round table)
   const u64 pool = std::max<u64>(1, std::min<u64>(p->n_max + 1, free_b / 4 / per_pool));
   if ((free_b - std::min(free_b, 2 * pool * per_pool)) / (per_k + 4) < min_cap) return false;
   u64 cap = (free_b - std::min(free_b, pool * per_pool)) / per_k;
   for (; cap >= min_cap; cap -= std::max<u64>(1, cap / 64)) {
-    q = *p;
+    q = base;
     q.rounds = 2;
     q.cap_k = cap;
     q.cap_r = cap * (w + 4) / rb;   // records of a round fit the regions sized for its k-mers
@@ -446,6 +470,24 @@ bool plan_rounds(Plan* p, u64 budget) {
       return true;
     }
   }
+  return false;
+}
+// One pass with fewer buckets, or rounds, with as many buckets as one pass could have (the more
+// coarse groups, the better they fill the rounds) or as few as log_b_min, where the tables of more
+// leave too little of a small budget.
+bool plan_budget(Plan* p, u64 budget) {
+  const int most = __builtin_ctz(p->B_cap);
+  for (int log_b = most - 1; log_b >= p->log_b_min; --log_b) {
+    Plan q = *p;
+    plan_buckets(&q, std::min(log_b, p->log_b), log_b);
+    plan_layout(&q);
+    if (q.bytes <= budget) {
+      *p = q;
+      return true;
+    }
+  }
+  for (int log_b = most; log_b >= p->log_b_min; --log_b)
+    if (plan_rounds_at(p, budget, log_b)) return true;
   return false;
 }
 
@@ -463,7 +505,7 @@ const char* rounds_failure(u64 flags) {
 int fit_budget(Plan* p, const kc_config* cfg) {
   const u64 budget = cfg ? cfg->hbm_budget : 0;
   if (!budget || p->bytes <= budget) return KC_OK;
-  if (plan_rounds(p, budget)) return KC_OK;
+  if (plan_budget(p, budget)) return KC_OK;
   return fail(KC_ENOMEM, "no plan fits a workspace budget of %llu bytes (one pass needs %llu)",
               (unsigned long long)budget, (unsigned long long)p->bytes);
 }
@@ -580,15 +622,10 @@ inline dim3 grid_for(u64 n, u32 block, u32 max_blocks = 1u << 20) {
 // Queue one full count on `st`.
 constexpr int SEG_T = 512;                                    // threads of k_seg_sort ...
 constexpr u32 SEG_CAP_64 = SEG_T * 8, SEG_CAP_128 = SEG_T * 4;   // ... and pairs sorted on chip per segment
-// Segments of at most seg_wave_cap pairs are sorted by one wave each (k_seg_wave); the
-// survivors' key ranges aim below that on average so that nearly all of them are (ranges by
-// powers of two average between half the target and the target).
-template <typename K> constexpr u32 seg_wave_cap() { return sizeof(K) == 8 ? 768u : 448u; }
-template <typename K> constexpr u32 seg_range_target() { return seg_wave_cap<K>() - (sizeof(K) == 8 ? 112u : 80u); }
 
 // max_seg: a host-side bound on the number of segments (the grids need no more blocks).
 template <typename K>
-int seg_sort(K* keys, u32* vals, K* tmp_k, u32* tmp_v, K* out_k, u32* out_v, u64 out_cap, const u64* seg,
+int seg_sort(K* keys, u32* vals, K* tmp_k, u32* tmp_v, K* out_k, u32* out_v, u64 out_cap, u64* seg,
              const u64* n_seg, u64 max_seg, int nbits, bool canonical, const u64* msd_n, u32 msd_target, int n_cu,
              hipStream_t st, int* grid) {
   constexpr int IT = sizeof(K) == 8 ? 8 : 4;
@@ -971,10 +1008,10 @@ int sort_survivors(const Plan& P, const Ws<K>& W, K* in_k, u32* in_c, K* mid_k, 
   }
   hipLaunchKernelGGL((k_msd_fine<K>), dim3(256), dim3(1024), 0, st, ma);
   // the key ranges number 256 << g2, g2 growing with the survivor count (at most n_cap)
-  const u64 max_ranges = 256ull << msd_g2(n_cap, seg_range_target<K>());
+  const u64 ranges = 256ull << msd_g2(n_cap, seg_range_target<K>());
   int seg_grid = 0;
   return seg_sort<K>(in_k, in_c, mid_k, mid_c, reinterpret_cast<K*>(d_kmers), d_counts, pair_cap, W.seg,
-                     W.ctrl + C_NSEG, max_ranges, nbits, key_bits == 0, n_ptr, seg_range_target<K>(), n_cu, st, &seg_grid);
+                     W.ctrl + C_NSEG, ranges, nbits, key_bits == 0, n_ptr, seg_range_target<K>(), n_cu, st, &seg_grid);
 }
 
 template <typename K>
