@@ -8,8 +8,9 @@
 // A segment that fits on chip is sorted there in one read and one write, by one digit of about
 // log2(length) bits and a ranking inside the digit's bin: keys of a segment spread over the
 // bins, so a bin holds one or two keys and each key's rank is its bin's start plus the smaller
-// keys of its bin.  A longer segment is sorted by its block through HBM (stable LSD passes
-// over LDS tiles).
+// keys of its bin.  Where a bin holds more than SEG_BIN_MAX (keys that share their leading 32 bits:
+// reads with a primer or an insert in common), a block sorts the segment by LSD passes in LDS.  A
+// longer segment is sorted by its block through HBM (stable LSD passes over LDS tiles).
 #pragma once
 #include "kc_common.hpp"
 #include "kc_count.hpp"
@@ -93,7 +94,7 @@ struct SegArgs {
   void* out_k;             // sorted output (may equal keys); positions >= out_cap are dropped
   u32* out_v;
   u64 out_cap;
-  const u64* seg;          // segment i = [seg[i], seg[i + 1])
+  u64* seg;                // segment i = [seg[i], seg[i + 1]); SEG_CROWDED: left to k_seg_sort
   const u64* n_seg_ptr;    // number of segments
   int nbits;               // key bits (2k)
   int canonical;           // see key_place
@@ -101,6 +102,13 @@ struct SegArgs {
   u32 msd_target;
   u32 wave_cap;            // segments of at most this many pairs are left to k_seg_wave
 };
+
+// A ranking compares each key with its whole bin.  60,000 reads of 150 bases with one of 20 inserts of
+// 100 bases (795,000 k-mers of 31 bases, 500 and more of which share 16): 4.26 ms for the output of
+// all k-mers where any bin is ranked, 0.44 by LSD passes in LDS alone, 0.68 with this limit.
+constexpr u32 SEG_BIN_MAX = 64;
+constexpr u64 SEG_CROWDED = 1ull << 63;   // set in a segment's start by k_seg_wave
+__device__ __forceinline__ u64 seg_start(const SegArgs& A, u64 i) { return A.seg[i] & ~SEG_CROWDED; }
 
 // Bits of the keys' places that a segment's keys share: those of its range.
 __device__ __forceinline__ int seg_place_bits(const SegArgs& A) {
@@ -145,9 +153,10 @@ struct SegSmem {
 };
 
 // The block's m pairs (kr, vr; thread t holds pairs t, t + T, ...) sorted into S.keys and
-// S.b.vals by bin(key), below 2^db, then by key.  db: 2^db of at least T and m.
-template <int T, int ITEMS, typename K, typename SM, typename Bin>
-__device__ __forceinline__ void seg_sort_chip(SM& S, u32 m, int db, const K (&kr)[ITEMS], const u32 (&vr)[ITEMS], Bin bin) {
+// S.b.vals by bin(key), below 2^db, then by key.  db: 2^db of at least T and m.  With CHECK false,
+// and nothing done, where a bin holds more than SEG_BIN_MAX.
+template <int T, int ITEMS, bool CHECK, typename K, typename SM, typename Bin>
+__device__ __forceinline__ bool seg_sort_chip(SM& S, u32 m, int db, const K (&kr)[ITEMS], const u32 (&vr)[ITEMS], Bin bin) {
   const u32 tid = threadIdx.x, per = (1u << db) / T;   // bins per thread
   for (u32 i = tid; i < 1u << db; i += T) S.b.bins[i] = 0;
   __syncthreads();
@@ -156,6 +165,7 @@ __device__ __forceinline__ void seg_sort_chip(SM& S, u32 m, int db, const K (&kr
   for (int j = 0; j < ITEMS; ++j)
     if (tid + (u32)j * T < m) rk[j] = atomicAdd(&S.b.bins[bin(kr[j])], 1u);
   __syncthreads();
+  u32 most = 0;
   {
     u64 sum = 0, tot;
     for (u32 q = 0; q < per; ++q) sum += S.b.bins[tid * per + q];
@@ -164,10 +174,15 @@ __device__ __forceinline__ void seg_sort_chip(SM& S, u32 m, int db, const K (&kr
       const u32 c = S.b.bins[tid * per + q];
       S.b.bins[tid * per + q] = run;
       run += c;
+      if constexpr (CHECK) most = max(most, c);
     }
     if (tid == 0) S.b.bins[1u << db] = m;
   }
-  __syncthreads();
+  if constexpr (CHECK) {
+    if (__syncthreads_or(most > SEG_BIN_MAX)) return false;
+  } else {
+    __syncthreads();
+  }
 #pragma unroll
   for (int j = 0; j < ITEMS; ++j)
     if (tid + (u32)j * T < m) {
@@ -189,6 +204,7 @@ __device__ __forceinline__ void seg_sort_chip(SM& S, u32 m, int db, const K (&kr
       S.b.vals[rk[j]] = vr[j];
     }
   __syncthreads();
+  return true;
 }
 
 // A segment [s0, s0 + n) longer than a block holds: stable LSD passes through HBM, ping-pong
@@ -265,8 +281,9 @@ __device__ __forceinline__ void seg_sort_long(SM& S, K*& src_k, u32*& src_v, K*&
   }
 }
 
+// (128-bit keys: LDS holds two blocks per CU, so the registers have to)
 template <typename K, int T, int ITEMS>
-__global__ __launch_bounds__(T) void k_seg_sort(SegArgs A) {
+__global__ __launch_bounds__(T, sizeof(K) == 16 ? 4 : 2) void k_seg_sort(SegArgs A) {
   using SM = SegSmem<K, T, ITEMS>;
   constexpr u32 CAP = SM::CAP;
   __shared__ SM S;
@@ -283,18 +300,23 @@ __global__ __launch_bounds__(T) void k_seg_sort(SegArgs A) {
    __syncthreads();
    {
     const u64 sgi = c0 + (u64)tid * gridDim.x;
-    if (sgi < n_seg && A.seg[sgi + 1] > A.seg[sgi] + A.wave_cap) S.lng[atomicAdd(&S.n_long, 1u)] = (u16)tid;
+    if (sgi < n_seg && (A.seg[sgi] >= SEG_CROWDED || seg_start(A, sgi + 1) > seg_start(A, sgi) + A.wave_cap))
+      S.lng[atomicAdd(&S.n_long, 1u)] = (u16)tid;
    }
    __syncthreads();
    const u32 n_long = S.n_long;
+   // those that a block holds, where their bins allow it; the others stay in the list (in two loops:
+   // in one the registers of both would halve the blocks per CU)
+   u32 rest = 0;
    for (u32 li = 0; li < n_long; ++li) {
-    const u64 sgi = c0 + (u64)S.lng[li] * gridDim.x;
-    const u64 s0 = A.seg[sgi], s1 = A.seg[sgi + 1];
-    const u64 n = s1 - s0;
+    const u32 at = S.lng[li];
+    const u64 sgi = c0 + (u64)at * gridDim.x;
+    const u64 s0 = seg_start(A, sgi), n = seg_start(A, sgi + 1) - s0;
     __syncthreads();                             // LDS of the previous segment is free
-    if (n <= CAP) {
+    bool done = false;
+    if (n <= CAP && A.seg[sgi] < SEG_CROWDED) {
       const u32 m = (u32)n;
-      const int db = seg_bin_bits(m);              // (m > wave_cap >= T: at least T bins)
+      const int db = max(__builtin_ctz(T), seg_bin_bits(m));
       K kr[ITEMS];
       u32 vr[ITEMS];
 #pragma unroll
@@ -303,7 +325,32 @@ __global__ __launch_bounds__(T) void k_seg_sort(SegArgs A) {
         kr[j] = i < m ? in_k[s0 + i] : key_zero<K>();
         vr[j] = i < m ? A.vals[s0 + i] : 0u;
       }
-      seg_sort_chip<T, ITEMS>(S, m, db, kr, vr, [&](K k) { return seg_bin(A, k, pbits, db); });
+      done = seg_sort_chip<T, ITEMS, true>(S, m, db, kr, vr, [&](K k) { return seg_bin(A, k, pbits, db); });
+      for (u32 i = tid; done && i < m; i += T) {
+        if (s0 + i < A.out_cap) {
+          out_k[s0 + i] = S.keys[i];
+          A.out_v[s0 + i] = S.b.vals[i];
+        }
+      }
+    }
+    if (!done) {
+      if (tid == 0) S.lng[rest] = (u16)at;
+      ++rest;
+    }
+   }
+   for (u32 li = 0; li < rest; ++li) {
+    __syncthreads();
+    const u64 sgi = c0 + (u64)S.lng[li] * gridDim.x;
+    const u64 s0 = seg_start(A, sgi), n = seg_start(A, sgi + 1) - s0;
+    if (n <= CAP) {
+      constexpr u32 WB = 64u * (T / 64);
+      const u32 m = (u32)n, m_pad = (m + WB - 1) / WB * WB;
+      for (u32 i = tid; i < m_pad; i += T) {
+        S.keys[i] = i < m ? in_k[s0 + i] : key_pad<K>();
+        S.b.vals[i] = i < m ? A.vals[s0 + i] : 0u;
+      }
+      __syncthreads();
+      lds_sort_passes<K, T, ITEMS, true>(S.keys, S.b.vals, S.tbl, S.cnt, S.gtot, m_pad, 0, (A.nbits + 7) / 8, true);
       for (u32 i = tid; i < m; i += T) {
         if (s0 + i < A.out_cap) {
           out_k[s0 + i] = S.keys[i];
@@ -442,7 +489,8 @@ __global__ __launch_bounds__(T) void k_merge_lists(MergeArgs M) {
         vr[j] = i < m ? S.b.vals[i] : 0u;
       }
       __syncthreads();
-      seg_sort_chip<T, ITEMS>(S, m, db, kr, vr, [&](K k) { return key_field(mix_key(k), 0, db); });
+      // (bins of mixed keys: a crowded one holds copies of one k-mer, from that many chunks)
+      seg_sort_chip<T, ITEMS, false>(S, m, db, kr, vr, [&](K k) { return key_field(mix_key(k), 0, db); });
     } else {
       K* dst_k = reinterpret_cast<K*>(M.k1);
       u32* dst_v = M.v1;
@@ -546,7 +594,7 @@ struct SegWaveSmem {
 };
 
 // Waves take segments in turn (segment = global wave index, + all waves of the grid, ...);
-// a segment longer than WCAP is left to k_seg_sort.
+// a segment longer than WCAP, or with a crowded bin, is left to k_seg_sort.
 template <typename K, int WCAP, int WPB>
 __global__ __launch_bounds__(WPB * 64) void k_seg_wave(SegArgs A) {
   constexpr int ITEMS = WCAP / 64;
@@ -558,7 +606,7 @@ __global__ __launch_bounds__(WPB * 64) void k_seg_wave(SegArgs A) {
   const K* in_k = reinterpret_cast<const K*>(A.keys);
   K* out_k = reinterpret_cast<K*>(A.out_k);
   for (u64 sgi = (u64)blockIdx.x * WPB + wave; sgi < n_seg; sgi += (u64)gridDim.x * WPB) {
-    const u64 s0 = uniform(A.seg[sgi]), s1 = uniform(A.seg[sgi + 1]);
+    const u64 s0 = uniform(seg_start(A, sgi)), s1 = uniform(seg_start(A, sgi + 1));
     if (s1 <= s0 || s1 - s0 > WCAP) continue;    // uniform over the wave
     const u32 m = (u32)(s1 - s0), rows = (m + 63) / 64;
     const int db = seg_bin_bits(m);
@@ -579,6 +627,7 @@ __global__ __launch_bounds__(WPB * 64) void k_seg_wave(SegArgs A) {
     for (int j = 0; j < ITEMS; ++j)
       if ((u32)j < rows && (u32)j * 64 + lane < m) rk[j] = atomicAdd(&S.b.bins[seg_bin(A, kr[j], pbits, db)], 1u);
     __builtin_amdgcn_wave_barrier();
+    u32 most = 0;
     {
       u32 sum = 0;
       for (u32 q = 0; q < per; ++q) sum += S.b.bins[lane * per + q];
@@ -587,10 +636,15 @@ __global__ __launch_bounds__(WPB * 64) void k_seg_wave(SegArgs A) {
         const u32 c = S.b.bins[lane * per + q];
         S.b.bins[lane * per + q] = run;
         run += c;
+        most = max(most, c);
       }
       if (lane == 0) S.b.bins[1u << db] = m;
     }
     __builtin_amdgcn_wave_barrier();
+    if (__any(most > SEG_BIN_MAX)) {             // (uniform; other waves may read the start just now)
+      if (lane == 0) atomicOr((unsigned long long*)&A.seg[sgi], (unsigned long long)SEG_CROWDED);
+      continue;
+    }
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j)
       if ((u32)j < rows && (u32)j * 64 + lane < m) {
