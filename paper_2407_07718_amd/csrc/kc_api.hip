@@ -968,7 +968,7 @@ int count_buckets(const Plan& P, const Ws<K>& W, const u32* blk_base, uint32_t l
 // The survivors of a one-pass count where count_buckets left them.
 template <typename K>
 SurvSegs surv_segs(const Plan& P, const Ws<K>& W) {
-  return SurvSegs{W.s0k, W.s0c, W.kall, W.scnt, P.B};
+  return SurvSegs{W.s0k, W.s0c, W.kall, W.scnt, P.B, W.meta};
 }
 
 // Survivors in[0, *n_ptr) (their count at most n_cap) -> split into key ranges by their

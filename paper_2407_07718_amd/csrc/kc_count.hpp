@@ -731,6 +731,14 @@ __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A,
         load_records(I.ra, I.rb);
         continue;
       }
+      // (lanes of the first wave: the item's buckets' first k-mer slots and k-mers)
+      u32 place = 0, size = 0;
+      if constexpr (!CHUNKS) {
+        if (wave == 0 && lane < (merge ? I.after - item : 1u)) {
+          place = (u32)(A.kall_off[item + lane] - base);
+          size = (u32)A.bcnt[item + lane];
+        }
+      }
       // each wave lists the occupied slots of its rows, then counts, reports and frees them
       u16* const list = reinterpret_cast<u16*>(&H);
       u32 dist = 0;
@@ -778,7 +786,16 @@ __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A,
       if (lane == 0) atomicAdd(&S.dist[parity], dist);
       if (tid == 0) S.dist[parity ^ 1] = 0;
       __syncthreads();
-      if (!next_class(cls)) break;
+      if (!next_class(cls)) {
+        // each bucket of the item gets what lies at its own slots (the next item adds to S.kept
+        // after its first barrier)
+        if (!CHUNKS && wave == 0) {
+          const u32 kept = S.kept;
+          if (lane < (merge ? I.after - item : 1u)) A.surv_cnt[item + lane] = min(max(kept, place) - place, size);
+          if (lane == 0) S.kept = 0;
+        }
+        break;
+      }
       load_records(I.ra, I.rb);
     }
     // what this item teaches: the class depth to start with, and how many k-mers fill about a
@@ -787,8 +804,8 @@ __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A,
     parity ^= 1;
     learned = deepest && (d >> deepest) <= SLOTS / 4 ? deepest - 1 : deepest;
     if (merge) room = (u32)min((float)cap, (float)n * (SLOTS / 4) / (float)max(d, 1u));
-    if (tid == 0) {   // (the next item adds to S.kept after its first barrier)
-      (CHUNKS ? A.kl_cnt : A.surv_cnt)[item] = S.kept;
+    if (CHUNKS && tid == 0) {   // (the next item adds to S.kept after its first barrier)
+      A.kl_cnt[item] = S.kept;
       S.kept = 0;
     }
   };

@@ -52,13 +52,15 @@ __host__ __device__ __forceinline__ u32 key_place(K k, int nbits, int canonical)
   return canonical ? ~(u32)(((u64)~t * ~t) >> 32) : t;
 }
 
-// Survivors where the count left them: bucket i's s_cnt[i] at s_base[i] of (s_k, s_c).
+// Survivors where the count left them: bucket i's s_cnt[i] from its first k-mer slot s_base[i] of
+// (s_k, s_c) on, at most as many as it has slots (see plan_meta for `meta`).
 struct SurvSegs {
   const void* s_k;
   const u32* s_c;
   const u64* s_base;
   const u32* s_cnt;
   u32 n_buckets;
+  const u64* meta;
 };
 struct MsdArgs {
   const void* in_k;        // dense survivors ...
@@ -684,38 +686,54 @@ __global__ __launch_bounds__(WPB * 64) void k_seg_wave(SegArgs A) {
 // table in key order.
 //
 // The coarse pass of a one-pass count reads the survivors from where the count left them: a
-// block takes an equal share of the buckets, its waves their segments in turn, one row of up to 64 at a time.  (Gathered into one dense array first, 1 Gbp with 43 M
-// survivors took 13.19 ms instead of 12.87, 60 Mbp with 20 M 1.76 instead of 1.65, and every
-// count five launches more.)
+// block takes an equal share of the k-mer slots and so does each of its waves, whatever the buckets'
+// sizes, and reads their segments in turn, one row of up to 64 at a time.  (Gathered into one dense
+// array first, 1 Gbp with 43 M survivors took 13.19 ms instead of 12.87, 60 Mbp with 20 M 1.76 instead
+// of 1.65, and every count five launches more.  With shares by buckets, a wave reads a long segment
+// alone: 300 kbp in one bucket (minimizers of one base) had an output stage of 1.94 ms, 0.08 so.)
 template <typename K, u32 NW>
 struct SegRows {
   const SurvSegs& V;
-  u32 b0, n;           // the block's buckets [b0, b0 + n)
-  u32 i0;              // the wave's current 64 buckets: i0 + NW * lane
-  u32 c;               // lane: its bucket's survivors ...
-  u64 base;            // ... and place
+  u64 w0, w1;          // the wave's slots
+  u32 i0;              // its current 64 buckets: i0 + lane
+  u32 c;               // lane: its bucket's survivors in these slots ...
+  u64 base;            // ... and the first one's slot
   u64 left;            // lanes whose buckets are still to do
   u32 off;             // done of the first of them
+  bool last;           // no buckets after these
 
   __device__ __forceinline__ SegRows(const SurvSegs& v, u32 n_blk) : V(v) {
-    const u32 per = (v.n_buckets + n_blk - 1) / n_blk;
-    b0 = min(v.n_buckets, blockIdx.x * per);
-    n = min(v.n_buckets - b0, per);
-    i0 = uniform(threadIdx.x >> 6);
+    const u64 n = uniform(v.meta[2] + v.meta[6] + v.meta[7]);   // k-mer slots
+    const u64 per = (n + n_blk - 1) / n_blk, per_w = (per + NW - 1) / NW;
+    const u64 b0 = min(n, blockIdx.x * per), b1 = min(n, b0 + per);
+    w0 = min(b1, b0 + uniform(threadIdx.x >> 6) * per_w);
+    w1 = min(b1, w0 + per_w);
+    // the last bucket that starts at or before w0: 64 probes at a time
+    u32 lo = 0, hi = v.n_buckets;
+    while (hi - lo > 1) {
+      const u32 step = (hi - lo + 63) / 64, i = lo + lane_id() * step;
+      const u32 at = 63u - (u32)__clzll(__ballot(lane_id() == 0 || (i < hi && v.s_base[i] <= w0)));
+      lo += at * step;
+      hi = min(hi, lo + step);
+    }
+    i0 = lo;
     load();
   }
   __device__ __forceinline__ void load() {
-    const u32 i = i0 + NW * lane_id();
-    c = i < n ? V.s_cnt[b0 + i] : 0u;
-    base = i < n ? V.s_base[b0 + i] : 0ull;
+    const u32 i = i0 + lane_id();
+    const bool in = i < V.n_buckets;
+    const u64 s = in ? V.s_base[i] : w1, e = in ? s + V.s_cnt[i] : w1;
+    base = max(s, w0);
+    c = min(e, w1) > base ? (u32)(min(e, w1) - base) : 0u;
     left = __ballot(c != 0);
+    last = __any(s >= w1);
     off = 0;
   }
   // The next row's keys, one per lane: true where the lane has one.  (Past the last row: none.)
   __device__ __forceinline__ bool row(const K** k, const u32** v) {
     while (!left) {
-      if (i0 + 64 * NW >= n) return false;
-      i0 += 64 * NW;
+      if (last) return false;
+      i0 += 64;
       load();
     }
     const int l = __builtin_ctzll(left);
@@ -730,7 +748,7 @@ struct SegRows {
     }
     return o < cl;
   }
-  __device__ __forceinline__ bool done() const { return !left && i0 + 64 * NW >= n; }
+  __device__ __forceinline__ bool done() const { return !left && last; }
 };
 
 template <typename K, bool SEGS>
