@@ -719,13 +719,20 @@ struct SegRows {
     i0 = lo;
     load();
   }
+  // Buckets whose slots are full up to the next one's (those counted together, but the last of them)
+  // are one segment with it: the lane of the first holds it.
   __device__ __forceinline__ void load() {
     const u32 i = i0 + lane_id();
     const bool in = i < V.n_buckets;
     const u64 s = in ? V.s_base[i] : w1, e = in ? s + V.s_cnt[i] : w1;
-    base = max(s, w0);
-    c = min(e, w1) > base ? (u32)(min(e, w1) - base) : 0u;
-    left = __ballot(c != 0);
+    base = min(max(s, w0), w1);
+    const u64 end = min(max(e, w0), w1);
+    const u64 pe = ((u64)lane_prev((u32)(end >> 32), ~0u) << 32) | lane_prev((u32)end, ~0u);
+    const u64 goes_on = __ballot(base == pe);     // (never of lane 0)
+    const u64 after = lane_id() == 63 ? 0ull : goes_on >> (lane_id() + 1);
+    const int l = (int)lane_id() + __builtin_ctzll(~after);
+    c = (u32)(__shfl((unsigned long long)end, l, 64) - base);
+    left = __ballot(c != 0) & ~goes_on;
     last = __any(s >= w1);
     off = 0;
   }
