@@ -143,14 +143,15 @@ def kernel_roofline(dom: str, per: dict, tot: dict, k: int, traffic) -> dict:
     n_win = max(1, tot["n_windows"])
     s_avg = rb * tot["n_records"] / n_win          # record bytes per k-mer
     surv = tot["n_pairs"]
-    # (the stage names are those of the profile's slots: the chunks' and the buckets' count)
+    # (the stage names are those of the profile's slots: the buckets' count, and the chunks' with the
+    # classes of the buckets that the first left over)
     name = {"extract": "k_extract", "block_sort": "k_hash_count", "wave_sort": "k_hash_count"}[dom]
     if dom == "extract":
         # 2-bit bases + invalid-base mask + cut mask read once (0.5 B per base), records
         # written once
         algo = 0.5 * tot["bases"] + rb * tot["n_records"]
         basis = "0.5 B per base read + one record write"
-    elif dom == "block_sort":
+    elif dom == "wave_sort":
         # large-bucket chunks: keys read, (k-mer, count) lists written
         algo = tot["large_keys"] * w + tot["list_entries"] * (w + 4)
         basis = "large keys x w + lists x (w+4)"

@@ -370,8 +370,8 @@ int kc_server_destroy(kc_server *s);
  *   1 extract     (minimizers, supermers into span slots)           -- one kernel
  *   2 partition   (two-pass record partition into buckets, bucket plan)
  *   3 expand      (k-mers of large buckets into HBM)                -- one kernel
- *   4 block_sort  (chunks of large buckets counted on chip)         -- one kernel
- *   5 wave_sort   (all other buckets counted on chip)               -- one kernel
+ *   4 block_sort  (all buckets but the large ones counted on chip)  -- one kernel
+ *   5 wave_sort   (chunks of large buckets, and what 4 left over)   -- one kernel
  *   6 merge       (chunk lists: compact, sort, summed runs)
  *   7 output      (survivor compaction, sort by key, copy, totals)
  * A plain count in rounds (memory-bounded) uses 1 for the count pass and the round

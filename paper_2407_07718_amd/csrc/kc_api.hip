@@ -115,6 +115,7 @@ enum Ctrl : int {
   C_META = 2,       // 8 words, see plan_meta
   C_FLAGS = 10,
   C_SURV_N = 11,
+  C_LATE = 12,      // buckets left to the count's second launch
   C_SURV_NC = 13,   // survivors, clamped to capacity
   C_KL_N = 14,      // (k-mer, count) list entries
   C_NSEG = 16,      // key ranges of the survivors
@@ -903,6 +904,8 @@ int count_buckets(const Plan& P, const Ws<K>& W, const u32* blk_base, uint32_t l
   ca.surv_k = W.s0k;           // sparse: bucket b's survivors at kall[b] + i
   ca.surv_c = W.s0c;
   ca.surv_cnt = W.scnt;
+  ca.late = W.soff;            // (free until the survivors are compacted)
+  ca.late_n = reinterpret_cast<u32*>(W.ctrl + C_LATE);
   ca.lkeys = W.lk0;
   ca.kl_k = W.s0k;             // a large bucket has no survivors there
   ca.kl_c = W.s0c;
@@ -922,18 +925,20 @@ int count_buckets(const Plan& P, const Ws<K>& W, const u32* blk_base, uint32_t l
                        ms ? md->n_buckets : P.B, P.cap);
     return KC_OK;
   };
-  auto chunks = [&](auto shape) {
+  auto rest = [&](auto shape) {
     using H = decltype(shape);
-    return hash_count(k_hash_count<K, H::T, H::SLOTS, true, false>, H::T, P.chunk_cap);
+    const u64 items = P.chunk_cap + ((u64)P.B << LATE_DEPTH);
+    return ms ? hash_count(k_hash_count<K, H::T, H::SLOTS, true, true>, H::T, items)
+              : hash_count(k_hash_count<K, H::T, H::SLOTS, true, false>, H::T, items);
   };
   auto buckets = [&](auto shape) {
     using H = decltype(shape);
     return ms ? hash_count(k_hash_count<K, H::T, H::SLOTS, false, true>, H::T, P.B)
               : hash_count(k_hash_count<K, H::T, H::SLOTS, false, false>, H::T, P.B);
   };
-  if ((rc = with_hash_shape<K>(P.variant, chunks))) return rc;
-  if (marks) stage_mark(5, st);
   if ((rc = with_hash_shape<K>(P.variant, buckets))) return rc;
+  if (marks) stage_mark(5, st);
+  if ((rc = with_hash_shape<K>(P.variant, rest))) return rc;
   if (marks) stage_mark(6, st);
   // merge the large buckets' chunks' (k-mer, count) lists
   {
@@ -1119,6 +1124,7 @@ int warm_launch_facts() {
         using H = decltype(shape);
         int r;
         if ((r = blocks_per_cu(k_hash_count<K, H::T, H::SLOTS, true, false>, H::T, &v))) return r;
+        if ((r = blocks_per_cu(k_hash_count<K, H::T, H::SLOTS, true, true>, H::T, &v))) return r;
         if ((r = blocks_per_cu(k_hash_count<K, H::T, H::SLOTS, false, true>, H::T, &v))) return r;
         return blocks_per_cu(k_hash_count<K, H::T, H::SLOTS, false, false>, H::T, &v);
       });

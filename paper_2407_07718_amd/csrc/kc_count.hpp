@@ -45,6 +45,8 @@ struct CountArgs {
   void* surv_k;            // survivors of bucket b at slots kall_off[b] + i: keys ...
   u32* surv_c;             // ... and counts
   u32* surv_cnt;           // survivors per bucket
+  u32* late;               // buckets left to the second launch: bucket | class depth << 24 ...
+  u32* late_n;             // ... and their number
   const void* lkeys;       // expanded keys of the large buckets, at their buckets' k-mer slots
   void* kl_k;              // (k-mer, count) list of chunk c at slots chunk_start[c] + i (an array of
                            // its own: a chunk counted in classes reads its keys several times)
@@ -271,7 +273,8 @@ __device__ __forceinline__ void flush_stats(const RunSink& S, u64 ndist) {
 // key has one slot whatever the order of the lanes.  After PROBES full pairs the table is
 // given up as too full, and the item is counted in two halves, by the next bit of the
 // keys' mixed images (DFS over the bits; the images are a bijection, so a class at full
-// depth holds one key).  Only the distinct keys count against the table, so an item may
+// depth holds one key), or, where that would take four passes over a bucket and more, in as many
+// classes by other blocks.  Only the distinct keys count against the table, so an item may
 // hold many times SLOTS keys.
 // One wave's scratch: the records it expands, one bit per unit of them (a unit is up to U
 // consecutive k-mers of one record, expanded by one lane) at each record's first unit, and
@@ -292,7 +295,7 @@ struct HashSmem {
   u32 cnt[SLOTS / 2];              // two 16-bit counts per word, one word per pair
   HashWave<K> w[W];
   u32 hist_s[256];
-  u32 lmax, kept, full, dist[2];   // (dist: of this item and the next)
+  u32 lmax, kept, full, seen, dist[2];   // (dist: of this item and the next)
   unsigned long long lover, ndist;
 };
 // No canonical k-mer has these words: 2k <= 62 bits for k <= 31; for k >= 32 a low word of
@@ -324,6 +327,7 @@ template <> struct HashClass<u64> {
   }
   __device__ __forceinline__ bool bit() const { return (p >> (d - 1)) & 1; }
   __device__ __forceinline__ void flip() { p ^= 1ull << (d - 1); }
+  __device__ __forceinline__ void set(u32 d_, u32 p_) { d = d_, p = p_; }
 };
 template <> struct HashClass<k128> {
   u32 d = 0;
@@ -338,15 +342,16 @@ template <> struct HashClass<k128> {
     if (d <= 64) p.lo ^= 1ull << (d - 1);
     else p.hi ^= 1ull << (d - 65);
   }
+  __device__ __forceinline__ void set(u32 d_, u32 p_) { d = d_, p = k128{p_, 0}; }
 };
-// The next class after c is counted; false when all are.
+// The next class after c, of those that share its low d0 bits; false when all are counted.
 template <typename K>
-__device__ __forceinline__ bool next_class(HashClass<K>& c) {
-  while (c.d > 0 && c.bit()) {
+__device__ __forceinline__ bool next_class(HashClass<K>& c, u32 d0) {
+  while (c.d > d0 && c.bit()) {
     c.flip();
     --c.d;
   }
-  if (c.d == 0) return false;
+  if (c.d == d0) return false;
   c.flip();
   return true;
 }
@@ -467,8 +472,9 @@ __device__ __forceinline__ void canon_two(const u32* rec, u32 o, int k, k128 (&o
   out[1] = key_lt(f1, c1) ? f1 : c1;
 }
 
-// Blocks take buckets (CHUNKS = false) or chunks of large buckets (whose keys are already
-// expanded in HBM) in turn.  A bucket's slots are final counts: statistics, and the
+// Blocks take buckets (REST = false), or in a second launch (REST) the chunks of large buckets
+// (whose keys are already expanded in HBM) and the classes of the buckets that the first one left
+// to it, in turn.  A bucket's slots are final counts: statistics, and the
 // survivors to the bucket's own k-mer slots; a chunk's are the (k-mer, count) list of its
 // slots -- the paper's kmerlist form of a heavy-hitter task (Section 3.5) -- merged later
 // through HBM.  Several read sets (MS): a contiguous range of buckets per block (they are
@@ -487,7 +493,15 @@ __device__ __forceinline__ void canon_two(const u32* rec, u32 o, int k, k128 (&o
 // Neighbouring buckets share a table while their distinct keys fill about a quarter of it,
 // which spares barriers and table scans (2^18 buckets: 4.15 -> 3.67 ms); at half full the first
 // pair misses too often (4.8 ms), at a tenth the scans show again (4.3 ms).
-template <typename K, int T, u32 SLOTS, bool CHUNKS, bool MS>
+// A bucket of more k-mers than slots whose table overflows is given up at once: the share of its
+// records that filled the table tells how many classes it takes.  Two are counted by the
+// block; four to 16 are left to the second launch, where they run side by side.  (With all classes one
+// after the other in the bucket's block: 5 Mbp at 0.7x, k = 21, minimizers of 6 bases 4.2 ms, 1.9 so;
+// 9 Mbp of reads with 80 % A and T, k = 21, minimizers of 11 bases 2.9 and 1.1.  With buckets above two
+// tables cut into chunks and merged, for any input: 2.0 and 1.9, but 400 Mbp of long reads, k = 51,
+// 7.9 instead of 6.7 ms.)
+constexpr u32 LATE_DEPTH = 4;      // classes of a bucket left over: 2^2 to 2^4
+template <typename K, int T, u32 SLOTS, bool REST, bool MS>
 __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A, u32 B, u32 cap) {
   using SM = HashSmem<K, T, SLOTS>;
   using HW = HashWave<K>;
@@ -496,6 +510,10 @@ __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A,
   static_assert(sizeof(HW) >= 2 * 64 * ROWS, "the list of a wave's occupied slots");
   __shared__ SM S;
   const u32 tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6);
+  // second launch: the chunks, then the classes, class by class over the buckets left over
+  const u32 n_chunks = REST ? (u32)A.meta[4] : 0u, n_late = REST ? *A.late_n : 0u;
+  const u32 n_rest = n_chunks + (n_late << LATE_DEPTH);
+  if (REST && blockIdx.x >= n_rest) return;
   HW& H = S.w[wave];
   auto clear_table = [&]() {
     for (u32 i = tid; i < SLOTS; i += T) {
@@ -513,6 +531,7 @@ __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A,
     S.ndist = 0;
     S.kept = 0;
     S.full = 0;
+    S.seen = 0;
     S.dist[0] = S.dist[1] = 0;
   }
   // the marks hold 1,024 units: records of up to 32 k-mers RECS at a time, longer ones 24
@@ -524,7 +543,7 @@ __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A,
   // Many buckets per block: consecutive ones are counted together while they fit.  (Equal
   // k-mers share a bucket, and the records and k-mer slots of neighbouring buckets adjoin.)
   const u32 b0 = A.rng ? A.rng[0] << A.log_f : 0u, nb = (A.rng ? A.rng[1] << A.log_f : B) - b0;
-  const bool merge = !CHUNKS && nb >= 8 * gridDim.x;
+  const bool merge = !REST && nb >= 8 * gridDim.x;
   const u32 stride = MS || merge ? 1u : gridDim.x;
   u32 room = 0, parity = 0;
   u32 learned = 0;   // class depth that the last full item ended at
@@ -540,8 +559,7 @@ __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A,
     u64 base;
     u32 n, ra, rb, after;
   };
-  // The plan's figures of the buckets from b on, one bucket per lane (a chunk's in lane 0),
-  // loaded an item ahead.
+  // The plan's figures of the buckets from b on, one bucket per lane, loaded an item ahead.
   struct Ahead {
     u64 c, ko;
     u32 ro, st;
@@ -550,15 +568,10 @@ __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A,
     Ahead R{0, 0, 0, 0};
     if (b < end) {
       const u32 i = merge ? min(b + lane, end - 1) : b;
-      if constexpr (CHUNKS) {
-        R.ko = A.chunk_start[i];
-        R.c = A.chunk_len[i];
-      } else {
-        R.c = A.bcnt[i];
-        R.ko = A.kall_off[i];
-        R.ro = A.rec_off[i];
-        if constexpr (MS) R.st = A.bset[i];
-      }
+      R.c = A.bcnt[i];
+      R.ko = A.kall_off[i];
+      R.ro = A.rec_off[i];
+      if constexpr (MS) R.st = A.bset[i];
     }
     return R;
   };
@@ -570,20 +583,18 @@ __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A,
     const u32 nk = (u32)R.c, nr = (u32)(R.c >> 32);
     I.base = uniform(R.ko);
     I.n = uniform(nk);
-    if constexpr (!CHUNKS) {
-      u32 m = 1;
-      if (merge) {
-        const bool fits =
-            b + lane < end && nk <= cap && R.ko + nk - I.base <= room && (!MS || R.st == uniform(R.st));
-        m = max(1u, (u32)__builtin_ctzll(~__ballot(fits) | (1ull << 63)));
-        I.after = b + m;
-      }
-      const u32 r0 = uniform(R.ro), r1 = lane_read(R.ro + nr, (int)m - 1), per = (r1 - r0 + W - 1) / W;
-      I.n = I.n > cap ? 0u : lane_read((u32)(R.ko - I.base) + nk, (int)m - 1);
-      if (I.n) {
-        I.ra = min(r1, r0 + wave * per);
-        I.rb = min(r1, I.ra + per);
-      }
+    u32 m = 1;
+    if (merge) {
+      const bool fits =
+          b + lane < end && nk <= cap && R.ko + nk - I.base <= room && (!MS || R.st == uniform(R.st));
+      m = max(1u, (u32)__builtin_ctzll(~__ballot(fits) | (1ull << 63)));
+      I.after = b + m;
+    }
+    const u32 r0 = uniform(R.ro), r1 = lane_read(R.ro + nr, (int)m - 1), per = (r1 - r0 + W - 1) / W;
+    I.n = I.n > cap ? 0u : lane_read((u32)(R.ko - I.base) + nk, (int)m - 1);
+    if (I.n) {
+      I.ra = min(r1, r0 + wave * per);
+      I.rb = min(r1, I.ra + per);
     }
     return I;
   };
@@ -595,17 +606,22 @@ __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A,
       v[q] = lane < step && c0 + lane < rb ? reinterpret_cast<const uint4*>(A.rec)[(u64)(c0 + lane) * (RW / 4) + q]
                                            : make_uint4(0u, 0u, 0u, 0u);
   };
-  auto do_item = [&](u32 item, const Item& I, const Item& next) {
+  // (REST: `chunk` tells chunks from classes of a bucket; of the latter, the class p at depth d0)
+  auto do_item = [&](u32 item, const Item& I, const Item& next, bool chunk, u32 d0, u32 p) {
     const u32 n = I.n;
     const u64 base = I.base;
     if (n == 0) {
       load_records(next.ra, next.rb);
       return;
     }
-    K* const out_k = reinterpret_cast<K*>(CHUNKS ? A.kl_k : A.surv_k) + base;
-    u32* const out_c = (CHUNKS ? A.kl_c : A.surv_c) + base;
+    K* const out_k = reinterpret_cast<K*>(chunk ? A.kl_k : A.surv_k) + base;
+    u32* const out_c = (chunk ? A.kl_c : A.surv_c) + base;
+    const u32 n_buckets = merge ? I.after - item : 1u;
+    // whether the item may be left to the second launch (not once a class of it is counted)
+    bool may_leave = !REST && n > SLOTS && n_buckets == 1;
     HashClass<K> cls;
-    cls.d = n > SLOTS / 2 ? learned : 0u;
+    if (REST && !chunk) cls.set(d0, p);
+    else cls.d = !may_leave && n > SLOTS / 2 ? learned : 0u;
     u32 deepest = cls.d;
     for (;;) {
       bool ok = true;
@@ -646,7 +662,8 @@ __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A,
           }
         }
       };
-      if constexpr (CHUNKS) {
+      u32 seen = I.rb - I.ra;   // records that the wave has added
+      if (chunk) {
         for (u32 i0 = wave * 64 * U; i0 < n; i0 += T * U) {
           K key[U];
           bool on[U];
@@ -663,10 +680,17 @@ __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A,
         // their record by the marks of the records' first units; the units past the last full
         // row of 64 are left to the next step, which starts with their record (`skip` units of
         // it done)
-        auto expand = [&](auto filtered) {
+        auto expand = [&](auto filtered, auto leaving) {
+          constexpr bool LEAVING = decltype(leaving)::value;
           if (I.ra >= I.rb) load_records(next.ra, next.rb);
           u32 skip = 0;
           for (u32 c0 = I.ra; c0 < I.rb;) {
+            if constexpr (LEAVING) {   // (the table is too full: nothing of this pass is of use)
+              if (uniform(*(volatile u32*)&S.full)) {
+                seen = c0 - I.ra;
+                break;
+              }
+            }
             const u32 cnt = min(step, I.rb - c0);
             const u32 g = lane < cnt ? (v[RW / 4 - 1].w >> 26) + 1u : 0u;
             const u32 units = (g + U - 1) / U - (lane == 0 ? skip : 0u);
@@ -713,28 +737,49 @@ __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A,
               if (m) first = q0 + 63u - (u32)__clzll(m);
             }
             c0 = c1;
+            if (LEAVING && !__all(ok)) S.full = 1;
           }
         };
-        if (cls.d == 0) expand(std::false_type());
-        else expand(std::true_type());
+        if (cls.d) expand(std::true_type(), std::false_type());
+        else if (may_leave) expand(std::false_type(), std::bool_constant<!REST>());
+        else expand(std::false_type(), std::false_type());
       }
       if (queued) drain();
       if (!ok) S.full = 1;
       __syncthreads();
-      if (uniform(S.full)) {
+      if (__builtin_expect(uniform(S.full), 0)) {
+        if (may_leave && lane == 0) atomicAdd(&S.seen, seen);
         __syncthreads();
+        // a table takes about nine tenths of its slots of distinct keys; a class is to have no more
+        // than seven
+        u32 depth = cls.d + 1;
+        if (may_leave) {
+          const u32 all = (u32)(A.bcnt[item] >> 32), part = max(1u, uniform(S.seen));
+          while (depth < LATE_DEPTH && (u64)part << (depth - cls.d) < all + all / 4) ++depth;
+        }
         clear_table();
-        if (tid == 0) S.full = 0;
+        const bool leave = may_leave && depth >= 2;
         __syncthreads();
+        if (tid == 0) {
+          S.full = 0;
+          S.seen = 0;
+          if (leave) A.late[atomicAdd(A.late_n, 1u)] = item | depth << 24;
+        }
+        __syncthreads();
+        if (leave) {
+          load_records(next.ra, next.rb);
+          return;
+        }
         ++cls.d;   // the class's first half
         deepest = max(deepest, cls.d);
         load_records(I.ra, I.rb);
         continue;
       }
+      may_leave = false;
       // (lanes of the first wave: the item's buckets' first k-mer slots and k-mers)
       u32 place = 0, size = 0;
-      if constexpr (!CHUNKS) {
-        if (wave == 0 && lane < (merge ? I.after - item : 1u)) {
+      if constexpr (!REST) {
+        if (wave == 0 && lane < n_buckets) {
           place = (u32)(A.kall_off[item + lane] - base);
           size = (u32)A.bcnt[item + lane];
         }
@@ -760,14 +805,14 @@ __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A,
         u16* const cs = reinterpret_cast<u16*>(S.cnt) + s;
         const u32 c = act ? *cs : 0u;
         bool emit = act;
-        if constexpr (!CHUNKS) {
+        if (!chunk) {
           emit = c >= A.min_freq && c <= A.max_freq;   // (min_freq >= 1)
           run_stats_lanes(sink, c, act);
         }
         const u64 em = __ballot(emit);
         if (em) {
           u32 at = 0;
-          if (lane == 0) at = atomicAdd(&S.kept, (u32)__popcll(em));
+          if (lane == 0) at = atomicAdd(REST && !chunk ? &A.surv_cnt[item] : &S.kept, (u32)__popcll(em));
           at = lane_read(at, 0) + mbcnt64(em);
           if (emit) {
             if constexpr (sizeof(K) == 8) out_k[at] = S.lo[s];
@@ -782,16 +827,16 @@ __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A,
         }
       }
       if (lane < 4) H.rec[HW::RECS * RW + lane] = 0;
-      ndist += dist;
+      if (!chunk) ndist += dist;   // (a list's k-mers are counted where the lists are merged)
       if (lane == 0) atomicAdd(&S.dist[parity], dist);
       if (tid == 0) S.dist[parity ^ 1] = 0;
       __syncthreads();
-      if (!next_class(cls)) {
+      if (!next_class(cls, d0)) {
         // each bucket of the item gets what lies at its own slots (the next item adds to S.kept
         // after its first barrier)
-        if (!CHUNKS && wave == 0) {
+        if (!REST && wave == 0) {
           const u32 kept = S.kept;
-          if (lane < (merge ? I.after - item : 1u)) A.surv_cnt[item + lane] = min(max(kept, place) - place, size);
+          if (lane < n_buckets) A.surv_cnt[item + lane] = min(max(kept, place) - place, size);
           if (lane == 0) S.kept = 0;
         }
         break;
@@ -802,47 +847,77 @@ __global__ __launch_bounds__(T, T <= 512 ? 6 : 4) void k_hash_count(CountArgs A,
     // quarter of a table
     const u32 d = uniform(S.dist[parity]);
     parity ^= 1;
-    learned = deepest && (d >> deepest) <= SLOTS / 4 ? deepest - 1 : deepest;
+    if (!REST || chunk) learned = deepest && (d >> deepest) <= SLOTS / 4 ? deepest - 1 : deepest;
     if (merge) room = (u32)min((float)cap, (float)n * (SLOTS / 4) / (float)max(d, 1u));
-    if (CHUNKS && tid == 0) {   // (the next item adds to S.kept after its first barrier)
+    if (chunk && tid == 0) {   // (the next item adds to S.kept after its first barrier)
       A.kl_cnt[item] = S.kept;
       S.kept = 0;
     }
   };
   __syncthreads();
-  const bool ranges = MS || merge;
-  u32 item = CHUNKS ? blockIdx.x : b0 + (ranges ? (u32)((u64)nb * blockIdx.x / gridDim.x) : blockIdx.x);
-  const u32 end = CHUNKS ? (u32)A.meta[4] : b0 + (ranges ? (u32)((u64)nb * (blockIdx.x + 1) / gridDim.x) : nb);
-  Item I = look_up(load_ahead(item, end), item, end);
-  load_records(I.ra, I.rb);
-  Ahead ahead = load_ahead(I.after, end);
   u32 cur = ~0u;
-  while (item < end) {
+  // several sets: the statistics are those of the set of bucket b from here on
+  auto to_set = [&](u32 b) {
     if constexpr (MS) {
-      const u32 st = A.bset[item];
-      if (st != cur) {
-        if (cur != ~0u) {
-          flush();
-          __syncthreads();
-          for (u32 i = tid; i < 256; i += T) S.hist_s[i] = 0;
-          if (tid == 0) {
-            S.lmax = 0;
-            S.lover = 0;
-            S.ndist = 0;
-          }
-          __syncthreads();
+      const u32 st = A.bset[b];
+      if (st == cur) return;
+      if (cur != ~0u) {
+        flush();
+        __syncthreads();
+        for (u32 i = tid; i < 256; i += T) S.hist_s[i] = 0;
+        if (tid == 0) {
+          S.lmax = 0;
+          S.lover = 0;
+          S.ndist = 0;
         }
-        sink_to_set(sink, A.hist, A.tot, st);
-        cur = st;
+        __syncthreads();
       }
+      sink_to_set(sink, A.hist, A.tot, st);
+      cur = st;
     }
-    const Item next = look_up(ahead, I.after, end);
-    ahead = load_ahead(next.after, end);
-    do_item(item, I, next);
-    item = I.after;
-    I = next;
+  };
+  if constexpr (REST) {
+    const Item none{0, 0, 0, 0, 0};
+    bool stats = false;
+    for (u32 r = blockIdx.x; r < n_rest; r += gridDim.x) {
+      Item I = none;
+      if (r < n_chunks) {
+        I.base = A.chunk_start[r];
+        I.n = A.chunk_len[r];
+        do_item(r, I, none, true, 0u, 0u);
+        continue;
+      }
+      const u32 e = A.late[(r - n_chunks) % n_late], p = (r - n_chunks) / n_late, b = e & 0xFFFFFFu, d = e >> 24;
+      if (p >> d) continue;
+      const u64 c = A.bcnt[b];
+      const u32 r0 = A.rec_off[b], r1 = r0 + (u32)(c >> 32), per = (r1 - r0 + W - 1) / W;
+      I.base = A.kall_off[b];
+      I.n = (u32)c;
+      I.ra = min(r1, r0 + wave * per);
+      I.rb = min(r1, I.ra + per);
+      to_set(b);
+      load_records(I.ra, I.rb);
+      do_item(b, I, none, false, d, p);
+      stats = true;
+    }
+    if (stats) flush();
+  } else {
+    const bool ranges = MS || merge;
+    u32 item = b0 + (ranges ? (u32)((u64)nb * blockIdx.x / gridDim.x) : blockIdx.x);
+    const u32 end = b0 + (ranges ? (u32)((u64)nb * (blockIdx.x + 1) / gridDim.x) : nb);
+    Item I = look_up(load_ahead(item, end), item, end);
+    load_records(I.ra, I.rb);
+    Ahead ahead = load_ahead(I.after, end);
+    while (item < end) {
+      to_set(item);
+      const Item next = look_up(ahead, I.after, end);
+      ahead = load_ahead(next.after, end);
+      do_item(item, I, next, false, 0u, 0u);
+      item = I.after;
+      I = next;
+    }
+    flush();
   }
-  if constexpr (!CHUNKS) flush();
 }
 
 // ---------------------------------------------------------------------------- LDS radix passes
