@@ -21,6 +21,7 @@
 #include "kc_common.hpp"
 #include "kc_count.hpp"
 #include "kc_partition.hpp"
+#include "kc_rules.hpp"
 #include "kc_sort.hpp"
 #include "kc_segsort.hpp"
 #include "kc_ext.hpp"
@@ -248,36 +249,6 @@ struct HostBlock {
   }
 };
 
-// On-chip shapes of the bucket count, as slots of the block's hash table (half as many for
-// 128-bit keys): 1 = 4,096 (the default: the most that leaves three blocks of 512 threads per
-// CU), 2 = 8,192, 3 = 2,048.
-constexpr u32 DEFAULT_VARIANT = 1;
-u32 hash_slots(int key_words, u32 variant) {
-  return (variant == 2 ? 8192u : variant == 3 ? 2048u : 4096u) >> (key_words - 1);
-}
-// Buckets of a count of n_max k-mers: a mean of at most the table's slots, but for small
-// inputs up to 1,024 buckets of 512 k-mers, so that every CU has some.  Larger buckets would
-// suit repeated k-mers (1 Gbp at 20x: 15.1 ms with 3,800 k-mers per bucket, 14.7 ms with 7,600),
-// but where nearly all are distinct they overflow the table and are counted in classes
-// (400 Mbp at 0.8x: 12.2 ms with 3,050, 13.2 ms with 6,100).
-int auto_log_b(u64 n_max, u64 slots) {
-  int lb = 1, few = 1;
-  while (lb < 20 && (n_max >> lb) > slots) ++lb;
-  while (few < 10 && (n_max >> few) > 512) ++few;
-  return std::max(lb, few);
-}
-// The same where minimizers of at least 9 bases (2^17 of them) spread the k-mers evenly over few
-// buckets: from 64 buckets on only as many as bring the mean to half the slots, because each costs
-// its share of an empty table.  (240,000 k-mers of 31 bases, 6x: 87 us of kernels in 128 buckets,
-// 100 in 512; 500,000: 103 us in 256, 120 in 1,024; 800,000 in 64 210 us, in 128 123.  With
-// minimizers of 5 bases 500,000 k-mers seen once take 1.33 ms in 256 buckets, 0.79 in 1,024, with 8
-// bases 240,000 of 51 bases 158 us in 256 and 147 in 512.)
-int even_log_b(u64 n_max, u64 slots) {
-  int lb = auto_log_b(n_max, slots), few = 6;
-  while (few < lb && (n_max >> few) > slots / 2) ++few;
-  return std::min(lb, few);
-}
-
 // Segments of at most seg_wave_cap pairs are sorted by one wave each (k_seg_wave); the
 // survivors' key ranges aim below that on average so that nearly all of them are (ranges by
 // powers of two average between half the target and the target).
@@ -319,7 +290,7 @@ bool make_plan(u64 R, u64 n_reads, u64 n_max, int k, int m, uint32_t min_freq, c
     if (cfg->log2_buckets > 20) return false;
     p->log_b = (int)cfg->log2_buckets;
   } else {
-    p->log_b = m >= 9 ? even_log_b(n_max, slots) : auto_log_b(n_max, slots);
+    p->log_b = default_log_b(n_max, m, slots);
   }
   // (the workspace may not depend on m, see below)
   const int log_b_cap = cfg && cfg->log2_buckets ? p->log_b : auto_log_b(n_max, slots);

@@ -64,30 +64,30 @@ std::vector<int> assign_lanes(const std::vector<u64>& sizes, int lanes) {
 
 // ---------------------------------------------------------------- autotune cache
 struct TuneKey {
-  int key_words, k, size_class, long_reads;
+  int key_words, k, size_class, long_reads, even;   // (even: the bucket rule for minimizers of 9 bases and more)
   bool operator<(const TuneKey& o) const {
-    return std::tie(key_words, k, size_class, long_reads) < std::tie(o.key_words, o.k, o.size_class, o.long_reads);
+    return std::tie(key_words, k, size_class, long_reads, even) <
+           std::tie(o.key_words, o.k, o.size_class, o.long_reads, o.even);
   }
 };
 struct TuneVal {
-  int log_b_delta;   // relative to the size rule of make_plan
-  u32 variant;
+  TuneChoice choice;
   double ms;
 };
 std::mutex g_tune_mu;
 std::map<TuneKey, TuneVal> g_tune;
 
-TuneKey tune_key(const JobInfo& ji, int k, u64 n_reads) {
+TuneKey tune_key(const JobInfo& ji, int k, int m, u64 n_reads) {
   int sc = 0;
   while (sc < 40 && (ji.R >> (sc + 1)) > 0) ++sc;
   const bool lr = n_reads && ji.R / n_reads >= 1000;
-  return TuneKey{ji.key_words, k, sc, lr ? 1 : 0};
+  return TuneKey{ji.key_words, k, sc, lr ? 1 : 0, m >= 9 ? 1 : 0};
 }
 
-kc_config tuned_config(const kc_config& base, const JobInfo& ji, const TuneVal& tv) {
+kc_config tuned_config(const kc_config& base, const JobInfo& ji, int m, TuneChoice choice) {
   kc_config c = base;
-  c.small_variant = tv.variant;
-  c.log2_buckets = (u32)std::min(20, std::max(1, auto_log_b(ji.n_max, hash_slots(ji.key_words, tv.variant)) + tv.log_b_delta));
+  c.small_variant = choice.variant;
+  c.log2_buckets = (u32)tuned_log_b(ji.n_max, m, ji.key_words, choice);
   return c;
 }
 
@@ -133,12 +133,9 @@ u64 outputs_bytes(const JobInfo& ji, u64 hist_len) {
 int autotune_device(const kc_job& j, const JobInfo& ji, const kc_config* base, kc_config* out, double* best_ms) {
   kc_config b{};
   if (base) b = *base;
-  std::vector<TuneVal> cand;
-  for (u32 var : {1u, 2u, 3u})
-    for (int d : {-1, 0, 1}) cand.push_back(TuneVal{d, var, 0.0});
   u64 ws_bytes = 0;
-  for (auto& c : cand) {
-    kc_config cc = tuned_config(b, ji, c);
+  for (const TuneChoice& c : TUNE_CHOICES) {
+    kc_config cc = tuned_config(b, ji, j.m, c);
     Plan P;
     if (!make_plan(ji.R, j.n_reads, ji.n_max, j.k, j.m, j.min_freq, &cc, &P)) return fail(KC_EINVAL, "bad config");
     ws_bytes = std::max<u64>(ws_bytes, P.bytes);
@@ -152,21 +149,21 @@ int autotune_device(const kc_job& j, const JobInfo& ji, const kc_config* base, k
     return fail(KC_EDEVICE, "stream creation failed");
   }
   int rc = KC_OK;
-  TuneVal best{0, 1, 1e30};
-  for (auto& c : cand) {
+  TuneVal best{{DEFAULT_VARIANT, 0}, 1e30};
+  for (const TuneChoice& c : TUNE_CHOICES) {
     double ms = 0;
-    rc = time_count(j, ji, tuned_config(b, ji, c), mem, ws_bytes, mem + ws_bytes, st, 2, &ms);
+    rc = time_count(j, ji, tuned_config(b, ji, j.m, c), mem, ws_bytes, mem + ws_bytes, st, 2, &ms);
     if (rc) break;
-    if (ms < best.ms) best = TuneVal{c.log_b_delta, c.variant, ms};
+    if (ms < best.ms) best = TuneVal{c, ms};
   }
   (void)hipStreamDestroy(st);
   (void)hipFree(mem);
   if (rc) return rc;
   {
     std::lock_guard<std::mutex> g(g_tune_mu);
-    g_tune[tune_key(ji, j.k, j.n_reads)] = best;
+    g_tune[tune_key(ji, j.k, j.m, j.n_reads)] = best;
   }
-  *out = tuned_config(b, ji, best);
+  *out = tuned_config(b, ji, j.m, best.choice);
   if (best_ms) *best_ms = best.ms;
   return KC_OK;
 }
@@ -229,7 +226,7 @@ int tune_radix_bits(const kc_job& j, const JobInfo& ji, u32* best_bits) {
   if (rc) return rc;
   {
     std::lock_guard<std::mutex> g(g_tune_mu);
-    g_tune_bits[tune_key(ji, j.k, j.n_reads)] = bb;
+    g_tune_bits[tune_key(ji, j.k, j.m, j.n_reads)] = bb;
   }
   *best_bits = bb;
   return KC_OK;
@@ -468,7 +465,7 @@ int batch_build(std::vector<kc_batch::Job>&& jobs, const kc_config* cfg, kc_batc
   for (auto& J : b->jobs) {
     J.cfg = cfg ? *cfg : kc_config{};
     if (cfg && cfg->autotune && J.group < 0) {
-      TuneKey key = tune_key(J.ji, J.j.k, J.j.n_reads);
+      TuneKey key = tune_key(J.ji, J.j.k, J.j.m, J.j.n_reads);
       TuneVal tv{};
       bool have = false;
       {
@@ -480,7 +477,7 @@ int batch_build(std::vector<kc_batch::Job>&& jobs, const kc_config* cfg, kc_batc
         }
       }
       if (have) {
-        J.cfg = tuned_config(J.cfg, J.ji, tv);
+        J.cfg = tuned_config(J.cfg, J.ji, J.j.m, tv.choice);
       } else {
         kc_config t;
         int rc = autotune_device(J.j, J.ji, &J.cfg, &t, nullptr);
