@@ -108,13 +108,19 @@ const char *kc_last_error(void);
  *   cfg may be NULL; cfg->hbm_budget bounds the device workspace (rounds, see
  *   kc_workspace_size).  On KC_OK, *out owns host arrays that kc_result_free releases.
  *   Without a budget, up to 4 GiB of a call's device memory stay with the library for the
- *   next host call (of any thread) and go back when an allocation of the library runs short.
+ *   next host call (of any thread) and go back when an allocation of the library runs short, or
+ *   with kc_release_memory.
  *   Errors: KC_EINVAL (arguments, non-monotone offsets, more than 2^32-1 windows),
  *   KC_ENOMEM (no plan fits the budget or free HBM; a count in rounds that could not
  *   finish), KC_EDEVICE. */
 int kc_count(const uint8_t *reads, const uint64_t *offsets, uint64_t n_reads, int k, int m,
              uint32_t min_freq, uint32_t max_freq, uint64_t hist_len, const kc_config *cfg,
              kc_result *out);
+
+/* Gives the device memory that stayed with the library after host calls back to the driver, on all
+ * devices (for another allocator of the process, or another process); *freed (may be NULL) gets the
+ * bytes.  Calls that run meanwhile keep theirs. */
+int kc_release_memory(uint64_t *freed);
 
 /* Release the arrays of a kc_result filled by kc_count (safe on a zeroed result). */
 void kc_result_free(kc_result *res);

@@ -134,7 +134,8 @@ static_assert(C_META + 8 <= C_FLAGS, "meta overlaps the flags");
 // next allocation may wait until the pages are cleared (16 Mbp: 30 ms a call, 2.7 ms without; 60
 // Mbp: 28.5 and 27.5 ms, the rest being the result's pages on the host).  So up
 // to KEEP_MAX bytes (1.5 % of the HBM) of blocks stay here for the next call, and go back to the
-// driver when newer ones take their place or an allocation of this library runs short.  A block
+// driver when newer ones take their place, an allocation of this library runs short or
+// kc_release_memory is called.  A block
 // is kept only after its call's work on it has completed, and a call with a budget of its own
 // neither takes nor leaves one.  (Never destroyed: at the process's end the driver is gone first.)
 constexpr u64 KEEP_MAX = 4ull << 30;
@@ -183,17 +184,21 @@ class KeptBlocks {
     }
     for (int i = 0; i < n_old; ++i) (void)hipFree(old[i].p);
   }
-  // all kept blocks of the device back to the driver; false: there were none
-  bool drop(int dev) {
+  // all kept blocks of the device (below 0: of every device) back to the driver; their bytes
+  u64 drop(int dev) {
     DevBlock old[N];
     int n_old = 0;
+    u64 bytes = 0;
     {
       std::lock_guard<std::mutex> g(mu_);
       for (int i = n_ - 1; i >= 0; --i)
-        if (b_[i].dev == dev) old[n_old++] = remove(i);
+        if (dev < 0 || b_[i].dev == dev) old[n_old++] = remove(i);
     }
-    for (int i = 0; i < n_old; ++i) (void)hipFree(old[i].p);
-    return n_old > 0;
+    for (int i = 0; i < n_old; ++i) {
+      (void)hipFree(old[i].p);
+      bytes += old[i].bytes;
+    }
+    return bytes;
   }
   u64 held(int dev) {
     std::lock_guard<std::mutex> g(mu_);
@@ -2156,6 +2161,13 @@ int kc_count(const uint8_t* reads, const uint64_t* offsets, uint64_t n_reads, in
       hipMemcpy(out->hist, d_hist, hist_len * 8, hipMemcpyDeviceToHost) != hipSuccess)
     return cleanup(fail(KC_EDEVICE, "D2H failed"));
   return cleanup(KC_OK);
+}
+
+int kc_release_memory(uint64_t* freed) {
+  g_err.clear();
+  const u64 bytes = kept_blocks().drop(-1);
+  if (freed) *freed = bytes;
+  return KC_OK;
 }
 
 // ---------------------------------------------------------------- partition inspection

@@ -234,6 +234,13 @@ def kc_count(reads: np.ndarray, offsets: np.ndarray, k: int, m: int, min_freq: i
         _lib.kc_result_free(ctypes.byref(res))
 
 
+def kc_release_memory() -> int:
+    """Device memory kept between host calls back to the driver; returns its bytes."""
+    freed = ctypes.c_uint64()
+    _check(_lib.kc_release_memory(ctypes.byref(freed)))
+    return int(freed.value)
+
+
 @dataclass
 class Partition:
     log2_buckets: int
