@@ -238,6 +238,9 @@ void kc_ext_result_free(kc_ext_result *res);
  * identical to a one-pass count.  KC_ENOMEM when a single 12-bit key prefix holds more
  * windows than a round (reported by the count). */
 size_t kc_ext_workspace_size(uint64_t total_bases, uint64_t n_reads, int k, const kc_config *cfg);
+/* The same for counts with this min_freq, which never go through their pairs at 1. */
+size_t kc_ext_workspace_size_for(uint64_t total_bases, uint64_t n_reads, int k, uint32_t min_freq,
+                                 const kc_config *cfg);
 
 /* Device API of the extension version; every buffer is caller-owned device memory:
  *   d_kmers (pair_capacity * key_words words), d_counts (pair_capacity), d_occ_off

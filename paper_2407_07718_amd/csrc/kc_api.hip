@@ -2247,11 +2247,17 @@ int kc_partition_inspect(const uint8_t* reads, const uint64_t* offsets, uint64_t
 }
 
 // ---------------------------------------------------------------- extension version
-size_t kc_ext_workspace_size(uint64_t total_bases, uint64_t n_reads, int k, const kc_config* cfg) {
+size_t kc_ext_workspace_size_for(uint64_t total_bases, uint64_t n_reads, int k, uint32_t min_freq,
+                                 const kc_config* cfg) {
   if (k < 1 || k > 63 || total_bases >= (1ull << 32) || n_reads >= (1ull << 32)) return 0;
   ExtPlan P;
   if (!make_ext_plan(total_bases, n_reads, k, cfg ? cfg->hbm_budget : 0, &P)) return 0;
+  if (min_freq < 2) ext_fit(&P, P.bytes_sort);
   return (size_t)P.bytes;
+}
+
+size_t kc_ext_workspace_size(uint64_t total_bases, uint64_t n_reads, int k, const kc_config* cfg) {
+  return kc_ext_workspace_size_for(total_bases, n_reads, k, 2, cfg);
 }
 
 static int ext_device_common(const uint8_t* d_reads, uint64_t total_bases, const uint64_t* d_offsets, uint64_t n_reads,

@@ -150,6 +150,10 @@ def _load() -> ctypes.CDLL:
     lib.kc_ext_workspace_size.restype = ctypes.c_size_t
     ext_args = [vp, u64, vp, u64, i32, u32, u32, u64, P(kc_config), vp, ctypes.c_size_t, vp, vp, u64, vp, vp, vp,
                 u64, vp, vp, vp]
+    lib.kc_ext_workspace_size_for.argtypes = [u64, u64, i32, u32, P(kc_config)]
+    lib.kc_ext_workspace_size_for.restype = ctypes.c_size_t
+    lib.kc_release_memory.argtypes = [P(ctypes.c_uint64)]
+    lib.kc_release_memory.restype = i32
     lib.kc_count_ext_device.argtypes = ext_args + [P(kc_totals)]
     lib.kc_count_ext_device.restype = i32
     lib.kc_count_ext_device_async.argtypes = ext_args
@@ -520,9 +524,16 @@ def kc_ext_workspace_size(total_bases: int, n_reads: int, k: int, cfg: Optional[
     return int(_lib.kc_ext_workspace_size(total_bases, n_reads, k, ctypes.byref(cfg) if cfg is not None else None))
 
 
+def kc_ext_workspace_size_for(total_bases: int, n_reads: int, k: int, min_freq: int,
+                              cfg: Optional[kc_config] = None) -> int:
+    return int(_lib.kc_ext_workspace_size_for(total_bases, n_reads, k, min_freq,
+                                              ctypes.byref(cfg) if cfg is not None else None))
+
+
 class DeviceExtCounter:
     """Workspace and output buffers on the GPU for repeated extension counts of read sets
-    up to ``max_bases`` bases / ``max_reads`` reads at one k."""
+    up to ``max_bases`` bases / ``max_reads`` reads at one k.  (Where the GPU has no room for the
+    larger workspace of counts that go through their pairs, it takes the one that sorts.)"""
 
     def __init__(self, max_bases: int, max_reads: int, k: int, min_freq: int, max_freq: int,
                  hist_len: int = 65536, cfg: Optional[kc_config] = None, pair_capacity: Optional[int] = None,
@@ -530,10 +541,10 @@ class DeviceExtCounter:
         import torch
         self.k, self.lo, self.hi, self.H, self.cfg = k, min_freq, max_freq, hist_len, cfg
         self.key_words = 1 if k <= 31 else 2
-        ws = kc_ext_workspace_size(max_bases, max_reads, k, cfg)
+        ws = kc_ext_workspace_size_for(max_bases, max_reads, k, min_freq, cfg)
         if ws == 0:
             raise KCError(KC_EINVAL, "kc_ext_workspace_size rejected the arguments")
-        self.workspace = torch.empty(ws, dtype=torch.uint8, device=device)
+        least = kc_ext_workspace_size_for(max_bases, max_reads, k, 1, cfg)
         cap = pair_capacity if pair_capacity is not None else max(1, max_bases // max(1, min_freq))
         ocap = occ_capacity if occ_capacity is not None else max(1, max_bases)
         self.kmers = torch.empty((cap, self.key_words), dtype=torch.int64, device=device)
@@ -543,6 +554,12 @@ class DeviceExtCounter:
         self.occ_pos = torch.empty(ocap, dtype=torch.int32, device=device)
         self.hist = torch.empty(hist_len, dtype=torch.int64, device=device)
         self.totals = torch.zeros(ctypes.sizeof(kc_totals) // 8, dtype=torch.int64, device=device)
+        try:
+            self.workspace = torch.empty(ws, dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:
+            if least == ws:
+                raise
+            self.workspace = torch.empty(least, dtype=torch.uint8, device=device)
 
     def count(self, d_reads, d_offsets, stream=None, sync: bool = True):
         import torch

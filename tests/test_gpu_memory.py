@@ -1,4 +1,6 @@
-"""What host calls leave with the library goes back on request."""
+"""Device memory that is asked for and held: what host calls leave with the library goes back on
+request, and an occurrence count's workspace is no larger than its counts use, or than the GPU has room
+for."""
 import numpy as np
 import pytest
 
@@ -28,3 +30,31 @@ def test_release_memory():
         assert held >= kc.kc_release_memory() > 60 * len(r)
         assert free - torch.cuda.mem_get_info()[0] < 8 << 20
     assert kc.kc_release_memory() == 0
+
+
+@pytest.mark.parametrize("k,bases", [(31, 1 << 25), (51, 1 << 22)])
+def test_occurrence_workspace(k, bases):
+    import torch
+    from paper_2407_07718_amd import kc
+    per = 30 if k <= 31 else 46   # bytes per base where the windows are sorted
+    assert kc.DeviceExtCounter(bases, 1000, k, 1, 100, 64).workspace.numel() < per * bases
+    large = kc.DeviceExtCounter(bases, 1000, k, 2, 100, 64).workspace.numel()
+    assert large == kc.kc_ext_workspace_size(bases, 1000, k, None) > 45 * bases
+    # room for the outputs (pairs for half of the windows, each window's occurrence) and the sort's
+    # workspace only
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    room = bases // 2 * (8 * (1 if k <= 31 else 2) + 12) + 8 * bases + per * bases + (64 << 20)
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + room) / total)
+    try:
+        ctr = kc.DeviceExtCounter(bases, 1000, k, 2, 100, 64)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert ctr.workspace.numel() < per * bases
+    rng = np.random.default_rng(k)
+    r = np.tile(_ACGT[rng.integers(0, 4, size=50_000)], 3)
+    off = np.array([0, 60_000, len(r)], np.uint64)
+    got = ctr.result(ctr.count(torch.from_numpy(r).cuda(), torch.from_numpy(off.view(np.int64)).cuda()))
+    ref = oracle.count_ext(r, off, k, 2, 100, 64)
+    assert_same(got.pairs, ref.base)
+    assert np.array_equal(got.occ_read, ref.occ_read) and np.array_equal(got.occ_pos, ref.occ_pos)
