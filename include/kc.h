@@ -135,11 +135,11 @@ void kc_result_free(kc_result *res);
  * the budget: a count pass of the minimizer stage finds the records and k-mers of every
  * coarse group of buckets; the groups are split into consecutive ranges that fit a
  * round; each round regenerates the supermers of its groups from the 2-bit reads and
- * partitions, sorts and counts them exactly as the one-pass count does; the survivors
+ * partitions and counts them exactly as the one-pass count does; the survivors
  * of all rounds are sorted by k-mer at the end.  A distinct k-mer lies in one bucket,
  * hence in one round, so results are identical to a one-pass count.  What the fixed part
- * (2-bit reads, masks, bucket tables) leaves of the budget goes half to the rounds and
- * half to a pool for the survivors.  A count in rounds fails with KC_ENOMEM when one
+ * (2-bit reads, masks, bucket tables) leaves of the budget goes a quarter to a pool for the
+ * survivors and the rest to the rounds.  A count in rounds fails with KC_ENOMEM when one
  * coarse group holds more k-mers than a round (extreme skew) or when the survivors
  * outgrow the pool (e.g. min_freq = 1 on mostly distinct k-mers under a small budget). */
 size_t kc_workspace_size(uint64_t total_bases, uint64_t n_reads, int k, const kc_config *cfg);
@@ -183,8 +183,8 @@ int kc_count_device_async(const uint8_t *d_reads, uint64_t total_bases, const ui
  * (totals.flags != 0 marks a failed count, n_pairs > pair_capacity a truncation).  The
  * first call on a device looks up the buffer's address on that device.
  *   Errors: KC_EINVAL as kc_count_device; KC_ENOMEM when kc_workspace_size(total_bases,
- *   n_reads, k, cfg) exceeds KC_NOALLOC_SCRATCH_BYTES (about 5.3 M bases at k <= 31,
- *   2.9 M bases at k >= 32); KC_EDEVICE if the buffer cannot be located.
+ *   n_reads, k, cfg) exceeds KC_NOALLOC_SCRATCH_BYTES (about 5.8 M bases at k <= 31,
+ *   3.0 M bases at k >= 32); KC_EDEVICE if the buffer cannot be located.
  *   Every call on one GPU shares that GPU's buffer (it keeps the last call's contents;
  *   each count clears what it needs): calls that overlap on one GPU, from two streams or
  *   two threads, race and must be serialized by the caller. */

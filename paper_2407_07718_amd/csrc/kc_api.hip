@@ -367,11 +367,11 @@ void plan_layout(Plan* p) {
   p->o_starts = take(4 * p->n_mask);
   // Three large regions whose contents rotate as the stages retire them:
   //   X: extract block record slots -> records in bucket order (fine partition, read
-  //      by the sorts) -> first buffer of the chunk-list sort
-  //   Y: records grouped by coarse digit (partition) -> large-bucket keys,
-  //      overwritten in place by the chunk lists, + list counts -> second sort buffer
-  //   Z: survivors at their bucket's k-mer slots -> second buffer of the survivor sort
-  // The final dense survivors use whichever of X / Y the chunk-list sort left free.
+  //      by the count) -> first buffer of the list merge -> survivors by coarse key range
+  //   Y: records grouped by coarse digit (partition) -> large-bucket keys -> second buffer
+  //      of the list merge
+  //   Z: chunk lists of large buckets and survivors, at their bucket's k-mer slots ->
+  //      survivors by key range
   // (rounds: records packed densely, cap_r of them; one pass: one slot per k-mer position)
   p->o_X = take(std::max(rounds ? rb * p->rec_cap : std::max(rb * p->slots, rb * N), (w + 4) * N));
   p->o_Y = take(std::max(rb * p->rec_cap, (w + 4) * N));
@@ -596,7 +596,6 @@ inline dim3 grid_for(u64 n, u32 block, u32 max_blocks = 1u << 20) {
   return dim3((u32)std::max<u64>(1, std::min<u64>(max_blocks, ceil_div(n, block))));
 }
 
-// Queue one full count on `st`.
 constexpr int SEG_T = 512;                                    // threads of k_seg_sort ...
 constexpr u32 SEG_CAP_64 = SEG_T * 8, SEG_CAP_128 = SEG_T * 4;   // ... and pairs sorted on chip per segment
 
@@ -700,14 +699,8 @@ Ws<K> ws_ptrs(const Plan& P, void* ws) {
   return W;
 }
 
-// From the extract stage's records to the survivors of every bucket, compacted into
-// out_k / out_c from the slot *out_base on (a null out_base: from slot 0) and at most out_cap
-// slots: partition, bucket plan, the per-bucket sorts and counts, the merge of the heavy
-// buckets' chunk lists.  One pass runs it once; a memory-bounded count once per round
-// (blk_base: the round's dense record slots of every extract block; no stage marks).
-// Device side of a count over several read sets (null for one set): bucket -> set, the
-// merged lists' segment-start bits, the sets of the merged runs' survivors, and the
-// wide-key survivor buffers (capacity wide_cap).
+// Device side of a count over several read sets (null for one set): bucket -> set, and the
+// buffers of the survivors with their sets (capacity wide_cap).
 struct MultiDev {
   u32 n_sets = 0, n_buckets = 0;   // (the sets' buckets; the plan's number is a power of two)
   const u32* bset = nullptr;
@@ -839,6 +832,12 @@ int with_hash_shape(u32 variant, F f) {
   return f(HashShape<512, 4096 / D>());
 }
 
+// From the extract stage's records to the survivors of every bucket: partition, bucket plan, the
+// count, the merge of the large buckets' chunk lists.  One pass runs it once and leaves the
+// survivors at their bucket's k-mer slots (out_k null); a memory-bounded count once per round
+// (blk_base: the round's dense record slots of every extract block; no stage marks), compacted
+// into out_k / out_c from the slot *out_base on and at most out_cap slots; several sets into md's
+// buffers.
 template <typename K>
 int count_buckets(const Plan& P, const Ws<K>& W, const u32* blk_base, uint32_t lo, uint32_t hi, uint64_t hist_len,
                   uint64_t* d_hist, DevTotals* d_tot, K* out_k, u32* out_c, const u64* out_base, u64 out_cap,
@@ -860,7 +859,7 @@ int count_buckets(const Plan& P, const Ws<K>& W, const u32* blk_base, uint32_t l
   }
 
   if (marks) stage_mark(3, st);
-  // ---- per bucket sort + count
+  // ---- per bucket count
   CountArgs ca;
   ca.rec = W.recB;
   ca.rec_off = W.recoff;
@@ -890,7 +889,7 @@ int count_buckets(const Plan& P, const Ws<K>& W, const u32* blk_base, uint32_t l
   ca.n_sets = ms ? md->n_sets : 1u;
   ca.rng = rng;
   ca.log_f = P.log_f;
-  // large buckets: expand their k-mers into HBM, cut later into chunks
+  // large buckets: expand their k-mers into HBM, counted in chunks
   hipLaunchKernelGGL((k_expand_large<K, 256>), dim3(1024), dim3(256), 0, st, ca, W.lk0);
   if (marks) stage_mark(4, st);
   auto hash_count = [&](auto kern, int T, u64 items) -> int {
@@ -1019,7 +1018,6 @@ int enqueue(const Plan& P, void* ws, const uint8_t* d_reads, const uint64_t* d_o
                                n_cu, st)))
       return rc;
     // ---- output: the survivors sorted by key straight into the caller's buffers
-    // (first to where the sorted lists were)
     const SurvSegs segs = surv_segs<K>(P, W);
     if ((rc = sort_survivors<K>(P, W, W.s0k, W.s0c, W.kl0k, W.kl0c, W.surv_nc, P.surv_cap, d_kmers, d_counts, pair_cap,
                                 n_cu, st, 0, &segs)))

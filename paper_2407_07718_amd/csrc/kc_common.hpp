@@ -77,10 +77,6 @@ __device__ __forceinline__ u32 mbcnt64(u64 m) {
 __device__ __forceinline__ u32 lane_prev(u32 v, u32 fill) {
   return (u32)__builtin_amdgcn_update_dpp((int)fill, (int)v, 0x138, 0xF, 0xF, false);
 }
-// v of lane l+1 (lane 63 gets `fill`): DPP wave_shl:1.
-__device__ __forceinline__ u32 lane_next(u32 v, u32 fill) {
-  return (u32)__builtin_amdgcn_update_dpp((int)fill, (int)v, 0x130, 0xF, 0xF, false);
-}
 // v of lane (l-1) mod 64: DPP wave_ror:1.
 __device__ __forceinline__ u32 lane_rot1(u32 v) {
   return (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x13C, 0xF, 0xF, false);

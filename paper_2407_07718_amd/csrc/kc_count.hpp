@@ -1,12 +1,13 @@
-// Stage 3 of the pipeline: per bucket, expand supermers into canonical k-mer keys, sort
-// them, and count each distinct key as a run of equal keys; keys whose count lies in
-// [min_freq, max_freq] survive, every run feeds the frequency histogram.
+// Stage 3 of the pipeline: per bucket, expand supermers into canonical k-mer keys and count
+// them in a hash table on chip; keys whose count lies in [min_freq, max_freq] survive, every
+// distinct key feeds the frequency histogram.  Large buckets are cut into chunks whose
+// (k-mer, count) lists are merged (kc_segsort.hpp).
 //
-// Paper mapping: k-mers are extracted from the supermers of a task and sorted (Section
-// 3.5, heavy-hitter transform; Section 3.1), and one linear scan over the sorted array
-// counts each value and records the histogram or copies the k-mers that meet the
-// frequency requirement to another array (Section 3.1).  A bucket is a task (Section
-// 3.4): independent of all others because equal k-mers never span two buckets.
+// Paper mapping: k-mers are extracted from the supermers of a task and counted (there by a sort
+// and a linear scan over the sorted array, Section 3.5, heavy-hitter transform; Section 3.1), and
+// the scan records the histogram or copies the k-mers that meet the frequency requirement to
+// another array (Section 3.1).  A bucket is a task (Section 3.4): independent of all others because
+// equal k-mers never span two buckets.
 #pragma once
 #include <type_traits>
 
@@ -62,7 +63,8 @@ struct CountArgs {
 };
 
 // ---------------------------------------------------------------------------- key mixing
-// A bucket is sorted only to bring equal keys together, so its keys are sorted as images
+// The classes of a bucket that overflows its table, and the sorts that bring equal keys of a large
+// bucket's lists together (whatever their order), go by the keys' images
 // under a bijection whose low bits depend on every key bit: y = b ^ (b >> 32) with
 // b = a * C mod 2^64 and a = x ^ (x >> 32).  Both xor-shifts are involutions and C is
 // odd, so the map is undone exactly by the same steps in reverse with C^-1.  K-mers that
@@ -95,73 +97,6 @@ __device__ __forceinline__ k128 mix_key(k128 x) { return k128{mix64(x.lo) ^ mix6
 __device__ __forceinline__ k128 unmix_key(k128 y) { return k128{unmix64(y.lo ^ mix64(y.hi ^ MIX_C)), y.hi}; }
 
 // ---------------------------------------------------------------------------- expand
-__device__ __forceinline__ u32 record_g(const u32* __restrict__ rec, u64 r, int rec_words) {
-  return (rec[r * (u64)rec_words + (u64)rec_words - 1] >> 26) + 1u;
-}
-
-// k <= 31: record = 4 words, bases LSB first in 122 bits.
-__device__ __forceinline__ void expand_record(const u32* __restrict__ rec, u64 r, int k, u64* dst, u32 g,
-                                              bool mix = false) {
-  const uint4 v = reinterpret_cast<const uint4*>(rec)[r];
-  const u64 lo = (u64)v.x | ((u64)v.y << 32);
-  const u64 hi = ((u64)v.z | ((u64)v.w << 32)) & ((1ull << 58) - 1);
-  const u64 mask = (1ull << (2 * k)) - 1;
-  const u64 V = lo & mask;
-  u64 F = rev2_64(V) >> (64 - 2 * k);
-  u64 RC = ~V & mask;
-  u64 cv = F < RC ? F : RC;
-  dst[0] = mix ? mix_key(cv) : cv;
-  for (u32 j = 1; j < g; ++j) {
-    const u32 p = j + (u32)k - 1;   // index of the base entering the window
-    const u64 c = p < 32 ? (lo >> (2 * p)) & 3ull : (hi >> (2 * p - 64)) & 3ull;
-    F = ((F << 2) | c) & mask;
-    RC = (RC >> 2) | ((3ull - c) << (2 * k - 2));
-    cv = F < RC ? F : RC;
-    dst[j] = mix ? mix_key(cv) : cv;
-  }
-}
-
-// 32 <= k <= 63: record = 8 words, bases LSB first in 250 bits.
-__device__ __forceinline__ void expand_record(const u32* __restrict__ rec, u64 r, int k, k128* dst, u32 g,
-                                              bool mix = false) {
-  const uint4* p4 = reinterpret_cast<const uint4*>(rec) + 2 * r;
-  const uint4 a = p4[0], b = p4[1];
-  u64 w[4];
-  w[0] = (u64)a.x | ((u64)a.y << 32);
-  w[1] = (u64)a.z | ((u64)a.w << 32);
-  w[2] = (u64)b.x | ((u64)b.y << 32);
-  w[3] = ((u64)b.z | ((u64)b.w << 32)) & ((1ull << 58) - 1);
-  const int hb = 2 * k - 64;                      // bits in the high word, 0..62
-  const u64 mhi = hb ? ((1ull << hb) - 1) : 0ull;
-  const u64 vlo = w[0], vhi = w[1] & mhi;
-  // forward value = 2-bit reversal of the 128-bit window, shifted down by 128 - 2k
-  const u64 rlo = rev2_64(vhi), rhi = rev2_64(vlo);
-  const int s = 128 - 2 * k;                      // 2..64
-  k128 F, RC;
-  if (s == 64) { F.lo = rhi; F.hi = 0; }
-  else { F.lo = (rlo >> s) | (rhi << (64 - s)); F.hi = rhi >> s; }
-  RC.lo = ~vlo;
-  RC.hi = ~vhi & mhi;
-  k128 v = key_lt(F, RC) ? F : RC;
-  dst[0] = mix ? mix_key(v) : v;
-  for (u32 j = 1; j < g; ++j) {
-    const u32 p = j + (u32)k - 1;
-    const u64 wsel = p < 64 ? (p < 32 ? w[0] : w[1]) : (p < 96 ? w[2] : w[3]);   // no dynamic register index
-    const u64 c = (wsel >> (2 * (p & 31))) & 3ull;
-    // F = ((F << 2) | c) masked to 2k bits
-    F.hi = ((F.hi << 2) | (F.lo >> 62)) & mhi;
-    F.lo = (F.lo << 2) | c;
-    // RC = (RC >> 2) | ((3 - c) << (2k - 2))
-    RC.lo = (RC.lo >> 2) | (RC.hi << 62);
-    RC.hi = RC.hi >> 2;
-    const int t = 2 * k - 2;                      // 62..124
-    if (t >= 64) RC.hi |= (3ull - c) << (t - 64);
-    else RC.lo |= (3ull - c) << t;
-    v = key_lt(F, RC) ? F : RC;
-    dst[j] = mix ? mix_key(v) : v;
-  }
-}
-
 // The canonical k-mer whose first base is bit q of a record's base field (k <= 31: a
 // u64; k >= 32: a 128-bit key), read with funnel shifts from the record words at rec.
 __device__ __forceinline__ u64 rec_bits64(const u32* p, u32 q) {   // 64 bits from bit q of p
@@ -224,25 +159,6 @@ __device__ __forceinline__ void run_stats_lanes(const RunSink& S, u64 c, bool ac
 __device__ __forceinline__ void sink_to_set(RunSink& S, u64* hist, DevTotals* tot, u32 s) {
   S.hist = hist + (u64)s * S.hist_len;
   S.tot = tot + s;
-}
-
-// One wave's statistics (its own LDS slice) to the global targets, then cleared.
-__device__ __forceinline__ void flush_stats_wave(const RunSink& S, u64 ndist) {
-  const u32 H = (u32)min(S.hist_len, (u64)256);
-  __builtin_amdgcn_wave_barrier();
-  for (u32 i = lane_id(); i < H; i += 64) {
-    const u32 v = S.hist_s[i];
-    if (v) atomicAdd((unsigned long long*)&S.hist[i], (unsigned long long)v);
-    S.hist_s[i] = 0;
-  }
-  if (lane_id() == 0) {
-    if (*S.lmax) atomicMax((unsigned long long*)&S.tot->max_count, (unsigned long long)*S.lmax);
-    if (*S.lover) atomicAdd((unsigned long long*)&S.tot->overflow_sum, *S.lover);
-    if (ndist) atomicAdd((unsigned long long*)&S.tot->n_distinct, (unsigned long long)ndist);
-    *S.lmax = 0;
-    *S.lover = 0;
-  }
-  __builtin_amdgcn_wave_barrier();
 }
 
 __device__ __forceinline__ void flush_stats(const RunSink& S, u64 ndist) {
@@ -928,11 +844,6 @@ template <typename K> __device__ __forceinline__ K key_pad();
 template <> __device__ __forceinline__ u64 key_pad<u64>() { return ~0ull; }
 template <> __device__ __forceinline__ k128 key_pad<k128>() { return k128{~0ull, ~0ull}; }
 
-// v of the previous lane (lane 0 gets `fill`): one DPP wave_shr:1 move.
-__device__ __forceinline__ u32 prev_lane(u32 v, u32 fill) {
-  return (u32)__builtin_amdgcn_update_dpp((int)fill, (int)v, 0x138, 0xF, 0xF, false);
-}
-
 // Lanes of a fully active wave that share digit d with this lane, as a lane mask.  Every
 // lane ORs its bit into the wave's table entry of its digit and reads the entry back;
 // when neighbouring lanes hold equal digits (frequent once equal keys cluster) only the
@@ -940,7 +851,7 @@ __device__ __forceinline__ u32 prev_lane(u32 v, u32 fill) {
 // a wave do not pile up on one address.
 __device__ __forceinline__ u64 digit_peers_full(u64* tbl, u32 d, u64 ge_mask) {
   const u32 lane = lane_id();
-  const bool same = prev_lane(d, d ^ 1u) == d;   // lane 0 never matches
+  const bool same = lane_prev(d, d ^ 1u) == d;   // lane 0 never matches
   const u64 S = __ballot(same);
   u64 bits = 1ull << lane;
   if (S != 0) {
@@ -1039,7 +950,7 @@ __device__ __forceinline__ void lds_sort_passes(K* keys, u32* vals, u64* tbl, Cn
   }
 }
 
-// Counting needs equal keys adjacent, not ascending order (the survivors of all buckets
+// Merging lists needs equal keys adjacent, not ascending order (the survivors of all buckets
 // are sorted by key at the end).  After the LSD passes over the low `bits` bits the
 // keys are ordered by those bits, so equal keys already share one group of equal low
 // bits; if no two neighbours in [0, n) have equal low bits but different keys, every

@@ -495,9 +495,8 @@ __global__ __launch_bounds__(256) void k_extract(ExtractArgs A) {
 // ---------------------------------------------------------------------------- bucket plan
 // The plan classifies buckets by k-mer count n: tiny (n <= cap_tiny) and small (n <=
 // cap_small), counted on chip from their records, and large (cut into chunks of at most
-// cap_chunk k-mers, see the counting stage).  It
-// is three kernels: per-block sums, one scan of the block sums, then the writes (one
-// kernel when the buckets fit one block).
+// cap_chunk k-mers, see the counting stage).  It is two kernels: per-block sums, then the writes,
+// whose blocks add up the sums before theirs (one kernel when the buckets fit one block).
 // Quantities per bucket: q0 records, q1 k-mers, q2 classes packed (tiny | small << 21 |
 // large << 42), q3 k-mers of large buckets, q4 chunks, q5 k-mers of tiny buckets, q6
 // k-mers of small buckets.
@@ -509,7 +508,7 @@ constexpr int PLAN_Q = 7;
 struct PlanArgs {
   const u64* bcnt;
   u32 B, cap_tiny, cap_small, cap_chunk;
-  u64* bsum;             // [nblocks][PLAN_Q] block sums -> block offsets
+  u64* bsum;             // [nblocks][PLAN_Q] block sums
   u32* rec_off;          // [B + 1]
   u32* large_list;
   u64* chunk_start;
