@@ -686,37 +686,43 @@ __global__ __launch_bounds__(WPB * 64) void k_seg_wave(SegArgs A) {
 // table in key order.
 //
 // The coarse pass of a one-pass count reads the survivors from where the count left them: a
-// block takes an equal share of the k-mer slots and so does each of its waves, whatever the buckets'
-// sizes, and reads their segments in turn, one row of up to 64 at a time.  (Gathered into one dense
-// array first, 1 Gbp with 43 M survivors took 13.19 ms instead of 12.87, 60 Mbp with 20 M 1.76 instead
-// of 1.65, and every count five launches more.  With shares by buckets, a wave reads a long segment
-// alone: 300 kbp in one bucket (minimizers of one base) had an output stage of 1.94 ms, 0.08 so.)
+// block takes an equal share of the k-mer slots, whatever the buckets' sizes, and its waves the rows
+// of up to 64 survivors in it in turn.  (Gathered into one dense array first, 1 Gbp with 43 M
+// survivors took 13.19 ms instead of 12.87, 60 Mbp with 20 M 1.76 instead of 1.65, and every count
+// five launches more.  With shares by buckets, a wave reads a long segment alone: 300 kbp in one
+// bucket (minimizers of one base) had an output stage of 1.94 ms, 0.08 so.  With a share of the slots
+// for each wave, whose rows differ in number, 60 Mbp with 20 M survivors took 211 us in
+// k_msd_scatter, with the rows in turn 163.)
 template <typename K, u32 NW>
 struct SegRows {
   const SurvSegs& V;
-  u64 w0, w1;          // the wave's slots
-  u32 i0;              // its current 64 buckets: i0 + lane
-  u32 c;               // lane: its bucket's survivors in these slots ...
+  u64 w0, w1;          // the block's slots
+  u32 i0;              // 64 buckets: i0 + lane
+  u32 c;               // lane: survivors of its segment in these slots ...
   u64 base;            // ... and the first one's slot
-  u64 left;            // lanes whose buckets are still to do
-  u32 off;             // done of the first of them
+  u32 ex, inc;         // rows of the lanes' segments before it, and with it
+  u32 r, rows;         // the wave's next row, all rows of these buckets
   bool last;           // no buckets after these
 
   __device__ __forceinline__ SegRows(const SurvSegs& v, u32 n_blk) : V(v) {
-    const u64 n = uniform(v.meta[2] + v.meta[6] + v.meta[7]);   // k-mer slots
-    const u64 per = (n + n_blk - 1) / n_blk, per_w = (per + NW - 1) / NW;
-    const u64 b0 = min(n, blockIdx.x * per), b1 = min(n, b0 + per);
-    w0 = min(b1, b0 + uniform(threadIdx.x >> 6) * per_w);
-    w1 = min(b1, w0 + per_w);
-    // the last bucket that starts at or before w0: 64 probes at a time
+    // 64 buckets that hold the share's first slot: 64 probes at a time
     u32 lo = 0, hi = v.n_buckets;
-    while (hi - lo > 1) {
+    u64 n = 0;
+    for (bool first = true; first || hi - lo > 64; first = false) {
       const u32 step = (hi - lo + 63) / 64, i = lo + lane_id() * step;
-      const u32 at = 63u - (u32)__clzll(__ballot(lane_id() == 0 || (i < hi && v.s_base[i] <= w0)));
-      lo += at * step;
+      const u64 x = i < hi ? v.s_base[i] : ~0ull;
+      if (first) {
+        n = uniform(v.meta[2] + v.meta[6] + v.meta[7]);   // k-mer slots
+        const u64 per = (n + n_blk - 1) / n_blk;
+        w0 = min(n, blockIdx.x * per);
+        w1 = min(n, w0 + per);
+        if (hi <= 64) break;
+      }
+      lo += (63u - (u32)__clzll(__ballot(lane_id() == 0 || x <= w0))) * step;
       hi = min(hi, lo + step);
     }
     i0 = lo;
+    r = uniform(threadIdx.x >> 6);
     load();
   }
   // Buckets whose slots are full up to the next one's (those counted together, but the last of them)
@@ -732,30 +738,30 @@ struct SegRows {
     const u64 after = lane_id() == 63 ? 0ull : goes_on >> (lane_id() + 1);
     const int l = (int)lane_id() + __builtin_ctzll(~after);
     c = (u32)(__shfl((unsigned long long)end, l, 64) - base);
-    left = __ballot(c != 0) & ~goes_on;
+    if ((goes_on >> lane_id()) & 1) c = 0;
+    const u32 m = (c + 63) / 64;
+    inc = wave_scan_u32(m);
+    ex = inc - m;
+    rows = lane_read(inc, 63);
     last = __any(s >= w1);
-    off = 0;
   }
   // The next row's keys, one per lane: true where the lane has one.  (Past the last row: none.)
   __device__ __forceinline__ bool row(const K** k, const u32** v) {
-    while (!left) {
+    while (r >= rows) {
       if (last) return false;
+      r -= rows;
       i0 += 64;
       load();
     }
-    const int l = __builtin_ctzll(left);
-    const u32 cl = lane_read(c, l), o = off + lane_id();
+    const int l = (int)__popcll(__ballot(inc <= r));
+    const u32 cl = lane_read(c, l), o = (r - lane_read(ex, l)) * 64 + lane_id();
     const u64 at = (((u64)lane_read((u32)(base >> 32), l) << 32) | lane_read((u32)base, l)) + o;
     *k = reinterpret_cast<const K*>(V.s_k) + at;
     *v = V.s_c + at;
-    off += 64;
-    if (off >= cl) {
-      off = 0;
-      left &= left - 1;
-    }
+    r += NW;
     return o < cl;
   }
-  __device__ __forceinline__ bool done() const { return !left && last; }
+  __device__ __forceinline__ bool done() const { return r >= rows && last; }
 };
 
 template <typename K, bool SEGS>
