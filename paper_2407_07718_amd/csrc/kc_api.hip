@@ -130,9 +130,10 @@ static_assert(C_META + 8 <= C_FLAGS, "meta overlaps the flags");
 
 // ---------------------------------------------------------------- device memory of host calls
 // A host call (kc_count, kc_count_ext, kc_partition_inspect) needs about 58 bytes of HBM per
-// base for as long as it runs.  Handing them back to the driver costs more than the count: the
-// next allocation may wait until the pages are cleared (16 Mbp: 30 ms a call, 2.7 ms without; 60
-// Mbp: 28.5 and 27.5 ms, the rest being the result's pages on the host).  So up
+// base for as long as it runs.  Handing them back to the driver can cost more than the count: the
+// next allocation may wait until the pages are cleared (20 Mbp: 20 to 30 ms a call on some machines, 3.0
+// on one that does not wait; 2.2 to 2.7 ms with the block kept.  60 Mbp there: 15.1 and 13.7 ms, most of it
+// the result's pages on the host).  So up
 // to KEEP_MAX bytes (1.5 % of the HBM) of blocks stay here for the next call, and go back to the
 // driver when newer ones take their place, an allocation of this library runs short or
 // kc_release_memory is called.  A block

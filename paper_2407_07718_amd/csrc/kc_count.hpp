@@ -396,8 +396,8 @@ __device__ __forceinline__ void canon_two(const u32* rec, u32 o, int k, k128 (&o
 // through HBM.  Several read sets (MS): a contiguous range of buckets per block (they are
 // numbered set by set), whose statistics are flushed when the set changes.
 //
-// Bound by VALU issue (on the 1 Gbp long reads, k = 31: 78% of the issue slots, 47% of the LDS
-// cycles; HBM is idle): about 85 vector instructions per 64 k-mers, half of them the
+// Bound by VALU issue and LDS round trips (on the 1 Gbp long reads, k = 31: 68% of the VALU slots, 46%
+// of the LDS cycles; HBM is idle): about 97 vector instructions per 64 k-mers, half of them the
 // expansion.  Hence two k-mers per lane from one window of bits, 24-bit hash products, full
 // rows of 64 units, and a queue for the keys that need more than one look (10% there, but
 // nearly every row of 64 has some).  512 threads on 4,096 slots: 53 KB and at most 80 VGPRs, so
