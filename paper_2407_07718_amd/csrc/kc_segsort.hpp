@@ -699,8 +699,8 @@ struct SegRows {
   u64 w0, w1;          // the block's slots
   u32 i0;              // 64 buckets: i0 + lane
   u32 c;               // lane: survivors of its segment in these slots ...
-  u64 base;            // ... and the first one's slot
-  u32 ex, inc;         // rows of the lanes' segments before it, and with it
+  u32 at;              // ... and the first one's slot, from w0
+  u32 inc;             // rows of the lanes' segments up to it
   u32 r, rows;         // the wave's next row, all rows of these buckets
   bool last;           // no buckets after these
 
@@ -731,17 +731,14 @@ struct SegRows {
     const u32 i = i0 + lane_id();
     const bool in = i < V.n_buckets;
     const u64 s = in ? V.s_base[i] : w1, e = in ? s + V.s_cnt[i] : w1;
-    base = min(max(s, w0), w1);
-    const u64 end = min(max(e, w0), w1);
-    const u64 pe = ((u64)lane_prev((u32)(end >> 32), ~0u) << 32) | lane_prev((u32)end, ~0u);
-    const u64 goes_on = __ballot(base == pe);     // (never of lane 0)
+    at = (u32)(min(max(s, w0), w1) - w0);
+    const u32 end = (u32)(min(max(e, w0), w1) - w0);
+    const u64 goes_on = __ballot(at == lane_prev(end, ~0u));     // (never of lane 0)
     const u64 after = lane_id() == 63 ? 0ull : goes_on >> (lane_id() + 1);
     const int l = (int)lane_id() + __builtin_ctzll(~after);
-    c = (u32)(__shfl((unsigned long long)end, l, 64) - base);
+    c = __shfl(end, l, 64) - at;
     if ((goes_on >> lane_id()) & 1) c = 0;
-    const u32 m = (c + 63) / 64;
-    inc = wave_scan_u32(m);
-    ex = inc - m;
+    inc = wave_scan_u32((c + 63) / 64);
     rows = lane_read(inc, 63);
     last = __any(s >= w1);
   }
@@ -754,10 +751,10 @@ struct SegRows {
       load();
     }
     const int l = (int)__popcll(__ballot(inc <= r));
-    const u32 cl = lane_read(c, l), o = (r - lane_read(ex, l)) * 64 + lane_id();
-    const u64 at = (((u64)lane_read((u32)(base >> 32), l) << 32) | lane_read((u32)base, l)) + o;
-    *k = reinterpret_cast<const K*>(V.s_k) + at;
-    *v = V.s_c + at;
+    const u32 cl = lane_read(c, l), o = (r - (lane_read(inc, l) - (cl + 63) / 64)) * 64 + lane_id();
+    const u64 slot = w0 + lane_read(at, l);
+    *k = reinterpret_cast<const K*>(V.s_k) + slot + o;
+    *v = V.s_c + slot + o;
     r += NW;
     return o < cl;
   }
@@ -885,9 +882,11 @@ __device__ __forceinline__ void msd_rounds(In& in, const MsdArgs& A, int pb, int
   }
 }
 
-// Coarse scatter: the block's range in rounds staged through LDS, written group by group.
+// Coarse scatter: the block's range in rounds staged through LDS, written group by group.  At most 80
+// VGPRs where the survivors' rows are read, so that three blocks share a CU, as their LDS allows: a count
+// of 12 Mbp has 519 blocks, seven more than two each would hold (17.2 us, 13.2 so).
 template <typename K, bool SEGS>
-__global__ __launch_bounds__(512) void k_msd_scatter(MsdArgs A) {
+__global__ __launch_bounds__(512, SEGS ? 6 : 1) void k_msd_scatter(MsdArgs A) {
   constexpr u32 T = 512, R = sizeof(K) == 8 ? 4096u : 2048u;
   __shared__ K sk[R];
   __shared__ u32 sv[R];
