@@ -687,7 +687,9 @@ __global__ __launch_bounds__(WPB * 64) void k_seg_wave(SegArgs A) {
 //
 // The coarse pass of a one-pass count reads the survivors from where the count left them: a
 // block takes an equal share of the k-mer slots, whatever the buckets' sizes, and its waves the rows
-// of up to 64 survivors in it in turn.  (Gathered into one dense array first, 1 Gbp with 43 M
+// of up to 64 survivors in it in turn; where a share has more than four times 64 buckets, fewer waves
+// read the same ones (300 kbp in 2^18 buckets, 215 times 64 a share: the count takes 415 us where
+// all waves look at all of them, 212 so).  (Gathered into one dense array first, 1 Gbp with 43 M
 // survivors took 13.19 ms instead of 12.87, 60 Mbp with 20 M 1.76 instead of 1.65, and every count
 // five launches more.  With shares by buckets, a wave reads a long segment alone: 300 kbp in one
 // bucket (minimizers of one base) had an output stage of 1.94 ms, 0.08 so.  With a share of the slots
@@ -702,6 +704,8 @@ struct SegRows {
   u32 at;              // ... and the first one's slot, from w0
   u32 inc;             // rows of the lanes' segments up to it
   u32 r, rows;         // the wave's next row, all rows of these buckets
+  u32 nw;              // waves that share them ...
+  u32 step;            // ... and the buckets from these to the wave's next
   bool last;           // no buckets after these
 
   __device__ __forceinline__ SegRows(const SurvSegs& v, u32 n_blk) : V(v) {
@@ -721,8 +725,16 @@ struct SegRows {
       lo += (63u - (u32)__clzll(__ballot(lane_id() == 0 || x <= w0))) * step;
       hi = min(hi, lo + step);
     }
-    i0 = lo;
     r = uniform(threadIdx.x >> 6);
+    i0 = lo;
+    nw = NW;
+    step = 64;
+    while (nw > 1 && v.n_buckets > 4 * step * n_blk) {
+      nw >>= 1;
+      if (r & nw) i0 += step;
+      step <<= 1;
+    }
+    r &= nw - 1;
     load();
   }
   // Buckets whose slots are full up to the next one's (those counted together, but the last of them)
@@ -747,7 +759,7 @@ struct SegRows {
     while (r >= rows) {
       if (last) return false;
       r -= rows;
-      i0 += 64;
+      i0 += step;
       load();
     }
     const int l = (int)__popcll(__ballot(inc <= r));
@@ -755,7 +767,7 @@ struct SegRows {
     const u64 slot = w0 + lane_read(at, l);
     *k = reinterpret_cast<const K*>(V.s_k) + slot + o;
     *v = V.s_c + slot + o;
-    r += NW;
+    r += nw;
     return o < cl;
   }
   __device__ __forceinline__ bool done() const { return r >= rows && last; }

@@ -38,3 +38,17 @@ def test_several_buckets_at_a_time():
     for k, log2_buckets in ((21, 14), (31, 16), (51, 14), (51, 18)):
         for lo in (1, 2):
             check(r, off, k, 13, lo, 1 << 30, 64, cfg=kc.make_config(log2_buckets=log2_buckets), label="unequal buckets")
+
+
+@pytest.mark.parametrize("k,m", [(21, 13), (51, 21)])
+@pytest.mark.parametrize("log2_buckets", [12, 13, 14, 15])
+def test_waves_that_share_buckets(k, m, log2_buckets):
+    """19 shares of 3 to 27 times 64 buckets: rows dealt to all waves of a block, to half of them, ... to one;
+    a long repeat makes one bucket of many rows among them."""
+    from paper_2407_07718_amd import kc
+    rng = np.random.default_rng(log2_buckets)
+    u = _ACGT[rng.integers(0, 4, size=280_017)]
+    r = np.concatenate([u, np.tile(u[:300], 60), u[1000:3000]])
+    for lo in (1, 2):
+        check(r, np.array([0, len(r)], np.uint64), k, m, lo, 1 << 20, 64,
+              cfg=kc.make_config(log2_buckets=log2_buckets), label="shared buckets")
