@@ -303,9 +303,9 @@ __device__ __forceinline__ u32 window_min_carry(u32 v, int nst, u32 rest, const 
 // which returns the same minimum score.
 // A wave stages its span's window of the packed bases in its LDS slice and works on
 // span-relative 32-bit positions; the span's mask words stay in registers, one per lane.
-// Bound by VALU issue (84% of its slots at four cycles an instruction, and the score's 64-bit products
-// take more): about 105 vector instructions per tile, a third of their time in those products.  A tile closes about ten records (k = 31 at 6
-// k-mers a record), so they are queued and written 64 at a time, one per lane, and the
+// Bound by VALU issue (83% of its slots at four cycles an instruction, and the score's 64-bit products
+// take more): about 105 vector instructions per tile, a third of their time in those products.  A tile
+// closes about ten records (k = 31 at 6 k-mers a record), so they are queued and written 64 at a time, one per lane, and the
 // validity of the positions is tested on wave-uniform masks first: a tile far from any read
 // start or non-base skips it.  Measured against writing each tile's records from the lanes that
 // close them and a 64-bit view of the cut mask per lane (157 instructions): 1 Gbp long reads
